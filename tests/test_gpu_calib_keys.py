@@ -1,0 +1,44 @@
+"""Per-channel Key calibration at the edges of its launch rule: every channel grouping, row counts around the
+tail sample's threshold, outlier counts from none to almost half, unaligned input.  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import kvq_calib_oracle as C
+
+pytestmark = pytest.mark.gpu
+
+
+def _keys(T, D, seed, kind):
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((T, D)) * np.exp(rng.standard_normal(D)) + rng.standard_normal(D)
+    if kind == "drift":                       # later rows ever larger: the sampled rows are no random sample
+        x = x * (1.0 + np.arange(T)[:, None] / 7.0)
+    elif kind == "coarse":                    # a handful of distinct values, zeros of both signs among them
+        x = np.round(x) * 0.5
+    return x.astype(np.float16)
+
+
+@pytest.mark.parametrize("T,D,p,shift,kind", [
+    (1200, 4096, 0.01, 0, "plain"),           # 16 channels per workgroup
+    (513, 5120, 0.02, 0, "coarse"),           # 16, row steps with a remainder
+    (1009, 2048, 0.01, 0, "plain"),           # 8; the smallest row count whose rows are sampled
+    (1008, 2048, 0.01, 0, "drift"),           # 8; one row fewer: no sample
+    (1100, 1024, 0.0563, 0, "plain"),         # 4; 2 (k + 1) just fits the sample of 69 rows
+    (1100, 1024, 0.07, 0, "drift"),           # 4; and just does not
+    (3000, 514, 0.01, 0, "drift"),            # 2
+    (3000, 300, 0.99, 0, "coarse"),           # 1; both sides meet in the middle
+    (1500, 515, 0.01, 0, "plain"),            # 1; odd row length
+    (1100, 4096, 0.0, 1, "coarse"),           # 1; input not 16-byte aligned; no outliers
+    (32768, 24, 0.01, 0, "drift"),            # the most rows
+    (3, 4096, 0.5, 0, "plain"),               # fewer rows than a workgroup step
+])
+def test_channel_constants_at_the_edges(T, D, p, shift, kind):
+    import torch
+    import paper_2401_18079_amd as K
+    x = _keys(T, D, T + D, kind)
+    buf = torch.zeros(T * D + shift, dtype=torch.float16, device="cuda")
+    dev = buf[shift:].view(T, D)
+    dev.copy_(torch.from_numpy(x))
+    got = K.kvq_calibrate_key_channels(dev, p)
+    for name, a, b in zip(("s", "z", "lo", "hi"), got, C.key_channel_constants(x, p)):
+        assert np.array_equal(a, b), (name, np.nonzero(a != b)[0][:5])
