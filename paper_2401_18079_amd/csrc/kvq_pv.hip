@@ -3,31 +3,22 @@
 // one result.
 //
 // Design (gfx950).  out[q][c] = sum_n p[q][n] (s_n lut[code_{n,c}] + z_n) + sparse.  The storage format
-// keeps the codes of two consecutive tokens of one channel side by side in a 2b-bit field, so the hot
-// loop per field is: extract, one LDS gather of the fp16 pair (lut[a], lut[b]) from a layer-wide table,
-// two mixed-precision FMAs with the fp32 weights w = p*s of the two tokens.  The table is replicated
-// 32 times across LDS banks so gathers never conflict.  Lanes are token pairs, a wavefront owns one
-// (query head, 64-channel half) and keeps 64 fp32 accumulators per lane; lanes are summed once at the
-// end of the wavefront's token slab.  The zero-point term sum_n p z_n is a per-head scalar.  Sparse
-// outliers are handled by a balanced kernel (lanes = outlier entries, fixed-point LDS accumulators);
-// all partial results, and the fp16 rows of attention-sink tokens (paper Sec. 3.5) if any, are
-// summed in a fixed order by a final small kernel.
-#include <utility>
+// keeps the codes of two consecutive tokens of one channel side by side in a 2b-bit field, so one LDS
+// gather of the fp16 pair (lut[a], lut[b]) from a layer-wide table gives two consecutive elements of a
+// matrix-core operand; the weights w = p*s, split in three fp16 parts, are the other operand (kvq_pv_dense).
+// The zero-point term sum_n p z_n is a per-head scalar.  Sparse outliers are handled by a balanced kernel
+// (lanes = outlier entries, fixed-point LDS accumulators); all partial results, and the fp16 rows of
+// attention-sink tokens (paper Sec. 3.5) if any, are summed in a fixed order by a final small kernel.
 #include "kvq_common.hpp"
-
-#ifndef KVQ_ROTATE_PRIORITY
-#define KVQ_ROTATE_PRIORITY 1
-#endif
 
 namespace {
 
-constexpr int PV_NT = 256;                 // 4 wavefronts = 4 (query head, half) combinations
-constexpr int PV_WAVES = PV_NT / 64;
-constexpr int PV_FIELD_GROUP = 8;
+constexpr int PV_TILE = 64;                // tokens per tile of the dense kernel (32 token pairs)
+constexpr int PV_MIN_TILES = 8;            // tiles a workgroup should at least have: half of its wavefronts busy
 
 struct PvPlan {
-    int slabs;              // token slabs of the dense kernel (tiles are split evenly among them)
-    int tiles;              // tiles of 128 tokens
+    int slabs;              // workgroups per head group of the dense kernel (tiles are split evenly among them)
+    int tiles;              // tiles of PV_TILE tokens
     int sslabs;             // workgroups of the sparse kernel
     int swaves;             // its wavefronts per workgroup
     int64_t tokens_per_swave;
@@ -46,15 +37,16 @@ __host__ __device__ constexpr int pvs_wave_lds_floats(int n_q_heads)
     return n_q_heads * PVS_ROW;                          // the sub-range's probabilities
 }
 
-inline PvPlan pv_plan(int64_t L, int n_q_heads)
+inline PvPlan pv_plan(int64_t L, int n_q_heads, int rg)
 {
     PvPlan p;
-    const int64_t tiles = (L + 127) / 128;
-    // aim at ~16 wavefronts per compute unit: CUs * 16 / (2 * Hq) slabs
-    int64_t want = ((int64_t)kvq_cu_count() * 16) / (2 * (int64_t)n_q_heads);
-    if (want < 1) want = 1;
+    const int64_t tiles = (L + PV_TILE - 1) / PV_TILE;
+    // one workgroup per compute unit (its table and staging take most of the LDS), none with fewer than
+    // PV_MIN_TILES tiles
+    int64_t want = (int64_t)kvq_cu_count() / (n_q_heads / rg);
+    if (want > (tiles + PV_MIN_TILES - 1) / PV_MIN_TILES) want = (tiles + PV_MIN_TILES - 1) / PV_MIN_TILES;
     if (want > 512) want = 512;
-    if (want > tiles) want = tiles;
+    if (want < 1) want = 1;
     p.tiles = (int)tiles;
     p.slabs = (int)want;
     // sparse kernel: LDS holds Hq*128 64-bit accumulators shared by the workgroup plus a private slice
@@ -86,7 +78,7 @@ inline PvPlan pv_plan(int64_t L, int n_q_heads)
 template <int FBITS>
 __device__ inline uint32_t pv_field_off(const uint32_t *W, int i, uint32_t lane_off)
 {
-    // (field value * 128) | lane_off : entry e of the replicated table sits at dword e*32 + (lane & 31)
+    // (field value * 128) | lane_off : entry e of the replicated table sits at byte e * 128 + lane_off
     const int bit = i * FBITS, wi = bit >> 5, sh = bit & 31;
     constexpr uint32_t M = ((1u << FBITS) - 1u) << 7;
     uint32_t x;
@@ -99,221 +91,273 @@ __device__ inline uint32_t pv_field_off(const uint32_t *W, int i, uint32_t lane_
     return kvq_and_or(x, M, lane_off);
 }
 
-// One group of PV_FIELD_GROUP fields of a lane's slice.  RG query heads share the fields (grouped-query
-// attention): one extraction and one gather per field, two multiply-adds per field and head.
-// Accumulator of (head h, field i): acc[h * (64 / RG) + i].
-template <int BITS, int RG, int G0>
-__device__ __forceinline__ void pv_group(const uint32_t (&W)[4 * BITS / RG], float (&acc)[64], const half2_t *ptab,
-                                         uint32_t lane_off, const float (&w0)[RG], const float (&w1)[RG])
-{
-    constexpr int NF = 64 / RG;
-    half2_t t[PV_FIELD_GROUP];
-#pragma unroll
-    for (int k = 0; k < PV_FIELD_GROUP; ++k) {
-        const uint32_t off = pv_field_off<2 * BITS>(W, G0 * PV_FIELD_GROUP + k, lane_off);
-        t[k] = *(const half2_t *)((const uint8_t *)ptab + off);
-    }
-    // the two FMAs of a field depend on each other: issue the group's first halves, then its second
-    // halves, so that no instruction waits for the one right before it
-#pragma unroll
-    for (int h = 0; h < RG; ++h)
-#pragma unroll
-        for (int k = 0; k < PV_FIELD_GROUP; ++k) {
-            float &a = acc[h * NF + G0 * PV_FIELD_GROUP + k];
-            a = __builtin_fmaf((float)t[k].x, w0[h], a);
-        }
-#pragma unroll
-    for (int h = 0; h < RG; ++h)
-#pragma unroll
-        for (int k = 0; k < PV_FIELD_GROUP; ++k) asm volatile("" : "+v"(acc[h * NF + G0 * PV_FIELD_GROUP + k]));
-#pragma unroll
-    for (int h = 0; h < RG; ++h)
-#pragma unroll
-        for (int k = 0; k < PV_FIELD_GROUP; ++k) {
-            float &a = acc[h * NF + G0 * PV_FIELD_GROUP + k];
-            a = __builtin_fmaf((float)t[k].y, w1[h], a);
-        }
-    // an empty asm that "modifies" the group's accumulators and clobbers memory keeps the groups in
-    // order (otherwise every gather of the tile is issued first and register pressure explodes)
-#pragma unroll
-    for (int h = 0; h < RG; ++h)
-#pragma unroll
-        for (int k = 0; k < PV_FIELD_GROUP; ++k)
-            asm volatile("" : "+v"(acc[h * NF + G0 * PV_FIELD_GROUP + k]) : : "memory");
-}
+// Dense part: a matrix product on the matrix cores.  A wavefront owns one group of RG query heads that share
+// a KV head and takes tiles of 64 tokens.  The right operand of v_mfma_f32_16x16x32_f16 is signposts: column
+// n of a step stands for channel 8 n + t (t = 0..7: eight steps cover the KV head's 128 channels), its 32
+// rows for 32 tokens, and a lane's eight values are four fields of the storage format as the table returns
+// them, (lut[a], lut[b]) of a token pair: fp16 numbers, exact.  The left operand is weights w = p s: row
+// 4 h + i holds part i of head h's weights, w = w_0 + w_1 + w_2 in fp16 (33 bits: more than the fp32 weight
+// has wherever it is within 2^-15 of the largest one), under a power-of-two scale per wavefront and head that
+// keeps the largest weight below 2^15 (lowered, with an exact rescaling of the sums, when a tile exceeds it).
+// Products are exact and sums fp32, as in a chain of fp32 multiply-adds; rows i = 3 are not used.
+//
+// Per field a lane spends two instructions (cut the field out, form the table address) and one LDS gather
+// (2-bit codes: per pair of fields, whose byte indexes a table of both), whatever RG: the multiply-adds, 2 RG instructions per field before, are off the vector ALUs.  What the
+// layout costs is a transposition: a chunk is loaded 16 bytes per lane (512 contiguous bytes per half and
+// piece), left in LDS in [pair][128 channels] order (row length 32 BITS + 16 bytes: writes and reads without
+// bank conflicts) and read back as the lane's four pairs; the next tile's codes are requested as soon as the
+// current ones have left their registers.  Weights are computed once per (head, token), one token per lane.
+//
+// Bound: HBM (5.5 TB/s of loads alone on 131072 tokens of 32 heads, 6.6 TB/s on a million), with VALU and LDS
+// about 60 % busy each on 3-bit codes.  Measured against one lane per token pair with fp32 multiply-adds (four
+// or two heads sharing a field at most): 524288 tokens, 2-bit, 32 heads on 8: 153 -> 53 us; 33001 tokens, 4-bit,
+// 32 on 8: 20.0 -> 13.5 us; one head per KV head: 16384 tokens, 4-bit, 16.0 -> 12 us, 131072 tokens, 3-bit, 50-54 ->
+// 47-50 us, a million, 4-bit: HBM-bound before and after (340-400 us).
+//
+// grid = (slabs, head groups); the wavefronts of a workgroup take its tiles in turn and add their sums
+// through LDS.  Writes partial[slab][q][128], zpart[slab][q] and (with statistics) lpart[slab][q].
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
 
-template <int BITS, int RG, int... G>
-__device__ __forceinline__ void pv_all_fields(std::integer_sequence<int, G...>, const uint32_t (&W)[4 * BITS / RG],
-                                              float (&acc)[64], const half2_t *ptab, uint32_t lane_off,
-                                              const float (&w0)[RG], const float (&w1)[RG])
-{
-    (pv_group<BITS, RG, G>(W, acc, ptab, lane_off, w0, w1), ...);
-}
+template <int BITS, int RG>
+struct PvCfg {
+    static constexpr int NT = RG == 8 ? 512 : 1024;                 // eight heads: twice the sums, half the wavefronts
+    static constexpr int WAVES = NT / 64;
+    static constexpr int SETS = (RG + 3) / 4;                       // left operands of 16 rows
+    static constexpr int FG = BITS == 2 ? 2 : 1;                    // fields per gather: two 4-bit fields are one byte
+    // table of signpost pairs: an entry for every value of FG fields, in copies side by side so that no two
+    // lanes of a gather meet in a bank.  Rows of 256 bytes (4-bit codes, where they fit): the address of a
+    // gather is then two bytes, the field and the lane's place, and one byte permute forms it
+    static constexpr bool BYTES = BITS == 4 && RG <= 2;
+    static constexpr int ROW = BYTES ? 256 : 128;
+    static constexpr int TAB = (1 << (2 * BITS * FG)) * ROW;
+    static constexpr int PAIR = 32 * BITS + 16;                     // staged codes of a token pair
+    static constexpr int WROW = 2 * PV_TILE + 16;                   // a row of weight parts
+    static constexpr int WAVE = (PV_TILE / 2) * PAIR + 3 * RG * WROW;
+    static constexpr int LDS = TAB + WAVES * WAVE;
+};
 
-// Dense part.  A wavefront owns one combination of (group of RG query heads that share a KV head,
-// 64-channel half, slice of 64/RG channels of that half): its lanes are token pairs and keep the
-// RG x 64/RG = 64 accumulators of their pair's fields.  RG = 1: one query head, the whole half.  With
-// grouped-query attention RG > 1 heads share every extraction and gather.  grid = (slabs, 2*Hq / 4):
-// wavefront w of a workgroup owns combination blockIdx.y*4 + w.  Writes partial[slab][q][128] and
-// zpart[slab][q].
-// (Four wavefronts per SIMD: the register allocation is held to 128, which every instantiation but
-// the 3-bit one for four heads meets without spilling.)
 template <int BITS, int RG, bool SPAN = false>
-__global__ __launch_bounds__(PV_NT, (BITS == 3 && RG == 4) ? 3 : 4) void kvq_pv_dense(const void *__restrict__ params, int D, int n_kv_heads,
-                                                      int n_q_heads, int64_t cap, int64_t L,
-                                                      const uint8_t *__restrict__ v_codes,
-                                                      const uint16_t *__restrict__ v_sz,
-                                                      const float *__restrict__ probs, int64_t ld,
-                                                      float *__restrict__ partial, float *__restrict__ zpart,
-                                                      int n_tiles, int n_sink,
-                                                      const float *__restrict__ stat_slots, int n_stat,
-                                                      float *__restrict__ lpart, unsigned long long *span, int n_cu)
+__global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
+    const void *__restrict__ params, int D, int n_kv_heads, int n_q_heads, int64_t cap, int64_t L,
+    const uint8_t *__restrict__ v_codes, const uint16_t *__restrict__ v_sz, const float *__restrict__ probs, int64_t ld,
+    float *__restrict__ partial, float *__restrict__ zpart, int n_tiles, int n_sink,
+    const float *__restrict__ stat_slots, int n_stat, float *__restrict__ lpart, unsigned long long *span)
 {
     if (SPAN) kvq_span_start(span);       // timing-aid instantiation (kvq_profile_*): workgroup start and end times
     // tokens below n_sink are attention-sink tokens kept in fp16: their quantized form gets weight 0
     // here and the reduce kernel adds their fp16 rows.
     // stat_slots != null: `probs` holds raw scores x; a wavefront takes the maximum m of each of its
-    // heads' n_stat slots once, weights every token by exp(x - m) as it loads its score, and also writes
-    // the sum of these weights over its slab to lpart[slab][q] (the reduce kernel divides by their total)
-    constexpr int NE2 = 1 << (2 * BITS);
-    constexpr int NF = 64 / RG;                    // fields (channels) per lane and head
-    constexpr int ND = 4 * BITS / RG;              // dwords of a chunk that hold them
-    static_assert((4 * BITS) % RG == 0 && NF % PV_FIELD_GROUP == 0, "a slice is whole dwords and whole field groups");
-    // One array for the replicated pair table (used by the tile loop) and for the lane reduction after
-    // it: with the 4-bit table (32 KB) next to the reduction's 17 KB only three workgroups fit a CU.
-    constexpr int LDS_WORDS = (NE2 * 32 > PV_WAVES * 64 * 17) ? NE2 * 32 : PV_WAVES * 64 * 17;
-    __shared__ __attribute__((aligned(16))) uint32_t lds_words[LDS_WORDS];
-    half2_t *ptab = (half2_t *)lds_words;                                 // [NE2 * 32]
-    float (*red)[64][17] = (float (*)[64][17])lds_words;                  // [PV_WAVES][64][17]
+    // heads' n_stat slots once, weights every token by exp(x - m) as it loads its score, and the workgroup
+    // also writes the sum of these weights to lpart[slab][q] (the reduce kernel divides by their total)
+    using C = PvCfg<BITS, RG>;
+    constexpr int WAVES = C::WAVES, SETS = C::SETS;
+    __shared__ __attribute__((aligned(16))) uint8_t lds[C::LDS];
+    static_assert(C::LDS >= WAVES * RG * 130 * 4, "the workgroup's sums reuse the array");
     const KvqParamsView pv = kvq_params_view(params, D);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int e = tid; e < NE2 * 32; e += PV_NT) {
-        const int f = e >> 5;
-        ptab[e] = half2_t{(half_t)pv.hdr->lut_v[f & ((1 << BITS) - 1)], (half_t)pv.hdr->lut_v[f >> BITS]};
-    }
-    __syncthreads();
-
-    const int combo = blockIdx.y * PV_WAVES + wave;
-    const bool active = combo < 2 * n_q_heads;
-    const int slice = combo % RG, half = (combo / RG) & 1;
-    const int q0 = active ? (combo / (2 * RG)) * RG : 0;          // first query head of the group
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q0 = blockIdx.y * RG;                                 // first query head of the group
     const int kvh = q0 / (n_q_heads / n_kv_heads);
-    const uint32_t lane_off = (uint32_t)(lane & 31) << 2;
-    float m2[RG], lacc[RG], zacc[RG];
+    const int tile1 = (int)(((int64_t)(blockIdx.x + 1) * n_tiles) / gridDim.x);
+    int tile = (int)(((int64_t)blockIdx.x * n_tiles) / gridDim.x) + wave;
+
+    // the tile's loads: lane = token for scores and (scale, zero-point), lane = (half, pair) for the codes
+    uint4 cw[BITS];
+    float xs[RG];
+    uint32_t szw = 0;
+    const int64_t plane = (cap >> 1) * 16 * BITS;                   // bytes between the two halves of a KV head
+    auto request = [&](int t) {
+        const int64_t m = (int64_t)t * (PV_TILE / 2) + (lane & 31);
+        const uint8_t *p = v_codes + kvq_v_piece0(BITS, cap, m, kvh, 0) + (lane >> 5) * plane;
+#pragma unroll
+        for (int j = 0; j < BITS; ++j) cw[j] = kvq_load_stream16(p + j * 1024);
+        // (loaded whatever the conditions below say, from an index that exists: a load inside a
+        // conditional block is followed by a wait for every load in flight)
+        int64_t n = (int64_t)t * PV_TILE + lane;
+        n = n < L ? n : L - 1;
+        szw = *(const uint32_t *)(v_sz + 2 * n);
+#pragma unroll
+        for (int h = 0; h < RG; ++h) xs[h] = probs[(int64_t)(q0 + h) * ld + n];
+    };
+    if (tile < tile1) request(tile);
+
+    float m2[RG], lacc[RG], zacc[RG], scale[RG];
+    int expo[RG];                                                   // scale = 2^expo; 0: no tile seen yet
 #pragma unroll
     for (int h = 0; h < RG; ++h) {
-        m2[h] = 0.f; lacc[h] = 0.f; zacc[h] = 0.f;
+        m2[h] = 0.f; lacc[h] = 0.f; zacc[h] = 0.f; scale[h] = 0.f; expo[h] = 0;
         if (stat_slots) {
             float m = KVQ_STAT_FLOOR;
             for (int i = lane; i < n_stat; i += 64) m = __builtin_fmaxf(m, stat_slots[(int64_t)(q0 + h) * KVQ_STAT_SLOTS + i]);
             m2[h] = kvq_wave_max(m) * KVQ_LOG2E;
         }
     }
-
-    float acc[64];
-#pragma unroll
-    for (int j = 0; j < 64; ++j) acc[j] = 0.f;
-
-    const int64_t tile0 = ((int64_t)blockIdx.x * n_tiles) / gridDim.x;
-    const int64_t tile1 = ((int64_t)(blockIdx.x + 1) * n_tiles) / gridDim.x;
-    // the workgroups that share a compute unit were dispatched n_cu apart; see kvq_set_wave_priority
-    const int prio_slot = (int)((blockIdx.y * gridDim.x + blockIdx.x) / (unsigned)n_cu);
-    if (active) {
-        for (int64_t t = tile0; t < tile1; ++t) {
-            if (KVQ_ROTATE_PRIORITY) kvq_set_wave_priority(prio_slot + (int)(t - tile0));
-            const int64_t m = t * 64 + lane;                // token pair
-            const int64_t n0 = 2 * m;
-            if (n0 >= L) continue;
-            uint32_t W[ND];
-            const uint8_t *p = v_codes + kvq_v_piece0(BITS, cap, m, kvh, half);
-            if constexpr (RG == 1) {
-#pragma unroll
-                for (int j = 0; j < BITS; ++j) {
-                    const uint4 v = kvq_load_stream16(p + j * 1024);
-                    W[4 * j + 0] = v.x; W[4 * j + 1] = v.y; W[4 * j + 2] = v.z; W[4 * j + 3] = v.w;
-                }
-            } else {
-                // dword d of the chunk sits in 16-byte piece d / 4 (pieces are 1024 bytes apart)
-#pragma unroll
-                for (int j = 0; j < ND; ++j) {
-                    const int d = slice * ND + j;
-                    W[j] = *(const uint32_t *)(p + (d >> 2) * 1024 + (d & 3) * 4);
-                }
-            }
-            const uint2 sz = *(const uint2 *)(v_sz + n0 * 2);            // (s0, z0, s1, z1) fp16
-            const bool ok0 = n0 >= n_sink, ok1 = n0 + 1 < L && n0 + 1 >= n_sink;   // odd tail: second token absent
-            const float s0 = kvq_h2f((uint16_t)(sz.x & 0xFFFFu)), z0 = kvq_h2f((uint16_t)(sz.x >> 16));
-            // (scale, zero-point) of an absent second token may be anything, NaN included
-            const float s1 = ok1 ? kvq_h2f((uint16_t)(sz.y & 0xFFFFu)) : 0.f, z1 = ok1 ? kvq_h2f((uint16_t)(sz.y >> 16)) : 0.f;
-            // The scores (probabilities) are loaded whatever ok0 / ok1 say (the second from an index that
-            // always exists), and the empty asm keeps the compiler from moving the loads back under those
-            // conditions: a load inside a conditional block is followed by a wait for every load in
-            // flight, the tile's codes included, and the tile then costs two or three memory latencies
-            // instead of one.
-            const int64_t n1 = n0 + 1 < L ? n0 + 1 : n0;
-            float pl0[RG], pl1[RG];
-#pragma unroll
-            for (int h = 0; h < RG; ++h) {
-                const float *prow = probs + (int64_t)(q0 + h) * ld;
-                pl0[h] = prow[n0];
-                pl1[h] = prow[n1];
-            }
-#pragma unroll
-            for (int h = 0; h < RG; ++h) asm volatile("" : "+v"(pl0[h]), "+v"(pl1[h]));
-            float w0[RG], w1[RG];
-#pragma unroll
-            for (int h = 0; h < RG; ++h) {
-                float p0 = ok0 ? pl0[h] : 0.f;
-                float p1 = ok1 ? pl1[h] : 0.f;
-                if (stat_slots) {
-                    p0 = ok0 ? kvq_stat_weight(p0, m2[h]) : 0.f;
-                    p1 = ok1 ? kvq_stat_weight(p1, m2[h]) : 0.f;
-                    lacc[h] += p0 + p1;
-                }
-                w0[h] = p0 * s0;
-                w1[h] = p1 * s1;
-                zacc[h] = __builtin_fmaf(p0, z0, zacc[h]);
-                zacc[h] = __builtin_fmaf(p1, z1, zacc[h]);
-            }
-            pv_all_fields<BITS, RG>(std::make_integer_sequence<int, NF / PV_FIELD_GROUP>{}, W, acc, ptab, lane_off, w0, w1);
-        }
+    for (int e = tid; e < C::TAB / 4; e += C::NT) {
+        const int f = C::FG == 1 ? e / (C::ROW / 4) : ((e >> 5) >> (4 * (e & 1))) & 15;     // field that dword e stands for
+        ((half2_t *)lds)[e] = half2_t{(half_t)pv.hdr->lut_v[f & ((1 << BITS) - 1)], (half_t)pv.hdr->lut_v[f >> BITS]};
     }
-    if (KVQ_ROTATE_PRIORITY) __builtin_amdgcn_s_setprio(0);
-    // sum the 64 lanes: four rounds of 16 accumulators through LDS (over the table, once every
-    // wavefront of the workgroup has left the tile loop)
     __syncthreads();
-    float outv = 0.f;      // lane l (< 64) ends up with the sum of accumulator l
+
+    const uint32_t lane_off = (uint32_t)(lane & (C::ROW / (4 * C::FG) - 1)) * 4 * C::FG;
+    uint8_t *mine = lds + C::TAB + wave * C::WAVE;                  // staged codes, then rows of weight parts
+    uint8_t *wrows = mine + (PV_TILE / 2) * C::PAIR;
+    const int col = lane & 15, kg = lane >> 4;                      // column / row of an operand, group of 8 tokens
+    // where this lane reads its operands: row 4 h + i of a left operand is part i of head h (rows without a
+    // meaning read some other row: what they give ends up in sums that nobody reads)
+    const uint8_t *arow[SETS];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-#pragma unroll
-        for (int k = 0; k < 16; ++k) red[wave][lane][k] = acc[r * 16 + k];
-        __syncthreads();
-        const int col = lane & 15, quarter = lane >> 4;
-        float s = 0.f;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) s += red[wave][quarter * 16 + j][col];
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        if ((lane >> 4) == r) outv = s;          // lanes 16r..16r+15 keep accumulators 16r..16r+15
-        __syncthreads();
+    for (int q = 0; q < SETS; ++q) {
+        int h = 4 * q + (col >> 2);
+        h = h < RG ? h : RG - 1;
+        arow[q] = wrows + (3 * h + ((col & 3) < 3 ? (col & 3) : 2)) * C::WROW + kg * 16;
     }
+    // 8 fields = 2 BITS bytes at 2 BITS col; for 3 bits the two dwords around them
+    const uint8_t *brow = mine + kg * 4 * C::PAIR + (BITS == 3 ? (col >> 1) * 12 + (col & 1) * 4 : 2 * BITS * col);
+    const uint32_t bshift = (uint32_t)(col & 1) * 16;
+    float4_t acc[SETS][8];
+#pragma unroll
+    for (int q = 0; q < SETS; ++q)
+#pragma unroll
+        for (int t = 0; t < 8; ++t) acc[q][t] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+    for (; tile < tile1; tile += WAVES) {
+        const int64_t n = (int64_t)tile * PV_TILE + lane;
+        const bool ok = n < L && n >= n_sink;
+        const float s = kvq_h2f((uint16_t)(szw & 0xFFFFu)), z = kvq_h2f((uint16_t)(szw >> 16));
+        float w[RG], top = 0.f;
+#pragma unroll
+        for (int h = 0; h < RG; ++h) {
+            float p = xs[h];
+            if (stat_slots) p = kvq_stat_weight(p, m2[h]);
+            p = ok ? p : 0.f;
+            lacc[h] += p;
+            zacc[h] = __builtin_fmaf(p, z, zacc[h]);
+            w[h] = p * s;
+            top = __builtin_fmaxf(top, __builtin_fabsf(w[h] * scale[h]));
+        }
+        // the first tile, or a weight beyond the range of its head's scale (rare: weights have to grow by
+        // 2^6 over all that came before): set the scales anew
+        if (scale[0] == 0.f || __ballot(!(top < 32768.f)) != 0ull) {
+            float ratio[RG];
+#pragma unroll
+            for (int h = 0; h < RG; ++h) {
+                const float m = kvq_wave_max(__builtin_fabsf(w[h]));
+                ratio[h] = 1.f;
+                if (scale[h] == 0.f || !(m * scale[h] < 32768.f)) {
+                    int e = m > 0.f ? 9 - __builtin_amdgcn_frexp_expf(m) : 120;       // m * 2^e in [2^8, 2^9)
+                    e = e > 120 ? 120 : e < -120 ? -120 : e;
+                    ratio[h] = scale[h] == 0.f ? 0.f : __builtin_ldexpf(1.f, e - expo[h]);
+                    scale[h] = __builtin_ldexpf(1.f, e);
+                    expo[h] = e;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < SETS; ++q) {
+                float r = 1.f;                                      // sums of head h sit in the lanes of group h
+#pragma unroll
+                for (int h = 0; h < 4 && 4 * q + h < RG; ++h) r = kg == h ? ratio[4 * q + h] : r;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) acc[q][t] *= r;
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < RG; ++h) {
+            const float ws = w[h] * scale[h];
+            const half_t a = (half_t)ws;
+            const float r1 = ws - (float)a;
+            const half_t b = (half_t)r1;
+            const half_t c = (half_t)(r1 - (float)b);
+            half_t *row = (half_t *)(wrows + 3 * h * C::WROW) + lane;
+            row[0] = a;
+            row[C::WROW / 2] = b;
+            row[C::WROW] = c;
+        }
+        uint8_t *to = mine + (lane & 31) * C::PAIR + (lane >> 5) * 16 * BITS;
+#pragma unroll
+        for (int j = 0; j < BITS; ++j) *(uint4 *)(to + 16 * j) = cw[j];
+        if (tile + WAVES < tile1) request(tile + WAVES);
+        // (LDS operations of one wavefront execute in order; the fences keep the compiler from reordering them)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int k = 0; k < PV_TILE / 32; ++k) {
+            half8_t a[SETS];
+#pragma unroll
+            for (int q = 0; q < SETS; ++q) a[q] = *(const half8_t *)(arow[q] + k * 64);
+            uint32_t W[4][2];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t *b = (const uint32_t *)(brow + (16 * k + j) * C::PAIR);
+                W[j][0] = b[0];
+                W[j][1] = BITS == 2 ? 0u : b[1];
+                if (BITS == 3) {
+                    W[j][0] = __builtin_amdgcn_alignbit(W[j][1], W[j][0], bshift);
+                    W[j][1] >>= bshift;
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < 8; t += C::FG) {
+                uint32_t g[C::FG][4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint8_t *e;
+                    if constexpr (C::BYTES) e = lds + __builtin_amdgcn_perm(W[j][t >> 2], lane_off, 0x0c0c0400u + ((t & 3) << 8));
+                    else e = lds + pv_field_off<2 * BITS * C::FG>(W[j], t / C::FG, lane_off);
+                    if (C::FG == 1) {
+                        g[0][j] = *(const uint32_t *)e;
+                    } else {
+                        const uint2 v = *(const uint2 *)e;
+                        g[0][j] = v.x;
+                        g[C::FG - 1][j] = v.y;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < C::FG; ++u) {
+                    const half8_t b = __builtin_bit_cast(half8_t, uint4{g[u][0], g[u][1], g[u][2], g[u][3]});
+#pragma unroll
+                    for (int q = 0; q < SETS; ++q)
+                        acc[q][t + u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[q], b, acc[q][t + u], 0, 0, 0);
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    // the workgroup's sums: wavefronts leave theirs in LDS, [wave][head][128 channels, zero-point, weights]
 #pragma unroll
     for (int h = 0; h < RG; ++h) {
-        for (int o = 32; o > 0; o >>= 1) zacc[h] += __shfl_xor(zacc[h], o);
-        if (stat_slots)
-            for (int o = 32; o > 0; o >>= 1) lacc[h] += __shfl_xor(lacc[h], o);
-    }
-    if (active) {
-        // accumulator a = (head a / NF of the group, channel a % NF of the slice)
-        const int qh = q0 + lane / NF;
-        partial[((int64_t)blockIdx.x * n_q_heads + qh) * 128 + half * 64 + slice * NF + lane % NF] = outv;
-        if (half == 0 && slice == 0 && lane == 0) {
-#pragma unroll
-            for (int h = 0; h < RG; ++h) {
-                zpart[(int64_t)blockIdx.x * n_q_heads + q0 + h] = zacc[h];
-                if (stat_slots) lpart[(int64_t)blockIdx.x * n_q_heads + q0 + h] = lacc[h];
-            }
+        for (int o = 32; o > 0; o >>= 1) {
+            zacc[h] += __shfl_xor(zacc[h], o);
+            lacc[h] += __shfl_xor(lacc[h], o);
         }
+    }
+    __syncthreads();                      // every wavefront has left the table
+    float *sums = (float *)lds + wave * RG * 130;
+#pragma unroll
+    for (int q = 0; q < SETS; ++q) {
+        const int h = 4 * q + kg;
+        float inv = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4 && 4 * q + i < RG; ++i) inv = kg == i ? (scale[4 * q + i] == 0.f ? 0.f : __builtin_ldexpf(1.f, -expo[4 * q + i])) : inv;
+        if (h < RG) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) sums[h * 130 + 8 * col + t] = (acc[q][t][0] + (acc[q][t][1] + acc[q][t][2])) * inv;
+        }
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int h = 0; h < RG; ++h) { sums[h * 130 + 128] = zacc[h]; sums[h * 130 + 129] = lacc[h]; }
+    }
+    __syncthreads();
+    for (int i = tid; i < RG * 130; i += C::NT) {
+        float v = 0.f;
+#pragma unroll
+        for (int k = 0; k < WAVES; ++k) v += ((const float *)lds)[k * RG * 130 + i];
+        const int h = i / 130, c = i - 130 * h;
+        const int64_t o = (int64_t)blockIdx.x * n_q_heads + q0 + h;
+        if (c < 128) partial[o * 128 + c] = v;
+        else if (c == 128) zpart[o] = v;
+        else if (stat_slots) lpart[o] = v;
     }
     if (SPAN) kvq_span_end(span);
 }
@@ -626,13 +670,15 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
     if (ld_probs < L) return KVQ_ERR_INVALID_ARG;
     const int Hq = cache->n_q_heads, D = cache->n_kv_heads * KVQ_HEAD_DIM;
     if (!cache->workspace || cache->workspace_bytes < kvq_pv_workspace_bytes(Hq)) return KVQ_ERR_CAPACITY;
-    const PvPlan plan = (L > 0) ? pv_plan(L, Hq) : PvPlan{0, 0, 0, 0, 0, 0};
+    const int r = Hq / cache->n_kv_heads;
+    // query heads of one KV head that a wavefront of the dense kernel takes together (they share the codes)
+    const int rg = (r % 8 == 0) ? 8 : (r % 4 == 0) ? 4 : (r % 2 == 0) ? 2 : 1;
+    const PvPlan plan = (L > 0) ? pv_plan(L, Hq, rg) : PvPlan{0, 0, 0, 0, 0, 0};
     float *partial = (float *)cache->workspace;
     float *zpart = partial + (int64_t)512 * Hq * 128;
     float *spartial = zpart + (int64_t)512 * Hq;
     float *lpart = spartial + (int64_t)512 * Hq * 128;
     if (L > 0) {
-        const int r = Hq / cache->n_kv_heads;
         const bool sink = cache->n_sink > 0;
         const int ri = (r == 1) ? 1 : (r == 2) ? 2 : (r == 4) ? 3 : (r == 8) ? 4 : 0;
         const bool fused = stat_slots != nullptr;
@@ -643,27 +689,29 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
                                     stat_slots, n_stat, s);
         if (st != KVQ_OK) return st;
 
-        dim3 grid((unsigned)plan.slabs, (unsigned)((2 * Hq + PV_WAVES - 1) / PV_WAVES));
+        dim3 grid((unsigned)plan.slabs, (unsigned)(Hq / rg));
 #define LAUNCH_PV(B, G)                                                                                        \
     do {                                                                                                       \
         auto kern = span ? kvq_pv_dense<B, G, true> : kvq_pv_dense<B, G, false>;                               \
-        kern<<<grid, PV_NT, 0, s>>>(cache->params, D, cache->n_kv_heads, Hq, cache->cap_tokens, L,             \
-                                    cache->v_codes, cache->v_sz, d_probs, ld_probs, partial, zpart,            \
-                                    plan.tiles, cache->n_sink, stat_slots, n_stat, lpart, span, kvq_cu_count()); \
+        kern<<<grid, (PvCfg<B, G>::NT), 0, s>>>(cache->params, D, cache->n_kv_heads, Hq, cache->cap_tokens, L,   \
+                                              cache->v_codes, cache->v_sz, d_probs, ld_probs, partial, zpart,  \
+                                              plan.tiles, cache->n_sink, stat_slots, n_stat, lpart, span);     \
+    } while (0)
+#define LAUNCH_PV_B(B)                                                                                         \
+    do {                                                                                                       \
+        if (rg == 8) LAUNCH_PV(B, 8);                                                                          \
+        else if (rg == 4) LAUNCH_PV(B, 4);                                                                     \
+        else if (rg == 2) LAUNCH_PV(B, 2);                                                                     \
+        else LAUNCH_PV(B, 1);                                                                                  \
     } while (0)
         KvqProfile &prof = kvq_profile_state();
         unsigned long long *span = kvq_profile_span_slot(prof, 1, (int64_t)grid.x * grid.y);
         hipEvent_t *pev = (prof.enabled && prof.use_events) ? prof.ev[1][prof.count[1] % KVQ_PROFILE_RING] : nullptr;
         if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[0], s));
-        // query heads of one KV head that a wavefront takes together (they share extraction and gather).
-        // When the kernel also turns scores into weights every wavefront that covers a head evaluates
-        // that head's exponentials, and grouping multiplies the wavefronts per head: pairs of heads
-        // still pay there, fours do not (measured, 32 / 8 heads, 2-bit, 512K tokens: 142 us with two,
-        // 155 us with one, 156 us with four heads per wavefront).
-        const int rg = stat_slots ? ((r % 2 == 0) ? 2 : 1) : (r % 4 == 0) ? 4 : (r % 2 == 0) ? 2 : 1;
-        if (cache->bits == 2) { if (rg == 4) LAUNCH_PV(2, 4); else if (rg == 2) LAUNCH_PV(2, 2); else LAUNCH_PV(2, 1); }
-        else if (cache->bits == 3) { if (rg == 4) LAUNCH_PV(3, 4); else if (rg == 2) LAUNCH_PV(3, 2); else LAUNCH_PV(3, 1); }
-        else { if (rg == 4) LAUNCH_PV(4, 4); else if (rg == 2) LAUNCH_PV(4, 2); else LAUNCH_PV(4, 1); }
+        if (cache->bits == 2) LAUNCH_PV_B(2);
+        else if (cache->bits == 3) LAUNCH_PV_B(3);
+        else LAUNCH_PV_B(4);
+#undef LAUNCH_PV_B
 #undef LAUNCH_PV
         if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[1], s));
         if (prof.enabled) ++prof.count[1];
