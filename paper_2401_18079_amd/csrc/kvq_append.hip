@@ -10,18 +10,63 @@
 
 namespace {
 
-// Measured on 4096-channel tokens with the workgroup-per-token bodies: 1024-thread workgroups finish
-// a call of up to 256 tokens in one round (Values: 25 us against 37 us with 256 threads), break even
-// at 512 tokens and lose beyond (4096 tokens: 216 us against 105 us), where eight small workgroups
-// per compute unit hide each other's barriers.  Values of 1024, 2048 or 4096 channels take the
-// four-wavefront body (v_quant_token4) at every call size instead, those of 5120, 6656 or 8192
-// channels (40, 52, 64 heads) in bulk appends.
+// Launch rules.  Keys: a wavefront per token from KVQ_WAVE_TOKENS tokens on (4096 tokens of 4096 channels, 3 bits:
+// 30 us), sixteen wavefronts per token below (one token of 5120 channels: 10.9 us with the looping body, 5.7 us;
+// 777 tokens, 4 bits: 19.9 us with 256 threads per token, 17.2 us).  Values of 1024, 2048, 4096 and (but for
+// middling calls) 5120, 6656 and 8192 channels keep a token in registers (v_quant_token4): four wavefronts per
+// token and two tokens, the pair that shares dwords, per workgroup in calls of KVQ_VW_SMALL_TOKENS tokens and
+// more (4096 tokens: 74 us with a token's bits merged into memory by two atomics per dword, 51 us with whole
+// dwords stored; 777 tokens of 5120 channels: 37.6 -> 22.7 us), eight or sixteen wavefronts on single tokens
+// below (two tokens per workgroup there would lengthen the one chain that counts).
 constexpr int KVQ_BULK_TOKENS = 512;      // calls with at least this many tokens count as bulk appends
 constexpr int KVQ_KV_SPLIT_TOKENS = 256;  // from here on the combined call runs the Key and Value kernels in turn
 constexpr int KVQ_WAVE_TOKENS = 1024;     // Key appends of at least this many tokens: one wavefront per token
 
 // Workgroups have NT threads: 256 for narrow models, 1024 once a token vector has >= 2048 channels
 // (fewer passes over the vector, hence fewer barriers, for the single-token decode append).
+
+// Code of a normalised value: the number of thresholds it has reached (a compare and an add with carry each),
+// or, beyond the range in which that is the nearest signpost, the exhaustive search (KVQ_CODE_RANGE).  The
+// search costs four instructions per signpost; a token's channels are within the range all but always.
+template <int NE>
+struct KvqCoder {
+    float thr[NE - 1], range;
+    const float *lut;
+    __device__ __forceinline__ KvqCoder(const float *thresholds, const float *signposts) : lut(signposts)
+    {
+#pragma unroll
+        for (int j = 0; j < NE - 1; ++j) thr[j] = thresholds[j];
+        range = (thr[0] == thr[0]) ? KVQ_CODE_RANGE : -1.0f;
+    }
+    __device__ __forceinline__ bool far(float xn) const { return !(__builtin_fabsf(xn) <= range); }
+    __device__ __forceinline__ int count(float xn) const            // not far(xn) only
+    {
+        int code = 0;
+#pragma unroll
+        for (int j = 0; j < NE - 1; ++j) code += (xn >= thr[j]) ? 1 : 0;
+        return code;
+    }
+    __device__ __forceinline__ int search(float xn) const
+    {
+        float sp;
+        return kvq_nearest<NE>(lut, xn, sp);
+    }
+    __device__ __forceinline__ int operator()(float xn) const
+    {
+        int code = count(xn);
+        const bool f = far(xn);
+        if (__ballot(f) != 0ull) {
+            if (f) code = search(xn);
+        }
+        return code;
+    }
+};
+// The signposts in LDS, for the residuals of outliers (a dynamic index).  The caller's next barrier makes them visible.
+template <int NE>
+__device__ __forceinline__ void stage_lut(float *lut_s, const float *lut)
+{
+    if (threadIdx.x < NE) lut_s[threadIdx.x] = lut[threadIdx.x];
+}
 
 // Exclusive rank of this thread's flag among all flags of the workgroup, in thread order, plus
 // the workgroup total.  `wave_tot` is a shared array of NT/64 words.  Contains two barriers.
@@ -179,9 +224,10 @@ __device__ __forceinline__ void k_quant_token(const void *__restrict__ params, i
     __shared__ uint32_t chunk_s[IT][HB][CW + 1];
     __shared__ uint32_t wave_tot[IT * NW];
     KvqParamsView pv = kvq_params_view(params, D);
-    float lut[NE];
-#pragma unroll
-    for (int j = 0; j < NE; ++j) lut[j] = pv.hdr->lut_k[j];
+    __shared__ float lut_s[NE];
+    const KvqCoder<NE> coder(pv.hdr->thr_k, pv.hdr->lut_k);
+    stage_lut<NE>(lut_s, pv.hdr->lut_k);
+    __syncthreads();
 
     const int tid = threadIdx.x;
     const int64_t n = n0 + t;
@@ -208,11 +254,10 @@ __device__ __forceinline__ void k_quant_token(const void *__restrict__ params, i
             const float x = kvq_h2f(xb[j]);
             const float diff = x - zc[j];
             const float xn = diff * ri[j];
-            float sp;
-            const int code = kvq_nearest<NE>(lut, xn, sp);
-            const float deq = __builtin_fmaf(sc[j], sp, zc[j]);
+            const int code = coder(xn);
             is_out[j] = (c < D) & ((x < lo[j]) | (x > hi[j]));
-            resid[j] = kvq_f2h_rn(x - deq);
+            resid[j] = 0;
+            if (is_out[j]) resid[j] = kvq_f2h_rn(x - __builtin_fmaf(sc[j], lut_s[code], zc[j]));
             codes_s[j][tid] = (uint8_t)code;
         }
         for (int i = tid; i < IT * HB * (CW + 1); i += NT) (&chunk_s[0][0][0])[i] = 0;
@@ -256,6 +301,97 @@ __device__ __forceinline__ void k_quant_token(const void *__restrict__ params, i
         k_ptr[n + 1] = (uint32_t)(p > (uint64_t)cap_nnz ? (uint64_t)cap_nnz : p);
     }
     if (overflow || (single && tid == 0 && (uint64_t)base + running > (uint64_t)cap_nnz))
+        atomicExch(d_status, (int32_t)KVQ_ERR_NNZ_OVERFLOW);
+}
+
+// The same for up to W * HW heads: W wavefronts, HW heads each, one pass and one workgroup barrier.  Lane l takes
+// channels l and l+64 of a head, the pair that shares a field, and a wavefront packs its heads' chunks on its
+// own; outliers keep channel order (within a head the lower channels, then the upper ones) by ballots, across
+// wavefronts by their counts.  A token is latency: what counts is the length of a lane's chain.  Measured (4096
+// channels, 4-bit codes, one token): see the launch rule.
+template <int BITS, int HW, int W, class SP>
+__device__ __forceinline__ void k_quant_token_w(const void *__restrict__ params, int D, int64_t cap, int64_t n0,
+                                                const uint16_t *__restrict__ k_new, uint8_t *__restrict__ k_codes,
+                                                uint32_t *__restrict__ k_ptr, const SP ksp, int64_t cap_nnz, int single,
+                                                int32_t *d_status, const int t)
+{
+    constexpr int NE = 1 << BITS;
+    constexpr int CW = 4 * BITS;                 // dwords per chunk
+    __shared__ uint32_t chunk_s[W][HW][CW + 1];
+    __shared__ uint32_t wave_tot[W];
+    __shared__ float lut_s[NE];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int H = D / KVQ_HEAD_DIM, h0 = wave * HW;
+    const KvqParamsView pv = kvq_params_view(params, D);
+    const int64_t n = n0 + t;
+    const uint32_t base = k_ptr[n];
+    // every load first; heads past the last one repeat it and store nothing
+    uint16_t xb[HW][2];
+    float z[HW][2], sc[HW][2], ri[HW][2], lo[HW][2], hi[HW][2];
+#pragma unroll
+    for (int i = 0; i < HW; ++i)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int h = h0 + i < H ? h0 + i : H - 1, c = h * KVQ_HEAD_DIM + 64 * u + lane;
+            xb[i][u] = k_new[(int64_t)t * D + c];
+            z[i][u] = pv.z[c]; sc[i][u] = pv.s[c]; ri[i][u] = pv.rinv[c]; lo[i][u] = pv.lo[c]; hi[i][u] = pv.hi[c];
+        }
+    const KvqCoder<NE> coder(pv.hdr->thr_k, pv.hdr->lut_k);
+    stage_lut<NE>(lut_s, pv.hdr->lut_k);
+    for (int e = lane; e < HW * (CW + 1); e += 64) (&chunk_s[wave][0][0])[e] = 0;
+    uint32_t mine = 0;
+    bool out[HW][2];
+#pragma unroll
+    for (int i = 0; i < HW; ++i)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const float x = kvq_h2f(xb[i][u]);
+            out[i][u] = (h0 + i < H) & ((x < lo[i][u]) | (x > hi[i][u]));
+            mine += (uint32_t)__popcll(__ballot(out[i][u]));
+        }
+    if (lane == 0) wave_tot[wave] = mine;
+    __syncthreads();
+    uint32_t running = 0, total = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const uint32_t c = wave_tot[w];
+        running += w < wave ? c : 0u;
+        total += c;
+    }
+    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    bool overflow = false;
+#pragma unroll
+    for (int i = 0; i < HW; ++i) {
+        if (h0 + i >= H) break;
+        int code[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const float x = kvq_h2f(xb[i][u]);
+            const float diff = x - z[i][u];
+            code[u] = coder(diff * ri[i][u]);
+            const unsigned long long b = __ballot(out[i][u]);
+            if (out[i][u]) {
+                const uint64_t pos = (uint64_t)base + running + (uint32_t)__popcll(b & lt_mask);
+                if (pos < (uint64_t)cap_nnz)
+                    ksp.put(pos, (uint16_t)((h0 + i) * KVQ_HEAD_DIM + 64 * u + lane),
+                            kvq_f2h_rn(x - __builtin_fmaf(sc[i][u], lut_s[code[u]], z[i][u])));
+                else overflow = true;
+            }
+            running += (uint32_t)__popcll(b);
+        }
+        stream_or(chunk_s[wave][i], lane * 2 * BITS, (uint32_t)code[0] | ((uint32_t)code[1] << BITS), 2 * BITS);
+    }
+    // LDS operations of one wavefront execute in order; the fence keeps the compiler from reordering them
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int e = lane; e < HW * CW; e += 64) {
+        const int i = e / CW, wd = e - i * CW;
+        if (h0 + i < H)
+            *(uint32_t *)(k_codes + kvq_k_piece0(BITS, cap, n, h0 + i) + (wd >> 2) * 1024 + (wd & 3) * 4) = chunk_s[wave][i][wd];
+    }
+    const uint64_t end = (uint64_t)base + total;
+    if (single && threadIdx.x == 0) k_ptr[n + 1] = (uint32_t)(end > (uint64_t)cap_nnz ? (uint64_t)cap_nnz : end);
+    if (overflow || (single && threadIdx.x == 0 && end > (uint64_t)cap_nnz))
         atomicExch(d_status, (int32_t)KVQ_ERR_NNZ_OVERFLOW);
 }
 
@@ -462,10 +598,10 @@ __device__ __forceinline__ void v_quant_token(const void *__restrict__ params, i
     __shared__ uint8_t codes_s[IT][NT];
     __shared__ uint32_t bits_s[IT][CB][CW + 1], mask_s[IT][CB][CW + 1];
 
+    __shared__ float lut_s[NE];
     KvqParamsView pv = kvq_params_view(params, D);
-    float lut[NE];
-#pragma unroll
-    for (int j = 0; j < NE; ++j) lut[j] = pv.hdr->lut_v[j];
+    const KvqCoder<NE> coder(pv.hdr->thr_v, pv.hdr->lut_v);
+    stage_lut<NE>(lut_s, pv.hdr->lut_v);             // (visible after the barriers of the selection)
     const int tid = threadIdx.x;
     const int64_t n = n0 + t;
     const uint16_t *x16 = v_new + (int64_t)t * D;
@@ -528,11 +664,10 @@ __device__ __forceinline__ void v_quant_token(const void *__restrict__ params, i
             const float x = kvq_h2f(cb == 0 ? xc[j] : x16[cc]);      // the first pass has its elements in registers
             const float diff = x - zf;
             const float xn = diff * rinv;
-            float sp;
-            const int code = kvq_nearest<NE>(lut, xn, sp);
-            const float deq = __builtin_fmaf(sf, sp, zf);
+            const int code = coder(xn);
             is_out[j] = (c < D) && state[cc] != 0;
-            resid[j] = kvq_f2h_rn(x - deq);
+            resid[j] = 0;
+            if (is_out[j]) resid[j] = kvq_f2h_rn(x - __builtin_fmaf(sf, lut_s[code], zf));
             codes_s[j][tid] = (uint8_t)code;
         }
         for (int i = tid; i < IT * CB * (CW + 1); i += NT) { (&bits_s[0][0][0])[i] = 0; (&mask_s[0][0][0])[i] = 0; }
@@ -606,13 +741,14 @@ __global__ __launch_bounds__(KVQ_KW_NT) void kvq_k_quant_wave(const void *__rest
     constexpr int NE = 1 << BITS;
     constexpr int CW = 4 * BITS;                 // dwords per chunk
     __shared__ uint32_t chunk_s[KVQ_KW_NT / 64][CW + 1];
+    __shared__ float lut_s[NE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t = blockIdx.x * (KVQ_KW_NT / 64) + wave;
-    if (t >= T) return;                          // whole wavefronts leave; there is no workgroup barrier below
     KvqParamsView pv = kvq_params_view(params, D);
-    float lut[NE];
-#pragma unroll
-    for (int j = 0; j < NE; ++j) lut[j] = pv.hdr->lut_k[j];
+    const KvqCoder<NE> coder(pv.hdr->thr_k, pv.hdr->lut_k);
+    stage_lut<NE>(lut_s, pv.hdr->lut_k);
+    __syncthreads();
+    if (t >= T) return;                          // whole wavefronts leave; there is no workgroup barrier below
     const int64_t n = n0 + t;
     const uint32_t base = k_ptr[n];
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
@@ -627,11 +763,13 @@ __global__ __launch_bounds__(KVQ_KW_NT) void kvq_k_quant_wave(const void *__rest
         const float z1 = pv.z[c1], s1 = pv.s[c1], r1 = pv.rinv[c1], lo1 = pv.lo[c1], hi1 = pv.hi[c1];
         if (lane <= CW) chunk[lane] = 0;
         const float x0 = kvq_h2f(xb0), x1 = kvq_h2f(xb1);
-        float sp0, sp1;
         const float d0 = x0 - z0, d1 = x1 - z1;
-        const int code0 = kvq_nearest<NE>(lut, d0 * r0, sp0);
-        const int code1 = kvq_nearest<NE>(lut, d1 * r1, sp1);
-        const float deq0 = __builtin_fmaf(s0, sp0, z0), deq1 = __builtin_fmaf(s1, sp1, z1);
+        const float xn0 = d0 * r0, xn1 = d1 * r1;
+        int code0 = coder.count(xn0), code1 = coder.count(xn1);
+        if (__ballot(coder.far(xn0) | coder.far(xn1)) != 0ull) {
+            if (coder.far(xn0)) code0 = coder.search(xn0);
+            if (coder.far(xn1)) code1 = coder.search(xn1);
+        }
         const bool o0 = (x0 < lo0) | (x0 > hi0), o1 = (x1 < lo1) | (x1 > hi1);
         // outliers of this head in channel order
         const unsigned long long b0 = __ballot(o0), b1 = __ballot(o1);
@@ -641,12 +779,12 @@ __global__ __launch_bounds__(KVQ_KW_NT) void kvq_k_quant_wave(const void *__rest
         running += (uint32_t)__popcll(b1);
         if (o0) {
             const uint64_t pos = (uint64_t)base + rank0;
-            if (pos < (uint64_t)cap_nnz) ksp.put(pos, (uint16_t)c0, kvq_f2h_rn(x0 - deq0));
+            if (pos < (uint64_t)cap_nnz) ksp.put(pos, (uint16_t)c0, kvq_f2h_rn(x0 - __builtin_fmaf(s0, lut_s[code0], z0)));
             else overflow = true;
         }
         if (o1) {
             const uint64_t pos = (uint64_t)base + rank1;
-            if (pos < (uint64_t)cap_nnz) ksp.put(pos, (uint16_t)c1, kvq_f2h_rn(x1 - deq1));
+            if (pos < (uint64_t)cap_nnz) ksp.put(pos, (uint16_t)c1, kvq_f2h_rn(x1 - __builtin_fmaf(s1, lut_s[code1], z1)));
             else overflow = true;
         }
         // the head's chunk: 64 fields of 2*BITS bits, assembled in the wavefront's LDS slice (LDS
@@ -671,125 +809,201 @@ __global__ __launch_bounds__(KVQ_KW_NT) void kvq_k_quant_wave(const void *__rest
 // 20, 26 or 32).  Wavefront w takes the channel groups j = w JW .. (w + 1) JW - 1, lane l of it the channels
 // 64 j + l (half j & 1 of head j >> 1), so a wavefront packs whole chunks on its own, channel order is
 // wavefront order, and a lane keeps its JW elements in registers from the one load to the end.  The
-// selection is the two-level radix selection of select_both on histograms shared by the four
-// wavefronts (each reads the bins it needs itself); equal keys at a threshold are taken in channel
-// order, ranked with ballots and the wavefronts' counts, and when the two thresholds coincide the
+// thresholds of the selection are found among the few keys that pass a bound (or, where these are too
+// many, by a two-level radix selection on histograms shared by the wavefronts); equal keys at a threshold
+// are taken in channel order, ranked with ballots and the wavefronts' counts, and when the two thresholds coincide the
 // upper outliers take the first of the equal keys and the lower ones the next, which is what taking
 // the k largest first and then the k smallest of the rest comes to.  The packed codes of all JW chunks
-// are gathered in the wavefront's LDS slice and written by all 64 lanes at the end.  Five workgroup
-// barriers per token (six when equal keys must be ranked).  Same arithmetic, same results, as
+// are gathered in the wavefront's LDS slice and written by all 64 lanes at the end.  Four workgroup
+// barriers per token (five when equal keys must be ranked).  Same arithmetic, same results, as
 // v_quant_token.
 // W wavefronts per token instead of four (D = 64 W JW): the same routine with fewer elements per lane,
 // for calls of a few tokens, where the time of a token is the length of a lane's instruction stream
 // (a 4096-channel token: 16 elements per lane on four wavefronts, 4 on sixteen).
 constexpr int KVQ_VW_WAVES = 4;
+constexpr int KVQ_V_CAND = 128;              // candidates per side that a wavefront looks through (two per lane)
 constexpr int KVQ_VW_NT = 64 * KVQ_VW_WAVES;
 constexpr int KVQ_VW_SMALL_TOKENS = 64;      // calls below this many tokens use one lane per four elements
-template <int BITS, int JW, int W, class SP>
+template <int BITS, int JW, int W, int TOK, class SP>
 __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, int D, int64_t cap, int64_t n0,
                                                int k_side, const uint16_t *__restrict__ v_new,
                                                uint8_t *__restrict__ v_codes, uint16_t *__restrict__ v_sz,
                                                uint32_t *__restrict__ v_ptr, const SP vsp, int64_t cap_nnz, int32_t *d_status,
-                                               const int t)
+                                               const int first, const int T)
 {
     constexpr int NE = 1 << BITS;
     constexpr int CW = 4 * BITS;
-    constexpr int NTW = 64 * W;                  // threads that work on the token
-    constexpr int WB = W < 4 ? W : 4;            // wavefronts whose lane extremes bound the thresholds
-    __shared__ __attribute__((aligned(16))) uint32_t hist[768];
-    __shared__ uint32_t bits_s[W][JW][CW + 1], mask_s[W][CW + 1];
-    __shared__ uint32_t eq_cnt[W][2], out_cnt[W];
-    __shared__ uint16_t lane_max[NTW], lane_min[NTW];
-    __shared__ float red_mx[W], red_mn[W];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    constexpr int NTW = 64 * W;                  // threads that work on a token
+    __shared__ __attribute__((aligned(16))) uint32_t hist_s[TOK][768];
+    __shared__ uint32_t bits_s[W][JW][CW + 1], mask_s[TOK][W][CW + 1];
+    __shared__ uint32_t eq_cnt_s[TOK][W][2], out_cnt_s[TOK][W];
+    // the largest keys of the 64 columns (lane l of every wavefront), of the keys and of their complements; the
+    // candidates of either side and how many there are
+    __shared__ uint32_t col_max_s[TOK][2][64], n_cand_s[TOK][2];
+    __shared__ uint16_t cand_s[TOK][2][KVQ_V_CAND];
+    __shared__ float red_mx_s[TOK][W], red_mn_s[TOK][W];
+    // wavefronts 0 .. W-1 take the pair's first token, the next W its second; `wave`: within the token
+    const int lane = threadIdx.x & 63;
+    const int tok = TOK == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / NTW));
+    const int wave = (int)(threadIdx.x >> 6) - tok * W, ttid = (int)threadIdx.x - tok * NTW;
+    uint32_t *hist = hist_s[tok];
+    uint32_t(*eq_cnt)[2] = eq_cnt_s[tok];
+    uint32_t *out_cnt = out_cnt_s[tok];
+    uint32_t(*col_max)[64] = col_max_s[tok];
+    uint32_t *n_cand = n_cand_s[tok];
+    uint16_t(*cand)[KVQ_V_CAND] = cand_s[tok];
+    float *red_mx = red_mx_s[tok], *red_mn = red_mn_s[tok];
     uint32_t(*bits)[CW + 1] = bits_s[wave];
-    uint32_t *mask = mask_s[wave];
+    uint32_t *mask = mask_s[tok][wave];
+    __shared__ float lut_s[NE];
     KvqParamsView pv = kvq_params_view(params, D);
-    float lut[NE];
-#pragma unroll
-    for (int j = 0; j < NE; ++j) lut[j] = pv.hdr->lut_v[j];
+    const KvqCoder<NE> coder(pv.hdr->thr_v, pv.hdr->lut_v);
+    stage_lut<NE>(lut_s, pv.hdr->lut_v);         // (visible after the barrier that follows the ranges)
+    if (ttid < 64) {
+        col_max[0][ttid] = 0u;
+        col_max[1][ttid] = 0u;
+        if (ttid < 2) n_cand[ttid] = 0u;
+    }
+    // the wavefronts' packing areas, cleared here and filled after the barrier that follows the ranges
+    for (int e = threadIdx.x; e < W * JW * (CW + 1); e += TOK * NTW) (&bits_s[0][0][0])[e] = 0;
+    if (lane <= CW) mask[lane] = 0;
+    __syncthreads();
     const int jb = wave * JW;                    // this wavefront's first channel group (D = 64 W JW)
+    // Two tokens of a pair share the dwords of their codes.  TOK = 2: the workgroup has both (or, at either end
+    // of the call, one: the other's wavefronts then repeat its work and store nothing).
+    const int t_mine = TOK == 1 ? first : 2 * first + tok - (int)(n0 & 1);
+    const bool valid = TOK == 1 || (t_mine >= 0 && t_mine < T);
+    const int t = valid ? t_mine : (tok == 0 ? t_mine + 1 : t_mine - 1);
     const int64_t n = n0 + t;
     const uint16_t *x16 = v_new + (int64_t)t * D + lane;
     const uint32_t base = v_ptr[n0] + (uint32_t)t * 2u * (uint32_t)k_side;
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
     const uint32_t K = (uint32_t)k_side;
 
-    // the wavefront's packing area, cleared here and filled after the barrier that follows the ranges
-    for (int e = lane; e < JW * (CW + 1); e += 64) (&bits[0][0])[e] = 0;
-    if (lane <= CW) mask[lane] = 0;
     uint16_t xc[JW];                             // this lane's elements, kept in registers
 #pragma unroll
     for (int i = 0; i < JW; ++i) xc[i] = x16[64 * (jb + i)];
 
     uint32_t top = 0, bot = 0;                   // bit i: channel 64 (jb + i) + lane is an upper / lower outlier
     static_assert(JW <= 32, "one mask bit per element of a lane");
+    uint32_t kc[JW];                             // the elements' order-preserving keys
+    uint32_t kmax = 0, kmin = 0xffffu;           // this lane's extremes
+#pragma unroll
+    for (int i = 0; i < JW; ++i) {
+        const uint32_t key = order_key(xc[i]);
+        kc[i] = key;
+        kmax = key > kmax ? key : kmax;
+        kmin = key < kmin ? key : kmin;
+    }
     if (K > 0) {
-        for (int i = threadIdx.x; i < 768; i += NTW) hist[i] = 0;
-        // Only the tails go into the histograms (shared-memory atomics on the few bins that hold the
-        // bulk of a token would serialize).  The K-th largest of the 64 W lanes' largest keys is a lower
-        // bound of the K-th largest key of the token, since that many elements are at least as large;
-        // likewise for the smallest.  Every wavefront finds both bounds by bisection over the 16 key
-        // bits, with ballots.  Histogram counts are then exact from the bounds outwards, which is all
-        // the searches below read.  More outliers per side than lanes: no bound, every key counts.
-        uint32_t kc[JW];                         // the elements' order-preserving keys
-#pragma unroll
-        for (int i = 0; i < JW; ++i) kc[i] = order_key(xc[i]);
-        uint32_t kmax = 0, kmin = 0xffffu;
-#pragma unroll
-        for (int i = 0; i < JW; ++i) {
-            const uint32_t key = kc[i];
-            kmax = key > kmax ? key : kmax;
-            kmin = key < kmin ? key : kmin;
-        }
-        lane_max[threadIdx.x] = (uint16_t)kmax;
-        lane_min[threadIdx.x] = (uint16_t)kmin;
+        // Bounds of the thresholds.  The K-th largest of the 64 columns' largest keys is a lower bound of the
+        // token's K-th largest key, since that many elements are at least as large; likewise for the smallest.
+        // Every wavefront finds both by bisection over the 16 key bits, with ballots.  (More outliers per side
+        // than columns: no bound, every key passes.)
+        atomicMax(&col_max[0][lane], kmax);
+        atomicMax(&col_max[1][lane], 0xffffu - kmin);
         __syncthreads();
         uint32_t m_top = 0, m_bot = 0xffffu;
-        if (K <= (uint32_t)(64 * WB)) {
-            // (the lanes of the first WB wavefronts are enough: the K-th largest of ANY 64 WB elements
-            // of the token is a lower bound of its K-th largest key)
-            uint32_t vt[WB], vb[WB];
-#pragma unroll
-            for (int r = 0; r < WB; ++r) { vt[r] = lane_max[lane + 64 * r]; vb[r] = 0xffffu - lane_min[lane + 64 * r]; }
+        if (K <= 64u) {
+            const uint32_t ct = col_max[0][lane], cb = col_max[1][lane];
             uint32_t inv_bot = 0;
             for (int bit = 15; bit >= 0; --bit) {
-                const uint32_t ct = m_top | (1u << bit), cb = inv_bot | (1u << bit);
-                uint32_t nt = 0, nb = 0;
-#pragma unroll
-                for (int r = 0; r < WB; ++r) {
-                    nt += (uint32_t)__popcll(__ballot(vt[r] >= ct));
-                    nb += (uint32_t)__popcll(__ballot(vb[r] >= cb));
-                }
-                if (nt >= K) m_top = ct;
-                if (nb >= K) inv_bot = cb;
+                const uint32_t mt = m_top | (1u << bit), mb = inv_bot | (1u << bit);
+                if ((uint32_t)__popcll(__ballot(ct >= mt)) >= K) m_top = mt;
+                if ((uint32_t)__popcll(__ballot(cb >= mb)) >= K) inv_bot = mb;
             }
             m_bot = 0xffffu - inv_bot;
         }
+        // The few keys on and beyond the bounds (24 a side are expected of 4096 for K = 20) are collected,
+        // in any order, and the thresholds are found among them.
+        uint32_t which = 0;                      // bit i: element i is a candidate
 #pragma unroll
-        for (int i = 0; i < JW; ++i) {
-            const uint32_t key = kc[i];
-            if (key >= m_top || key <= m_bot) atomicAdd(&hist[key >> 8], 1u);
+        for (int i = 0; i < JW; ++i) which |= (kc[i] >= m_top || kc[i] <= m_bot) ? (1u << i) : 0u;
+        while (__ballot(which != 0u) != 0ull) {  // (most lanes have none, hardly any more than two)
+            if (which != 0u) {
+                const int i = __ffs((int)which) - 1;
+                which &= which - 1u;
+                const uint32_t key = order_key(x16[64 * (jb + i)]);      // (re-read: a dynamic index)
+                if (key >= m_top) {
+                    const uint32_t at = atomicAdd(&n_cand[0], 1u);
+                    if (at < KVQ_V_CAND) cand[0][at] = (uint16_t)key;
+                }
+                if (key <= m_bot) {
+                    const uint32_t at = atomicAdd(&n_cand[1], 1u);
+                    if (at < KVQ_V_CAND) cand[1][at] = (uint16_t)(0xffffu - key);
+                }
+            } else {
+                which = 0u;
+            }
         }
         __syncthreads();
-        uint32_t bin_top, above_top, in_top, bin_bot, below_bot, in_bot;
-        wave_find_bin<true>(hist, K, lane, bin_top, above_top, in_top);
-        wave_find_bin<false>(hist, K, lane, bin_bot, below_bot, in_bot);
-#pragma unroll
-        for (int i = 0; i < JW; ++i) {
-            const uint32_t key = kc[i];
-            if ((key >> 8) == bin_top && key >= m_top) atomicAdd(&hist[256 + (key & 255u)], 1u);
-            if ((key >> 8) == bin_bot && key <= m_bot) atomicAdd(&hist[512 + (key & 255u)], 1u);
+        uint32_t tau_top, tau_bot, need_top, need_bot, n_eq_top, n_eq_bot;
+        const uint32_t nt = n_cand[0], nb = n_cand[1];
+        bool few = nt <= KVQ_V_CAND && nb <= KVQ_V_CAND;
+        if (TOK == 2) {                          // (barriers below: both tokens take the same way)
+            const uint32_t *other = n_cand_s[TOK - 1 - tok];
+            few = few && other[0] <= KVQ_V_CAND && other[1] <= KVQ_V_CAND;
         }
-        __syncthreads();
-        uint32_t lo_top, above_in, n_eq_top, lo_bot, below_in, n_eq_bot;
-        wave_find_bin<true>(hist + 256, K - above_top, lane, lo_top, above_in, n_eq_top);
-        wave_find_bin<false>(hist + 512, K - below_bot, lane, lo_bot, below_in, n_eq_bot);
-        const uint32_t tau_top = (bin_top << 8) | lo_top, tau_bot = (bin_bot << 8) | lo_bot;
-        const uint32_t need_top = K - (above_top + above_in), need_bot = K - (below_bot + below_in);
+        if (few) {
+            // K-th largest candidate of either list, bit by bit (a list has at least K entries)
+            uint32_t vt[KVQ_V_CAND / 64], vb[KVQ_V_CAND / 64];
+            constexpr int R = KVQ_V_CAND / 64;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const uint32_t e = (uint32_t)lane + 64u * r;
+                vt[r] = e < nt ? cand[0][e] + 1u : 0u;       // + 1: an absent entry is below every key
+                vb[r] = e < nb ? cand[1][e] + 1u : 0u;
+            }
+            auto at_least = [&](const uint32_t (&v)[R], uint32_t x) {
+                uint32_t c = 0;
+#pragma unroll
+                for (int r = 0; r < R; ++r) c += (uint32_t)__popcll(__ballot(v[r] >= x));
+                return c;
+            };
+            uint32_t tt = 0, tb = 0;
+            for (int bit = 16; bit >= 0; --bit) {
+                if (at_least(vt, tt | (1u << bit)) >= K) tt |= 1u << bit;
+                if (at_least(vb, tb | (1u << bit)) >= K) tb |= 1u << bit;
+            }
+            const uint32_t beyond_t = at_least(vt, tt + 1u), beyond_b = at_least(vb, tb + 1u);
+            n_eq_top = at_least(vt, tt) - beyond_t;
+            n_eq_bot = at_least(vb, tb) - beyond_b;
+            tau_top = tt - 1u;
+            tau_bot = 0xffffu - (tb - 1u);
+            need_top = K - beyond_t;
+            need_bot = K - beyond_b;
+        } else {
+            // Many equal keys, or more outliers per side than the bounds serve: radix selection on histograms,
+            // of the keys that passed.  Counts are exact from the bounds outwards, which is all the searches read.
+            for (int i = ttid; i < 768; i += NTW) hist[i] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < JW; ++i) {
+                const uint32_t key = kc[i];
+                if (key >= m_top || key <= m_bot) atomicAdd(&hist[key >> 8], 1u);
+            }
+            __syncthreads();
+            uint32_t bin_top, above_top, in_top, bin_bot, below_bot, in_bot;
+            wave_find_bin<true>(hist, K, lane, bin_top, above_top, in_top);
+            wave_find_bin<false>(hist, K, lane, bin_bot, below_bot, in_bot);
+#pragma unroll
+            for (int i = 0; i < JW; ++i) {
+                const uint32_t key = kc[i];
+                if ((key >> 8) == bin_top && key >= m_top) atomicAdd(&hist[256 + (key & 255u)], 1u);
+                if ((key >> 8) == bin_bot && key <= m_bot) atomicAdd(&hist[512 + (key & 255u)], 1u);
+            }
+            __syncthreads();
+            uint32_t lo_top, above_in, lo_bot, below_in;
+            wave_find_bin<true>(hist + 256, K - above_top, lane, lo_top, above_in, n_eq_top);
+            wave_find_bin<false>(hist + 512, K - below_bot, lane, lo_bot, below_in, n_eq_bot);
+            tau_top = (bin_top << 8) | lo_top;
+            tau_bot = (bin_bot << 8) | lo_bot;
+            need_top = K - (above_top + above_in);
+            need_bot = K - (below_bot + below_in);
+        }
         const bool same = tau_top == tau_bot;
-        // ranks of equal keys are only needed when some but not all of them are taken (wavefront-uniform,
-        // and the same in all four wavefronts: the barrier inside is reached by all or none)
+        // ranks of equal keys are only needed when some but not all of them are taken (the same in all of a
+        // token's wavefronts; with two tokens the barrier is reached whatever either needs)
         const bool ranked = same || need_top != n_eq_top || need_bot != n_eq_bot;
         uint32_t run_top = 0, run_bot = 0;       // equal keys before this wavefront's channels, then running
         if (ranked) {
@@ -801,9 +1015,11 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
                 cb += (uint32_t)__popcll(__ballot(key == tau_bot));
             }
             if (lane == 0) { eq_cnt[wave][0] = ct; eq_cnt[wave][1] = cb; }
-            __syncthreads();
-            for (int w = 0; w < wave; ++w) { run_top += eq_cnt[w][0]; run_bot += eq_cnt[w][1]; }
+            if (TOK == 1) __syncthreads();
         }
+        if (TOK == 2) __syncthreads();
+        if (ranked)
+            for (int w = 0; w < wave; ++w) { run_top += eq_cnt[w][0]; run_bot += eq_cnt[w][1]; }
 #pragma unroll
         for (int i = 0; i < JW; ++i) {
             const uint32_t key = kc[i];
@@ -851,46 +1067,64 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
     float zf = kvq_h2f(zb), sf = kvq_h2f(sb);
     if (sf == 0.0f) { sf = 1.0f; sb = 0x3c00u; }
     const float rinv = __fdiv_rn(1.0f, sf);
-    if (threadIdx.x == 0) { v_sz[n * 2 + 0] = sb; v_sz[n * 2 + 1] = zb; }
+    if (ttid == 0 && valid) { v_sz[n * 2 + 0] = sb; v_sz[n * 2 + 1] = zb; }
 
     const int parity = (int)(n & 1);
     bool overflow = false;
+    auto encode = [&](auto calm) {
 #pragma unroll
-    for (int i = 0; i < JW; ++i) {
-        const int j = jb + i;
-        const float x = kvq_h2f(xc[i]);
-        const float diff = x - zf;
-        const float xn = diff * rinv;
-        float sp;
-        const int code = kvq_nearest<NE>(lut, xn, sp);
-        const float deq = __builtin_fmaf(sf, sp, zf);
-        const bool is_out = (outl >> i) & 1u;
-        const unsigned long long b = __ballot(is_out);
-        if (is_out) {
-            const uint64_t pos = (uint64_t)base + running + (uint32_t)__popcll(b & lt_mask);
-            if (pos < (uint64_t)cap_nnz) vsp.put(pos, (uint16_t)(64 * j + lane), kvq_f2h_rn(x - deq));
-            else overflow = true;
+        for (int i = 0; i < JW; ++i) {
+            const int j = jb + i;
+            const float x = kvq_h2f(xc[i]);
+            const float diff = x - zf;
+            const float xn = diff * rinv;
+            const int code = decltype(calm)::value ? coder.count(xn) : coder(xn);
+            const bool is_out = (outl >> i) & 1u;
+            const unsigned long long b = __ballot(is_out);
+            if (is_out && valid) {
+                const uint64_t pos = (uint64_t)base + running + (uint32_t)__popcll(b & lt_mask);
+                if (pos < (uint64_t)cap_nnz)
+                    vsp.put(pos, (uint16_t)(64 * j + lane), kvq_f2h_rn(x - __builtin_fmaf(sf, lut_s[code], zf)));
+                else overflow = true;
+            }
+            running += (uint32_t)__popcll(b);
+            // the chunk of (head j >> 1, half j & 1): this token's bits of 64 fields, gathered in the
+            // wavefront's own LDS slice
+            if (valid) stream_or(bits[i], lane * 2 * BITS + parity * BITS, (uint32_t)code, BITS);
         }
-        running += (uint32_t)__popcll(b);
-        // the chunk of (head j >> 1, half j & 1): this token's bits of 64 fields, gathered in the
-        // wavefront's own LDS slice
-        stream_or(bits[i], lane * 2 * BITS + parity * BITS, (uint32_t)code, BITS);
+    };
+    // (normalising is monotone: a lane whose extremes are in the coder's range has all its elements there)
+    const float d_hi = key_value(kmax) - zf, d_lo = key_value(kmin) - zf;
+    if (__ballot(coder.far(d_hi * rinv) || coder.far(d_lo * rinv)) == 0ull) encode(std::true_type{});
+    else encode(std::false_type{});
+    if (TOK == 2) {
+        __syncthreads();                         // both tokens' codes are in the packing areas
+        if (T - 2 * first + (int)(n0 & 1) >= 2 && 2 * first >= (int)(n0 & 1)) {
+            // both tokens of the pair: whole dwords
+            for (int e = threadIdx.x; e < W * JW * CW; e += TOK * NTW) {
+                const int j = e / CW, d = e - j * CW;
+                *(uint32_t *)(v_codes + kvq_v_piece0(BITS, cap, n >> 1, j >> 1, j & 1) + (d >> 2) * 1024 + (d & 3) * 4) =
+                    bits_s[j / JW][j % JW][d];
+            }
+        }
     }
-    stream_or(mask, lane * 2 * BITS + parity * BITS, (uint32_t)(NE - 1), BITS);
-    // LDS operations of one wavefront execute in order; the fence keeps the compiler from moving the
-    // reads below above the atomics
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    for (int e = lane; e < JW * CW; e += 64) {
-        const int i = e / CW, d = e - i * CW, j = jb + i;
-        const int64_t off = kvq_v_piece0(BITS, cap, n >> 1, j >> 1, j & 1) + (d >> 2) * 1024 + (d & 3) * 4;
-        uint32_t *p = (uint32_t *)(v_codes + off);
-        // the partner token of the pair owns the other bits of this dword: clear this token's bits, then
-        // set them, with two atomics that return nothing (as in v_quant_token)
-        __hip_atomic_fetch_and(p, ~mask[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_or(p, bits[i][d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (TOK == 1 || (valid && (2 * first < (int)(n0 & 1) || T - 2 * first + (int)(n0 & 1) < 2))) {
+        stream_or(mask, lane * 2 * BITS + parity * BITS, (uint32_t)(NE - 1), BITS);
+        // LDS operations of one wavefront execute in order; the fence keeps the compiler from moving the
+        // reads below above the atomics
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int e = lane; e < JW * CW; e += 64) {
+            const int i = e / CW, d = e - i * CW, j = jb + i;
+            const int64_t off = kvq_v_piece0(BITS, cap, n >> 1, j >> 1, j & 1) + (d >> 2) * 1024 + (d & 3) * 4;
+            uint32_t *p = (uint32_t *)(v_codes + off);
+            // the partner token of the pair owns the other bits of this dword: clear this token's bits, then
+            // set them, with two atomics that return nothing (as in v_quant_token)
+            __hip_atomic_fetch_and(p, ~mask[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_or(p, bits[i][d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
-    if (threadIdx.x == 0) {
+    if (ttid == 0 && valid) {
         uint64_t p = (uint64_t)base + 2u * (uint32_t)k_side;
         if (p > (uint64_t)cap_nnz) { p = (uint64_t)cap_nnz; overflow = true; }
         v_ptr[n + 1] = (uint32_t)p;
@@ -898,26 +1132,29 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
     if (overflow) atomicExch(d_status, (int32_t)KVQ_ERR_NNZ_OVERFLOW);
 }
 
-template <int BITS, int JW, int W, class SP>
-__global__ __launch_bounds__(64 * W) void kvq_v_quant4(const void *__restrict__ params, int D, int64_t cap,
-                                                          int64_t n0, int k_side, const uint16_t *__restrict__ v_new,
+template <int BITS, int JW, int W, int TOK, class SP>
+__global__ __launch_bounds__(64 * W * TOK) void kvq_v_quant4(const void *__restrict__ params, int D, int64_t cap,
+                                                          int64_t n0, int T, int k_side,
+                                                          const uint16_t *__restrict__ v_new,
                                                           uint8_t *__restrict__ v_codes, uint16_t *__restrict__ v_sz,
                                                           uint32_t *__restrict__ v_ptr, const SP vsp, int64_t cap_nnz,
                                                           int32_t *d_status)
 {
-    v_quant_token4<BITS, JW, W>(params, D, cap, n0, k_side, v_new, v_codes, v_sz, v_ptr, vsp, cap_nnz, d_status,
-                                (int)blockIdx.x);
+    v_quant_token4<BITS, JW, W, TOK>(params, D, cap, n0, k_side, v_new, v_codes, v_sz, v_ptr, vsp, cap_nnz, d_status,
+                                     (int)blockIdx.x, T);
 }
 
-template <int BITS, int NT, class SP>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 256 ? 8 : 4)))
-void kvq_k_quant(const void *__restrict__ params, int D, int64_t cap, int64_t n0,
-                                                  const uint16_t *__restrict__ k_new, uint8_t *__restrict__ k_codes,
-                                                  uint32_t *__restrict__ k_ptr, const SP ksp, int64_t cap_nnz, int single,
-                                                  int32_t *d_status)
+// HW = 0: the body for any number of heads.
+template <int BITS, int HW, int W, class SP>
+__global__ __launch_bounds__(64 * W) void kvq_k_quant(const void *__restrict__ params, int D, int64_t cap, int64_t n0,
+                                                      const uint16_t *__restrict__ k_new, uint8_t *__restrict__ k_codes,
+                                                      uint32_t *__restrict__ k_ptr, const SP ksp, int64_t cap_nnz, int single,
+                                                      int32_t *d_status)
 {
-    k_quant_token<BITS, NT>(params, D, cap, n0, k_new, k_codes, k_ptr, ksp, cap_nnz, single, d_status,
-                            (int)blockIdx.x);
+    if constexpr (HW == 0)
+        k_quant_token<BITS, 64 * W>(params, D, cap, n0, k_new, k_codes, k_ptr, ksp, cap_nnz, single, d_status, (int)blockIdx.x);
+    else
+        k_quant_token_w<BITS, HW, W>(params, D, cap, n0, k_new, k_codes, k_ptr, ksp, cap_nnz, single, d_status, (int)blockIdx.x);
 }
 
 template <int BITS, int NT, class SP>
@@ -949,21 +1186,34 @@ template <int BITS, int NT, class SP>
 __global__ __launch_bounds__(NT) void kvq_kv_quant(const KvAppendArgs<SP> a)
 {
     const int t = (int)(blockIdx.x >> 1);
-    if ((blockIdx.x & 1) == 0)
-        k_quant_token<BITS, NT>(a.params, a.D, a.cap, a.n0_k, a.k_new, a.k_codes, a.k_ptr, a.ksp, a.cap_nnz_k,
-                                a.single, a.d_status, t);
-    else if (a.D == 4096 || a.D == 2048 || a.D == 1024) {
+    if ((blockIdx.x & 1) == 0) {
+        // a workgroup's wavefronts share out the heads (see the launch rule of kvq_quantize_append_k)
+        constexpr int W = NT / 64;
+        const int hw = (a.D / KVQ_HEAD_DIM + W - 1) / W;
+#define KW(HW)                                                                                                  \
+    k_quant_token_w<BITS, HW, W>(a.params, a.D, a.cap, a.n0_k, a.k_new, a.k_codes, a.k_ptr, a.ksp, a.cap_nnz_k,  \
+                                 a.single, a.d_status, t)
+        if (hw == 1) KW(1);
+        else if (hw == 2) KW(2);
+        else if (hw == 3) KW(3);
+        else if (hw == 4) KW(4);
+        else
+            k_quant_token<BITS, NT>(a.params, a.D, a.cap, a.n0_k, a.k_new, a.k_codes, a.k_ptr, a.ksp, a.cap_nnz_k,
+                                    a.single, a.d_status, t);
+#undef KW
+    } else if (a.D == 4096 || a.D == 2048 || a.D == 1024 || (NT == 1024 && a.D == 5120)) {
         // the routine with one workgroup per token; wavefronts of the workgroup it does not use end here
         // (a barrier waits only for the wavefronts that have not ended).  A wide workgroup puts sixteen
         // (4096 channels) or eight (2048) wavefronts on the token, a narrow one four.
 #define V4(J, WV)                                                                                                \
     do {                                                                                                         \
         if (threadIdx.x >= 64 * (WV)) return;                                                                    \
-        v_quant_token4<BITS, J, WV>(a.params, a.D, a.cap, a.n0_v, a.k_side, a.v_new, a.v_codes, a.v_sz, a.v_ptr, \
-                                    a.vsp, a.cap_nnz_v, a.d_status, t);                                          \
+        v_quant_token4<BITS, J, WV, 1>(a.params, a.D, a.cap, a.n0_v, a.k_side, a.v_new, a.v_codes, a.v_sz, a.v_ptr, \
+                                       a.vsp, a.cap_nnz_v, a.d_status, t, 0);                                    \
     } while (0)
         if (NT == 1024) {
             if (a.D == 4096) V4(4, 16);
+            else if (a.D == 5120) V4(5, 16);
             else if (a.D == 2048) V4(4, 8);
             else V4(4, 4);
         } else {
@@ -1000,18 +1250,17 @@ struct StepFrontArgs {
     float *scores;
     int64_t ld, tokens_per_wave;
 };
-constexpr int KVQ_STEP_K_NT = 256;        // threads of workgroup 0 that work
 
-// Sparse part of the scores of token a.n, whose entries threads 0 .. KVQ_STEP_K_NT-1 of this workgroup
+// Sparse part of the scores of token a.n, whose entries the NT threads left in this workgroup
 // have just stored: scale * v * (R_n^T q)_c summed per query head, as the sparse kernel does for the
 // other tokens (same arithmetic per entry; 64-bit fixed-point sums in LDS).
-template <int R>
+template <int R, int NT>
 __device__ __forceinline__ void qk_sparse_new_token(const StepFrontArgs &a)
 {
     extern __shared__ __attribute__((aligned(16))) float sparse_dyn[];
     unsigned long long *S = (unsigned long long *)sparse_dyn;            // [n_q_heads]
     const int tid = threadIdx.x;
-    for (int j = tid; j < a.n_q_heads; j += KVQ_STEP_K_NT) S[j] = 0ull;
+    for (int j = tid; j < a.n_q_heads; j += NT) S[j] = 0ull;
     // the workgroup's stores of the token's entries and of its end pointer are complete ...
     __threadfence_block();
     __syncthreads();
@@ -1019,7 +1268,7 @@ __device__ __forceinline__ void qk_sparse_new_token(const StepFrontArgs &a)
     const uint32_t p0 = __hip_atomic_load(a.k_ptr + a.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint32_t p1 = __hip_atomic_load(a.k_ptr + a.n + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const KvqParamsView pv = kvq_params_view(a.params, a.D);
-    for (uint32_t e = p0 + (uint32_t)tid; e < p1; e += KVQ_STEP_K_NT) {
+    for (uint32_t e = p0 + (uint32_t)tid; e < p1; e += NT) {
         const uint32_t ch = __hip_atomic_load(a.ksp.idx + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const float v = kvq_h2f(__hip_atomic_load(a.ksp.val + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
         const uint32_t i = ch & 63u;
@@ -1038,7 +1287,7 @@ __device__ __forceinline__ void qk_sparse_new_token(const StepFrontArgs &a)
         }
     }
     __syncthreads();
-    for (int j = tid; j < a.n_q_heads; j += KVQ_STEP_K_NT) a.scores[(int64_t)j * a.ld + a.n] = kvq_from_fixed_fast<0>(S[j]);
+    for (int j = tid; j < a.n_q_heads; j += NT) a.scores[(int64_t)j * a.ld + a.n] = kvq_from_fixed_fast<0>(S[j]);
 }
 
 // W: wavefronts on the Value token (D = 256 W channels: 16 or 4).  One instantiation per width: the
@@ -1059,16 +1308,17 @@ void kvq_step_front(const StepFrontArgs)
     asm volatile("" : "+s"(pa));
     if (blockIdx.x == 0) {
         // wavefronts that a role does not use end here (a barrier waits only for those that have not ended)
-        if (threadIdx.x >= KVQ_STEP_K_NT) return;
+        constexpr int KW = W == 16 ? 16 : 8, HW = W == 16 ? 2 : 1;         // 32 or 8 heads
+        if (threadIdx.x >= 64 * KW) return;
         const StepFrontArgs a = *pa;
-        k_quant_token<BITS, KVQ_STEP_K_NT>(a.params, a.D, a.cap, a.n, a.k_new, a.k_codes, a.k_ptr, a.ksp, a.cap_nnz_k, 1,
-                                           a.d_status, 0);
-        qk_sparse_new_token<R>(a);
+        k_quant_token_w<BITS, HW, KW>(a.params, a.D, a.cap, a.n, a.k_new, a.k_codes, a.k_ptr, a.ksp, a.cap_nnz_k, 1,
+                                      a.d_status, 0);
+        qk_sparse_new_token<R, 64 * KW>(a);
     } else if (blockIdx.x == 1) {
         if (threadIdx.x >= 64 * W) return;
         const StepFrontArgs a = *pa;
-        v_quant_token4<BITS, 4, W>(a.params, a.D, a.cap, a.n, a.k_side, a.v_new, a.v_codes, a.v_sz, a.v_ptr, a.vsp,
-                                   a.cap_nnz_v, a.d_status, 0);
+        v_quant_token4<BITS, 4, W, 1>(a.params, a.D, a.cap, a.n, a.k_side, a.v_new, a.v_codes, a.v_sz, a.v_ptr, a.vsp,
+                                      a.cap_nnz_v, a.d_status, 0, 1);
     } else {
         const KvqSparseFlat ksp{pa->ksp.idx, pa->ksp.val};
         qk_sparse_body<R, 8, KvqSparseFlat>((int)blockIdx.x - 2, pa->params, pa->D, pa->n_q_heads, pa->n, pa->k_ptr, ksp,
@@ -1120,20 +1370,25 @@ extern "C" kvq_status kvq_quantize_append_k(kvq_cache *cache, const uint16_t *d_
         kvq_k_count<<<(T + KVQ_COUNT_NT / 64 - 1) / (KVQ_COUNT_NT / 64), KVQ_COUNT_NT, 0, s>>>(cache->params, D, T, d_k_new, cnt);
         kvq_ptr_scan<<<1, 1024, 0, s>>>(cache->k_ptr, cache->n_tokens_k, T, cnt, cache->cap_nnz_k, cache->d_status);
     }
+#define LAUNCH_KW(B, HW, W)                                                                                     \
+    kvq_k_quant<B, HW, W><<<T, 64 * (W), 0, s>>>(cache->params, D, cache->cap_tokens, cache->n_tokens_k, d_k_new, \
+                                                 cache->k_codes, cache->k_ptr, ksp, cache->cap_nnz_k, single,    \
+                                                 cache->d_status)
+    // From KVQ_WAVE_TOKENS tokens on a wavefront each; below, sixteen wavefronts share out a token's heads (four
+    // where there are no more than four heads), up to four each; wider models take the body that loops.
 #define LAUNCH_K(B)                                                                                             \
     do {                                                                                                        \
+        const int H = cache->n_kv_heads;                                                                        \
         if (T >= KVQ_WAVE_TOKENS)                                                                               \
             kvq_k_quant_wave<B><<<(T + KVQ_KW_NT / 64 - 1) / (KVQ_KW_NT / 64), KVQ_KW_NT, 0, s>>>(               \
                 cache->params, D, T, cache->cap_tokens, cache->n_tokens_k, d_k_new, cache->k_codes,              \
                 cache->k_ptr, ksp, cache->cap_nnz_k, cache->d_status);                                           \
-        else if (wide_wg(D, T))                                                                                 \
-            kvq_k_quant<B, 1024><<<T, 1024, 0, s>>>(cache->params, D, cache->cap_tokens, cache->n_tokens_k,      \
-                                                    d_k_new, cache->k_codes, cache->k_ptr, ksp, cache->cap_nnz_k,    \
-                                                    single, cache->d_status);                                    \
-        else                                                                                                    \
-            kvq_k_quant<B, 256><<<T, 256, 0, s>>>(cache->params, D, cache->cap_tokens, cache->n_tokens_k,        \
-                                                  d_k_new, cache->k_codes, cache->k_ptr, ksp, cache->cap_nnz_k,      \
-                                                  single, cache->d_status);                                      \
+        else if (H <= 4) LAUNCH_KW(B, 1, 4);                                                                    \
+        else if (H <= 16) LAUNCH_KW(B, 1, 16);                                                                  \
+        else if (H <= 32) LAUNCH_KW(B, 2, 16);                                                                  \
+        else if (H <= 48) LAUNCH_KW(B, 3, 16);                                                                  \
+        else if (H <= 64) LAUNCH_KW(B, 4, 16);                                                                  \
+        else LAUNCH_KW(B, 0, 16);                                                                               \
     } while (0)
     // one set of kernels per layout of the outlier entries (flat arrays or a list of blocks)
     const auto launch = [&](const auto ksp) {
@@ -1144,6 +1399,7 @@ extern "C" kvq_status kvq_quantize_append_k(kvq_cache *cache, const uint16_t *d_
     if (cache->nnz_block_shift) launch(kvq_blocked_k(cache));
     else launch(kvq_flat_k(cache));
 #undef LAUNCH_K
+#undef LAUNCH_KW
     KVQ_HIP_CHECK(hipGetLastError());
     st = copy_sink_rows(cache, cache->sink_k, d_k_new, cache->n_tokens_k, T, s);
     if (st != KVQ_OK) return st;
@@ -1160,18 +1416,21 @@ extern "C" kvq_status kvq_quantize_append_v(kvq_cache *cache, const uint16_t *d_
     if (D > 16384) return KVQ_ERR_UNSUPPORTED;       // the per-token selection keeps the vector in LDS
     hipStream_t s = (hipStream_t)stream;
     const size_t dyn = 3 * (size_t)D;
-#define LAUNCH_V4W(B, J, WV)                                                                                   \
-    kvq_v_quant4<B, J, WV><<<T, 64 * (WV), 0, s>>>(cache->params, D, cache->cap_tokens, cache->n_tokens_v,     \
-                                               cache->k_side_v, d_v_new, cache->v_codes, cache->v_sz,          \
-                                               cache->v_ptr, vsp, cache->cap_nnz_v,                           \
-                                               cache->d_status)
-#define LAUNCH_V4(B, J) LAUNCH_V4W(B, J, KVQ_VW_WAVES)
+#define LAUNCH_V4W(B, J, WV, TOK, GRID)                                                                        \
+    kvq_v_quant4<B, J, WV, TOK><<<GRID, 64 * (WV) * (TOK), 0, s>>>(                                            \
+        cache->params, D, cache->cap_tokens, cache->n_tokens_v, T, cache->k_side_v, d_v_new, cache->v_codes,   \
+        cache->v_sz, cache->v_ptr, vsp, cache->cap_nnz_v, cache->d_status)
+    // a workgroup per pair of tokens (the two that share dwords), the first and the last perhaps with one token
+    const unsigned pairs = (unsigned)(((cache->n_tokens_v + T - 1) >> 1) - (cache->n_tokens_v >> 1) + 1);
+#define LAUNCH_V4(B, J) LAUNCH_V4W(B, J, KVQ_VW_WAVES, 2, pairs)
 #define LAUNCH_V(B)                                                                                             \
     do {                                                                                                        \
-        if (D == 4096 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 4, 16);                                         \
-        else if (D == 2048 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 4, 8);                                     \
+        if (D == 4096 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 4, 16, 1, T);                                   \
+        else if (D == 2048 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 4, 8, 1, T);                               \
+        else if (D == 5120 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 5, 16, 1, T);                              \
         else if (D == 4096) LAUNCH_V4(B, 16);                                                                   \
         else if (D == 2048) LAUNCH_V4(B, 8);                                                                    \
+        else if (D == 1024 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 4, 4, 1, T);                               \
         else if (D == 1024) LAUNCH_V4(B, 4);                                                                    \
         else if (D == 5120 && T >= KVQ_BULK_TOKENS) LAUNCH_V4(B, 20);                                           \
         else if (D == 6656 && T >= KVQ_BULK_TOKENS) LAUNCH_V4(B, 26);                                           \

@@ -22,11 +22,19 @@ struct KvqParamsHeader {
     float rope_vl[64];    // fp32 tail: (theta_i / (2 pi)) - rope_vh[i]
     int32_t D;
     int32_t bits;
-    int32_t pad[30];
+    float thr_k[15];      // code thresholds of lut_k / lut_v (see KVQ_CODE_RANGE): the code of a normalised
+    float thr_v[15];      // value x is the number of thresholds <= x; thr[0] is NaN where that does not hold
     float rope_cd[64];    // cos(KVQ_ROPE_STEP * theta_i): the rotation that advances a token's (cos, sin)
     float rope_sd[64];    // sin(KVQ_ROPE_STEP * theta_i)   of pair i by KVQ_ROPE_STEP positions
 };
 constexpr int KVQ_ROPE_STEP = 1024;
+// Range |x| <= KVQ_CODE_RANGE in which the nearest signpost (fp32 distances, ties to the smaller index) is a
+// monotone step function of x, so that counting thresholds gives the code.  It holds when the signposts
+// lie in [-1, 1] and differing ones are at least 2^-15 apart: fp32 distances of up to 128 are spaced 2^-16 at
+// most, so that two signposts on one side of x never have distances that round to the same number.  Beyond
+// the range (far outliers), and for other tables, the search over all signposts decides.
+constexpr float KVQ_CODE_RANGE = 127.0f;
+constexpr float KVQ_CODE_MIN_GAP = 1.0f / 32768.0f;
 constexpr int KVQ_PARAMS_HEADER_BYTES = 1280;
 static_assert(sizeof(KvqParamsHeader) == KVQ_PARAMS_HEADER_BYTES, "header layout");
 

@@ -177,6 +177,42 @@ static float kvq_signpost_fp16(float x)
     return y;
 }
 
+// Index of the nearest signpost exactly as the append kernels' exhaustive search finds it.
+static int kvq_nearest_host(const float *lut, int ne, float x)
+{
+    int best = 0;
+    float bestd = fabsf(x - lut[0]);
+    for (int j = 1; j < ne; ++j) {
+        const float d = fabsf(x - lut[j]);
+        if (d < bestd) { bestd = d; best = j; }
+    }
+    return best;
+}
+
+// thr[j] = the smallest fp32 x in the range whose nearest signpost has an index above j (+inf: none), by
+// bisection over the ordered fp32 numbers; thr[0] = NaN where the codes are not monotone in x.
+static void kvq_code_thresholds(const float *lut, int ne, float *thr)
+{
+    for (int j = 0; j < ne - 1; ++j) thr[j] = NAN;
+    for (int j = 0; j < ne; ++j)
+        if (!(fabsf(lut[j]) <= 1.0f)) return;
+    for (int j = 1; j < ne; ++j)
+        if (lut[j] != lut[j - 1] && !(lut[j] - lut[j - 1] >= KVQ_CODE_MIN_GAP)) return;
+    // order-preserving integers of the fp32 numbers (two's complement of the magnitude for negative ones)
+    auto key = [](float x) { int32_t b; memcpy(&b, &x, 4); return b >= 0 ? (int64_t)b : (int64_t)INT32_MIN - (int64_t)b; };
+    auto val = [](int64_t k) { const int32_t b = (int32_t)(k >= 0 ? k : (int64_t)INT32_MIN - k); float x; memcpy(&x, &b, 4); return x; };
+    for (int j = 0; j < ne - 1; ++j) {
+        int64_t lo = key(-KVQ_CODE_RANGE), hi = key(KVQ_CODE_RANGE);
+        if (kvq_nearest_host(lut, ne, KVQ_CODE_RANGE) <= j) { thr[j] = INFINITY; continue; }
+        while (lo < hi) {
+            const int64_t mid = lo + (hi - lo) / 2;
+            if (kvq_nearest_host(lut, ne, val(mid)) > j) hi = mid;
+            else lo = mid + 1;
+        }
+        thr[j] = val(lo);
+    }
+}
+
 // Expand the fp16 per-channel constants to fp32 and form the reciprocal scale with one IEEE division,
 // so every later kernel normalises with exactly (x - z) * (1/s).
 __global__ void kvq_params_expand(void *block, int D)
@@ -210,6 +246,8 @@ extern "C" kvq_status kvq_lut_load(kvq_cache *cache, const float *h_lut_k, const
     KvqParamsHeader hdr;
     memset(&hdr, 0, sizeof(hdr));
     for (int j = 0; j < ne; ++j) { hdr.lut_k[j] = kvq_signpost_fp16(h_lut_k[j]); hdr.lut_v[j] = kvq_signpost_fp16(h_lut_v[j]); }
+    kvq_code_thresholds(hdr.lut_k, ne, hdr.thr_k);
+    kvq_code_thresholds(hdr.lut_v, ne, hdr.thr_v);
     for (int i = 0; i < 64; ++i) {
         // rotation frequency of channel pair (i, i+64) in revolutions per position, split in two floats
         double rev = pow((double)cache->rope_base, -2.0 * (double)i / (double)KVQ_HEAD_DIM) / (2.0 * M_PI);

@@ -12,6 +12,12 @@ __device__ inline uint32_t order_key(uint16_t h)
     return (h & 0x8000u) ? (uint32_t)(uint16_t)~h : (uint32_t)(h | 0x8000u);
 }
 
+// The value of a key.
+__device__ inline float key_value(uint32_t key)
+{
+    return kvq_h2f((uint16_t)((key & 0x8000u) ? (key & 0x7FFFu) : (~key & 0xFFFFu)));
+}
+
 // In a histogram of 256 bins (lane l reads bins 4l..4l+3), the bin in which the K-th element counted
 // from the top (FROM_TOP) or from the bottom lies, the number of elements beyond that bin on that side,
 // and the bin's own count.  Wavefront-uniform results.  1 <= K <= number of elements.
