@@ -16,7 +16,8 @@
 // of the next token tile are requested as soon as the current tile no longer needs the registers
 // they land in, so HBM latency hides behind the table look-ups.  For 4-bit codes the joint table
 // would have 256 entries, so A and B are split into a part indexed by each code (two 16-entry
-// gathers).
+// gathers).  With several query heads per KV head the rotated Key itself is formed and multiplied with all of
+// them by fp32 matrix instructions (kvq_qkg_kernel).
 //
 // The sparse outliers are handled by a second, balanced kernel (lanes = outlier entries) launched
 // in front of the dense one in the same call: it writes its per-(head, token) sums to the score
@@ -71,6 +72,48 @@ __device__ __forceinline__ uint32_t field_shifted(const uint32_t (&Wg)[8], int i
         return chunk_dword(Wg, wi) << (3 - sh);
     }
     return __builtin_amdgcn_alignbit(chunk_dword(Wg, wi + 1), chunk_dword(Wg, wi), sh - 3);
+}
+
+// After the G0-th group of PAIR_GROUP channel pairs: request the pieces whose registers the group has freed.
+template <int BITS, int KVH, int PAIR_GROUP, int G0>
+__device__ __forceinline__ void qk_next_pieces(uint32_t (&W)[KVH][8], const uint8_t *cur_chunk, const uint8_t *next_chunk,
+                                               int64_t plane, bool valid, bool next_valid)
+{
+    // Software pipelining: a 16-byte piece of the chunk is dead once the last field that touches it
+    // has been consumed; the piece two positions further down the stream (of this tile, or of the
+    // next tile once this one runs out) is requested into its register slot right away, so every
+    // load has a third of a tile's arithmetic to hide behind.
+    constexpr int FB = 2 * BITS;
+    constexpr int first_field = G0 * PAIR_GROUP, last_field = first_field + PAIR_GROUP - 1;
+#pragma unroll
+    for (int j = 0; j < BITS; ++j) {
+        const int last_user = (128 * (j + 1) - 1) / FB;      // last field with a bit in piece j
+        if (last_user >= first_field && last_user <= last_field) {
+            const int jn = j + 2;                            // stream position of the piece to fetch
+            if (jn < BITS) {
+                if (valid) {
+#pragma unroll
+                    for (int g = 0; g < KVH; ++g) {
+                        const uint4 v = kvq_load_stream16(cur_chunk + g * plane + jn * 1024);
+                        W[g][(jn & 1) * 4 + 0] = v.x; W[g][(jn & 1) * 4 + 1] = v.y;
+                        W[g][(jn & 1) * 4 + 2] = v.z; W[g][(jn & 1) * 4 + 3] = v.w;
+                    }
+                }
+            } else if (jn - BITS == 0 || (BITS & 1) == 0) {
+                // next tile's piece 0 (or, for an even piece count, also its piece 1) lands in the slot just freed
+                const int jt = jn - BITS;
+                if (next_valid) {
+#pragma unroll
+                    for (int g = 0; g < KVH; ++g) {
+                        const uint4 v = kvq_load_stream16(next_chunk + g * plane + jt * 1024);
+                        W[g][(j & 1) * 4 + 0] = v.x; W[g][(j & 1) * 4 + 1] = v.y;
+                        W[g][(j & 1) * 4 + 2] = v.z; W[g][(j & 1) * 4 + 3] = v.w;
+                    }
+                }
+            }
+            // odd piece count, last piece: handled at the end of the tile (the slots swap roles there)
+        }
+    }
 }
 
 // PAIR_GROUP consecutive channel pairs of the dense part for one token.  Written gathers-first so
@@ -155,41 +198,7 @@ __device__ __forceinline__ void qk_group(uint32_t (&W)[KVH][8], float (&acc)[KVH
     // group's arithmetic below later gathers.
 #pragma unroll
     for (int qh = 0; qh < QH; ++qh) asm volatile("" : "+v"(acc[qh]) : : "memory");
-    // Software pipelining: a 16-byte piece of the chunk is dead once the last field that touches it
-    // has been consumed; the piece two positions further down the stream (of this tile, or of the
-    // next tile once this one runs out) is requested into its register slot right away, so every
-    // load has a third of a tile's arithmetic to hide behind.
-    constexpr int FB = 2 * BITS;
-    constexpr int first_field = G0 * PAIR_GROUP, last_field = first_field + PAIR_GROUP - 1;
-#pragma unroll
-    for (int j = 0; j < BITS; ++j) {
-        const int last_user = (128 * (j + 1) - 1) / FB;      // last field with a bit in piece j
-        if (last_user >= first_field && last_user <= last_field) {
-            const int jn = j + 2;                            // stream position of the piece to fetch
-            if (jn < BITS) {
-                if (valid) {
-#pragma unroll
-                    for (int g = 0; g < KVH; ++g) {
-                        const uint4 v = kvq_load_stream16(cur_chunk + g * plane + jn * 1024);
-                        W[g][(jn & 1) * 4 + 0] = v.x; W[g][(jn & 1) * 4 + 1] = v.y;
-                        W[g][(jn & 1) * 4 + 2] = v.z; W[g][(jn & 1) * 4 + 3] = v.w;
-                    }
-                }
-            } else if (jn - BITS == 0 || (BITS & 1) == 0) {
-                // next tile's piece 0 (or, for an even piece count, also its piece 1) lands in the slot just freed
-                const int jt = jn - BITS;
-                if (next_valid) {
-#pragma unroll
-                    for (int g = 0; g < KVH; ++g) {
-                        const uint4 v = kvq_load_stream16(next_chunk + g * plane + jt * 1024);
-                        W[g][(j & 1) * 4 + 0] = v.x; W[g][(j & 1) * 4 + 1] = v.y;
-                        W[g][(j & 1) * 4 + 2] = v.z; W[g][(j & 1) * 4 + 3] = v.w;
-                    }
-                }
-            }
-            // odd piece count, last piece: handled at the end of the tile (the slots swap roles there)
-        }
-    }
+    qk_next_pieces<BITS, KVH, PAIR_GROUP, G0>(W, cur_chunk, next_chunk, plane, valid, next_valid);
 }
 
 template <int BITS, int KVH, int RQ, int PG, int... G>
@@ -405,6 +414,241 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
             float m = KVQ_STAT_FLOOR;
 #pragma unroll
             for (int w = 0; w < NT / 64; ++w) m = __builtin_fmaxf(m, wst[w * QH + tid]);
+            stat_slots[(int64_t)(q0 + tid) * KVQ_STAT_SLOTS + blockIdx.x] = m;
+        }
+    }
+    if (SPAN) kvq_span_end(span);
+}
+
+// ---- grouped queries ---------------------------------------------------------------------------------
+// Several query heads per KV head: the rotated Key is worth forming, since they share it.  Per (token, pair,
+// KV head) a lane cuts the field out, gathers the pair of scaled Key elements (k_i, k_{i+64}) from a table
+// without a query in it (a fourth or an eighth of the (A,B) tables: more KV heads fit a workgroup and share the
+// sines and cosines), rotates it with four instructions and hands both elements to v_mfma_f32_4x4x1_16b_f32,
+// an outer product in fp32: a block of four lanes is four tokens (its column operand, each lane's own element),
+// its four rows are four query heads.  The row operand holds the query of 16 channels x 4 heads in one
+// register, of which an instruction broadcasts one channel to all blocks (cbsz = 4): two registers per KV head and
+// four heads, reloaded from LDS every 16 pairs.  One instruction then does what
+// four multiply-adds per element did, 2 RQ instructions and RQ gathers per pair.  Arithmetic, precision and
+// order of the sums over channels are those of an fp32 chain.
+// Lanes, tiles, piece streaming, grid and results as in kvq_qk_kernel.  Bound by VALU issue (7.5 instructions and
+// two matrix instructions per token, pair and KV head at four KV heads a workgroup; VALU busy 66 to 76 % of the
+// kernel, the matrix cores 25 %).  Times beside qk_grouped.
+typedef float float4_t __attribute__((ext_vector_type(4)));
+
+// q: four query heads of 16 channels; the instruction takes those of channel `C` of the 16.
+template <int C>
+__device__ __forceinline__ float4_t qkg_madd(float q, float k, float4_t acc)
+{
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(q, k, acc, 4, C, 0);
+}
+
+template <int BITS, int KVH, int RQ, int PG, int G0, int... P>
+__device__ __forceinline__ void qkg_group(std::integer_sequence<int, P...>, uint32_t (&W)[KVH][8],
+                                          float4_t (&acc)[KVH][(RQ + 3) / 4], float (&q)[KVH][(RQ + 3) / 4][2],
+                                          const float *qs, const uint8_t *tab, float nf, float wave_base, const KvqParamsHeader *hdr,
+                                          const uint8_t *cur_chunk, const uint8_t *next_chunk, int64_t plane, bool valid,
+                                          bool next_valid)
+{
+    using C = QkCfg<BITS>;
+    constexpr int SETS = (RQ + 3) / 4, NE = C::NE;
+    static_assert(16 % PG == 0, "a group's channels share the query registers");
+    if (G0 * PG % 16 == 0) {                       // the queries of the next 16 channels and of those 64 further up
+#pragma unroll
+        for (int g = 0; g < KVH; ++g)
+#pragma unroll
+            for (int u = 0; u < SETS; ++u)
+#pragma unroll
+                for (int z = 0; z < 2; ++z) q[g][u][z] = qs[((g * SETS + u) * 8 + G0 * PG / 16 + 4 * z) * 64];
+    }
+    float2_t k[PG][KVH];
+#pragma unroll
+    for (int p = 0; p < PG; ++p) {
+        const int I = G0 * PG + p;
+#pragma unroll
+        for (int g = 0; g < KVH; ++g) {
+            if constexpr (C::JOINT) {
+                constexpr uint32_t M = ((1u << (2 * BITS)) - 1u) << 3;
+                const uint32_t base = (uint32_t)((g * 64 + I) * C::ENTRIES) * 8u, hi = base & ~0xFFFFu;
+                const uint32_t f = field_shifted<2 * BITS>(W[g], I);
+                k[p][g] = *(const float2_t *)(tab + (base - hi) + (hi ? kvq_and_or(f, M, hi) : (f & M)));
+            } else {
+                // (4-byte entries: a code moved to bit 2)
+                constexpr uint32_t M = (uint32_t)(NE - 1) << 2;
+                const uint32_t base = (uint32_t)((g * 64 + I) * 2 * NE) * 4u;
+                const int bit = I * 2 * BITS, wi = bit >> 5, sh = bit & 31;
+                const uint32_t w = chunk_dword(W[g], wi);
+                const uint32_t lo = (sh >= 2 ? w >> (sh >= 2 ? sh - 2 : 0) : w << 2) & M, hi = (w >> (sh + BITS - 2)) & M;
+                k[p][g] = float2_t{*(const float *)(tab + base + lo), *(const float *)(tab + base + 4 * NE + hi)};
+            }
+        }
+    }
+    float cs[PG], sn[PG];
+#pragma unroll
+    for (int p = 0; p < PG; ++p) {
+        const int I = G0 * PG + p;
+        const float base = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_base), I));
+        const float rev = __builtin_fmaf(nf, hdr->rope_vh[I], base);
+        cs[p] = __builtin_amdgcn_cosf(rev);
+        sn[p] = __builtin_amdgcn_sinf(rev);
+    }
+    // the lower channels of all heads, then the upper ones: a matrix instruction waits for the one before it on
+    // the same sums (the compiler would put the two of a head side by side: 145 us instead of 137 at 524288 tokens)
+    auto pair = [&](auto pc) {
+        constexpr int p = decltype(pc)::value, I = G0 * PG + p;
+#pragma unroll
+        for (int g = 0; g < KVH; ++g) {
+            const float x = __builtin_fmaf(-k[p][g].y, sn[p], k[p][g].x * cs[p]);
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) acc[g][u] = qkg_madd<I % 16>(q[g][u][0], x, acc[g][u]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < KVH; ++g) {
+            const float y = __builtin_fmaf(k[p][g].x, sn[p], k[p][g].y * cs[p]);
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) acc[g][u] = qkg_madd<I % 16>(q[g][u][1], y, acc[g][u]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    (pair(std::integral_constant<int, P>{}), ...);
+    // keeps the groups in order (see qk_group)
+#pragma unroll
+    for (int g = 0; g < KVH; ++g)
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) asm volatile("" : "+v"(acc[g][u]) : : "memory");
+    qk_next_pieces<BITS, KVH, PG, G0>(W, cur_chunk, next_chunk, plane, valid, next_valid);
+}
+
+template <int BITS, int KVH, int RQ, int PG, int... G>
+__device__ __forceinline__ void qkg_all_pairs(std::integer_sequence<int, G...>, uint32_t (&W)[KVH][8],
+                                              float4_t (&acc)[KVH][(RQ + 3) / 4], const float *qs,
+                                              const uint8_t *tab, float nf, float wave_base, const KvqParamsHeader *hdr,
+                                              const uint8_t *cur_chunk, const uint8_t *next_chunk, int64_t plane,
+                                              bool valid, bool next_valid)
+{
+    float q[KVH][(RQ + 3) / 4][2];
+    (qkg_group<BITS, KVH, RQ, PG, G>(std::make_integer_sequence<int, PG>{}, W, acc, q, qs, tab, nf, wave_base, hdr, cur_chunk,
+                                     next_chunk, plane, valid, next_valid), ...);
+}
+
+template <int BITS, int KVH, int RQ, int NT, int PG, bool STATS, bool SPAN = false>
+__global__ __launch_bounds__(NT) void kvq_qkg_kernel(const void *__restrict__ params, int D, int r,
+                                                     int64_t cap, int64_t L, const uint8_t *__restrict__ k_codes,
+                                                     const float *__restrict__ q_rot, float scale,
+                                                     float *__restrict__ scores, int64_t ld, int n_tiles,
+                                                     int add_prev, float *__restrict__ stat_slots, int n_sink,
+                                                     unsigned long long *span)
+{
+    if (SPAN) kvq_span_start(span);
+    using C = QkCfg<BITS>;
+    constexpr int QH = KVH * RQ, SETS = (RQ + 3) / 4, NE = C::NE;
+    // Key elements of a (KV head, pair): joint entries (k_i, k_{i+64}) of 8 bytes, or NE + NE of 4 bytes
+    constexpr int TAB = KVH * 64 * C::ENTRIES * (C::JOINT ? 8 : 4);
+    __shared__ __attribute__((aligned(16))) uint8_t tab[TAB];
+    __shared__ float qs[KVH * SETS * 8 * 64];
+    __shared__ float wst[NT / 64][QH];
+    const KvqParamsView pv = kvq_params_view(params, D);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int q0 = blockIdx.y * QH, kv0 = q0 / r;
+
+    const int64_t plane = cap * 16 * BITS;                 // bytes between consecutive KV heads
+    const int tile_begin = (int)(((int64_t)blockIdx.x * n_tiles) / gridDim.x);
+    const int tile_end = (int)(((int64_t)(blockIdx.x + 1) * n_tiles) / gridDim.x);
+    const int tiles_per_wg = tile_end - tile_begin;
+    int64_t n = (int64_t)tile_begin * NT + tid;
+    bool valid = n < L;
+    uint32_t W[KVH][8];                                    // two 16-byte pieces per KV head
+    const uint8_t *cur_chunk = k_codes + kvq_k_piece0(BITS, cap, valid ? n : 0, kv0);
+    if (valid) {
+#pragma unroll
+        for (int g = 0; g < KVH; ++g)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint4 v = kvq_load_stream16(cur_chunk + g * plane + j * 1024);
+                W[g][4 * j + 0] = v.x; W[g][4 * j + 1] = v.y; W[g][4 * j + 2] = v.z; W[g][4 * j + 3] = v.w;
+            }
+    }
+    const float my_vh = pv.hdr->rope_vh[lane], my_vl = pv.hdr->rope_vl[lane];           // this lane's pair
+    // row operands: lane = (channel within 16, query head within 4), 16 channels per row of 64
+    for (int e = tid; e < KVH * SETS * 8 * 64; e += NT) {
+        const int l = e & 63, j = (e >> 6) & 7, u = (e >> 9) % SETS, g = e / (512 * SETS), h = 4 * u + (l & 3);
+        qs[e] = h < RQ ? q_rot[(int64_t)(q0 + g * RQ + h) * 128 + 16 * j + (l >> 2)] * scale : 0.f;
+    }
+    // tables
+    constexpr int ENT = C::ENTRIES;
+    for (int e = tid; e < KVH * 64 * ENT; e += NT) {
+        const int f = e % ENT, i = (e / ENT) & 63, c = (kv0 + e / (64 * ENT)) * 128 + i;
+        if constexpr (C::JOINT) {
+            const float lo = __builtin_fmaf(pv.s[c], pv.hdr->lut_k[f & (NE - 1)], pv.z[c]);
+            const float hi = __builtin_fmaf(pv.s[c + 64], pv.hdr->lut_k[f >> BITS], pv.z[c + 64]);
+            *(float2_t *)(tab + 8 * e) = float2_t{lo, hi};
+        } else {
+            const int cc = f >= NE ? c + 64 : c;
+            *(float *)(tab + 4 * e) = __builtin_fmaf(pv.s[cc], pv.hdr->lut_k[f & (NE - 1)], pv.z[cc]);
+        }
+    }
+    float stat_m[STATS ? QH : 1];
+    if (STATS) {
+#pragma unroll
+        for (int h = 0; h < QH; ++h) stat_m[h] = KVQ_STAT_FLOOR;
+    }
+    __syncthreads();
+    for (int tile = 0; tile < tiles_per_wg; ++tile) {
+        // wavefronts w, w + 4, ... of the workgroup share a SIMD: each takes every priority in turn
+        if (KVQ_ROTATE_PRIORITY) kvq_set_wave_priority(__builtin_amdgcn_readfirstlane(tid >> 8) + tile);
+        const int64_t nn = n + NT;
+        const bool next_valid = (tile + 1 < tiles_per_wg) && (nn < L);
+        const uint8_t *next_chunk = k_codes + kvq_k_piece0(BITS, cap, next_valid ? nn : n, kv0);
+        const float wave_base = rope_rev((float)(n - lane), my_vh, my_vl);
+        float4_t acc[KVH][SETS];
+#pragma unroll
+        for (int g = 0; g < KVH; ++g)
+#pragma unroll
+            for (int u = 0; u < SETS; ++u) acc[g][u] = float4_t{0.f, 0.f, 0.f, 0.f};
+        // a wavefront whose 64 tokens all lie past the end skips the arithmetic; in any other the matrix
+        // instructions run with every lane (lanes past the end on whatever their registers hold)
+        if (__ballot(valid) != 0ull)
+            qkg_all_pairs<BITS, KVH, RQ, PG>(std::make_integer_sequence<int, 64 / PG>{}, W, acc, qs + lane, tab, (float)lane, wave_base,
+                                             pv.hdr, cur_chunk, next_chunk, plane, valid, next_valid);
+        if (BITS & 1) {
+            // odd piece count: see kvq_qk_kernel
+#pragma unroll
+            for (int g = 0; g < KVH; ++g) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) W[g][k] = W[g][4 + k];
+                if (next_valid) {
+                    const uint4 v = kvq_load_stream16(next_chunk + g * plane + 1024);
+                    W[g][4] = v.x; W[g][5] = v.y; W[g][6] = v.z; W[g][7] = v.w;
+                }
+            }
+        }
+        float prev[QH];
+#pragma unroll
+        for (int h = 0; h < QH; ++h) prev[h] = (add_prev && valid) ? scores[(int64_t)(q0 + h) * ld + n] : 0.f;
+        if (valid) {
+#pragma unroll
+            for (int h = 0; h < QH; ++h) {
+                const float x = acc[h / RQ][(h % RQ) / 4][(h % RQ) & 3] + prev[h];
+                scores[(int64_t)(q0 + h) * ld + n] = x;
+                if (STATS && n >= n_sink) stat_m[STATS ? h : 0] = __builtin_fmaxf(stat_m[STATS ? h : 0], x);
+            }
+        }
+        n = nn;
+        valid = next_valid;
+        cur_chunk = next_chunk;
+    }
+    if (STATS) {
+#pragma unroll
+        for (int h = 0; h < QH; ++h) {
+            const float w = kvq_wave_max(stat_m[STATS ? h : 0]);
+            if (lane == 0) wst[tid >> 6][h] = w;
+        }
+        __syncthreads();
+        if (tid < QH) {
+            float m = KVQ_STAT_FLOOR;
+#pragma unroll
+            for (int w = 0; w < NT / 64; ++w) m = __builtin_fmaxf(m, wst[w][tid]);
             stat_slots[(int64_t)(q0 + tid) * KVQ_STAT_SLOTS + blockIdx.x] = m;
         }
     }
@@ -844,6 +1088,13 @@ __global__ __launch_bounds__(64) void kvq_qk_sink(const void *__restrict__ param
     }
 }
 
+// Which kernel takes `r` query heads per KV head: the grouped one from four heads on, and for two where the codes
+// have more than two bits.  Measured (us, (A,B) tables against grouped): 32 heads on 16, 100000 tokens: 2 bits 44
+// against 59, 3 bits 87 / 69, 4 bits 79 / 73; 32 on 8: 524288 tokens, 2 bits 168 / 137, 131072, 3 bits 88 / 47, 33001,
+// 4 bits 38 / 25, 4000, 4 bits 15.7 / 10.7; 32 on 4, 194971 tokens, 4 bits 121 / 54.  (Two heads use half the rows
+// of a matrix instruction, and 2-bit (A,B) tables of two heads are cheap to gather from.)
+constexpr bool qk_grouped(int bits, int r) { return r > 2 || (r == 2 && bits > 2); }
+
 // Store the address of the piece-major kernel's span slots (or null) in its device word and reset the
 // slots, on the launch stream: before every launch whose span is taken, and once when the word still
 // holds an address and no span is wanted any more.  Part of the timing aid: like the rest of it, not
@@ -862,17 +1113,22 @@ kvq_status qk3_publish_span(unsigned long long *span, hipStream_t s)
     return KVQ_OK;
 }
 
-template <int BITS, int KVH, int RQ, int NT, int PG, int R>
+template <int BITS, int KVH, int RQ, int NT, int PG>
 kvq_status launch_qk(const kvq_cache *c, const float *q, float scale, float *scores, int64_t ld, float *stat_slots,
                      int *n_stat, hipStream_t s)
 {
     constexpr int QH = KVH * RQ;
+    constexpr bool GROUPED = qk_grouped(BITS, RQ);
     const int D = c->n_kv_heads * KVQ_HEAD_DIM;
     const int64_t L = c->n_tokens_k;
-    auto kern = stat_slots ? kvq_qk_kernel<BITS, KVH, RQ, NT, PG, true> : kvq_qk_kernel<BITS, KVH, RQ, NT, PG, false>;
-    constexpr bool CAN_SPAN = QH < 8;
+    auto kernel = [&](auto stats, auto timed) {
+        if constexpr (GROUPED) return kvq_qkg_kernel<BITS, KVH, RQ, NT, PG, decltype(stats)::value, decltype(timed)::value>;
+        else return kvq_qk_kernel<BITS, KVH, RQ, NT, PG, decltype(stats)::value, decltype(timed)::value>;
+    };
+    auto kern = stat_slots ? kernel(std::true_type{}, std::false_type{}) : kernel(std::false_type{}, std::false_type{});
+    constexpr bool CAN_SPAN = GROUPED || QH < 8;
     // 3-bit codes, tiles of KVQ_ROPE_STEP tokens: the piece-major kernel (rotary recurrence over TT tiles)
-    constexpr bool PIECE_MAJOR = KVQ_QK3_ENABLE && BITS == 3 && NT == KVQ_ROPE_STEP && KVH * KVQ_QK3_TT <= 16;
+    constexpr bool PIECE_MAJOR = KVQ_QK3_ENABLE && !GROUPED && BITS == 3 && NT == KVQ_ROPE_STEP && KVH * KVQ_QK3_TT <= 16;
     // (it addresses the codes with 32-bit offsets)
     const bool piece_major = PIECE_MAJOR && (int64_t)c->n_kv_heads * c->cap_tokens * 16 * BITS < ((int64_t)1 << 32);
     if constexpr (PIECE_MAJOR) {
@@ -898,76 +1154,68 @@ kvq_status launch_qk(const kvq_cache *c, const float *q, float scale, float *sco
             kvq_status st = qk3_publish_span(span, s);
             if (st != KVQ_OK) return st;
         } else if (span)
-            kern = stat_slots ? kvq_qk_kernel<BITS, KVH, RQ, NT, PG, true, true>
-                              : kvq_qk_kernel<BITS, KVH, RQ, NT, PG, false, true>;
+            kern = stat_slots ? kernel(std::true_type{}, std::true_type{}) : kernel(std::false_type{}, std::true_type{});
     } else if constexpr (CAN_SPAN) {
         if (span)
-            kern = stat_slots ? kvq_qk_kernel<BITS, KVH, RQ, NT, PG, true, true>
-                              : kvq_qk_kernel<BITS, KVH, RQ, NT, PG, false, true>;
+            kern = stat_slots ? kernel(std::true_type{}, std::true_type{}) : kernel(std::false_type{}, std::true_type{});
     }
     // the sparse kernel goes first and writes its part of every score; the dense kernel adds its own
     const int sparse_first = !(c->loaded & 2);           // bit 1: thresholds admit no Key outliers
     // bit 2 (set on a copy of the descriptor by kvq_decode_step): the sparse part of every score is in
     // the buffer already, written by the step's first launch
     if (sparse_first && !(c->loaded & KVQ_LOADED_SPARSE_SCORES_DONE)) {
-        kvq_status st = launch_qk_sparse<R>(c, q, scale, scores, ld, s);
+        kvq_status st = launch_qk_sparse<RQ>(c, q, scale, scores, ld, s);
         if (st != KVQ_OK) return st;
     }
     hipEvent_t *pev = (prof.enabled && prof.use_events) ? prof.ev[0][prof.count[0] % KVQ_PROFILE_RING] : nullptr;
     if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[0], s));
     static_assert(KVQ_STAT_SLOTS >= 256 + KVQ_MAX_SINK, "a slot per workgroup of a head plus the sink tokens");
     const unsigned ns = (unsigned)(c->n_sink < L ? c->n_sink : L);
-    kern<<<grid, NT, 0, s>>>(c->params, D, R, c->cap_tokens, L, c->k_codes, q, scale, scores, ld, (int)tiles,
+    kern<<<grid, NT, 0, s>>>(c->params, D, RQ, c->cap_tokens, L, c->k_codes, q, scale, scores, ld, (int)tiles,
                              sparse_first, stat_slots, (int)ns, span);
     if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[1], s));
     if (prof.enabled) ++prof.count[0];
     if (ns > 0)
-        kvq_qk_sink<<<dim3(ns, (unsigned)c->n_q_heads), 64, 0, s>>>(c->params, D, R, c->sink_k, q, scale, scores, ld,
+        kvq_qk_sink<<<dim3(ns, (unsigned)c->n_q_heads), 64, 0, s>>>(c->params, D, RQ, c->sink_k, q, scale, scores, ld,
                                                                     stat_slots, (int)gx);
     if (n_stat) *n_stat = (int)gx + (int)ns;
     KVQ_HIP_CHECK(hipGetLastError());
     return KVQ_OK;
 }
 
-// Query heads per workgroup: as many as fit the LDS budget (fp32 (A,B) tables: 64 pairs x entries x
-// 8 bytes per query head = 8 / 32 / 16 KiB for 2 / 3 / 4 bits).
+// Query heads per workgroup: as many as fit the LDS budget (one query head per KV head: fp32 (A,B) tables, 64
+// pairs x entries x 8 bytes = 8 / 32 / 16 KiB per head for 2 / 3 / 4 bits; grouped: Key tables of 8 / 32 / 8 KiB per KV head).
 template <int BITS, int R>
 kvq_status dispatch_qk(const kvq_cache *c, const float *q, float scale, float *scores, int64_t ld, float *st,
                        int *n_stat, hipStream_t s)
 {
-    constexpr int QHMAX = (BITS == 3) ? 4 : 8;
-    constexpr int PGD = (BITS == 4) ? 1 : (BITS == 3 ? 4 : 2);
-    constexpr int PG = PGD;
-    if constexpr (R >= QHMAX) {
-        // one KV head per workgroup, QHMAX of its query heads (R / QHMAX workgroups share the KV head)
-        return launch_qk<BITS, 1, QHMAX, 1024, PG, R>(c, q, scale, scores, ld, st, n_stat, s);
-    } else {
-        constexpr int KVH = QHMAX / R;
-        // Many heads per workgroup share the rotary sines and cosines but need a long context to keep
-        // the chip busy (a workgroup builds its tables once, then takes tiles of 1024 tokens).  With a
-        // shorter context that leaves most compute units idle: half as many heads per workgroup and
-        // tiles of 512 tokens give four times as many workgroups (two fit a compute unit), one KV head
-        // per workgroup 2 * KVH times as many.  The largest grouping that still yields workgroups for
-        // five eighths of the compute units is taken.
-        const int64_t L = c->n_tokens_k;
-        auto workgroups = [&](int kvh, int nt) {
-            const int64_t groups = c->n_kv_heads / kvh, tiles = (L + nt - 1) / nt;
-            int64_t gx = kvq_cu_count() / groups;
-            if (gx < 1) gx = 1;
-            if (gx > 256) gx = 256;
-            if (gx > tiles) gx = tiles;
-            return gx * groups;
-        };
-        const int64_t enough = (int64_t)kvq_cu_count() * 5 / 8;      // workgroups that keep most of the chip busy
-        if (c->n_kv_heads % KVH == 0 && workgroups(KVH, 1024) >= enough)
-            return launch_qk<BITS, KVH, R, 1024, PG, R>(c, q, scale, scores, ld, st, n_stat, s);
-        if constexpr (KVH >= 4) {
-            if (c->n_kv_heads % (KVH / 2) == 0 && workgroups(KVH / 2, 512) >= enough)
-                return launch_qk<BITS, KVH / 2, R, 512, PG, R>(c, q, scale, scores, ld, st, n_stat, s);
-        }
-        // few KV heads or a short context: one KV head per workgroup
-        return launch_qk<BITS, 1, R, 512, PG, R>(c, q, scale, scores, ld, st, n_stat, s);
+    // Many heads per workgroup share the rotary sines and cosines but need a long context to keep
+    // the chip busy (a workgroup builds its tables once, then takes tiles of 1024 tokens).  With a
+    // shorter context that leaves most compute units idle: half as many heads per workgroup and
+    // tiles of 512 tokens give four times as many workgroups (two fit a compute unit), one KV head
+    // per workgroup 2 * KVH times as many.  The largest grouping that still yields workgroups for
+    // five eighths of the compute units is taken.
+    const int64_t L = c->n_tokens_k;
+    auto workgroups = [&](int kvh, int nt) {
+        const int64_t groups = c->n_kv_heads / kvh, tiles = (L + nt - 1) / nt;
+        int64_t gx = kvq_cu_count() / groups;
+        if (gx < 1) gx = 1;
+        if (gx > 256) gx = 256;
+        if (gx > tiles) gx = tiles;
+        return gx * groups;
+    };
+    const int64_t enough = (int64_t)kvq_cu_count() * 5 / 8;      // workgroups that keep most of the chip busy
+    constexpr bool G = qk_grouped(BITS, R);
+    constexpr int KVH = G ? (R == 8 ? 2 : 4) : (BITS == 3 ? 4 : 8) / R;
+    constexpr int PG = G ? 2 : (BITS == 4) ? 1 : (BITS == 3 ? 4 : 2);
+    if (c->n_kv_heads % KVH == 0 && workgroups(KVH, 1024) >= enough)
+        return launch_qk<BITS, KVH, R, 1024, PG>(c, q, scale, scores, ld, st, n_stat, s);
+    if constexpr (KVH >= 4) {
+        if (c->n_kv_heads % (KVH / 2) == 0 && workgroups(KVH / 2, 512) >= enough)
+            return launch_qk<BITS, KVH / 2, R, 512, PG>(c, q, scale, scores, ld, st, n_stat, s);
     }
+    // few KV heads or a short context: one KV head per workgroup
+    return launch_qk<BITS, 1, R, 512, PG>(c, q, scale, scores, ld, st, n_stat, s);
 }
 
 template <int BITS>
