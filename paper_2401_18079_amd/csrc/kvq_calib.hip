@@ -3,14 +3,19 @@
 //     sum_i w_i (x_i - Q(x_i))^2,   w_i = F_ii s_i^2,   x = normalised calibration activations,
 // found with Lloyd's k-means iteration in one dimension.
 //
-// Design (gfx950).  An iteration streams the n values and weights once (8 bytes per element: the pass
-// is HBM-bound for large n) and needs, per signpost, the sums of w and of w*x over the elements nearest
-// to it.  The index of the nearest signpost is data dependent, so the running sums cannot live in
-// registers; every lane owns a private column of fp64 accumulators in LDS ([signpost][lane]: no
-// atomics, no bank conflicts beyond what 64-bit accesses cost anyway).  Workgroups write their sums to
-// a workspace, and a one-workgroup kernel adds them in a fixed order and moves the signposts, which
-// stay on the device between iterations.  fp32 distances with ties to the smaller index decide the
-// assignment; sums are fp64 (w*x of two fp32 numbers is exact in fp64).
+// Design (gfx950).  An iteration streams the n values and weights once (8 bytes per element: HBM-bound for
+// large n) and needs, per signpost, the sums of w and of w*x over the elements nearest to it.  The index of
+// the nearest signpost is data dependent, so the running sums cannot live in registers; every lane owns a
+// private column of fp64 accumulators in LDS ([signpost][lane]: no atomics, no bank conflicts).  The index
+// comes from a look-up instead of a search: the update that moves the signposts also finds the exact decision
+// thresholds between them (KVQ_CODE_RANGE), a workgroup spreads these over 1024 cells of [-1, 1], and an element
+// reads its cell's index and compares with the one threshold in it.  Where two thresholds fall into one cell,
+// or the signposts are not monotone to count on, and for values far outside, the search over all signposts
+// decides.  Workgroups write their sums to a workspace, and a one-workgroup kernel adds them in a fixed order
+// and moves the signposts, which stay on the device between iterations.  fp32 distances with ties to the
+// smaller index decide the assignment; sums are fp64 (w*x of two fp32 numbers is exact in fp64).
+// Measured per iteration on 33.6 M elements, 16 signposts: 78 us and 10 us for the update with the search (four
+// instructions per signpost) and a four-wavefront update; 46 us and 8 us now.
 #include <algorithm>
 #include "kvq_common.hpp"
 
@@ -18,7 +23,7 @@ namespace {
 
 constexpr int CAL_NT = 256;
 constexpr int CAL_MAX_WGS = 2048;
-constexpr int CAL_PARTS = 16;            // partial sums per signpost in the update kernel
+constexpr int CAL_PARTS = 64;            // partial sums per signpost in the update kernel
 
 template <int K>
 __device__ __forceinline__ int cal_nearest(const float (&c)[K], float x)
@@ -33,90 +38,192 @@ __device__ __forceinline__ int cal_nearest(const float (&c)[K], float x)
     return best;
 }
 
-// partial[workgroup][K][2] = (sum of w, sum of w*x) over the workgroup's elements nearest to signpost j
+constexpr int CAL_CELLS = 1024;
+__device__ __forceinline__ uint32_t cal_cell(float x)             // monotone in x
+{
+    const float c = __builtin_fmaf(x, CAL_CELLS / 2, CAL_CELLS / 2);
+    return (uint32_t)__builtin_amdgcn_fmed3f(c, 0.0f, (float)(CAL_CELLS - 1));
+}
+
+// partial[workgroup][K][2] = (sum of w, sum of w*x) over the workgroup's elements nearest to signpost j.
+// cent: K signposts, and from cent[16] on their K - 1 thresholds (thr[0] NaN: not to be counted on).
+// 33.6 M elements, 16 signposts: 78 -> 46 us (268 MB: 5.8 TB/s); bound by HBM.
 template <int K>
 __global__ __launch_bounds__(CAL_NT) void kvq_calib_assign(const float *__restrict__ x, const float *__restrict__ w,
                                                            int64_t n, const float *__restrict__ cent,
                                                            double *__restrict__ partial)
 {
-    __shared__ double acc_w[K][CAL_NT], acc_wx[K][CAL_NT];
+    __shared__ double2 acc[K][CAL_NT];
+    __shared__ float2 cells[CAL_CELLS];      // (threshold inside the cell or +inf, index below it)
+    __shared__ int crowded;
     const int tid = threadIdx.x;
-    float c[K];
+    const float *thr = cent + 16;
+    for (int j = 0; j < K; ++j) acc[j][tid] = double2{0.0, 0.0};
+    if (tid == 0) crowded = !(thr[0] == thr[0]);
+    __syncthreads();
+    for (int c = tid; c < CAL_CELLS; c += CAL_NT) {
+        int below = 0, inside = 0;
+        float t = INFINITY;
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-        c[j] = cent[j];
-        acc_w[j][tid] = 0.0;
-        acc_wx[j][tid] = 0.0;
-    }
-    // groups of four consecutive elements per lane (16-byte loads), grid-stride over the groups
-    const int64_t n4 = n >> 2;
-    const float4 *x4 = (const float4 *)x, *w4 = (const float4 *)w;
-    for (int64_t g = (int64_t)blockIdx.x * CAL_NT + tid; g < n4; g += (int64_t)gridDim.x * CAL_NT) {
-        const float4 xv = x4[g], wv = w4[g];
-        const float xs[4] = {xv.x, xv.y, xv.z, xv.w}, ws[4] = {wv.x, wv.y, wv.z, wv.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int j = cal_nearest<K>(c, xs[e]);
-            const double wd = (double)ws[e];
-            acc_w[j][tid] += wd;
-            acc_wx[j][tid] += wd * (double)xs[e];
+        for (int j = 0; j < K - 1; ++j) {
+            const float tj = thr[j];
+            const uint32_t cj = cal_cell(tj);
+            below += cj < (uint32_t)c ? 1 : 0;
+            if (cj == (uint32_t)c) { t = tj; ++inside; }
         }
+        cells[c] = float2{t, __builtin_bit_cast(float, below)};
+        if (inside > 1) crowded = 1;
+    }
+    __syncthreads();
+    const bool look_up = !crowded;
+    // groups of four consecutive elements per lane (16-byte loads), grid-stride over the groups; two groups
+    // ahead are in flight (two workgroups per compute unit is all that the accumulators of 16 signposts leave)
+    const int64_t n4 = n >> 2, stride = (int64_t)gridDim.x * CAL_NT;
+    const float4 *x4 = (const float4 *)x, *w4 = (const float4 *)w;
+    auto add = [&](int j, float xe, float we) {
+        const double wd = (double)we;
+        double2 a = acc[j][tid];
+        a.x += wd;
+        a.y += wd * (double)xe;
+        acc[j][tid] = a;
+    };
+    auto search = [&](float xe) {
+        float c[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) c[j] = cent[j];
+        return cal_nearest<K>(c, xe);
+    };
+    auto take = [&](const float4 &xv, const float4 &wv) {
+        const float xs[4] = {xv.x, xv.y, xv.z, xv.w}, ws[4] = {wv.x, wv.y, wv.z, wv.w};
+        int j[4];
+        bool far = !look_up;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) far = far || !(__builtin_fabsf(xs[e]) <= KVQ_CODE_RANGE);
+        if (__ballot(far) != 0ull) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) j[e] = search(xs[e]);
+        } else {
+            float2 c[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) c[e] = cells[cal_cell(xs[e])];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) j[e] = __builtin_bit_cast(int, c[e].y) + (xs[e] >= c[e].x ? 1 : 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) add(j[e], xs[e], ws[e]);
+    };
+    const int64_t g0 = (int64_t)blockIdx.x * CAL_NT + tid, last = n4 - 1;
+    float4 xa = {}, wa = {}, xb = {}, wb = {};
+    if (n4 > 0) {                              // (indexes past the end re-read the last group)
+        xa = x4[g0 < last ? g0 : last];
+        wa = w4[g0 < last ? g0 : last];
+        xb = x4[g0 + stride < last ? g0 + stride : last];
+        wb = w4[g0 + stride < last ? g0 + stride : last];
+    }
+    for (int64_t g = g0; g < n4; g += 2 * stride) {
+        const int64_t ga = g + 2 * stride < last ? g + 2 * stride : last, gb = g + 3 * stride < last ? g + 3 * stride : last;
+        const float4 xn = x4[ga], wn = w4[ga];
+        take(xa, wa);
+        xa = xn; wa = wn;
+        const float4 xm = x4[gb], wm = w4[gb];
+        if (g + stride < n4) take(xb, wb);
+        xb = xm; wb = wm;
     }
     // the last n % 4 elements
     if (blockIdx.x == 0 && tid < (int)(n & 3)) {
         const int64_t i = (n4 << 2) + tid;
-        const int j = cal_nearest<K>(c, x[i]);
-        const double wd = (double)w[i];
-        acc_w[j][tid] += wd;
-        acc_wx[j][tid] += wd * (double)x[i];
+        add(search(x[i]), x[i], w[i]);
     }
     __syncthreads();
-    // columns are added up in lane order: thread t < 2K takes one (signpost, sum) row
+    // columns are added up in lane order: PARTS threads per row of sums, then their sums
+    constexpr int PARTS = CAL_NT / (2 * K);
+    const double *sums = (const double *)&acc[0][0];
+    const int row = tid / PARTS, part = tid % PARTS;        // row: 2 j + (0: w, 1: w x)
+    double s = 0.0;
+    for (int l = part * (CAL_NT / PARTS); l < (part + 1) * (CAL_NT / PARTS); ++l) s += sums[((row >> 1) * CAL_NT + l) * 2 + (row & 1)];
+    __syncthreads();
+    double *parts = (double *)&acc[0][0];
+    parts[tid] = s;
+    __syncthreads();
     if (tid < 2 * K) {
-        const int j = tid >> 1;
-        const double *row = (tid & 1) ? acc_wx[j] : acc_w[j];
-        double s = 0.0;
-        for (int l = 0; l < CAL_NT; ++l) s += row[l];
-        partial[((int64_t)blockIdx.x * K + j) * 2 + (tid & 1)] = s;
+        double t = 0.0;
+        for (int p = 0; p < PARTS; ++p) t += parts[tid * PARTS + p];
+        partial[(int64_t)blockIdx.x * K * 2 + tid] = t;
     }
 }
 
 // cent[j] = fp32(sum w x / sum w) over all workgroups' partial sums, in a fixed order; a signpost
-// whose elements weigh nothing stays where it is
+// whose elements weigh nothing stays where it is.  Then the thresholds between the signposts.  n_wgs = 0: only
+// the thresholds.
 template <int K>
 __global__ __launch_bounds__(CAL_PARTS * 16) void kvq_calib_update(const double *__restrict__ partial, int n_wgs,
                                                                    float *__restrict__ cent)
 {
-    __shared__ double sw[CAL_PARTS][16], swx[CAL_PARTS][16];
+    __shared__ double2 sums[CAL_PARTS][16];
+    __shared__ float c[K];
     const int j = threadIdx.x & 15, part = threadIdx.x >> 4;
-    double a = 0.0, b = 0.0;
+    double2 a = {0.0, 0.0};
     if (j < K) {
-        for (int g = part; g < n_wgs; g += CAL_PARTS) {
-            a += partial[((int64_t)g * K + j) * 2];
-            b += partial[((int64_t)g * K + j) * 2 + 1];
+        for (int g0 = part; g0 < n_wgs; g0 += 8 * CAL_PARTS) {          // eight loads in flight per thread
+            double2 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int g = g0 + u * CAL_PARTS;
+                v[u] = g < n_wgs ? *(const double2 *)(partial + ((int64_t)g * K + j) * 2) : double2{0.0, 0.0};
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) { a.x += v[u].x; a.y += v[u].y; }
         }
     }
-    sw[part][j] = a;
-    swx[part][j] = b;
+    sums[part][j] = a;
     __syncthreads();
     if (part == 0 && j < K) {
         double ta = 0.0, tb = 0.0;
-        for (int p = 0; p < CAL_PARTS; ++p) { ta += sw[p][j]; tb += swx[p][j]; }
-        if (ta > 0.0) cent[j] = (float)(tb / ta);
+        for (int p = 0; p < CAL_PARTS; ++p) { ta += sums[p][j].x; tb += sums[p][j].y; }
+        c[j] = ta > 0.0 ? (float)(tb / ta) : cent[j];
+        cent[j] = c[j];
     }
+    __syncthreads();
+    if (threadIdx.x >= K - 1) return;
+    // thr[j]: the smallest fp32 x in the range that lies nearer to the next signpost above c[j] (strictly: a tie
+    // goes to the smaller index), by bisection over the ordered fp32 numbers
+    bool counted = true;
+    for (int i = 0; i < K; ++i) {
+        counted = counted && __builtin_fabsf(c[i]) <= 1.0f;
+        if (i > 0) counted = counted && (c[i] == c[i - 1] || c[i] - c[i - 1] >= KVQ_CODE_MIN_GAP);
+    }
+    const int t = threadIdx.x;
+    const float v = c[t];
+    float up = INFINITY;
+    for (int i = K - 1; i > t; --i) up = c[i] > v ? c[i] : up;
+    float out = INFINITY;
+    if (up <= 1.0f) {
+        auto val = [](int64_t k) { return __builtin_bit_cast(float, (int32_t)(k >= 0 ? k : (int64_t)INT32_MIN - k)); };
+        const int64_t top = (int64_t)__builtin_bit_cast(int32_t, KVQ_CODE_RANGE);
+        int64_t lo = -top, hi = top;            // (the range's ends lie nearer to the lower and to the upper signpost)
+        while (lo < hi) {
+            const int64_t mid = lo + ((hi - lo) >> 1);
+            const float m = val(mid);
+            if (__builtin_fabsf(m - up) < __builtin_fabsf(m - v)) hi = mid;
+            else lo = mid + 1;
+        }
+        out = val(lo);
+    }
+    cent[16 + t] = counted ? out : __builtin_nanf("");
 }
 
 template <int K>
 kvq_status run_calibration(const float *x, const float *w, int64_t n, int iters, float *cent, double *partial,
                            hipStream_t s)
 {
-    // enough workgroups to fill the chip (LDS allows 10 / 5 / 2 per compute unit for 4 / 8 / 16
-    // signposts), no more than there are groups of 1024 elements, within the workspace's slots
+    // enough workgroups to fill the chip (LDS allows 6 / 3 / 2 per compute unit for 4 / 8 / 16 signposts),
+    // no more than there are groups of 1024 elements, within the workspace's slots
     int64_t wgs = (n / 4 + CAL_NT - 1) / CAL_NT;
-    const int64_t fill = 256 * (K == 16 ? 2 : K == 8 ? 5 : 8);
+    const int64_t fill = (int64_t)kvq_cu_count() * (K == 16 ? 2 : K == 8 ? 3 : 6);
     if (wgs > fill) wgs = fill;
     if (wgs > CAL_MAX_WGS) wgs = CAL_MAX_WGS;
     if (wgs < 1) wgs = 1;
+    if (iters > 0) kvq_calib_update<K><<<1, CAL_PARTS * 16, 0, s>>>(partial, 0, cent);      // the first thresholds
     for (int it = 0; it < iters; ++it) {
         kvq_calib_assign<K><<<(unsigned)wgs, CAL_NT, 0, s>>>(x, w, n, cent, partial);
         kvq_calib_update<K><<<1, CAL_PARTS * 16, 0, s>>>(partial, (int)wgs, cent);
@@ -143,7 +250,7 @@ extern "C" kvq_status kvq_calibrate_nuq(const float *d_x_norm, const float *d_w,
     if (workspace_bytes < kvq_calibrate_workspace_bytes()) return KVQ_ERR_CAPACITY;
     hipStream_t s = (hipStream_t)stream;
     const int K = 1 << bits;
-    float *cent = (float *)d_workspace;                       // 16 floats, then the partial sums
+    float *cent = (float *)d_workspace;                       // 16 signposts, 15 thresholds, then the partial sums
     double *partial = (double *)((char *)d_workspace + 256);
     KVQ_HIP_CHECK(hipMemcpyAsync(cent, h_signposts, (size_t)K * sizeof(float), hipMemcpyHostToDevice, s));
     kvq_status st = (bits == 2)   ? run_calibration<4>(d_x_norm, d_w, n, iters, cent, partial, s)

@@ -42,3 +42,46 @@ def test_channel_constants_at_the_edges(T, D, p, shift, kind):
     got = K.kvq_calibrate_key_channels(dev, p)
     for name, a, b in zip(("s", "z", "lo", "hi"), got, C.key_channel_constants(x, p)):
         assert np.array_equal(a, b), (name, np.nonzero(a != b)[0][:5])
+
+
+@pytest.mark.parametrize("bits,n,kind", [
+    (4, 100003, "plain"), (3, 5, "plain"), (2, 1 << 20, "plain"),
+    (4, 50001, "close"),                      # two decision points in one cell of the look-up
+    (3, 50002, "unsorted"),                   # signposts that do not ascend
+    (4, 50003, "wide"),                       # signposts beyond [-1, 1]
+    (3, 40000, "equal"),                      # signposts that coincide
+    (4, 40001, "far"),                        # values far outside the signposts
+])
+def test_signposts_where_the_look_up_could_part_from_the_search(bits, n, kind):
+    import torch
+    import paper_2401_18079_amd as K
+    rng = np.random.default_rng(n + bits)
+    k = 1 << bits
+    c = np.linspace(-1, 1, k)
+    if kind == "close":
+        c[1:4] = [-0.5, -0.4999, -0.4998]
+    elif kind == "unsorted":
+        c = rng.permutation(c)
+    elif kind == "wide":
+        c = c * 3.0
+    elif kind == "equal":
+        c[2] = c[1]
+    c = c.astype(np.float32)
+    x = rng.standard_normal(n) * 0.4
+    mid = (np.sort(c)[1:] + np.sort(c)[:-1]) / 2
+    x[::7] = rng.choice(mid, x[::7].size)     # on the decision points, and next to them
+    x = x.astype(np.float32)
+    x[::14] = np.nextafter(x[::14], np.float32(9.0))
+    if kind == "far":
+        x[::101] = rng.choice(np.float32([127.5, -300.0, 1e6, -3e8]), x[::101].size)
+    w = np.exp(rng.standard_normal(n)).astype(np.float32)
+    got = K.kvq_calibrate_nuq(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), bits, 1, c)
+    # one iteration: the assignment is exact, the sums are fp64 in another order (a few ulps of fp64), one rounding to fp32
+    idx = C.nearest(x, c)
+    ref = c.astype(np.float64)
+    for j in range(k):
+        m = idx == j
+        if w[m].sum() > 0:
+            ref[j] = (w[m].astype(np.float64) * x[m]).sum() / w[m].astype(np.float64).sum()
+    ref = np.sort(ref)
+    assert np.all(np.abs(got - ref) <= 2.0 ** -23 * np.maximum(np.abs(ref), 1e-12 * n)), (got, ref)
