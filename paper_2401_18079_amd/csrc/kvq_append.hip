@@ -10,8 +10,9 @@
 
 namespace {
 
-// Launch rules.  Keys: a wavefront per token from KVQ_WAVE_TOKENS tokens on (4096 tokens of 4096 channels, 3 bits:
-// 30 us), sixteen wavefronts per token below (one token of 5120 channels: 10.9 us with the looping body, 5.7 us;
+// Launch rules.  Keys: a wavefront per token from KVQ_WAVE_TOKENS tokens on, twice that above 16 heads (3 bits, 32 heads:
+// 4096 tokens 30 us against 38 us with sixteen wavefronts per token, 2500 tokens 24 / 25, 1500 tokens 22 / 17; 8 heads:
+// 1500 tokens 7.2 / 9.1), sixteen wavefronts per token below (one token of 5120 channels: 10.9 us with the looping body, 5.7 us;
 // 777 tokens, 4 bits: 19.9 us with 256 threads per token, 17.2 us).  Values of 1024, 2048, 4096 and (but for
 // middling calls) 5120, 6656 and 8192 channels keep a token in registers (v_quant_token4): four wavefronts per
 // token and two tokens, the pair that shares dwords, per workgroup in calls of KVQ_VW_SMALL_TOKENS tokens and
@@ -1379,7 +1380,7 @@ extern "C" kvq_status kvq_quantize_append_k(kvq_cache *cache, const uint16_t *d_
 #define LAUNCH_K(B)                                                                                             \
     do {                                                                                                        \
         const int H = cache->n_kv_heads;                                                                        \
-        if (T >= KVQ_WAVE_TOKENS)                                                                               \
+        if (T >= (H > 16 ? 2 : 1) * KVQ_WAVE_TOKENS)                                                            \
             kvq_k_quant_wave<B><<<(T + KVQ_KW_NT / 64 - 1) / (KVQ_KW_NT / 64), KVQ_KW_NT, 0, s>>>(               \
                 cache->params, D, T, cache->cap_tokens, cache->n_tokens_k, d_k_new, cache->k_codes,              \
                 cache->k_ptr, ksp, cache->cap_nnz_k, cache->d_status);                                           \

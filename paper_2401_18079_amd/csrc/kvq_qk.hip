@@ -1140,7 +1140,8 @@ kvq_status launch_qk(const kvq_cache *c, const float *q, float scale, float *sco
     const int64_t tiles = (L + NT - 1) / NT;
     // about one workgroup per compute unit in total (the tables fill most of a CU's LDS); each
     // workgroup builds its tables once and then streams its share of the tiles
-    int64_t gx = kvq_cu_count() / groups;
+    // (the grouped kernel's tables are small: two workgroups of 512 threads per compute unit)
+    int64_t gx = (GROUPED && NT == 512 ? 2 : 1) * kvq_cu_count() / groups;
     if (gx < 1) gx = 1;
     if (gx > 256) gx = 256;          // a head owns 256 statistics slots
     if (gx > tiles) gx = tiles;
