@@ -184,13 +184,18 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
     float m2[RG], lacc[RG], zacc[RG], scale[RG];
     int expo[RG];                                                   // scale = 2^expo; 0: no tile seen yet
 #pragma unroll
-    for (int h = 0; h < RG; ++h) {
-        m2[h] = 0.f; lacc[h] = 0.f; zacc[h] = 0.f; scale[h] = 0.f; expo[h] = 0;
-        if (stat_slots) {
-            float m = KVQ_STAT_FLOOR;
-            for (int i = lane; i < n_stat; i += 64) m = __builtin_fmaxf(m, stat_slots[(int64_t)(q0 + h) * KVQ_STAT_SLOTS + i]);
-            m2[h] = kvq_wave_max(m) * KVQ_LOG2E;
+    for (int h = 0; h < RG; ++h) { m2[h] = 0.f; lacc[h] = 0.f; zacc[h] = 0.f; scale[h] = 0.f; expo[h] = 0; }
+    if (stat_slots) {
+        float m[RG];                                                // (the heads' loads are in flight together)
+#pragma unroll
+        for (int h = 0; h < RG; ++h) m[h] = KVQ_STAT_FLOOR;
+        for (int i0 = 0; i0 < n_stat; i0 += 64) {
+            const int i = i0 + lane < n_stat ? i0 + lane : n_stat - 1;      // a repeated slot does not change a maximum
+#pragma unroll
+            for (int h = 0; h < RG; ++h) m[h] = __builtin_fmaxf(m[h], stat_slots[(int64_t)(q0 + h) * KVQ_STAT_SLOTS + i]);
         }
+#pragma unroll
+        for (int h = 0; h < RG; ++h) m2[h] = kvq_wave_max(m[h]) * KVQ_LOG2E;
     }
     for (int e = tid; e < C::TAB / 4; e += C::NT) {
         const int f = C::FG == 1 ? e / (C::ROW / 4) : ((e >> 5) >> (4 * (e & 1))) & 15;     // field that dword e stands for
