@@ -14,6 +14,7 @@
 namespace {
 
 constexpr int PV_TILE = 64;                // tokens per tile of the dense kernel (32 token pairs)
+constexpr int PV_CHAIN = 16;               // tiles whose products one accumulator takes up
 constexpr int PV_MIN_TILES = 8;            // tiles a workgroup should at least have: half of its wavefronts busy
 
 struct PvPlan {
@@ -96,10 +97,16 @@ __device__ inline uint32_t pv_field_off(const uint32_t *W, int i, uint32_t lane_
 // n of a step stands for channel 8 n + t (t = 0..7: eight steps cover the KV head's 128 channels), its 32
 // rows for 32 tokens, and a lane's eight values are four fields of the storage format as the table returns
 // them, (lut[a], lut[b]) of a token pair: fp16 numbers, exact.  The left operand is weights w = p s: row
-// 4 h + i holds part i of head h's weights, w = w_0 + w_1 + w_2 in fp16 (33 bits: more than the fp32 weight
-// has wherever it is within 2^-15 of the largest one), under a power-of-two scale per wavefront and head that
-// keeps the largest weight below 2^15 (lowered, with an exact rescaling of the sums, when a tile exceeds it).
-// Products are exact and sums fp32, as in a chain of fp32 multiply-adds; rows i = 3 are not used.
+// 4 h + i holds part i of head h's weights: w = w_0 + 2^-12 w_1 + 2^-24 w_2 under a power-of-two scale per
+// wavefront and head that keeps the largest weight below 2^15 (at 2^8 when it is set; lowered, with an exact
+// rescaling of the sums, when a tile exceeds it).  Each part is the fp16 number nearest to what the ones before it
+// leave, raised by 2^12: all 24 bits of an fp32 weight are held down to 2^-33 of the largest one, and a smaller one to
+// 2^-57 of the largest.  (Parts under one common scale end at 2^-24: a weight 2^-20 of the largest, beside an
+// attention sink, keeps 13 bits.)  Products are exact and sums fp32, rounded once per instruction (32 tokens); rows
+// i = 3 are not used.  A row's sum runs over PV_CHAIN tiles and is then added to the wavefront's (sum[]): at a
+// million tokens a wavefront has 8192, and the error against 64 bits on random codes and weights is 1.4e-7 of the
+// result instead of 2.8e-7 with one running sum (added every 4 tiles 1.4e-7 too, and 0.5 % slower at 131072 tokens;
+// every 16: no difference there or at a million, 56.1 -> 56.4 us for a step of 16384).
 //
 // Per field a lane spends two instructions (cut the field out, form the table address) and one LDS gather
 // (2-bit codes: per pair of fields, whose byte indexes a table of both), whatever RG: the multiply-adds, 2 RG instructions per field before, are off the vector ALUs.  What the
@@ -116,6 +123,7 @@ __device__ inline uint32_t pv_field_off(const uint32_t *W, int i, uint32_t lane_
 //
 // grid = (slabs, head groups); the wavefronts of a workgroup take its tiles in turn and add their sums
 // through LDS.  Writes partial[slab][q][128], zpart[slab][q] and (with statistics) lpart[slab][q].
+constexpr float PV_PART_UP = 4096.f, PV_PART_DOWN = 1.f / 4096.f;
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
@@ -220,12 +228,24 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
     const uint8_t *brow = mine + kg * 4 * C::PAIR + (BITS == 3 ? (col >> 1) * 12 + (col & 1) * 4 : 2 * BITS * col);
     const uint32_t bshift = (uint32_t)(col & 1) * 16;
     float4_t acc[SETS][8];
+    float sum[SETS][8];                                             // head 4 q + kg, channel 8 col + t, scaled
 #pragma unroll
     for (int q = 0; q < SETS; ++q)
 #pragma unroll
-        for (int t = 0; t < 8; ++t) acc[q][t] = float4_t{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < 8; ++t) { acc[q][t] = float4_t{0.f, 0.f, 0.f, 0.f}; sum[q][t] = 0.f; }
+    auto collect = [&] {                                            // the three parts of the weights meet
+#pragma unroll
+        for (int q = 0; q < SETS; ++q)
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const float small = __builtin_fmaf(acc[q][t][2], PV_PART_DOWN, acc[q][t][1]);
+                sum[q][t] += __builtin_fmaf(small, PV_PART_DOWN, acc[q][t][0]);
+                acc[q][t] = float4_t{0.f, 0.f, 0.f, 0.f};
+            }
+    };
 
-    for (; tile < tile1; tile += WAVES) {
+    for (int chain = 0; tile < tile1; tile += WAVES) {
+        if (chain++ == PV_CHAIN) { collect(); chain = 1; }
         const int64_t n = (int64_t)tile * PV_TILE + lane;
         const bool ok = n < L && n >= n_sink;
         const float s = kvq_h2f((uint16_t)(szw & 0xFFFFu)), z = kvq_h2f((uint16_t)(szw >> 16));
@@ -262,16 +282,16 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
 #pragma unroll
                 for (int h = 0; h < 4 && 4 * q + h < RG; ++h) r = kg == h ? ratio[4 * q + h] : r;
 #pragma unroll
-                for (int t = 0; t < 8; ++t) acc[q][t] *= r;
+                for (int t = 0; t < 8; ++t) { acc[q][t] *= r; sum[q][t] *= r; }
             }
         }
 #pragma unroll
         for (int h = 0; h < RG; ++h) {
             const float ws = w[h] * scale[h];
             const half_t a = (half_t)ws;
-            const float r1 = ws - (float)a;
+            const float r1 = (ws - (float)a) * PV_PART_UP;          // (below 2^15 again, and exact)
             const half_t b = (half_t)r1;
-            const half_t c = (half_t)(r1 - (float)b);
+            const half_t c = (half_t)((r1 - (float)b) * PV_PART_UP);
             half_t *row = (half_t *)(wrows + 3 * h * C::WROW) + lane;
             row[0] = a;
             row[C::WROW / 2] = b;
@@ -328,6 +348,7 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
+    collect();
     // the workgroup's sums: wavefronts leave theirs in LDS, [wave][head][128 channels, zero-point, weights]
 #pragma unroll
     for (int h = 0; h < RG; ++h) {
@@ -346,7 +367,7 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
         for (int i = 0; i < 4 && 4 * q + i < RG; ++i) inv = kg == i ? (scale[4 * q + i] == 0.f ? 0.f : __builtin_ldexpf(1.f, -expo[4 * q + i])) : inv;
         if (h < RG) {
 #pragma unroll
-            for (int t = 0; t < 8; ++t) sums[h * 130 + 8 * col + t] = (acc[q][t][0] + (acc[q][t][1] + acc[q][t][2])) * inv;
+            for (int t = 0; t < 8; ++t) sums[h * 130 + 8 * col + t] = sum[q][t] * inv;
         }
     }
     if (lane == 0) {
