@@ -376,8 +376,8 @@ __attribute__((visibility("hidden"))) int64_t kvq_pv_workspace_bytes(int n_q_hea
 // event pairs recorded around the launch: what the stream sees between the end of the kernel before
 // and the end of this one (the records themselves stall the queue by a few microseconds each).
 // (2) The kernel's own span: the first thread of every workgroup stores the GPU's constant-rate wall
-// clock when the workgroup starts and, after a barrier at the very end, when all its wavefronts are
-// done (plain stores to the workgroup's own slot of a caller-provided device buffer: atomics on one
+// clock at the workgroup's start and, after a barrier at the very end, when all its wavefronts are
+// done (both stored at the end; plain stores to the workgroup's own slot of a caller-provided device buffer: atomics on one
 // address would stall the kernel they are meant to time).  First start to last end over the
 // workgroups is the span a kernel trace reports, and nothing is inserted between kernels.
 // Buffer layout: [2 kernels][RING calls][KVQ_PROFILE_MAX_WGS][start, end], 64-bit ticks, zero = unused.
@@ -397,21 +397,29 @@ inline unsigned long long *kvq_profile_span_slot(KvqProfile &p, int which, int64
     if (!p.enabled || !p.spans || n_wgs > KVQ_PROFILE_MAX_WGS) return nullptr;
     return p.spans + ((int64_t)which * KVQ_PROFILE_RING + (p.count[which] % KVQ_PROFILE_RING)) * KVQ_PROFILE_MAX_WGS * 2;
 }
-__device__ __forceinline__ void kvq_span_start(unsigned long long *slots)
+// The constant-rate wall clock.  (The builtin counts as a write to memory: behind it, as behind a store, the
+// compiler no longer reads kernel constants with scalar loads.  With either at its start the span instantiation of a
+// kernel holds them in vector registers, 20 more, and spills where the plain one does not.)
+__device__ __forceinline__ unsigned long long kvq_wall_clock()
 {
-    if (slots && threadIdx.x == 0)
-        slots[2 * (blockIdx.y * gridDim.x + blockIdx.x)] = (unsigned long long)wall_clock64();
+    unsigned long long t;
+    asm volatile("s_memrealtime %0\n\ts_waitcnt lgkmcnt(0)" : "=s"(t));
+    return t;
 }
-// Every thread of the workgroup must call this (it holds a barrier when spans are being taken).
-__device__ __forceinline__ void kvq_span_end(unsigned long long *slots)
+// Every thread of the workgroup must call this (it holds a barrier when spans are being taken).  `start`: the clock
+// when the workgroup started; both times are stored here.
+__device__ __forceinline__ void kvq_span_end(unsigned long long *slots, unsigned long long start)
 {
     if (slots) {
         // this wavefront's stores have been acknowledged (a wait only: a fence would also write back
         // and invalidate caches that the workgroups still running depend on)
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x == 0)
-            slots[2 * (blockIdx.y * gridDim.x + blockIdx.x) + 1] = (unsigned long long)wall_clock64();
+        if (threadIdx.x == 0) {
+            unsigned long long *mine = slots + 2 * (blockIdx.y * gridDim.x + blockIdx.x);
+            mine[0] = start;
+            mine[1] = kvq_wall_clock();
+        }
     }
 }
 KvqProfile &kvq_profile_state();

@@ -152,7 +152,7 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
     float *__restrict__ partial, float *__restrict__ zpart, int n_tiles, int n_sink,
     const float *__restrict__ stat_slots, int n_stat, float *__restrict__ lpart, unsigned long long *span)
 {
-    if (SPAN) kvq_span_start(span);       // timing-aid instantiation (kvq_profile_*): workgroup start and end times
+    const unsigned long long span_start = SPAN ? kvq_wall_clock() : 0;      // timing-aid instantiation (kvq_profile_*)
     // tokens below n_sink are attention-sink tokens kept in fp16: their quantized form gets weight 0
     // here and the reduce kernel adds their fp16 rows.
     // stat_slots != null: `probs` holds raw scores x; a wavefront takes the maximum m of each of its
@@ -385,7 +385,7 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
         else if (c == 128) zpart[o] = v;
         else if (stat_slots) lpart[o] = v;
     }
-    if (SPAN) kvq_span_end(span);
+    if (SPAN) kvq_span_end(span, span_start);
 }
 
 // Sparse part, balanced (paper App. "Kernel Implementation Details": equal non-zeros per thread):

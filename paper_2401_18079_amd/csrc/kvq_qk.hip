@@ -271,9 +271,9 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
                                                     unsigned long long *span)
 {
     // SPAN: timing-aid instantiation (kvq_profile_*): the workgroup leaves its start and end times in
-    // `span`.  A separate instantiation, and none for the eight-head variants: they have no register
-    // to spare for the pointer, and the variant that is timed should be the one that is used.
-    if (SPAN) kvq_span_start(span);
+    // `span`.  A separate instantiation, with the registers of the plain one (see kvq_wall_clock), and none for
+    // the eight-head variants, which spill as they are: what is timed should be what is used.
+    const unsigned long long span_start = SPAN ? kvq_wall_clock() : 0;
     // add_prev != 0: the score buffer already holds the sparse part; add to it instead of overwriting.
     // STATS: the workgroup also leaves the maximum of the scores it wrote (tokens below n_sink
     // excepted: the attention-sink kernel replaces their scores) in slot blockIdx.x of each of its
@@ -417,7 +417,7 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
             stat_slots[(int64_t)(q0 + tid) * KVQ_STAT_SLOTS + blockIdx.x] = m;
         }
     }
-    if (SPAN) kvq_span_end(span);
+    if (SPAN) kvq_span_end(span, span_start);
 }
 
 // ---- grouped queries ---------------------------------------------------------------------------------
@@ -540,7 +540,7 @@ __global__ __launch_bounds__(NT) void kvq_qkg_kernel(const void *__restrict__ pa
                                                      int add_prev, float *__restrict__ stat_slots, int n_sink,
                                                      unsigned long long *span)
 {
-    if (SPAN) kvq_span_start(span);
+    const unsigned long long span_start = SPAN ? kvq_wall_clock() : 0;
     using C = QkCfg<BITS>;
     constexpr int QH = KVH * RQ, SETS = (RQ + 3) / 4, NE = C::NE;
     // Key elements of a (KV head, pair): joint entries (k_i, k_{i+64}) of 8 bytes, or NE + NE of 4 bytes
@@ -652,7 +652,7 @@ __global__ __launch_bounds__(NT) void kvq_qkg_kernel(const void *__restrict__ pa
             stat_slots[(int64_t)(q0 + tid) * KVQ_STAT_SLOTS + blockIdx.x] = m;
         }
     }
-    if (SPAN) kvq_span_end(span);
+    if (SPAN) kvq_span_end(span, span_start);
 }
 
 // ---- piece-major dense kernel for 3-bit codes ------------------------------------------------------
