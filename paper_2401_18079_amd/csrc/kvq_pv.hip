@@ -38,6 +38,22 @@ __host__ __device__ constexpr int pvs_wave_lds_floats(int n_q_heads)
     return n_q_heads * PVS_ROW;                          // the sub-range's probabilities
 }
 
+// Query heads of one KV head that a wavefront of the dense kernel takes together (they share the codes): a group of
+// several saves gathers and reads per tile and costs start and end of the kernel (maxima, sums over lanes and
+// wavefronts, one head after the other), so it pays once a wavefront has tiles enough.  Counted in tiles per
+// wavefront of the whole GPU with one head each: one head up to 1, two up to 3, four up to 12.  Measured, kvq_pv_matvec,
+// us with groups of 8 / 4 / 2 / 1 heads: 32 heads on 4, 2-bit, 1000 tokens (1/8 tile) 17.6 / 14.6 / 14.1 / 14.2, 12000
+// (1.5) 18.6 / 16.0 / 15.4 / 15.6; 3-bit, 24000 (2.9) 19.4 / 18.6 / 18.6 / 20.8, 48000 (5.9) 24.7 / 24.8 / 26.3 / 31.4, 131000
+// (16) 32.7 / 33.3 / 39.7 / 54.7; 64 on 8, 4-bit, 6000 (1.5) 31.5 / 28.8 / 28.8 / 29.8, 24000 (5.9) 38.6 / 37.6 / 39.5 / 44.6,
+// 131000 (32) 68.8 / 71.8 / 84.1 / 114.5.
+inline int pv_group(int64_t L, int n_q_heads, int r)
+{
+    const int64_t tiles = n_q_heads * ((L + PV_TILE - 1) / PV_TILE), waves = 16 * (int64_t)kvq_cu_count();
+    int rg = tiles <= waves ? 1 : tiles <= 3 * waves ? 2 : tiles <= 12 * waves ? 4 : 8;
+    while (r % rg) rg >>= 1;
+    return rg;
+}
+
 inline PvPlan pv_plan(int64_t L, int n_q_heads, int rg)
 {
     PvPlan p;
@@ -697,8 +713,7 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
     const int Hq = cache->n_q_heads, D = cache->n_kv_heads * KVQ_HEAD_DIM;
     if (!cache->workspace || cache->workspace_bytes < kvq_pv_workspace_bytes(Hq)) return KVQ_ERR_CAPACITY;
     const int r = Hq / cache->n_kv_heads;
-    // query heads of one KV head that a wavefront of the dense kernel takes together (they share the codes)
-    const int rg = (r % 8 == 0) ? 8 : (r % 4 == 0) ? 4 : (r % 2 == 0) ? 2 : 1;
+    const int rg = pv_group(L, Hq, r);
     const PvPlan plan = (L > 0) ? pv_plan(L, Hq, rg) : PvPlan{0, 0, 0, 0, 0, 0};
     float *partial = (float *)cache->workspace;
     float *zpart = partial + (int64_t)512 * Hq * 128;
