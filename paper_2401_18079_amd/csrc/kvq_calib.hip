@@ -7,22 +7,25 @@
 // large n) and needs, per signpost, the sums of w and of w*x over the elements nearest to it.  The index of
 // the nearest signpost is data dependent, so the running sums cannot live in registers; every lane owns a
 // private column of fp64 accumulators in LDS ([signpost][lane]: no atomics, no bank conflicts).  The index
-// comes from a look-up instead of a search: the update that moves the signposts also finds the exact decision
-// thresholds between them (KVQ_CODE_RANGE), a workgroup spreads these over 1024 cells of [-1, 1], and an element
-// reads its cell's index and compares with the one threshold in it.  Where two thresholds fall into one cell,
-// or the signposts are not monotone to count on, and for values far outside, the search over all signposts
-// decides.  Workgroups write their sums to a workspace, and a one-workgroup kernel adds them in a fixed order
-// and moves the signposts, which stay on the device between iterations.  fp32 distances with ties to the
+// comes from a search over all signposts or, for 16 of them and many elements, from a look-up: the update that moves
+// the signposts also finds the exact decision thresholds between them (KVQ_CODE_RANGE), a workgroup spreads these
+// over 1024 cells of [-1, 1], and an element reads its cell's index and compares with the one threshold in it.  Where
+// two thresholds fall into one cell, or the signposts are not monotone to count on, and for values far outside, the
+// search decides there too.  Workgroups write their sums to a workspace, and a one-workgroup kernel adds them in a
+// fixed order and moves the signposts, which stay on the device between iterations.  fp32 distances with ties to the
 // smaller index decide the assignment; sums are fp64 (w*x of two fp32 numbers is exact in fp64).
 // Measured per iteration on 33.6 M elements, 16 signposts: 78 us and 10 us for the update with the search (four
-// instructions per signpost) and a four-wavefront update; 46 us and 8 us now.
+// instructions per signpost), loads not ahead of it, and a four-wavefront update; 46 us and 8 us now.  On 65536
+// elements, where the search is taken: 5.0 and 2.3 us.
 #include <algorithm>
+#include <type_traits>
 #include "kvq_common.hpp"
 
 namespace {
 
 constexpr int CAL_NT = 256;
 constexpr int CAL_MAX_WGS = 2048;
+constexpr int64_t CAL_LOOK_UP_MIN = 6 << 20;      // elements from which 16 signposts are found by look-up
 constexpr int CAL_PARTS = 64;            // partial sums per signpost in the update kernel
 
 template <int K>
@@ -48,20 +51,23 @@ __device__ __forceinline__ uint32_t cal_cell(float x)             // monotone in
 // partial[workgroup][K][2] = (sum of w, sum of w*x) over the workgroup's elements nearest to signpost j.
 // cent: K signposts, and from cent[16] on their K - 1 thresholds (thr[0] NaN: not to be counted on).
 // 33.6 M elements, 16 signposts: 78 -> 46 us (268 MB: 5.8 TB/s); bound by HBM.
-template <int K>
+// LOOK_UP = false: every element takes the search (see run_calibration).
+template <int K, bool LOOK_UP>
 __global__ __launch_bounds__(CAL_NT) void kvq_calib_assign(const float *__restrict__ x, const float *__restrict__ w,
                                                            int64_t n, const float *__restrict__ cent,
                                                            double *__restrict__ partial)
 {
     __shared__ double2 acc[K][CAL_NT];
-    __shared__ float2 cells[CAL_CELLS];      // (threshold inside the cell or +inf, index below it)
+    __shared__ float2 cells[LOOK_UP ? CAL_CELLS : 1];        // (threshold inside the cell or +inf, index below it)
     __shared__ int crowded;
     const int tid = threadIdx.x;
     const float *thr = cent + 16;
     for (int j = 0; j < K; ++j) acc[j][tid] = double2{0.0, 0.0};
-    if (tid == 0) crowded = !(thr[0] == thr[0]);
-    __syncthreads();
-    for (int c = tid; c < CAL_CELLS; c += CAL_NT) {
+    if (LOOK_UP) {
+        if (tid == 0) crowded = !(thr[0] == thr[0]);
+        __syncthreads();
+    }
+    for (int c = tid; c < (LOOK_UP ? CAL_CELLS : 0); c += CAL_NT) {
         int below = 0, inside = 0;
         float t = INFINITY;
 #pragma unroll
@@ -74,8 +80,8 @@ __global__ __launch_bounds__(CAL_NT) void kvq_calib_assign(const float *__restri
         cells[c] = float2{t, __builtin_bit_cast(float, below)};
         if (inside > 1) crowded = 1;
     }
-    __syncthreads();
-    const bool look_up = !crowded;
+    if (LOOK_UP) __syncthreads();
+    const bool look_up = LOOK_UP && !crowded;
     // groups of four consecutive elements per lane (16-byte loads), grid-stride over the groups; two groups
     // ahead are in flight (two workgroups per compute unit is all that the accumulators of 16 signposts leave)
     const int64_t n4 = n >> 2, stride = (int64_t)gridDim.x * CAL_NT;
@@ -135,12 +141,13 @@ __global__ __launch_bounds__(CAL_NT) void kvq_calib_assign(const float *__restri
         add(search(x[i]), x[i], w[i]);
     }
     __syncthreads();
-    // columns are added up in lane order: PARTS threads per row of sums, then their sums
+    // columns are added up in a fixed order: PARTS threads per row of sums, each every PARTS-th column (next to each
+    // other in the banks), then their sums
     constexpr int PARTS = CAL_NT / (2 * K);
     const double *sums = (const double *)&acc[0][0];
     const int row = tid / PARTS, part = tid % PARTS;        // row: 2 j + (0: w, 1: w x)
     double s = 0.0;
-    for (int l = part * (CAL_NT / PARTS); l < (part + 1) * (CAL_NT / PARTS); ++l) s += sums[((row >> 1) * CAL_NT + l) * 2 + (row & 1)];
+    for (int l = part; l < CAL_NT; l += PARTS) s += sums[((row >> 1) * CAL_NT + l) * 2 + (row & 1)];
     __syncthreads();
     double *parts = (double *)&acc[0][0];
     parts[tid] = s;
@@ -155,7 +162,7 @@ __global__ __launch_bounds__(CAL_NT) void kvq_calib_assign(const float *__restri
 // cent[j] = fp32(sum w x / sum w) over all workgroups' partial sums, in a fixed order; a signpost
 // whose elements weigh nothing stays where it is.  Then the thresholds between the signposts.  n_wgs = 0: only
 // the thresholds.
-template <int K>
+template <int K, bool LOOK_UP>
 __global__ __launch_bounds__(CAL_PARTS * 16) void kvq_calib_update(const double *__restrict__ partial, int n_wgs,
                                                                    float *__restrict__ cent)
 {
@@ -179,10 +186,11 @@ __global__ __launch_bounds__(CAL_PARTS * 16) void kvq_calib_update(const double 
     __syncthreads();
     if (part == 0 && j < K) {
         double ta = 0.0, tb = 0.0;
-        for (int p = 0; p < CAL_PARTS; ++p) { ta += sums[p][j].x; tb += sums[p][j].y; }
+        for (int p = 0; p < (n_wgs < CAL_PARTS ? n_wgs : CAL_PARTS); ++p) { ta += sums[p][j].x; tb += sums[p][j].y; }
         c[j] = ta > 0.0 ? (float)(tb / ta) : cent[j];
         cent[j] = c[j];
     }
+    if (!LOOK_UP) return;
     __syncthreads();
     if (threadIdx.x >= K - 1) return;
     // thr[j]: the smallest fp32 x in the range that lies nearer to the next signpost above c[j] (strictly: a tie
@@ -223,10 +231,23 @@ kvq_status run_calibration(const float *x, const float *w, int64_t n, int iters,
     if (wgs > fill) wgs = fill;
     if (wgs > CAL_MAX_WGS) wgs = CAL_MAX_WGS;
     if (wgs < 1) wgs = 1;
-    if (iters > 0) kvq_calib_update<K><<<1, CAL_PARTS * 16, 0, s>>>(partial, 0, cent);      // the first thresholds
-    for (int it = 0; it < iters; ++it) {
-        kvq_calib_assign<K><<<(unsigned)wgs, CAL_NT, 0, s>>>(x, w, n, cent, partial);
-        kvq_calib_update<K><<<1, CAL_PARTS * 16, 0, s>>>(partial, (int)wgs, cent);
+    auto run = [&](auto look_up) {
+        constexpr bool LU = decltype(look_up)::value;
+        if (LU && iters > 0) kvq_calib_update<K, LU><<<1, CAL_PARTS * 16, 0, s>>>(partial, 0, cent);      // the first thresholds
+        for (int it = 0; it < iters; ++it) {
+            kvq_calib_assign<K, LU><<<(unsigned)wgs, CAL_NT, 0, s>>>(x, w, n, cent, partial);
+            kvq_calib_update<K, LU><<<1, CAL_PARTS * 16, 0, s>>>(partial, (int)wgs, cent);
+        }
+    };
+    // The look-up saves the search's four instructions per signpost and element and costs 3 us (4 signposts) to 5 us
+    // (16) per iteration for the thresholds and the workgroups' cells.  Whole calls of 20 iterations, us, look-up
+    // against search: 16 signposts, 100000 elements 310 / 210, 1 M 385 / 275, 4.2 M 432 / 407, 8.4 M 558 / 586, 16.8 M 729 / 938;
+    // 8 signposts, 100000 elements 278 / 202, 16.8 M 763 / 699; 4 signposts, 16.8 M 780 / 712.
+    if constexpr (K == 16) {
+        if (n >= CAL_LOOK_UP_MIN) run(std::true_type{});
+        else run(std::false_type{});
+    } else {
+        run(std::false_type{});
     }
     KVQ_HIP_CHECK(hipGetLastError());
     return KVQ_OK;

@@ -51,6 +51,9 @@ def test_channel_constants_at_the_edges(T, D, p, shift, kind):
     (4, 50003, "wide"),                       # signposts beyond [-1, 1]
     (3, 40000, "equal"),                      # signposts that coincide
     (4, 40001, "far"),                        # values far outside the signposts
+    # from 6 Mi elements of 16 signposts on the look-up is taken; the last size below it, and every way out of it
+    (4, (6 << 20) - 1, "plain"), (4, 6 << 20, "plain"), (4, (6 << 20) + 3, "close"), (4, (6 << 20) + 2, "unsorted"),
+    (4, (6 << 20) + 1, "wide"), (4, (6 << 20) + 5, "equal"), (4, (6 << 20) + 6, "far"),
 ])
 def test_signposts_where_the_look_up_could_part_from_the_search(bits, n, kind):
     import torch
