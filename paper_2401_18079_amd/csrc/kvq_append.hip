@@ -805,6 +805,25 @@ __global__ __launch_bounds__(KVQ_KW_NT) void kvq_k_quant_wave(const void *__rest
     if (overflow) atomicExch(d_status, (int32_t)KVQ_ERR_NNZ_OVERFLOW);
 }
 
+// Counts the lanes with `in` set in the bins of a histogram.  Additions to one word of LDS go one after the other:
+// where a token's keys are mostly equal (`tied`), the lanes that share the first one's bin are counted in one
+// addition.  64 tokens of 4096 equal channels, two per workgroup: 35 -> 23 us; done always, it costs 64 ordinary
+// tokens with 65 outliers a side 5 of 17 us.
+__device__ __forceinline__ void hist_count(uint32_t *hist, bool in, uint32_t bin, int lane, bool tied)
+{
+    if (!tied) {
+        if (in) atomicAdd(&hist[bin], 1u);
+        return;
+    }
+    const unsigned long long active = __ballot(in);
+    if (active == 0ull) return;
+    const int first = __ffsll(active) - 1;
+    const uint32_t bin0 = (uint32_t)__builtin_amdgcn_readlane((int)bin, first);
+    const unsigned long long same = __ballot(in && bin == bin0);
+    if (lane == first) atomicAdd(&hist[bin0], (uint32_t)__popcll(same));
+    else if (in && bin != bin0) atomicAdd(&hist[bin], 1u);
+}
+
 // ---- bulk Value append -----------------------------------------------------------------------
 // Value append: one workgroup of four wavefronts per token, D = 256 * JW channels (JW = 4, 8, 16,
 // 20, 26 or 32).  Wavefront w takes the channel groups j = w JW .. (w + 1) JW - 1, lane l of it the channels
@@ -823,7 +842,7 @@ __global__ __launch_bounds__(KVQ_KW_NT) void kvq_k_quant_wave(const void *__rest
 // (a 4096-channel token: 16 elements per lane on four wavefronts, 4 on sixteen).
 constexpr int KVQ_VW_WAVES = 4;
 constexpr int KVQ_V_CAND = 128;              // candidates per side that a wavefront looks through (two per lane)
-constexpr int KVQ_VW_NT = 64 * KVQ_VW_WAVES;
+constexpr uint32_t KVQ_V_BOUNDED = 52;       // outliers per side up to which the thresholds are bounded first
 constexpr int KVQ_VW_SMALL_TOKENS = 64;      // calls below this many tokens use one lane per four elements
 template <int BITS, int JW, int W, int TOK, class SP>
 __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, int D, int64_t cap, int64_t n0,
@@ -899,13 +918,14 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
     if (K > 0) {
         // Bounds of the thresholds.  The K-th largest of the 64 columns' largest keys is a lower bound of the
         // token's K-th largest key, since that many elements are at least as large; likewise for the smallest.
-        // Every wavefront finds both by bisection over the 16 key bits, with ballots.  (More outliers per side
-        // than columns: no bound, every key passes.)
+        // Every wavefront finds both by bisection over the 16 key bits, with ballots.  With more outliers per side
+        // than KVQ_V_BOUNDED the bounds let more keys pass than a list holds (64 columns: 64 ln(64 / (64 - K)) are
+        // expected, 107 for K = 52): none are taken, every key goes to the histograms.
         atomicMax(&col_max[0][lane], kmax);
         atomicMax(&col_max[1][lane], 0xffffu - kmin);
         __syncthreads();
         uint32_t m_top = 0, m_bot = 0xffffu;
-        if (K <= 64u) {
+        if (K <= KVQ_V_BOUNDED) {
             const uint32_t ct = col_max[0][lane], cb = col_max[1][lane];
             uint32_t inv_bot = 0;
             for (int bit = 15; bit >= 0; --bit) {
@@ -919,28 +939,30 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
         // in any order, and the thresholds are found among them.
         uint32_t which = 0;                      // bit i: element i is a candidate
 #pragma unroll
-        for (int i = 0; i < JW; ++i) which |= (kc[i] >= m_top || kc[i] <= m_bot) ? (1u << i) : 0u;
+        for (int i = 0; i < JW; ++i) which |= (K <= KVQ_V_BOUNDED && (kc[i] >= m_top || kc[i] <= m_bot)) ? (1u << i) : 0u;
+        // A lane that finds a list full stops: the lists are of no use then (see below), and with many equal keys
+        // every key would be read again and counted on two words of LDS (64 tokens of 4096 equal channels: 40 -> 35 us).
         while (__ballot(which != 0u) != 0ull) {  // (most lanes have none, hardly any more than two)
             if (which != 0u) {
                 const int i = __ffs((int)which) - 1;
                 which &= which - 1u;
                 const uint32_t key = order_key(x16[64 * (jb + i)]);      // (re-read: a dynamic index)
+                uint32_t at_top = 0u, at_bot = 0u;
                 if (key >= m_top) {
-                    const uint32_t at = atomicAdd(&n_cand[0], 1u);
-                    if (at < KVQ_V_CAND) cand[0][at] = (uint16_t)key;
+                    at_top = atomicAdd(&n_cand[0], 1u);
+                    if (at_top < KVQ_V_CAND) cand[0][at_top] = (uint16_t)key;
                 }
                 if (key <= m_bot) {
-                    const uint32_t at = atomicAdd(&n_cand[1], 1u);
-                    if (at < KVQ_V_CAND) cand[1][at] = (uint16_t)(0xffffu - key);
+                    at_bot = atomicAdd(&n_cand[1], 1u);
+                    if (at_bot < KVQ_V_CAND) cand[1][at_bot] = (uint16_t)(0xffffu - key);
                 }
-            } else {
-                which = 0u;
+                if (at_top >= KVQ_V_CAND || at_bot >= KVQ_V_CAND) which = 0u;
             }
         }
         __syncthreads();
         uint32_t tau_top, tau_bot, need_top, need_bot, n_eq_top, n_eq_bot;
         const uint32_t nt = n_cand[0], nb = n_cand[1];
-        bool few = nt <= KVQ_V_CAND && nb <= KVQ_V_CAND;
+        bool few = K <= KVQ_V_BOUNDED && nt <= KVQ_V_CAND && nb <= KVQ_V_CAND;
         if (TOK == 2) {                          // (barriers below: both tokens take the same way)
             const uint32_t *other = n_cand_s[TOK - 1 - tok];
             few = few && other[0] <= KVQ_V_CAND && other[1] <= KVQ_V_CAND;
@@ -978,21 +1000,33 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
             // of the keys that passed.  Counts are exact from the bounds outwards, which is all the searches read.
             for (int i = ttid; i < 768; i += NTW) hist[i] = 0;
             __syncthreads();
+            // more than half of this wavefront's first keys in one bin (asked of two lanes)
+            const uint32_t b0 = kc[0] >> 8;
+            const bool tied = __popcll(__ballot(b0 == (uint32_t)__builtin_amdgcn_readlane((int)b0, 0))) > 32 ||
+                              __popcll(__ballot(b0 == (uint32_t)__builtin_amdgcn_readlane((int)b0, 32))) > 32;
+            auto count_high = [&](auto t) {
 #pragma unroll
-            for (int i = 0; i < JW; ++i) {
-                const uint32_t key = kc[i];
-                if (key >= m_top || key <= m_bot) atomicAdd(&hist[key >> 8], 1u);
-            }
+                for (int i = 0; i < JW; ++i) {
+                    const uint32_t key = kc[i];
+                    hist_count(hist, key >= m_top || key <= m_bot, key >> 8, lane, decltype(t)::value);
+                }
+            };
+            if (tied) count_high(std::true_type{});
+            else count_high(std::false_type{});
             __syncthreads();
             uint32_t bin_top, above_top, in_top, bin_bot, below_bot, in_bot;
             wave_find_bin<true>(hist, K, lane, bin_top, above_top, in_top);
             wave_find_bin<false>(hist, K, lane, bin_bot, below_bot, in_bot);
+            auto count_low = [&](auto t) {
 #pragma unroll
-            for (int i = 0; i < JW; ++i) {
-                const uint32_t key = kc[i];
-                if ((key >> 8) == bin_top && key >= m_top) atomicAdd(&hist[256 + (key & 255u)], 1u);
-                if ((key >> 8) == bin_bot && key <= m_bot) atomicAdd(&hist[512 + (key & 255u)], 1u);
-            }
+                for (int i = 0; i < JW; ++i) {
+                    const uint32_t key = kc[i];
+                    hist_count(hist + 256, (key >> 8) == bin_top && key >= m_top, key & 255u, lane, decltype(t)::value);
+                    hist_count(hist + 512, (key >> 8) == bin_bot && key <= m_bot, key & 255u, lane, decltype(t)::value);
+                }
+            };
+            if (tied) count_low(std::true_type{});
+            else count_low(std::false_type{});
             __syncthreads();
             uint32_t lo_top, above_in, lo_bot, below_in;
             wave_find_bin<true>(hist + 256, K - above_top, lane, lo_top, above_in, n_eq_top);

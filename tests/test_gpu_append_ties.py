@@ -49,3 +49,31 @@ def test_value_append_ties(heads, bits):
     K.kvq_pv_matvec(gc, torch.from_numpy(p.astype(np.float32)).cuda(), out)
     ok, worst = matvec_close(out.cpu().numpy(), oc.pv(p.astype(np.float32)))
     assert ok, f"pv worst error / bound = {worst:.3f}"
+
+
+@pytest.mark.parametrize("heads,T", [(8, 1), (8, 65), (32, 3), (32, 66), (40, 514)])
+@pytest.mark.parametrize("k", [1, 52, 53, 65, 200])
+def test_outlier_counts_around_the_bounds(heads, T, k):
+    """The thresholds are bounded first up to 52 outliers per side, and lists of 128 candidates overflow into histograms
+    where keys are equal: rows of ties of every kind among ordinary ones, mostly equal rows beside rows that are not."""
+    import torch
+    import paper_2401_18079_amd as K
+    wl = S.workload("c2", n_kv_heads=heads, n_q_heads=heads, bits=3)
+    st = Setup(wl)
+    D, cap = wl.D, (T + 128) // 128 * 128
+    rng = np.random.default_rng(heads + T + k)
+    v = rng.standard_normal((T, D)).astype(np.float16)
+    ties = tie_vectors(D, k, rng)
+    at = np.arange(T) % 3 > 0 if T > 1 else np.array([True])
+    v[at] = ties[rng.integers(0, len(ties), int(at.sum()))]
+    # mostly zeros (of one sign: the sign of a zero-point between zeros of both is not defined)
+    v[::7] = (np.where(rng.random((len(v[::7]), D)) < 0.02, v[::7], 0) + 0.0).astype(np.float16)
+    oc = O.OracleCache(3, heads, heads, cap, k, wl.rope_base, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi,
+                       cap_nnz_k=st.cap_nnz_k(cap))
+    gc = K.KvqCache(3, heads, heads, cap, k, wl.rope_base, st.cap_nnz_k(cap))
+    K.kvq_lut_load(gc, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
+    keys = st.k(0, T)
+    oc.append_k(keys); oc.append_v(v)
+    K.kvq_quantize_append_k(gc, torch.from_numpy(keys).cuda())
+    K.kvq_quantize_append_v(gc, torch.from_numpy(v).cuda())
+    assert not compare_caches(oc, gc)
