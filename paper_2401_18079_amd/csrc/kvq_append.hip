@@ -1410,7 +1410,10 @@ extern "C" kvq_status kvq_quantize_append_k(kvq_cache *cache, const uint16_t *d_
                                                  cache->k_codes, cache->k_ptr, ksp, cache->cap_nnz_k, single,    \
                                                  cache->d_status)
     // From KVQ_WAVE_TOKENS tokens on a wavefront each; below, sixteen wavefronts share out a token's heads (four
-    // where there are no more than four heads), up to four each; wider models take the body that loops.
+    // where there are no more than four heads), up to four each.  Wider models take the body that loops, in bulk with
+    // 256 threads, of which a compute unit holds several (3 bits, 72 heads, us with 1024 / 256 threads / a wavefront per
+    // token: 256 tokens 25 / 32 / 48, 600 tokens 51 / 39 / 49, 1500 tokens 89 / 50 / 67, 3000 tokens 162 / 77 / 73; 128 heads: 512
+    // tokens 54 / 58 / 100, 600 tokens 71 / 61 / 99).
 #define LAUNCH_K(B)                                                                                             \
     do {                                                                                                        \
         const int H = cache->n_kv_heads;                                                                        \
@@ -1423,7 +1426,8 @@ extern "C" kvq_status kvq_quantize_append_k(kvq_cache *cache, const uint16_t *d_
         else if (H <= 32) LAUNCH_KW(B, 2, 16);                                                                  \
         else if (H <= 48) LAUNCH_KW(B, 3, 16);                                                                  \
         else if (H <= 64) LAUNCH_KW(B, 4, 16);                                                                  \
-        else LAUNCH_KW(B, 0, 16);                                                                               \
+        else if (T < KVQ_BULK_TOKENS) LAUNCH_KW(B, 0, 16);                                                      \
+        else LAUNCH_KW(B, 0, 4);                                                                                \
     } while (0)
     // one set of kernels per layout of the outlier entries (flat arrays or a list of blocks)
     const auto launch = [&](const auto ksp) {

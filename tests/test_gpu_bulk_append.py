@@ -108,3 +108,27 @@ def test_bulk_value_append_ties(heads, bits):
     assert gc.status() == 0
     bad = compare_caches(oc, gc)
     assert not bad, bad
+
+
+@pytest.mark.parametrize("heads,T,bits", [(65, 511, 4), (65, 512, 3), (66, 2047, 2), (66, 2048, 2)])
+def test_key_appends_above_64_heads(heads, T, bits):
+    """Both widths of the looping routine and the one by wavefront, on either side of where they change."""
+    import torch
+    import paper_2401_18079_amd as K
+    from oracle import kvq_oracle as O
+    D, cap = heads * 128, 2048 + 128
+    rng = np.random.default_rng(T)
+    lut = np.sort(rng.uniform(-1, 1, 1 << bits)).astype(np.float32)
+    s, z = rng.uniform(0.5, 2.0, D).astype(np.float16), rng.standard_normal(D).astype(np.float16)
+    lo, hi = (z - 2.5 * s).astype(np.float16), (z + 2.5 * s).astype(np.float16)
+    oc = O.OracleCache(bits, heads, heads, cap, 1, 1e4, lut, lut, s, z, lo, hi, cap_nnz_k=cap * D // 32)
+    gc = K.KvqCache(bits, heads, heads, cap, 1, 1e4, cap * D // 32)
+    K.kvq_lut_load(gc, lut, lut, s, z, lo, hi)
+    k = (rng.standard_normal((T, D)) * s + z).astype(np.float16)
+    oc.append_k(k)
+    K.kvq_quantize_append_k(gc, torch.from_numpy(k).cuda())
+    n = int(oc.k_ptr[T])
+    assert np.array_equal(oc.k_codes, gc.k_codes.cpu().numpy())
+    assert np.array_equal(oc.k_ptr[:T + 1], gc.k_ptr.cpu().numpy().view(np.uint32)[:T + 1])
+    assert np.array_equal(oc.k_idx[:n], gc.k_idx.cpu().numpy().view(np.uint16)[:n])
+    assert np.array_equal(oc.k_val[:n], gc.k_val.cpu().numpy().view(np.uint16)[:n])
