@@ -13,12 +13,14 @@ namespace {
 // Launch rules.  Keys: a wavefront per token from KVQ_WAVE_TOKENS tokens on, twice that above 16 heads (3 bits, 32 heads:
 // 4096 tokens 30 us against 38 us with sixteen wavefronts per token, 2500 tokens 24 / 25, 1500 tokens 22 / 17; 8 heads:
 // 1500 tokens 7.2 / 9.1), sixteen wavefronts per token below (one token of 5120 channels: 10.9 us with the looping body, 5.7 us;
-// 777 tokens, 4 bits: 19.9 us with 256 threads per token, 17.2 us).  Values of 1024, 2048, 4096 and (but for
-// middling calls) 5120, 6656 and 8192 channels keep a token in registers (v_quant_token4): four wavefronts per
-// token and two tokens, the pair that shares dwords, per workgroup in calls of KVQ_VW_SMALL_TOKENS tokens and
-// more (4096 tokens: 74 us with a token's bits merged into memory by two atomics per dword, 51 us with whole
-// dwords stored; 777 tokens of 5120 channels: 37.6 -> 22.7 us), eight or sixteen wavefronts on single tokens
-// below (two tokens per workgroup there would lengthen the one chain that counts).
+// 777 tokens, 4 bits: 19.9 us with 256 threads per token, 17.2 us).  Values: v_quant_token4 keeps a token in registers.
+// In calls of fewer than KVQ_VW_SMALL_TOKENS tokens it takes every multiple of 1024 channels up to 8192 (small_width;
+// both appends of one token, 4 bits, us with the routine for any width and with it: 24 heads 12.2 / 8.8, 48 heads
+// 27.6 / 12.4, 64 heads 33.2 / 13.2; 63 tokens of 64 heads 43.7 / 25.8), one token per workgroup (two would lengthen the
+// one chain that counts).  In longer calls a workgroup takes the two tokens that share dwords, four wavefronts each:
+// 1024, 2048 and 4096 channels, and 5120, 6656 and 8192 from KVQ_BULK_TOKENS tokens on (4096 tokens of 4096: 74 us with a
+// token's bits merged into memory by two atomics per dword, 51 us with whole dwords stored; 777 tokens of 5120
+// channels: 37.6 -> 22.7 us).  All others take the routine for any width.
 constexpr int KVQ_BULK_TOKENS = 512;      // calls with at least this many tokens count as bulk appends
 constexpr int KVQ_KV_SPLIT_TOKENS = 256;  // from here on the combined call runs the Key and Value kernels in turn
 constexpr int KVQ_WAVE_TOKENS = 1024;     // Key appends of at least this many tokens: one wavefront per token
@@ -1217,46 +1219,37 @@ struct KvAppendArgs {
     SP ksp, vsp;
     int32_t *d_status;
 };
-template <int BITS, int NT, class SP>
+// NT threads.  VJ, VW: the Values take v_quant_token4 with VJ elements per lane of VW wavefronts, VJ = 0: the routine
+// for any width.  One instantiation per width: static LDS of several widths would add up.
+template <int BITS, int NT, int VJ, int VW, class SP>
 __global__ __launch_bounds__(NT) void kvq_kv_quant(const KvAppendArgs<SP> a)
 {
     const int t = (int)(blockIdx.x >> 1);
     if ((blockIdx.x & 1) == 0) {
         // a workgroup's wavefronts share out the heads (see the launch rule of kvq_quantize_append_k)
         constexpr int W = NT / 64;
-        const int hw = (a.D / KVQ_HEAD_DIM + W - 1) / W;
 #define KW(HW)                                                                                                  \
     k_quant_token_w<BITS, HW, W>(a.params, a.D, a.cap, a.n0_k, a.k_new, a.k_codes, a.k_ptr, a.ksp, a.cap_nnz_k,  \
                                  a.single, a.d_status, t)
-        if (hw == 1) KW(1);
-        else if (hw == 2) KW(2);
-        else if (hw == 3) KW(3);
-        else if (hw == 4) KW(4);
-        else
-            k_quant_token<BITS, NT>(a.params, a.D, a.cap, a.n0_k, a.k_new, a.k_codes, a.k_ptr, a.ksp, a.cap_nnz_k,
-                                    a.single, a.d_status, t);
-#undef KW
-    } else if (a.D == 4096 || a.D == 2048 || a.D == 1024 || (NT == 1024 && a.D == 5120)) {
-        // the routine with one workgroup per token; wavefronts of the workgroup it does not use end here
-        // (a barrier waits only for the wavefronts that have not ended).  A wide workgroup puts sixteen
-        // (4096 channels) or eight (2048) wavefronts on the token, a narrow one four.
-#define V4(J, WV)                                                                                                \
-    do {                                                                                                         \
-        if (threadIdx.x >= 64 * (WV)) return;                                                                    \
-        v_quant_token4<BITS, J, WV, 1>(a.params, a.D, a.cap, a.n0_v, a.k_side, a.v_new, a.v_codes, a.v_sz, a.v_ptr, \
-                                       a.vsp, a.cap_nnz_v, a.d_status, t, 0);                                    \
-    } while (0)
-        if (NT == 1024) {
-            if (a.D == 4096) V4(4, 16);
-            else if (a.D == 5120) V4(5, 16);
-            else if (a.D == 2048) V4(4, 8);
-            else V4(4, 4);
+        if constexpr (VJ > 0) {
+            KW((64 * VJ * VW / KVQ_HEAD_DIM + W - 1) / W);
         } else {
-            if (a.D == 4096) V4(16, 4);
-            else if (a.D == 2048) V4(8, 4);
-            else V4(4, 4);
+            const int hw = (a.D / KVQ_HEAD_DIM + W - 1) / W;
+            if (hw == 1) KW(1);
+            else if (hw == 2) KW(2);
+            else if (hw == 3) KW(3);
+            else if (NT == 256 || hw == 4) KW(4);            // (narrow workgroups have fewer than 16 heads)
+            else
+                k_quant_token<BITS, NT>(a.params, a.D, a.cap, a.n0_k, a.k_new, a.k_codes, a.k_ptr, a.ksp, a.cap_nnz_k,
+                                        a.single, a.d_status, t);
         }
-#undef V4
+#undef KW
+    } else if constexpr (VJ > 0) {
+        // wavefronts of the workgroup that the routine does not use end here (a barrier waits only for the
+        // wavefronts that have not ended)
+        if (threadIdx.x >= 64 * VW) return;
+        v_quant_token4<BITS, VJ, VW, 1>(a.params, a.D, a.cap, a.n0_v, a.k_side, a.v_new, a.v_codes, a.v_sz, a.v_ptr,
+                                        a.vsp, a.cap_nnz_v, a.d_status, t, 0);
     } else
         v_quant_token<BITS, NT>(a.params, a.D, a.cap, a.n0_v, a.k_side, a.v_new, a.v_codes, a.v_sz, a.v_ptr, a.vsp, a.cap_nnz_v, a.d_status, t);
 }
@@ -1382,6 +1375,11 @@ static kvq_status copy_sink_rows(const kvq_cache *cache, uint16_t *sink, const u
 // of a bulk append.
 static bool wide_wg(int D, int T) { return D >= 2048 && T < KVQ_BULK_TOKENS; }
 
+// Widths whose Values stay in registers in calls of a few tokens: D / 1024 for whole multiples of 1024 channels up to
+// 8192, spread over four (1024), eight (2048) or sixteen wavefronts with D / 1024 elements per lane; 0 for the others,
+// whose tokens v_quant_token selects from in LDS.
+static int small_width(int D) { return D % 1024 == 0 && D <= 8192 ? D / 1024 : 0; }
+
 static kvq_status append_checks(const kvq_cache *cache, const void *src, int32_t T, int64_t n_now)
 {
     kvq_status st = kvq_check_cache(cache);
@@ -1459,17 +1457,22 @@ extern "C" kvq_status kvq_quantize_append_v(kvq_cache *cache, const uint16_t *d_
     kvq_v_quant4<B, J, WV, TOK><<<GRID, 64 * (WV) * (TOK), 0, s>>>(                                            \
         cache->params, D, cache->cap_tokens, cache->n_tokens_v, T, cache->k_side_v, d_v_new, cache->v_codes,   \
         cache->v_sz, cache->v_ptr, vsp, cache->cap_nnz_v, cache->d_status)
+    const int small = T < KVQ_VW_SMALL_TOKENS ? small_width(D) : 0;
     // a workgroup per pair of tokens (the two that share dwords), the first and the last perhaps with one token
     const unsigned pairs = (unsigned)(((cache->n_tokens_v + T - 1) >> 1) - (cache->n_tokens_v >> 1) + 1);
 #define LAUNCH_V4(B, J) LAUNCH_V4W(B, J, KVQ_VW_WAVES, 2, pairs)
 #define LAUNCH_V(B)                                                                                             \
     do {                                                                                                        \
-        if (D == 4096 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 4, 16, 1, T);                                   \
-        else if (D == 2048 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 4, 8, 1, T);                               \
-        else if (D == 5120 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 5, 16, 1, T);                              \
+        if (small == 1) LAUNCH_V4W(B, 4, 4, 1, T);                                                              \
+        else if (small == 2) LAUNCH_V4W(B, 4, 8, 1, T);                                                         \
+        else if (small == 3) LAUNCH_V4W(B, 3, 16, 1, T);                                                        \
+        else if (small == 4) LAUNCH_V4W(B, 4, 16, 1, T);                                                        \
+        else if (small == 5) LAUNCH_V4W(B, 5, 16, 1, T);                                                        \
+        else if (small == 6) LAUNCH_V4W(B, 6, 16, 1, T);                                                        \
+        else if (small == 7) LAUNCH_V4W(B, 7, 16, 1, T);                                                        \
+        else if (small == 8) LAUNCH_V4W(B, 8, 16, 1, T);                                                        \
         else if (D == 4096) LAUNCH_V4(B, 16);                                                                   \
         else if (D == 2048) LAUNCH_V4(B, 8);                                                                    \
-        else if (D == 1024 && T < KVQ_VW_SMALL_TOKENS) LAUNCH_V4W(B, 4, 4, 1, T);                               \
         else if (D == 1024) LAUNCH_V4(B, 4);                                                                    \
         else if (D == 5120 && T >= KVQ_BULK_TOKENS) LAUNCH_V4(B, 20);                                           \
         else if (D == 6656 && T >= KVQ_BULK_TOKENS) LAUNCH_V4(B, 26);                                           \
@@ -1513,10 +1516,10 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
     if (cache->k_side_v < 0 || 2 * (int64_t)cache->k_side_v >= D) return KVQ_ERR_INVALID_ARG;
     if (D > 16384) return KVQ_ERR_UNSUPPORTED;       // the per-token Value selection keeps the vector in LDS
     if (T >= KVQ_KV_SPLIT_TOKENS) {
-        // Such an append fills the GPU with either kernel alone, and compute units that run both bodies
-        // at once are slower than the two launches one after the other (measured: 50 us against 44 us
-        // for 256 tokens of 4096 channels, 233 us against 188 us for 4096); every check of both calls
-        // has passed above.
+        // Such an append fills the GPU with either kernel alone.  Just below (255 tokens, 4 bits, us in one launch / in
+        // turn): 8 heads 15 / 20, 16 heads 20 / 20, 32 heads 36 / 26, 40 heads 35 / 40, 52 heads 68 / 48, 64 heads 46 / 52.
+        // (From 129 tokens on, two workgroups of 1024 threads per token are more than the compute units hold at once.)
+        // Every check of both calls has passed above.
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
         st = kvq_quantize_append_k(cache, d_k_new, T, stream);
         if (st != KVQ_OK) return st;
@@ -1531,10 +1534,23 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
         kvq_ptr_scan<<<1, 1024, 0, s>>>(cache->k_ptr, cache->n_tokens_k, T, cnt, cache->cap_nnz_k, cache->d_status);
     }
     const size_t dyn = 3 * (size_t)D;
+    static_assert(KVQ_KV_SPLIT_TOKENS <= KVQ_BULK_TOKENS, "workgroups are wide for every D >= 2048 here");
+#define LAUNCH_KVW(B, NT, VJ, VW) kvq_kv_quant<B, NT, VJ, VW><<<2 * T, NT, (VJ) > 0 ? 0 : dyn, s>>>(a)
 #define LAUNCH_KV(B)                                                                     \
     do {                                                                                 \
-        if (wide_wg(D, T)) kvq_kv_quant<B, 1024><<<2 * T, 1024, dyn, s>>>(a);            \
-        else kvq_kv_quant<B, 256><<<2 * T, 256, dyn, s>>>(a);                            \
+        switch (small_width(D)) {                                                        \
+        case 1: LAUNCH_KVW(B, 256, 4, 4); break;                                         \
+        case 2: LAUNCH_KVW(B, 1024, 4, 8); break;                                        \
+        case 3: LAUNCH_KVW(B, 1024, 3, 16); break;                                       \
+        case 4: LAUNCH_KVW(B, 1024, 4, 16); break;                                       \
+        case 5: LAUNCH_KVW(B, 1024, 5, 16); break;                                       \
+        case 6: LAUNCH_KVW(B, 1024, 6, 16); break;                                       \
+        case 7: LAUNCH_KVW(B, 1024, 7, 16); break;                                       \
+        case 8: LAUNCH_KVW(B, 1024, 8, 16); break;                                       \
+        default:                                                                         \
+            if (wide_wg(D, T)) LAUNCH_KVW(B, 1024, 0, 0);                                \
+            else LAUNCH_KVW(B, 256, 0, 0);                                               \
+        }                                                                                \
     } while (0)
     const auto launch = [&](const auto ksp, const auto vsp) {
         KvAppendArgs<std::remove_cv_t<decltype(ksp)>> a;
@@ -1553,6 +1569,7 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
     if (cache->nnz_block_shift) launch(kvq_blocked_k(cache), kvq_blocked_v(cache));
     else launch(kvq_flat_k(cache), kvq_flat_v(cache));
 #undef LAUNCH_KV
+#undef LAUNCH_KVW
     KVQ_HIP_CHECK(hipGetLastError());
     st = copy_sink_rows(cache, cache->sink_k, d_k_new, cache->n_tokens_k, T, s);
     if (st != KVQ_OK) return st;

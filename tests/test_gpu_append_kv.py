@@ -58,6 +58,28 @@ def test_append_kv_bit_exact(name, ov, n_sink, chunks):
         assert np.array_equal(gc.sink_v.cpu().numpy().view(np.uint16)[:n_sink * D], oc.sink_v[:n_sink].reshape(-1))
 
 
+@pytest.mark.parametrize("heads", [24, 40, 48, 56, 64, 52])      # multiples of 1024 channels, and one that is not
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_small_calls_of_every_register_width(heads, bits):
+    import torch
+    import paper_2401_18079_amd as K
+    wl = S.workload("c2", n_kv_heads=heads, n_q_heads=heads, bits=bits)
+    st = Setup(wl)
+    oc, gc = _caches(st, 256)
+    t0 = 0
+    for i, T in enumerate((1, 2, 63, 1, 64, 5)):
+        k, v = st.k(t0, T), st.v(t0, T)
+        oc.append_k(k); oc.append_v(v)
+        dk, dv = torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda()
+        if i % 2:
+            K.kvq_quantize_append_kv(gc, dk, dv)
+        else:
+            K.kvq_quantize_append_k(gc, dk)
+            K.kvq_quantize_append_v(gc, dv)
+        t0 += T
+    assert not compare_caches(oc, gc)
+
+
 def test_append_kv_mixes_with_separate_appends_and_unequal_counts():
     import torch
     import paper_2401_18079_amd as K
