@@ -943,23 +943,26 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
         uint32_t which = 0;                      // bit i: element i is a candidate
 #pragma unroll
         for (int i = 0; i < JW; ++i) which |= (K <= KVQ_V_BOUNDED && (kc[i] >= m_top || kc[i] <= m_bot)) ? (1u << i) : 0u;
-        // A lane that finds a list full stops: the lists are of no use then (see below), and with many equal keys
-        // every key would be read again and counted on two words of LDS (64 tokens of 4096 equal channels: 40 -> 35 us).
+        // With many equal keys every key would be read again and counted on two words of LDS (64 tokens of 4096 equal
+        // channels: 40 us): from the third round on a wavefront stops when a list is full, since the lists are of no
+        // use then (see below).  (Not from what the additions return: waiting for it costs one token 0.4 us.)
+        int round = 0;
         while (__ballot(which != 0u) != 0ull) {  // (most lanes have none, hardly any more than two)
+            if (++round > 2 && (__hip_atomic_load(&n_cand[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > KVQ_V_CAND ||
+                                __hip_atomic_load(&n_cand[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > KVQ_V_CAND))
+                break;
             if (which != 0u) {
                 const int i = __ffs((int)which) - 1;
                 which &= which - 1u;
                 const uint32_t key = order_key(x16[64 * (jb + i)]);      // (re-read: a dynamic index)
-                uint32_t at_top = 0u, at_bot = 0u;
                 if (key >= m_top) {
-                    at_top = atomicAdd(&n_cand[0], 1u);
-                    if (at_top < KVQ_V_CAND) cand[0][at_top] = (uint16_t)key;
+                    const uint32_t at = atomicAdd(&n_cand[0], 1u);
+                    if (at < KVQ_V_CAND) cand[0][at] = (uint16_t)key;
                 }
                 if (key <= m_bot) {
-                    at_bot = atomicAdd(&n_cand[1], 1u);
-                    if (at_bot < KVQ_V_CAND) cand[1][at_bot] = (uint16_t)(0xffffu - key);
+                    const uint32_t at = atomicAdd(&n_cand[1], 1u);
+                    if (at < KVQ_V_CAND) cand[1][at] = (uint16_t)(0xffffu - key);
                 }
-                if (at_top >= KVQ_V_CAND || at_bot >= KVQ_V_CAND) which = 0u;
             }
         }
         __syncthreads();
