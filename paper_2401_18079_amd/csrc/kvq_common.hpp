@@ -294,11 +294,12 @@ __device__ __forceinline__ int kvq_sparse_token_scan(uint32_t pw, int tc, uint32
 }
 
 // Issue priority of the calling wavefront, 0 (lowest) to 3.  The SIMD's arbiter serves the highest
-// priority first and, among equals, the OLDEST wavefront: the four wavefronts that share a SIMD for a
-// whole kernel then finish one after the other (measured on the dense Value kernel: workgroups
-// dispatched first end at 34 us, those dispatched last at 48 us, and the tail runs with the SIMDs a
-// quarter full).  A wavefront that calls this with (its slot on the SIMD + a step counter) & 3 at every
-// step spends a quarter of its steps at each priority, so the four advance at the same average rate.
+// priority first and, among equals, the OLDEST wavefront: the wavefronts that share a SIMD for a whole
+// kernel then finish one after the other, and the tail runs with the SIMDs a quarter full (measured on a
+// Value kernel with four workgroups per compute unit: those dispatched first ended at 34 us, the last at 48).
+// A wavefront that calls this with (its slot on the SIMD + a step counter) & 3 at every step spends a
+// quarter of its steps at each priority, so the four advance at the same average rate.  The dense Key
+// kernels do; in the dense Value kernel the wavefronts of a workgroup share out its tiles and need not.
 // The instruction takes an immediate operand, hence the switch.
 __device__ __forceinline__ void kvq_set_wave_priority(int p)
 {

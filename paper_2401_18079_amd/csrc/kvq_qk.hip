@@ -260,10 +260,9 @@ __device__ __forceinline__ void qk_build_tables(float2_t *tab, float *qs, float2
     __syncthreads();
 }
 
-// KVH KV heads per workgroup, RQ query heads per KV head handled here (RQ divides the model's GQA
-// ratio `r`; when RQ < r several workgroups share a KV head), PG channel pairs per gather group.
+// KVH KV heads per workgroup, RQ query heads per KV head, PG channel pairs per gather group.
 template <int BITS, int KVH, int RQ, int NT, int PG, bool STATS, bool SPAN = false>
-__global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ params, int D, int r,
+__global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ params, int D,
                                                     int64_t cap, int64_t L, const uint8_t *__restrict__ k_codes,
                                                     const float *__restrict__ q_rot, float scale,
                                                     float *__restrict__ scores, int64_t ld, int n_tiles,
@@ -291,7 +290,7 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
     const KvqParamsView pv = kvq_params_view(params, D);
     const int tid = threadIdx.x;
     const int q0 = blockIdx.y * QH;
-    const int kv0 = q0 / r;
+    const int kv0 = q0 / RQ;
 
     qk_build_tables<BITS, KVH, RQ, NT>(tab, qs, szs, pv, q_rot, scale, q0, kv0);
 
@@ -432,8 +431,8 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
 // four multiply-adds per element did, 2 RQ instructions and RQ gathers per pair.  Arithmetic, precision and
 // order of the sums over channels are those of an fp32 chain.
 // Lanes, tiles, piece streaming, grid and results as in kvq_qk_kernel.  Bound by VALU issue (7.5 instructions and
-// two matrix instructions per token, pair and KV head at four KV heads a workgroup; VALU busy 66 to 76 % of the
-// kernel, the matrix cores 25 %).  Times beside qk_grouped.
+// two matrix instructions per token, pair and KV head at four KV heads a workgroup; VALU busy 70 % of the
+// kernel, the matrix cores 26 %).  Times beside qk_grouped.
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
 // q: four query heads of 16 channels; the instruction takes those of channel `C` of the 16.
@@ -493,7 +492,7 @@ __device__ __forceinline__ void qkg_group(std::integer_sequence<int, P...>, uint
         sn[p] = __builtin_amdgcn_sinf(rev);
     }
     // the lower channels of all heads, then the upper ones: a matrix instruction waits for the one before it on
-    // the same sums (the compiler would put the two of a head side by side: 145 us instead of 137 at 524288 tokens)
+    // the same sums (the compiler would put the two of a head side by side: 6 % slower at 524288 tokens)
     auto pair = [&](auto pc) {
         constexpr int p = decltype(pc)::value, I = G0 * PG + p;
 #pragma unroll
@@ -533,7 +532,7 @@ __device__ __forceinline__ void qkg_all_pairs(std::integer_sequence<int, G...>, 
 }
 
 template <int BITS, int KVH, int RQ, int NT, int PG, bool STATS, bool SPAN = false>
-__global__ __launch_bounds__(NT) void kvq_qkg_kernel(const void *__restrict__ params, int D, int r,
+__global__ __launch_bounds__(NT) void kvq_qkg_kernel(const void *__restrict__ params, int D,
                                                      int64_t cap, int64_t L, const uint8_t *__restrict__ k_codes,
                                                      const float *__restrict__ q_rot, float scale,
                                                      float *__restrict__ scores, int64_t ld, int n_tiles,
@@ -550,7 +549,7 @@ __global__ __launch_bounds__(NT) void kvq_qkg_kernel(const void *__restrict__ pa
     __shared__ float wst[NT / 64][QH];
     const KvqParamsView pv = kvq_params_view(params, D);
     const int tid = threadIdx.x, lane = tid & 63;
-    const int q0 = blockIdx.y * QH, kv0 = q0 / r;
+    const int q0 = blockIdx.y * QH, kv0 = q0 / RQ;
 
     const int64_t plane = cap * 16 * BITS;                 // bytes between consecutive KV heads
     const int tile_begin = (int)(((int64_t)blockIdx.x * n_tiles) / gridDim.x);
@@ -690,13 +689,13 @@ __device__ __forceinline__ uint32_t pm_field_shifted(const uint32_t (&P)[4], int
 }
 
 // PG consecutive fields (first one: number G0 * PG of pass J) of tile T for all heads of the workgroup.
-template <int KVH, int RQ, int TT, int PG, int J, int T, int G0>
-__device__ __forceinline__ void pm_group(const uint32_t (&P)[KVH][4], float (&acc)[TT * KVH * RQ],
+template <int KVH, int TT, int PG, int J, int T, int G0>
+__device__ __forceinline__ void pm_group(const uint32_t (&P)[KVH][4], float (&acc)[TT * KVH],
                                          float (&cs)[PM_MAXF], float (&sn)[PM_MAXF], const uint32_t (&carry)[3],
                                          const float2_t *tab, float nf, float wave_base,
                                          const KvqParamsHeader *hdr)
 {
-    constexpr int QH = KVH * RQ, R = RQ, ENT = 64;
+    constexpr int QH = KVH, ENT = 64;
     constexpr int F0 = pm_first(J), NF = pm_first(J + 1) - F0;
     constexpr uint32_t M = 63u << 3;
     float2_t t[PG][QH];
@@ -718,21 +717,10 @@ __device__ __forceinline__ void pm_group(const uint32_t (&P)[KVH][4], float (&ac
                     else c = __builtin_amdgcn_ubfe(carry[1 + (idx >> 3)], 4 * (idx & 7), 4);
                     sh = ((P[g][0] << nb) | c) << 3;
                 }
-                uint32_t off_lo = 0;
-                bool have_lo = false;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int qh = g * R + r;
-                    const uint32_t base = (uint32_t)((qh * 64 + I) * ENT) * 8u;
-                    const uint32_t hi = base & ~0xFFFFu;
-                    const uint8_t *tb = (const uint8_t *)tab + (base - hi);
-                    if (hi == 0) {
-                        if (!have_lo) { off_lo = sh & M; have_lo = true; }
-                        t[p][qh] = *(const float2_t *)(tb + off_lo);
-                    } else {
-                        t[p][qh] = *(const float2_t *)(tb + kvq_and_or(sh, M, hi));
-                    }
-                }
+                const uint32_t base = (uint32_t)((g * 64 + I) * ENT) * 8u;
+                const uint32_t hi = base & ~0xFFFFu;
+                const uint8_t *tb = (const uint8_t *)tab + (base - hi);
+                t[p][g] = *(const float2_t *)(tb + (hi == 0 ? (sh & M) : kvq_and_or(sh, M, hi)));
             }
         }
     }
@@ -773,21 +761,21 @@ __device__ __forceinline__ void pm_group(const uint32_t (&P)[KVH][4], float (&ac
     for (int qh = 0; qh < QH; ++qh) asm volatile("" : "+v"(acc[T * QH + qh]) : : "memory");
 }
 
-template <int KVH, int RQ, int TT, int PG, int J, int T, int... G>
+template <int KVH, int TT, int PG, int J, int T, int... G>
 __device__ __forceinline__ void pm_groups(std::integer_sequence<int, G...>, const uint32_t (&P)[KVH][4],
-                                          float (&acc)[TT * KVH * RQ], float (&cs)[PM_MAXF], float (&sn)[PM_MAXF],
+                                          float (&acc)[TT * KVH], float (&cs)[PM_MAXF], float (&sn)[PM_MAXF],
                                           const uint32_t (&carry)[3], const float2_t *tab, float nf, float wave_base,
                                           const KvqParamsHeader *hdr)
 {
-    (pm_group<KVH, RQ, TT, PG, J, T, G>(P, acc, cs, sn, carry, tab, nf, wave_base, hdr), ...);
+    (pm_group<KVH, TT, PG, J, T, G>(P, acc, cs, sn, carry, tab, nf, wave_base, hdr), ...);
 }
 
 // Stage S = J * TT + T of a block: piece J of tile T.  The piece sits in W[S & 1]; the next stage's
 // piece (this block's, or piece 0 of the next block's first tile) is requested into the other slot
 // before the arithmetic starts.  Addresses are a wavefront-uniform base plus 32-bit offsets (the
 // launcher checks that the codes are smaller than 4 GiB).
-template <int KVH, int RQ, int TT, int PG, int S>
-__device__ __forceinline__ void pm_stage(uint32_t (&W)[2][KVH][4], float (&acc)[TT * KVH * RQ], float (&cs)[PM_MAXF],
+template <int KVH, int TT, int PG, int S>
+__device__ __forceinline__ void pm_stage(uint32_t (&W)[2][KVH][4], float (&acc)[TT * KVH], float (&cs)[PM_MAXF],
                                          float (&sn)[PM_MAXF], uint32_t (&carry)[3], const float2_t *tab, float nf,
                                          float wave_base, const KvqParamsHeader *hdr,
                                          const uint8_t *__restrict__ k_codes, uint32_t off0, uint32_t plane,
@@ -827,22 +815,22 @@ __device__ __forceinline__ void pm_stage(uint32_t (&W)[2][KVH][4], float (&acc)[
             }
         }
         constexpr int NF = pm_first(J + 1) - pm_first(J);
-        pm_groups<KVH, RQ, TT, PG, J, T>(std::make_integer_sequence<int, (NF + PG - 1) / PG>{}, W[S & 1], acc, cs, sn,
+        pm_groups<KVH, TT, PG, J, T>(std::make_integer_sequence<int, (NF + PG - 1) / PG>{}, W[S & 1], acc, cs, sn,
                                          carry, tab, nf, wave_base, hdr);
     }
 }
 
 // Pass J of a block: piece J of each of the block's TT tiles.  The (cos, sin) of the pass's fields live
 // here, from the first tile (computed) to the last (rotated).
-template <int KVH, int RQ, int TT, int PG, int J, int... T>
+template <int KVH, int TT, int PG, int J, int... T>
 __device__ __forceinline__ void pm_pass(std::integer_sequence<int, T...>, uint32_t (&W)[2][KVH][4],
-                                        float (&acc)[TT * KVH * RQ], uint32_t (&carry)[3], const float2_t *tab,
+                                        float (&acc)[TT * KVH], uint32_t (&carry)[3], const float2_t *tab,
                                         float nf, float wave_base, const KvqParamsHeader *hdr,
                                         const uint8_t *__restrict__ k_codes, uint32_t off0, uint32_t plane,
                                         uint32_t vm, uint32_t any, bool next_block_valid)
 {
     float cs[PM_MAXF], sn[PM_MAXF];
-    (pm_stage<KVH, RQ, TT, PG, J * TT + T>(W, acc, cs, sn, carry, tab, nf, wave_base, hdr, k_codes, off0, plane, vm,
+    (pm_stage<KVH, TT, PG, J * TT + T>(W, acc, cs, sn, carry, tab, nf, wave_base, hdr, k_codes, off0, plane, vm,
                                            any, next_block_valid), ...);
 }
 
@@ -889,9 +877,9 @@ __device__ __forceinline__ void qk3_span_end()
     }
 }
 
-// Same arguments, grid and results as kvq_qk_kernel<3, KVH, RQ, 1024, ...>; tiles are KVQ_ROPE_STEP tokens.
-template <int KVH, int RQ, int TT, int PG, bool STATS, bool SPAN = false>
-__global__ __launch_bounds__(KVQ_ROPE_STEP) void kvq_qk3_kernel(const void *__restrict__ params, int D, int r,
+// Same arguments, grid and results as kvq_qk_kernel<3, KVH, 1, 1024, ...>; tiles are KVQ_ROPE_STEP tokens.
+template <int KVH, int TT, int PG, bool STATS, bool SPAN = false>
+__global__ __launch_bounds__(KVQ_ROPE_STEP) void kvq_qk3_kernel(const void *__restrict__ params, int D,
                                                                int64_t cap, int64_t L,
                                                                const uint8_t *__restrict__ k_codes,
                                                                const float *__restrict__ q_rot, float scale,
@@ -902,15 +890,15 @@ __global__ __launch_bounds__(KVQ_ROPE_STEP) void kvq_qk3_kernel(const void *__re
     qk3_span_start();
     constexpr int BITS = 3, NT = KVQ_ROPE_STEP;
     static_assert(KVH * TT <= 16, "the carried bits of a block are packed in 32 + 64 bits");
-    constexpr int QH = KVH * RQ, R = RQ, ENT = 64;
+    constexpr int QH = KVH, ENT = 64;
     __shared__ __attribute__((aligned(16))) float2_t tab[QH * 64 * ENT];  // [QH][64][ENT]
     __shared__ float qs[QH * 128];                                        // query * scale
-    __shared__ float2_t szs[(QH / R) * 128];                              // per-channel (scale, zero-point)
+    __shared__ float2_t szs[KVH * 128];                              // per-channel (scale, zero-point)
 
     const KvqParamsView pv = kvq_params_view(params, D);
     const int tid = threadIdx.x;
     const int q0 = blockIdx.y * QH;
-    const int kv0 = q0 / r;
+    const int kv0 = q0;                                     // (one query head per KV head)
     const uint32_t plane = (uint32_t)(cap * 16 * BITS);    // bytes between consecutive KV heads
     const int tile_begin = (int)(((int64_t)blockIdx.x * n_tiles) / gridDim.x);
     const int tile_end = (int)(((int64_t)(blockIdx.x + 1) * n_tiles) / gridDim.x);
@@ -927,7 +915,7 @@ __global__ __launch_bounds__(KVQ_ROPE_STEP) void kvq_qk3_kernel(const void *__re
             W[0][g][0] = v.x; W[0][g][1] = v.y; W[0][g][2] = v.z; W[0][g][3] = v.w;
         }
     }
-    qk_build_tables<BITS, KVH, RQ, NT>(tab, qs, szs, pv, q_rot, scale, q0, kv0);
+    qk_build_tables<BITS, KVH, 1, NT>(tab, qs, szs, pv, q_rot, scale, q0, kv0);
     const float my_vh = pv.hdr->rope_vh[lane_id], my_vl = pv.hdr->rope_vl[lane_id];   // this lane's pair
     // STATS: a wavefront keeps the maxima of the scores it wrote in LDS slots of its own (the staged
     // query's array, dead by now; only lane 0 of the wavefront touches its slots: no atomics)
@@ -954,11 +942,11 @@ __global__ __launch_bounds__(KVQ_ROPE_STEP) void kvq_qk3_kernel(const void *__re
         uint32_t carry[3] = {0u, 0u, 0u};
 #pragma unroll
         for (int a = 0; a < TT * QH; ++a) acc[a] = 0.f;
-        pm_pass<KVH, RQ, TT, PG, 0>(std::make_integer_sequence<int, TT>{}, W, acc, carry, tab, nf, wave_base, pv.hdr,
+        pm_pass<KVH, TT, PG, 0>(std::make_integer_sequence<int, TT>{}, W, acc, carry, tab, nf, wave_base, pv.hdr,
                                     k_codes, off0, plane, vm, any, next_block_valid);
-        pm_pass<KVH, RQ, TT, PG, 1>(std::make_integer_sequence<int, TT>{}, W, acc, carry, tab, nf, wave_base, pv.hdr,
+        pm_pass<KVH, TT, PG, 1>(std::make_integer_sequence<int, TT>{}, W, acc, carry, tab, nf, wave_base, pv.hdr,
                                     k_codes, off0, plane, vm, any, next_block_valid);
-        pm_pass<KVH, RQ, TT, PG, 2>(std::make_integer_sequence<int, TT>{}, W, acc, carry, tab, nf, wave_base, pv.hdr,
+        pm_pass<KVH, TT, PG, 2>(std::make_integer_sequence<int, TT>{}, W, acc, carry, tab, nf, wave_base, pv.hdr,
                                     k_codes, off0, plane, vm, any, next_block_valid);
         // the next block's first piece arrived in slot (3 * TT) & 1; the block expects it in slot 0
         if ((3 * TT) & 1) {
@@ -1128,13 +1116,13 @@ kvq_status launch_qk(const kvq_cache *c, const float *q, float scale, float *sco
     auto kern = stat_slots ? kernel(std::true_type{}, std::false_type{}) : kernel(std::false_type{}, std::false_type{});
     constexpr bool CAN_SPAN = GROUPED || QH < 8;
     // 3-bit codes, tiles of KVQ_ROPE_STEP tokens: the piece-major kernel (rotary recurrence over TT tiles)
-    constexpr bool PIECE_MAJOR = KVQ_QK3_ENABLE && !GROUPED && BITS == 3 && NT == KVQ_ROPE_STEP && KVH * KVQ_QK3_TT <= 16;
+    constexpr bool PIECE_MAJOR = KVQ_QK3_ENABLE && RQ == 1 && BITS == 3 && NT == KVQ_ROPE_STEP && KVH * KVQ_QK3_TT <= 16;
     // (it addresses the codes with 32-bit offsets)
     const bool piece_major = PIECE_MAJOR && (int64_t)c->n_kv_heads * c->cap_tokens * 16 * BITS < ((int64_t)1 << 32);
     if constexpr (PIECE_MAJOR) {
         if (piece_major)
-            kern = stat_slots ? kvq_qk3_kernel<KVH, RQ, KVQ_QK3_TT, KVQ_QK3_PG, true>
-                              : kvq_qk3_kernel<KVH, RQ, KVQ_QK3_TT, KVQ_QK3_PG, false>;
+            kern = stat_slots ? kvq_qk3_kernel<KVH, KVQ_QK3_TT, KVQ_QK3_PG, true>
+                              : kvq_qk3_kernel<KVH, KVQ_QK3_TT, KVQ_QK3_PG, false>;
     }
     const int groups = c->n_q_heads / QH;
     const int64_t tiles = (L + NT - 1) / NT;
@@ -1172,7 +1160,7 @@ kvq_status launch_qk(const kvq_cache *c, const float *q, float scale, float *sco
     if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[0], s));
     static_assert(KVQ_STAT_SLOTS >= 256 + KVQ_MAX_SINK, "a slot per workgroup of a head plus the sink tokens");
     const unsigned ns = (unsigned)(c->n_sink < L ? c->n_sink : L);
-    kern<<<grid, NT, 0, s>>>(c->params, D, RQ, c->cap_tokens, L, c->k_codes, q, scale, scores, ld, (int)tiles,
+    kern<<<grid, NT, 0, s>>>(c->params, D, c->cap_tokens, L, c->k_codes, q, scale, scores, ld, (int)tiles,
                              sparse_first, stat_slots, (int)ns, span);
     if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[1], s));
     if (prof.enabled) ++prof.count[0];
