@@ -21,10 +21,13 @@ def _keys(T, D, seed, kind):
 @pytest.mark.parametrize("T,D,p,shift,kind", [
     (1200, 4096, 0.01, 0, "plain"),           # 16 channels per workgroup
     (513, 5120, 0.02, 0, "coarse"),           # 16, row steps with a remainder
-    (1009, 2048, 0.01, 0, "plain"),           # 8; the smallest row count whose rows are sampled
-    (1008, 2048, 0.01, 0, "drift"),           # 8; one row fewer: no sample
-    (1100, 1024, 0.0563, 0, "plain"),         # 4; 2 (k + 1) just fits the sample of 69 rows
-    (1100, 1024, 0.07, 0, "drift"),           # 4; and just does not
+    (1009, 2048, 0.01, 0, "plain"), (1008, 2048, 0.01, 0, "drift"),         # 8
+    (8177, 2048, 0.01, 0, "plain"),           # 8; the smallest row count whose rows are sampled
+    (8176, 2048, 0.01, 0, "drift"),           # 8; one row fewer: no sample
+    (1100, 1024, 0.0563, 0, "plain"), (1100, 1024, 0.07, 0, "drift"),       # 4
+    (8200, 1024, 0.0622, 0, "plain"),         # 4; 2 (k + 1) just fits the sample of 513 rows
+    (8200, 1024, 0.0625, 0, "drift"),         # 4; and just does not
+    (9000, 4096, 0.01, 0, "drift"), (9001, 515, 0.01, 0, "coarse"),         # 16 and 1, sampled
     (3000, 514, 0.01, 0, "drift"),            # 2
     (3000, 300, 0.99, 0, "coarse"),           # 1; both sides meet in the middle
     (1500, 515, 0.01, 0, "plain"),            # 1; odd row length
