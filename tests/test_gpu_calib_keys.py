@@ -27,7 +27,9 @@ def _keys(T, D, seed, kind):
     (1100, 1024, 0.0563, 0, "plain"), (1100, 1024, 0.07, 0, "drift"),       # 4
     (8200, 1024, 0.0622, 0, "plain"),         # 4; 2 (k + 1) just fits the sample of 513 rows
     (8200, 1024, 0.0625, 0, "drift"),         # 4; and just does not
-    (9000, 4096, 0.01, 0, "drift"), (9001, 515, 0.01, 0, "coarse"),         # 16 and 1, sampled
+    # 16 and 1, sampled.  (Not "drift" over so many rows and channels: its factor of up to 1287 takes values past the
+    # largest fp16 number, and infinite inputs are outside the call's contract.)
+    (9000, 4096, 0.01, 0, "plain"), (9001, 515, 0.01, 0, "coarse"),
     (3000, 514, 0.01, 0, "drift"),            # 2
     (3000, 300, 0.99, 0, "coarse"),           # 1; both sides meet in the middle
     (1500, 515, 0.01, 0, "plain"),            # 1; odd row length
