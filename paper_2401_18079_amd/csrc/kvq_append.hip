@@ -725,8 +725,6 @@ __device__ __forceinline__ void v_quant_token(const void *__restrict__ params, i
     if (overflow) atomicExch(d_status, (int32_t)KVQ_ERR_NNZ_OVERFLOW);
 }
 
-// (256-thread workgroups serve small models and bulk appends: eight wavefronts per SIMD keep more
-// tokens in flight; the 1024-thread ones are one workgroup per compute unit anyway)
 // Bulk Key append: one wavefront per token, no workgroup barrier.  Lane l takes channels l and l+64
 // of every head, the pair that shares a field of the packed chunk, so a head's 64 fields come from the
 // 64 lanes; the chunk is assembled in a slice of LDS private to the wavefront.  Outliers keep channel
@@ -828,8 +826,8 @@ __device__ __forceinline__ void hist_count(uint32_t *hist, bool in, uint32_t bin
 }
 
 // ---- bulk Value append -----------------------------------------------------------------------
-// Value append: one workgroup of four wavefronts per token, D = 256 * JW channels (JW = 4, 8, 16,
-// 20, 26 or 32).  Wavefront w takes the channel groups j = w JW .. (w + 1) JW - 1, lane l of it the channels
+// Value append: W wavefronts per token, D = 64 W JW channels; in bulk four (JW = 4, 8, 16, 20, 26 or 32), with two
+// tokens (TOK), the pair that shares dwords, in a workgroup.  Wavefront w of a token takes the channel groups j = w JW .. (w + 1) JW - 1, lane l of it the channels
 // 64 j + l (half j & 1 of head j >> 1), so a wavefront packs whole chunks on its own, channel order is
 // wavefront order, and a lane keeps its JW elements in registers from the one load to the end.  The
 // thresholds of the selection are found among the few keys that pass a bound (or, where these are too
@@ -837,11 +835,10 @@ __device__ __forceinline__ void hist_count(uint32_t *hist, bool in, uint32_t bin
 // are taken in channel order, ranked with ballots and the wavefronts' counts, and when the two thresholds coincide the
 // upper outliers take the first of the equal keys and the lower ones the next, which is what taking
 // the k largest first and then the k smallest of the rest comes to.  The packed codes of all JW chunks
-// are gathered in the wavefront's LDS slice and written by all 64 lanes at the end.  Four workgroup
-// barriers per token (five when equal keys must be ranked).  Same arithmetic, same results, as
+// are gathered in the wavefront's LDS slice and written by all 64 lanes at the end (whole dwords where the
+// workgroup has both tokens of the pair).  Same arithmetic, same results, as
 // v_quant_token.
-// W wavefronts per token instead of four (D = 64 W JW): the same routine with fewer elements per lane,
-// for calls of a few tokens, where the time of a token is the length of a lane's instruction stream
+// Calls of a few tokens take more wavefronts and one token per workgroup: fewer elements per lane, where the time of a token is the length of a lane's instruction stream
 // (a 4096-channel token: 16 elements per lane on four wavefronts, 4 on sixteen).
 constexpr int KVQ_VW_WAVES = 4;
 constexpr int KVQ_V_CAND = 128;              // candidates per side that a wavefront looks through (two per lane)
@@ -1262,7 +1259,7 @@ __global__ __launch_bounds__(NT) void kvq_kv_quant(const KvAppendArgs<SP> a)
 // kvq_decode_step appends one token and then attends over the cache that ends with it.  The append is
 // two workgroups of pure latency (12 us), and the attention's first kernel, the sparse Key kernel, needs
 // the new token only for the last of its scores: here both run as workgroups of one launch.  Workgroup 0
-// quantizes the token's Key (the 256-thread body: 62 registers, so the kernel keeps the sparse
+// quantizes the token's Key (k_quant_token_w on sixteen or eight wavefronts, within the registers of the sparse
 // kernel's eight wavefronts per SIMD) and then adds up the sparse part of the token's own scores from
 // the entries it has just stored; workgroup 1 quantizes its Value; the others are the sparse Key
 // kernel over the tokens that were there before.
