@@ -876,18 +876,6 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
     uint32_t(*bits)[CW + 1] = bits_s[wave];
     uint32_t *mask = mask_s[tok][wave];
     __shared__ float lut_s[NE];
-    KvqParamsView pv = kvq_params_view(params, D);
-    const KvqCoder<NE> coder(pv.hdr->thr_v, pv.hdr->lut_v);
-    stage_lut<NE>(lut_s, pv.hdr->lut_v);         // (visible after the barrier that follows the ranges)
-    if (ttid < 64) {
-        col_max[0][ttid] = 0u;
-        col_max[1][ttid] = 0u;
-        if (ttid < 2) n_cand[ttid] = 0u;
-    }
-    // the wavefronts' packing areas, cleared here and filled after the barrier that follows the ranges
-    for (int e = threadIdx.x; e < W * JW * (CW + 1); e += TOK * NTW) (&bits_s[0][0][0])[e] = 0;
-    if (lane <= CW) mask[lane] = 0;
-    __syncthreads();
     const int jb = wave * JW;                    // this wavefront's first channel group (D = 64 W JW)
     // Two tokens of a pair share the dwords of their codes.  TOK = 2: the workgroup has both (or, at either end
     // of the call, one: the other's wavefronts then repeat its work and store nothing).
@@ -901,9 +889,24 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
     const uint32_t K = (uint32_t)k_side;
 
     uint16_t xc[JW];                             // this lane's elements, kept in registers
+    auto load = [&] {
 #pragma unroll
-    for (int i = 0; i < JW; ++i) xc[i] = x16[64 * (jb + i)];
-
+        for (int i = 0; i < JW; ++i) xc[i] = x16[64 * (jb + i)];
+    };
+    if (TOK == 1) load();                        // (a lone token is latency; in bulk the registers are better free)
+    KvqParamsView pv = kvq_params_view(params, D);
+    const KvqCoder<NE> coder(pv.hdr->thr_v, pv.hdr->lut_v);
+    stage_lut<NE>(lut_s, pv.hdr->lut_v);         // (visible after the barrier that follows the ranges)
+    if (ttid < 64) {
+        col_max[0][ttid] = 0u;
+        col_max[1][ttid] = 0u;
+        if (ttid < 2) n_cand[ttid] = 0u;
+    }
+    // the wavefronts' packing areas, cleared here and filled after the barrier that follows the ranges
+    for (int e = threadIdx.x; e < W * JW * (CW + 1); e += TOK * NTW) (&bits_s[0][0][0])[e] = 0;
+    if (lane <= CW) mask[lane] = 0;
+    __syncthreads();
+    if (TOK == 2) load();
     uint32_t top = 0, bot = 0;                   // bit i: channel 64 (jb + i) + lane is an upper / lower outlier
     static_assert(JW <= 32, "one mask bit per element of a lane");
     uint32_t kc[JW];                             // the elements' order-preserving keys
@@ -951,7 +954,14 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
             if (which != 0u) {
                 const int i = __ffs((int)which) - 1;
                 which &= which - 1u;
-                const uint32_t key = order_key(x16[64 * (jb + i)]);      // (re-read: a dynamic index)
+                // (a dynamic index: few elements are looked through, many read again)
+                uint32_t key = kc[0];
+                if constexpr (JW <= 8) {
+#pragma unroll
+                    for (int j = 1; j < JW; ++j) key = i == j ? kc[j] : key;
+                } else {
+                    key = order_key(x16[64 * (jb + i)]);
+                }
                 if (key >= m_top) {
                     const uint32_t at = atomicAdd(&n_cand[0], 1u);
                     if (at < KVQ_V_CAND) cand[0][at] = (uint16_t)key;
@@ -1087,11 +1097,19 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
 #pragma unroll
     for (int i = 0; i < JW; ++i)
         if (!((outl >> i) & 1u)) { const float x = kvq_h2f(xc[i]); mx = fmaxf(mx, x); mn = fminf(mn, x); }
-    uint32_t n_out = (uint32_t)__popc(outl);
-    for (int o = 32; o > 0; o >>= 1) {
-        mx = fmaxf(mx, __shfl_xor(mx, o));
-        mn = fminf(mn, __shfl_xor(mn, o));
-        n_out += __shfl_xor(n_out, o);
+    uint32_t n_out = 0;
+    if constexpr (JW <= 8) {                     // (no trip through LDS: latency is what a call of few tokens is made of)
+#pragma unroll
+        for (int i = 0; i < JW; ++i) n_out += (uint32_t)__popcll(__ballot((outl >> i) & 1u));
+        mx = kvq_wave_max(mx);
+        mn = -kvq_wave_max(-mn);
+    } else {
+        n_out = (uint32_t)__popc(outl);
+        for (int o = 32; o > 0; o >>= 1) {
+            mx = fmaxf(mx, __shfl_xor(mx, o));
+            mn = fminf(mn, __shfl_xor(mn, o));
+            n_out += __shfl_xor(n_out, o);
+        }
     }
     if (lane == 0) { red_mx[wave] = mx; red_mn[wave] = mn; out_cnt[wave] = n_out; }
     __syncthreads();
@@ -1319,11 +1337,13 @@ __device__ __forceinline__ void qk_sparse_new_token(const StepFrontArgs &a)
     for (int j = tid; j < a.n_q_heads; j += NT) a.scores[(int64_t)j * a.ld + a.n] = kvq_from_fixed_fast<0>(S[j]);
 }
 
+// ROOMY: sixteen wavefronts per compute unit instead of 32, for contexts that do not fill more (the append roles are then
+// the launch's length: 16 us with their registers spilled at 2048 tokens of 4096 channels, 10.4 us without).
 // W: wavefronts on the Value token (D = 256 W channels: 16 or 4).  One instantiation per width: the
 // Value routine's static LDS arrays of several widths would add up and cost the sparse role a workgroup
 // per compute unit.
-template <int BITS, int R, int W>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8)))
+template <int BITS, int R, int W, bool ROOMY>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(ROOMY ? 4 : 8, ROOMY ? 4 : 8)))
 void kvq_step_front(const StepFrontArgs)
 {
     // The argument block is read where a role needs it, through a pointer the compiler cannot see
@@ -1582,21 +1602,21 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
 }
 
 
-template <int BITS, int R, int W>
+template <int BITS, int R, int W, bool ROOMY>
 static kvq_status step_front_launch_brw(kvq_cache *cache, StepFrontArgs &a, hipStream_t s, bool *done, bool dry)
 {
     // static LDS of the kernel (the append bodies' arrays) comes on top of the sparse role's dynamic LDS
     static const int static_lds = [] {
         hipFuncAttributes fa;
-        if (hipFuncGetAttributes(&fa, (const void *)kvq_step_front<BITS, R, W>) != hipSuccess) return -1;
+        if (hipFuncGetAttributes(&fa, (const void *)kvq_step_front<BITS, R, W, ROOMY>) != hipSuccess) return -1;
         return (int)fa.sharedSizeBytes;
     }();
-    static const hipError_t lds_attr = hipFuncSetAttribute((const void *)kvq_step_front<BITS, R, W>,
+    static const hipError_t lds_attr = hipFuncSetAttribute((const void *)kvq_step_front<BITS, R, W, ROOMY>,
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, 147456 - 16384);
     if (static_lds < 0 || static_lds > 16384) return KVQ_OK;             // *done stays false
     KVQ_HIP_CHECK(lds_attr);
     QkSparsePlan plan;
-    if (!qk_sparse_plan(cache->n_q_heads, a.n, 8, (size_t)static_lds, plan) || plan.waves != 16) return KVQ_OK;
+    if (!qk_sparse_plan(cache->n_q_heads, a.n, 8, (size_t)static_lds, ROOMY ? 1 : 2, plan) || plan.waves != 16) return KVQ_OK;
     if (plan.lds < (size_t)cache->n_q_heads * 8) return KVQ_OK;
     a.tokens_per_wave = plan.tokens_per_wave;
     if (dry) {                                    // the caller only asks whether this launch applies
@@ -1607,7 +1627,7 @@ static kvq_status step_front_launch_brw(kvq_cache *cache, StepFrontArgs &a, hipS
     if (st != KVQ_OK) return st;
     st = copy_sink_rows(cache, cache->sink_v, a.v_new, a.n, 1, s);
     if (st != KVQ_OK) return st;
-    kvq_step_front<BITS, R, W><<<plan.grid + 2, 1024, plan.lds, s>>>(a);
+    kvq_step_front<BITS, R, W, ROOMY><<<plan.grid + 2, 1024, plan.lds, s>>>(a);
     KVQ_HIP_CHECK(hipGetLastError());
     cache->n_tokens_k += 1;
     cache->n_tokens_v += 1;
@@ -1618,8 +1638,14 @@ static kvq_status step_front_launch_brw(kvq_cache *cache, StepFrontArgs &a, hipS
 template <int BITS, int R>
 static kvq_status step_front_launch_br(kvq_cache *cache, StepFrontArgs &a, hipStream_t s, bool *done, bool dry)
 {
-    if (a.D == 4096) return step_front_launch_brw<BITS, R, 16>(cache, a, s, done, dry);
-    return step_front_launch_brw<BITS, R, 4>(cache, a, s, done, dry);
+    // 4096 channels: up to twelve tokens per wavefront of one workgroup per compute unit, the launch with the registers
+    // that the append roles want.  us per step with it / with two workgroups per unit, whose append roles spill: 32
+    // heads, 4 bits, 1000 tokens 34.8 / 40.0, 8000 42.9 / 48.9, 16383 50.1 / 56.0, 32767 73.8 / 79.0; 3 bits, 50000 tokens
+    // 79.3 / 79.5, 131071 149 / 144.  (1024 channels spill nothing: 8 heads, 4 bits, 16000 tokens 32.6 / 30.7.)
+    if (a.D == 4096)
+        return a.n <= 12 * 16 * (int64_t)kvq_cu_count() ? step_front_launch_brw<BITS, R, 16, true>(cache, a, s, done, dry)
+                                                        : step_front_launch_brw<BITS, R, 16, false>(cache, a, s, done, dry);
+    return step_front_launch_brw<BITS, R, 4, false>(cache, a, s, done, dry);
 }
 
 template <int BITS>

@@ -1017,7 +1017,7 @@ kvq_status launch_qk_sparse_tw(const kvq_cache *c, const SP ksp, const float *q,
     const int Hq = c->n_q_heads;
     const int64_t L = c->n_tokens_k;
     QkSparsePlan plan;
-    if (!qk_sparse_plan(Hq, L, TW, 0, plan)) return KVQ_ERR_UNSUPPORTED;
+    if (!qk_sparse_plan(Hq, L, TW, 0, 32, plan)) return KVQ_ERR_UNSUPPORTED;
     // the kernel's dynamic-LDS limit is raised once per instantiation, to the most any launch asks for
     // (initialisation of a function-local static is thread-safe)
     static const hipError_t lds_attr = hipFuncSetAttribute((const void *)kvq_qk_sparse<R, TW, SP>,

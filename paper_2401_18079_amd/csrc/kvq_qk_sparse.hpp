@@ -185,7 +185,7 @@ struct QkSparsePlan {
     int64_t tokens_per_wave;
     unsigned grid;             // workgroups
 };
-inline bool qk_sparse_plan(int n_q_heads, int64_t L, int tw, size_t static_lds, QkSparsePlan &p)
+inline bool qk_sparse_plan(int n_q_heads, int64_t L, int tw, size_t static_lds, int most_per_cu, QkSparsePlan &p)
 {
     const int per_wave = qs_wave_lds_bytes(n_q_heads, tw);
     int waves = 16;
@@ -195,6 +195,7 @@ inline bool qk_sparse_plan(int n_q_heads, int64_t L, int tw, size_t static_lds, 
     if (static_lds + lds > 147456) return false;
     int wgs_per_cu = (int)(163840 / (static_lds + lds));
     if (wgs_per_cu * waves > 32) wgs_per_cu = 32 / waves;
+    if (wgs_per_cu > most_per_cu) wgs_per_cu = most_per_cu;
     if (wgs_per_cu < 1) wgs_per_cu = 1;
     const int64_t resident = (int64_t)kvq_cu_count() * wgs_per_cu * waves;
     int64_t tpw = (L + resident - 1) / resident;
