@@ -52,6 +52,11 @@ struct QkCfg {
     static constexpr int NE = 1 << BITS;
     static constexpr int ENTRIES = JOINT ? (1 << (2 * BITS)) : 2 * NE;   // (A,B) entries per (head, pair)
     static constexpr int CW = 4 * BITS;                                  // dwords per chunk
+    // 8-byte slot of entry f of table t = 64 * head + pair (nibble_x16: 2- and 4-bit entries lie 16 bytes apart)
+    static constexpr __host__ __device__ int slot(int t, int f)
+    {
+        return BITS == 2 ? (t >> 1) * 32 + 2 * f + (t & 1) : BITS == 4 ? t * 32 + 2 * (f & (NE - 1)) + f / NE : t * ENTRIES + f;
+    }
 };
 
 // The chunk of one (token, head) is consumed front to back, so only two of its 16-byte pieces need to
@@ -72,6 +77,39 @@ __device__ __forceinline__ uint32_t field_shifted(const uint32_t (&Wg)[8], int i
         return chunk_dword(Wg, wi) << (3 - sh);
     }
     return __builtin_amdgcn_alignbit(chunk_dword(Wg, wi + 1), chunk_dword(Wg, wi), sh - 3);
+}
+
+// 2- and 4-bit codes: nibble NIB of a dword, times 16, in one instruction that takes its byte out of the source as it
+// reads it (SDWA; a shift and a mask otherwise).  The tables of these widths therefore have entries 16 bytes apart,
+// with those of a neighbour in between: the two codes of a pair (4 bits) or two pairs (2 bits).
+template <int NIB>
+__device__ __forceinline__ uint32_t nibble_x16(uint32_t w)
+{
+    uint32_t r;
+#define KVQ_NIB(K)                                                                                                     \
+    if constexpr (NIB == 2 * K)                                                                                        \
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_" #K       \
+            : "=v"(r) : "s"(4u), "v"(w));                                                                              \
+    if constexpr (NIB == 2 * K + 1)                                                                                    \
+        asm("v_and_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_" #K            \
+            : "=v"(r) : "s"(0xF0u), "v"(w));
+    KVQ_NIB(0) KVQ_NIB(1) KVQ_NIB(2) KVQ_NIB(3)
+#undef KVQ_NIB
+    return r;
+}
+// The same into the low byte of `r`, whose other bytes stay: the place of a table that an immediate offset does not reach.
+template <int NIB>
+__device__ __forceinline__ void nibble_x16_into(uint32_t &r, uint32_t w)
+{
+#define KVQ_NIB(K)                                                                                                     \
+    if constexpr (NIB == 2 * K)                                                                                        \
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:BYTE_" #K  \
+            : "+v"(r) : "s"(4u), "v"(w));                                                                              \
+    if constexpr (NIB == 2 * K + 1)                                                                                    \
+        asm("v_and_b32_sdwa %0, %1, %2 dst_sel:BYTE_0 dst_unused:UNUSED_PRESERVE src0_sel:DWORD src1_sel:BYTE_" #K      \
+            : "+v"(r) : "s"(0xF0u), "v"(w));
+    KVQ_NIB(0) KVQ_NIB(1) KVQ_NIB(2) KVQ_NIB(3)
+#undef KVQ_NIB
 }
 
 // After the G0-th group of PAIR_GROUP channel pairs: request the pieces whose registers the group has freed.
@@ -123,7 +161,7 @@ __device__ __forceinline__ void qk_next_pieces(uint32_t (&W)[KVH][8], const uint
 //   3. two fp32 FMAs per (pair, query head) and table part.
 // G0 is a compile-time constant so that all register-array indices fold.
 template <int BITS, int KVH, int RQ, int PAIR_GROUP, int G0>
-__device__ __forceinline__ void qk_group(uint32_t (&W)[KVH][8], float (&acc)[KVH * RQ],
+__device__ __forceinline__ void qk_group(uint32_t (&W)[KVH][8], float (&acc)[KVH * RQ], uint32_t &far,
                                          const float2_t *tab, float nf, float wave_base, const KvqParamsHeader *hdr,
                                          const uint8_t *cur_chunk, const uint8_t *next_chunk, int64_t plane,
                                          bool valid, bool next_valid)
@@ -136,42 +174,56 @@ __device__ __forceinline__ void qk_group(uint32_t (&W)[KVH][8], float (&acc)[KVH
     constexpr int ENT = C::ENTRIES;
     constexpr int NG = C::JOINT ? 1 : 2;          // gathers per (pair, query head)
     float2_t t[PAIR_GROUP][QH][NG];
+    if constexpr (BITS == 3) {
 #pragma unroll
-    for (int p = 0; p < PAIR_GROUP; ++p) {
-        const int I = G0 * PAIR_GROUP + p;
+        for (int p = 0; p < PAIR_GROUP; ++p) {
+            const int I = G0 * PAIR_GROUP + p;
+            constexpr uint32_t M = ((1u << (2 * BITS)) - 1u) << 3;
 #pragma unroll
-        for (int g = 0; g < KVH; ++g) {
-            uint32_t sh[NG];
-            constexpr uint32_t M = ((C::JOINT ? (1u << (2 * BITS)) : (1u << BITS)) - 1u) << 3;
-            if (C::JOINT) sh[0] = field_shifted<2 * BITS>(W[g], I);
-            else { sh[0] = field_shifted<BITS>(W[g], 2 * I); sh[NG - 1] = field_shifted<BITS>(W[g], 2 * I + 1); }
-            uint32_t off_lo[NG];
-            bool have_lo = false;
+            for (int g = 0; g < KVH; ++g) {
+                const uint32_t sh = field_shifted<2 * BITS>(W[g], I);
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int qh = g * R + r;
-                // LDS instructions reach 64 KiB past their address register; tables further up get the
-                // excess folded into the masking instruction instead of an extra add
-                const uint32_t base = (uint32_t)((qh * 64 + I) * ENT) * 8u;
-                const uint32_t hi = base & ~0xFFFFu;
-                const uint8_t *tb = (const uint8_t *)tab + (base - hi);
-                if (hi == 0) {
-                    if (!have_lo) {
-#pragma unroll
-                        for (int k = 0; k < NG; ++k) off_lo[k] = sh[k] & M;
-                        have_lo = true;
-                    }
-#pragma unroll
-                    for (int k = 0; k < NG; ++k) t[p][qh][k] = *(const float2_t *)(tb + k * NE * 8 + off_lo[k]);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < NG; ++k) {
-                        const uint32_t off = kvq_and_or(sh[k], M, hi);
-                        t[p][qh][k] = *(const float2_t *)(tb + k * NE * 8 + off);
-                    }
+                for (int r = 0; r < R; ++r) {
+                    const int qh = g * R + r;
+                    // LDS instructions reach 64 KiB past their address register; tables further up get the
+                    // excess folded into the masking instruction instead of an extra add
+                    const uint32_t base = (uint32_t)C::slot(qh * 64 + I, 0) * 8u, hi = base & ~0xFFFFu;
+                    t[p][qh][0] = *(const float2_t *)((const uint8_t *)tab + (base - hi) + (hi ? kvq_and_or(sh, M, hi) : (sh & M)));
                 }
             }
         }
+    } else {
+        auto gather = [&](auto pc) {
+            constexpr int p = decltype(pc)::value, I = G0 * PAIR_GROUP + p;
+            auto part = [&](auto kc) {
+                constexpr int k = decltype(kc)::value, NIB = (NG * I + k) % 8, WI = (NG * I + k) / 8;
+#pragma unroll
+                for (int g = 0; g < KVH; ++g) {
+                    const uint32_t w = chunk_dword(W[g], WI);
+                    uint32_t off = 0;
+                    bool have = false;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const int qh = g * R + r;
+                        const uint32_t base = (uint32_t)C::slot(qh * 64 + I, k * NE) * 8u, hi = base & ~0xFFFFu;
+                        static_assert(C::slot(QH * 64, 0) * 8 <= 131072, "one place beyond the reach of immediate offsets");
+                        if (hi == 0) {
+                            if (!have) off = nibble_x16<NIB>(w);
+                            have = true;
+                            t[p][qh][k] = *(const float2_t *)((const uint8_t *)tab + base + off);
+                        } else {
+                            nibble_x16_into<NIB>(far, w);
+                            t[p][qh][k] = *(const float2_t *)((const uint8_t *)tab + (base - hi) + far);
+                        }
+                    }
+                }
+            };
+            part(std::integral_constant<int, 0>{});
+            if constexpr (NG == 2) part(std::integral_constant<int, 1>{});
+        };
+        gather(std::integral_constant<int, 0>{});
+        if constexpr (PAIR_GROUP == 2) gather(std::integral_constant<int, 1>{});
+        static_assert(BITS == 3 || PAIR_GROUP <= 2, "two pairs a group at most");
     }
     float cs[PAIR_GROUP], sn[PAIR_GROUP];
 #pragma unroll
@@ -203,12 +255,12 @@ __device__ __forceinline__ void qk_group(uint32_t (&W)[KVH][8], float (&acc)[KVH
 
 template <int BITS, int KVH, int RQ, int PG, int... G>
 __device__ __forceinline__ void qk_all_pairs(std::integer_sequence<int, G...>,
-                                             uint32_t (&W)[KVH][8], float (&acc)[KVH * RQ],
+                                             uint32_t (&W)[KVH][8], float (&acc)[KVH * RQ], uint32_t &far,
                                              const float2_t *tab, float nf, float wave_base,
                                              const KvqParamsHeader *hdr, const uint8_t *cur_chunk,
                                              const uint8_t *next_chunk, int64_t plane, bool valid, bool next_valid)
 {
-    (qk_group<BITS, KVH, RQ, PG, G>(W, acc, tab, nf, wave_base, hdr, cur_chunk, next_chunk, plane, valid, next_valid), ...);
+    (qk_group<BITS, KVH, RQ, PG, G>(W, acc, far, tab, nf, wave_base, hdr, cur_chunk, next_chunk, plane, valid, next_valid), ...);
 }
 
 // Stage the scaled query and the per-channel (scale, zero-point) of the workgroup's heads in LDS and
@@ -255,7 +307,7 @@ __device__ __forceinline__ void qk_build_tables(float2_t *tab, float *qs, float2
             a = upper ? qb * k : qa * k;
             b = upper ? -qa * k : qb * k;
         }
-        tab[tb * ENT + f] = float2_t{a, b};
+        tab[C::slot(tb, f)] = float2_t{a, b};
     }
     __syncthreads();
 }
@@ -304,6 +356,7 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
     bool valid = n < L;
     const float my_vh = pv.hdr->rope_vh[tid & 63], my_vl = pv.hdr->rope_vl[tid & 63];   // this lane's pair
     uint32_t W[KVH][8];                                    // two 16-byte pieces per KV head
+    uint32_t far = 0x10000u;                               // address of the tables 64 KiB up, the entry in its low byte
     const uint8_t *cur_chunk = k_codes + kvq_k_piece0(BITS, cap, valid ? n : 0, kv0);
     if (valid) {
 #pragma unroll
@@ -353,7 +406,7 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
         // masked, so every gather stays inside the table) and simply skip loads and stores
         // a wavefront whose 64 tokens all lie past the end (ragged last tile) skips the arithmetic
         if (__ballot(valid) != 0ull)
-            qk_all_pairs<BITS, KVH, RQ, PG>(std::make_integer_sequence<int, 64 / PG>{}, W, acc, tab, nf, wave_base,
+            qk_all_pairs<BITS, KVH, RQ, PG>(std::make_integer_sequence<int, 64 / PG>{}, W, acc, far, tab, nf, wave_base,
                                             pv.hdr, cur_chunk, next_chunk, plane, valid, next_valid);
         if (BITS & 1) {
             // odd piece count: the next tile's piece 0 arrived in slot 1; move it to slot 0 (whose last
@@ -435,6 +488,10 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
 // kernel, the matrix cores 26 %).  Times beside qk_grouped.
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
+// 4-byte slot of entry f (16 of channel i, then 16 of channel i + 64) of table t = 64 * KV head + pair, 4-bit codes: entries
+// 16 bytes apart (nibble_x16), two pairs' between each other.
+__host__ __device__ constexpr int qkg_slot4(int t, int f) { return (t >> 1) * 64 + 4 * (f & 15) + 2 * (t & 1) + f / 16; }
+
 // q: four query heads of 16 channels; the instruction takes those of channel `C` of the 16.
 template <int C>
 __device__ __forceinline__ float4_t qkg_madd(float q, float k, float4_t acc)
@@ -461,27 +518,27 @@ __device__ __forceinline__ void qkg_group(std::integer_sequence<int, P...>, uint
                 for (int z = 0; z < 2; ++z) q[g][u][z] = qs[((g * SETS + u) * 8 + G0 * PG / 16 + 4 * z) * 64];
     }
     float2_t k[PG][KVH];
-#pragma unroll
-    for (int p = 0; p < PG; ++p) {
-        const int I = G0 * PG + p;
+    auto gather = [&](auto pc) {
+        constexpr int p = decltype(pc)::value, I = G0 * PG + p;
 #pragma unroll
         for (int g = 0; g < KVH; ++g) {
-            if constexpr (C::JOINT) {
+            const int tb = g * 64 + I;
+            if constexpr (BITS == 3) {
                 constexpr uint32_t M = ((1u << (2 * BITS)) - 1u) << 3;
-                const uint32_t base = (uint32_t)((g * 64 + I) * C::ENTRIES) * 8u, hi = base & ~0xFFFFu;
+                const uint32_t base = (uint32_t)C::slot(tb, 0) * 8u, hi = base & ~0xFFFFu;
                 const uint32_t f = field_shifted<2 * BITS>(W[g], I);
                 k[p][g] = *(const float2_t *)(tab + (base - hi) + (hi ? kvq_and_or(f, M, hi) : (f & M)));
+            } else if constexpr (BITS == 2) {
+                static_assert(BITS == 3 || C::slot(KVH * 64, 0) * 8 <= 65536, "within reach of immediate offsets");
+                k[p][g] = *(const float2_t *)(tab + C::slot(tb, 0) * 8 + nibble_x16<I % 8>(chunk_dword(W[g], I / 8)));
             } else {
-                // (4-byte entries: a code moved to bit 2)
-                constexpr uint32_t M = (uint32_t)(NE - 1) << 2;
-                const uint32_t base = (uint32_t)((g * 64 + I) * 2 * NE) * 4u;
-                const int bit = I * 2 * BITS, wi = bit >> 5, sh = bit & 31;
-                const uint32_t w = chunk_dword(W[g], wi);
-                const uint32_t lo = (sh >= 2 ? w >> (sh >= 2 ? sh - 2 : 0) : w << 2) & M, hi = (w >> (sh + BITS - 2)) & M;
-                k[p][g] = float2_t{*(const float *)(tab + base + lo), *(const float *)(tab + base + 4 * NE + hi)};
+                const uint32_t w = chunk_dword(W[g], I / 4);
+                k[p][g] = float2_t{*(const float *)(tab + qkg_slot4(tb, 0) * 4 + nibble_x16<2 * (I % 4)>(w)),
+                                   *(const float *)(tab + qkg_slot4(tb, NE) * 4 + nibble_x16<2 * (I % 4) + 1>(w))};
             }
         }
-    }
+    };
+    (gather(std::integral_constant<int, P>{}), ...);
     float cs[PG], sn[PG];
 #pragma unroll
     for (int p = 0; p < PG; ++p) {
@@ -581,10 +638,10 @@ __global__ __launch_bounds__(NT) void kvq_qkg_kernel(const void *__restrict__ pa
         if constexpr (C::JOINT) {
             const float lo = __builtin_fmaf(pv.s[c], pv.hdr->lut_k[f & (NE - 1)], pv.z[c]);
             const float hi = __builtin_fmaf(pv.s[c + 64], pv.hdr->lut_k[f >> BITS], pv.z[c + 64]);
-            *(float2_t *)(tab + 8 * e) = float2_t{lo, hi};
+            *(float2_t *)(tab + 8 * C::slot(e / ENT, f)) = float2_t{lo, hi};
         } else {
             const int cc = f >= NE ? c + 64 : c;
-            *(float *)(tab + 4 * e) = __builtin_fmaf(pv.s[cc], pv.hdr->lut_k[f & (NE - 1)], pv.z[cc]);
+            *(float *)(tab + 4 * qkg_slot4(e / ENT, f)) = __builtin_fmaf(pv.s[cc], pv.hdr->lut_k[f & (NE - 1)], pv.z[cc]);
         }
     }
     float stat_m[STATS ? QH : 1];
