@@ -437,11 +437,15 @@ def kvq_calibrate_key_channels(k_cal: torch.Tensor, outlier_fraction: float, str
     """Per-channel Key constants (s, z, lo, hi) as fp16 numpy arrays, from calibration Keys [T][D] on the GPU."""
     assert k_cal.is_cuda and k_cal.dtype == torch.float16 and k_cal.dim() == 2 and k_cal.is_contiguous()
     T, D = k_cal.shape
-    outs = torch.empty((4, D), dtype=torch.int16, device=k_cal.device)     # one copy to the host, one wait for the GPU
+    # The kernel stores its 8 D bytes to host memory itself: one wait, no copy (32768 x 4096: 213 us with the copy, 200 us
+    # without).
+    outs = torch.empty(4 * D, dtype=torch.int16, pin_memory=True)
+    p = outs.data_ptr()
     _check(load_library().kvq_calibrate_key_channels(k_cal.data_ptr(), T, D, float(outlier_fraction),
-                                                     *[o.data_ptr() for o in outs], _stream_ptr(stream)),
+                                                     p, p + 2 * D, p + 4 * D, p + 6 * D, _stream_ptr(stream)),
            "kvq_calibrate_key_channels")
-    return tuple(outs.cpu().numpy().view(np.float16))
+    (torch.cuda.current_stream() if stream is None else stream).synchronize()
+    return tuple(outs.numpy().view(np.float16).reshape(4, D).copy())
 
 
 def kvq_calibrate_nuq(x_norm: torch.Tensor, w: torch.Tensor, bits: int, iters: int, init, stream=None) -> np.ndarray:
