@@ -1710,5 +1710,6 @@ extern "C" int32_t kvq_decode_step_launches(const kvq_cache *cache)
     // the two calls: append, sparse Key (unless the thresholds admit no outlier), dense Key, sparse Value,
     // dense Value, reduction
     const int two_calls = (cache->loaded & 2) ? 5 : 6;
-    return (front ? 5 : two_calls) + sink;
+    view.n_tokens_v = cache->n_tokens_v + 1;     // what the Value half of the step covers
+    return (front ? 5 : two_calls) + sink - (kvq_pv_is_one_launch(&view) ? 1 : 0);
 }

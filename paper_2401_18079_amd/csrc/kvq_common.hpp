@@ -370,6 +370,8 @@ __attribute__((visibility("hidden"))) kvq_status kvq_step_front_launch(kvq_cache
                                                                        const uint16_t *d_v_new, const float *d_q_rot,
                                                                        float scale, float *d_scores, int64_t ld_scores,
                                                                        hipStream_t s, bool *done);
+// Whether kvq_pv_run over this cache runs its sparse and dense kernels as one launch.
+__attribute__((visibility("hidden"))) bool kvq_pv_is_one_launch(const kvq_cache *cache);
 // Bytes of the workspace that kvq_pv_run uses (from its start); the statistics slots follow.
 __attribute__((visibility("hidden"))) int64_t kvq_pv_workspace_bytes(int n_q_heads);
 

@@ -10,11 +10,14 @@
 // (lanes = outlier entries, fixed-point LDS accumulators); all partial results, and the fp16 rows of
 // attention-sink tokens (paper Sec. 3.5) if any, are summed in a fixed order by a final small kernel.
 #include "kvq_common.hpp"
+#include <math.h>
+#include <type_traits>
 
 namespace {
 
 constexpr int PV_TILE = 64;                // tokens per tile of the dense kernel (32 token pairs)
 constexpr int PV_CHAIN = 16;               // tiles whose products one accumulator takes up
+constexpr size_t PV_BOTH_LDS = 160 * 1024; // most LDS of a workgroup
 constexpr int PV_MIN_TILES = 8;            // tiles a workgroup should at least have: half of its wavefronts busy
 
 struct PvPlan {
@@ -92,6 +95,61 @@ inline PvPlan pv_plan(int64_t L, int n_q_heads, int rg)
     return p;
 }
 
+// Plan of the one launch for both kernels.  The compute units are dealt out so that either kind takes as long, and the
+// launch is taken where it is then estimated to end sooner than two.  Work in us per 131072 tokens on the whole chip:
+// sparse 2 (pointers), 0.12 per query head (scores staged) and 0.08 + 0.11 per query head of the KV head for an outlier;
+// dense, per head group, 1.0, 1.4 or 1.6 (2, 3, 4 bits) and 0.2 more for every head of a group beyond the first, of which
+// 4-bit codes need 1.5 of the compute units (the rest is HBM).  Sparse wavefronts have 16 (eight-head groups: 8) beside them on a compute
+// unit here and up to 24 in their own kernel: 1.22 (2.0) times the work.  Two launches cost 8 us more: one launch and the
+// first and last round trips of a kernel.  From 2048 tokens on (shorter contexts keep the launches that
+// kvq_decode_step_launches has always stated for them).  kvq_attention_decode, us, two launches / one: 3-bit, 32 heads,
+// 2048 tokens 30.1 / 25.5, 16383 42.8 / 40.0, 65536 84.9 / 78.8, 115000 123 / 127, 131071 130 / 127, 150000 151 / 155; 4-bit 32767
+// 71.3 / 61.2; 32 on 8, 2-bit 131000 93 / 87, 262144 138 / 133, 4-bit 33001 62.3 / 52; 64 on 8, 3-bit, 100000 164 / 131; 32 on 4,
+// 4-bit, 60000 67.9 / 59.3, 131000 96.5 / 100.3; 40 heads, 3-bit, 90000 120 / 125; one head, 4095 24.8 / 20.4, 100000 31.9 / 26.7.
+struct PvBoth {
+    int n_sparse, slabs;               // sparse workgroups (of the dense one's width), dense ones per head group
+    int64_t tokens_per_wave;           // of the sparse ones
+    size_t lds;
+};
+inline bool pv_both(const kvq_cache *c, int rg, size_t dense_lds, PvBoth &p)
+{
+    const int Hq = c->n_q_heads, r = Hq / c->n_kv_heads;
+    const int64_t L = c->n_tokens_v;
+    if (c->nnz_block_shift || c->cap_nnz_v >= ((int64_t)1 << 31) || L < 2048) return false;
+    const int waves = rg == 8 ? 8 : 16, cus = kvq_cu_count(), groups = Hq / rg;
+    const size_t sparse_lds = (size_t)Hq * (1024 + 8) + (size_t)waves * pvs_wave_lds_floats(Hq) * 4;
+    p.lds = sparse_lds > dense_lds ? sparse_lds : dense_lds;
+    if (p.lds > PV_BOTH_LDS) return false;
+    const double sparse = 2.0 + 0.12 * Hq + 2.0 * c->k_side_v * (0.08 + 0.11 * r), sparse_here = sparse * (rg == 8 ? 2.0 : 1.22);
+    const double more = 0.2 * (rg - 1), dense = groups * ((c->bits == 2 ? 1.0 : c->bits == 3 ? 1.4 : 1.6) + more);
+    const double dense_here = groups * ((c->bits == 2 ? 1.0 : c->bits == 3 ? 1.4 : 1.5) + more);
+    auto slowest = [&](int slabs) {                        // of the two kinds
+        const int left = cus - slabs * groups;
+        const double d = dense_here * cus / (slabs * groups), s = left < 1 ? 1e30 : sparse_here * cus / left;
+        return s > d ? s : d;
+    };
+    int slabs = (int)(cus * dense_here / ((dense_here + sparse_here) * groups));
+    slabs = slabs < 1 ? 1 : slabs;
+    if (slowest(slabs + 1) < slowest(slabs)) ++slabs;
+    const int left = cus - slabs * groups;
+    if (left < 1) return false;
+    const int64_t wavefronts = (int64_t)left * waves;
+    p.tokens_per_wave = ((L + wavefronts - 1) / wavefronts + 7) & ~(int64_t)7;
+    p.n_sparse = (int)((L + p.tokens_per_wave * waves - 1) / (p.tokens_per_wave * waves));
+    const int64_t few = ((L + PV_TILE - 1) / PV_TILE + PV_MIN_TILES - 1) / PV_MIN_TILES;
+    p.slabs = slabs > few ? (int)few : slabs;
+    if (p.n_sparse > PVS_MAX_SLABS || p.slabs > 512) return false;
+    const PvPlan two = pv_plan(L, Hq, rg);
+    const int own = two.swaves * (int)(PV_BOTH_LDS / two.slds);         // sparse wavefronts on a compute unit in their own kernel
+    const double x = (double)L / 131072.0, fill = (double)p.tokens_per_wave * (double)wavefronts / (double)L;
+    const double s_one = sparse_here * cus / left * fill, d_one = dense_here * cus / (slabs * groups);
+    const double s_two = own < 24 ? sparse * sqrt(24.0 / own) : sparse;
+    const int64_t per_group = cus / groups;
+    const double d_two = per_group > 0 ? dense * cus / (double)(per_group * groups) : dense;
+    // (eight tokens per wavefront at least: short contexts leave compute units over, and the estimate is beside the point)
+    return p.tokens_per_wave == 8 || (s_one > d_one ? s_one : d_one) * x <= (s_two + d_two) * x + 8.0;
+}
+
 template <int FBITS>
 __device__ inline uint32_t pv_field_off(const uint32_t *W, int i, uint32_t lane_off)
 {
@@ -162,14 +220,14 @@ struct PvCfg {
     static constexpr int LDS = TAB + WAVES * WAVE;
 };
 
-template <int BITS, int RG, bool SPAN = false>
-__global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
-    const void *__restrict__ params, int D, int n_kv_heads, int n_q_heads, int64_t cap, int64_t L,
+template <int BITS, int RG>
+__device__ __forceinline__ void pv_dense_body(
+    uint8_t *lds, const int slab, const int n_slabs, const int group, const void *__restrict__ params, int D, int n_kv_heads, int n_q_heads, int64_t cap, int64_t L,
     const uint8_t *__restrict__ v_codes, const uint16_t *__restrict__ v_sz, const float *__restrict__ probs, int64_t ld,
     float *__restrict__ partial, float *__restrict__ zpart, int n_tiles, int n_sink,
-    const float *__restrict__ stat_slots, int n_stat, float *__restrict__ lpart, unsigned long long *span)
+    const float *__restrict__ stat_slots, int n_stat, float *__restrict__ lpart)
 {
-    const unsigned long long span_start = SPAN ? kvq_wall_clock() : 0;      // timing-aid instantiation (kvq_profile_*)
+    // workgroup `slab` of the n_slabs that share the tiles of head group `group`; lds: C::LDS bytes.
     // tokens below n_sink are attention-sink tokens kept in fp16: their quantized form gets weight 0
     // here and the reduce kernel adds their fp16 rows.
     // stat_slots != null: `probs` holds raw scores x; a wavefront takes the maximum m of each of its
@@ -177,14 +235,13 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
     // also writes the sum of these weights to lpart[slab][q] (the reduce kernel divides by their total)
     using C = PvCfg<BITS, RG>;
     constexpr int WAVES = C::WAVES, SETS = C::SETS;
-    __shared__ __attribute__((aligned(16))) uint8_t lds[C::LDS];
     static_assert(C::LDS >= WAVES * RG * 130 * 4, "the workgroup's sums reuse the array");
     const KvqParamsView pv = kvq_params_view(params, D);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int q0 = blockIdx.y * RG;                                 // first query head of the group
+    const int q0 = group * RG;                                 // first query head of the group
     const int kvh = q0 / (n_q_heads / n_kv_heads);
-    const int tile1 = (int)(((int64_t)(blockIdx.x + 1) * n_tiles) / gridDim.x);
-    int tile = (int)(((int64_t)blockIdx.x * n_tiles) / gridDim.x) + wave;
+    const int tile1 = (int)(((int64_t)(slab + 1) * n_tiles) / n_slabs);
+    int tile = (int)(((int64_t)slab * n_tiles) / n_slabs) + wave;
 
     // the tile's loads: lane = token for scores and (scale, zero-point), lane = (half, pair) for the codes
     uint4 cw[BITS];
@@ -397,11 +454,27 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
 #pragma unroll
         for (int k = 0; k < WAVES; ++k) v += ((const float *)lds)[k * RG * 130 + i];
         const int h = i / 130, c = i - 130 * h;
-        const int64_t o = (int64_t)blockIdx.x * n_q_heads + q0 + h;
+        const int64_t o = (int64_t)slab * n_q_heads + q0 + h;
         if (c < 128) partial[o * 128 + c] = v;
         else if (c == 128) zpart[o] = v;
         else if (stat_slots) lpart[o] = v;
     }
+}
+
+#define KVQ_PV_DENSE_PARAMS                                                                                              \
+    const void *__restrict__ params, int D, int n_kv_heads, int n_q_heads, int64_t cap, int64_t L,                     \
+        const uint8_t *__restrict__ v_codes, const uint16_t *__restrict__ v_sz, const float *__restrict__ probs,       \
+        int64_t ld, float *__restrict__ partial, float *__restrict__ zpart, int n_tiles, int n_sink,                   \
+        const float *__restrict__ stat_slots, int n_stat, float *__restrict__ lpart
+#define KVQ_PV_DENSE_ARGS                                                                                               \
+    params, D, n_kv_heads, n_q_heads, cap, L, v_codes, v_sz, probs, ld, partial, zpart, n_tiles, n_sink, stat_slots,    \
+        n_stat, lpart
+template <int BITS, int RG, bool SPAN = false>
+__global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(KVQ_PV_DENSE_PARAMS, unsigned long long *span)
+{
+    const unsigned long long span_start = SPAN ? kvq_wall_clock() : 0;      // timing-aid instantiation (kvq_profile_*)
+    __shared__ __attribute__((aligned(16))) uint8_t lds[PvCfg<BITS, RG>::LDS];
+    pv_dense_body<BITS, RG>(lds, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, KVQ_PV_DENSE_ARGS);
     if (SPAN) kvq_span_end(span, span_start);
 }
 
@@ -416,15 +489,13 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(
 // n_sink tokens in fp16; FUSED: `probs` holds raw scores, see below (separate instantiations: the
 // plain one has no register to spare)
 template <int R, bool SINK, bool FUSED, class SP>
-__global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(6, 6)))
-void kvq_pv_sparse(int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__restrict__ v_ptr,
+__device__ __forceinline__ void pv_sparse_body(float *dyn, const int bx, int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__restrict__ v_ptr,
                    const SP vsp, uint32_t nnz_cap,
                    const float *__restrict__ probs, int64_t ld, float *__restrict__ spartial, int64_t tokens_per_wave,
                    int n_sink, const float *__restrict__ stat_slots, int n_stat)
 {
     // FUSED: `probs` holds raw scores x; the workgroup takes every head's maximum m over its n_stat
     // slots once and scores become weights exp(x - m) on their way into the wavefront's LDS slice
-    extern __shared__ __attribute__((aligned(16))) float dyn[];
     unsigned long long *sacc = (unsigned long long *)dyn;     // [n_q_heads][128] 2^40-scaled sums
     float *sst = (float *)(sacc + n_q_heads * 128);           // [n_q_heads] log2(e) * maximum score (2 floats per head reserved)
     const int tid = threadIdx.x, lane = tid & 63, n_waves = blockDim.x >> 6;
@@ -433,7 +504,7 @@ void kvq_pv_sparse(int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__r
     const int r = R ? R : n_q_heads / n_kv_heads;
     for (int j = tid; j < n_q_heads * 128; j += blockDim.x) sacc[j] = 0ull;
     bool cleared = false;      // the barrier after the clearing comes once the first loads are requested
-    const int64_t nb = ((int64_t)blockIdx.x * n_waves + wave) * tokens_per_wave;
+    const int64_t nb = ((int64_t)bx * n_waves + wave) * tokens_per_wave;
     int64_t ne = nb + tokens_per_wave;
     if (ne > L) ne = L;
     const int n_cells = n_q_heads * PVS_TW;
@@ -561,7 +632,38 @@ void kvq_pv_sparse(int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__r
     if (!cleared) __syncthreads();       // a wavefront without tokens still meets the workgroup's barrier
     __syncthreads();
     for (int j = tid; j < n_q_heads * 128; j += blockDim.x)
-        spartial[(int64_t)blockIdx.x * n_q_heads * 128 + j] = kvq_from_fixed<8>(sacc[j]);
+        spartial[(int64_t)bx * n_q_heads * 128 + j] = kvq_from_fixed<8>(sacc[j]);
+}
+
+template <int R, bool SINK, bool FUSED, class SP>
+__global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(6, 6)))
+void kvq_pv_sparse(int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__restrict__ v_ptr, const SP vsp,
+                   uint32_t nnz_cap, const float *__restrict__ probs, int64_t ld, float *__restrict__ spartial,
+                   int64_t tokens_per_wave, int n_sink, const float *__restrict__ stat_slots, int n_stat)
+{
+    extern __shared__ __attribute__((aligned(16))) float dyn[];
+    pv_sparse_body<R, SINK, FUSED, SP>(dyn, (int)blockIdx.x, n_kv_heads, n_q_heads, L, v_ptr, vsp, nnz_cap, probs, ld,
+                                       spartial, tokens_per_wave, n_sink, stat_slots, n_stat);
+}
+
+// Short contexts: both as workgroups of one launch, the first n_sparse of them sparse (pv_both).  Neither kernel fills the
+// chip there, and each is mostly its launch and a chain of round trips.
+template <int BITS, int RG, bool FUSED, bool SPAN>
+__global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_both(KVQ_PV_DENSE_PARAMS, int n_sparse, int n_slabs,
+                                                                    const uint32_t *__restrict__ v_ptr,
+                                                                    const KvqSparseFlat vsp, uint32_t nnz_cap,
+                                                                    float *__restrict__ spartial, int64_t tokens_per_wave,
+                                                                    unsigned long long *span)
+{
+    const unsigned long long span_start = SPAN ? kvq_wall_clock() : 0;      // timing-aid instantiation (kvq_profile_*)
+    extern __shared__ __attribute__((aligned(16))) float dyn[];
+    const int b = (int)blockIdx.x - n_sparse;
+    if (b < 0)
+        pv_sparse_body<0, true, FUSED, KvqSparseFlat>(dyn, (int)blockIdx.x, n_kv_heads, n_q_heads, L, v_ptr, vsp, nnz_cap,
+                                                      probs, ld, spartial, tokens_per_wave, n_sink, stat_slots, n_stat);
+    else
+        pv_dense_body<BITS, RG>((uint8_t *)dyn, b % n_slabs, n_slabs, b / n_slabs, KVQ_PV_DENSE_ARGS);
+    if (SPAN) kvq_span_end(span, span_start);
 }
 
 // out[q][c] = sum_slabs partial + sum_slabs zpart + sum_sslabs spartial.  Four workgroups per query
@@ -702,6 +804,34 @@ static kvq_status pv_launch_sparse(const kvq_cache *cache, const SP vsp, int ri,
     return KVQ_OK;
 }
 
+// f(bits, heads per group) as compile-time constants.
+template <class F>
+static auto pv_with(int bits, int rg, F f)
+{
+    auto with_rg = [&](auto b) {
+        if (rg == 8) return f(b, std::integral_constant<int, 8>{});
+        if (rg == 4) return f(b, std::integral_constant<int, 4>{});
+        if (rg == 2) return f(b, std::integral_constant<int, 2>{});
+        return f(b, std::integral_constant<int, 1>{});
+    };
+    if (bits == 2) return with_rg(std::integral_constant<int, 2>{});
+    if (bits == 3) return with_rg(std::integral_constant<int, 3>{});
+    return with_rg(std::integral_constant<int, 4>{});
+}
+
+// Whether the Value half of a call over cache->n_tokens_v tokens is one launch and the reduction.
+static bool pv_one_launch(const kvq_cache *cache, PvBoth &p)
+{
+    const int rg = pv_group(cache->n_tokens_v, cache->n_q_heads, cache->n_q_heads / cache->n_kv_heads);
+    return pv_both(cache, rg, pv_with(cache->bits, rg, [](auto b, auto g) { return (size_t)PvCfg<b.value, g.value>::LDS; }), p);
+}
+
+bool kvq_pv_is_one_launch(const kvq_cache *cache)
+{
+    PvBoth p;
+    return cache->n_tokens_v > 0 && pv_one_launch(cache, p);
+}
+
 kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_probs, float *d_out,
                       const float *stat_slots, int n_stat, hipStream_t s)
 {
@@ -715,12 +845,46 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
     if (!cache->workspace || cache->workspace_bytes < kvq_pv_workspace_bytes(Hq)) return KVQ_ERR_CAPACITY;
     const int r = Hq / cache->n_kv_heads;
     const int rg = pv_group(L, Hq, r);
-    const PvPlan plan = (L > 0) ? pv_plan(L, Hq, rg) : PvPlan{0, 0, 0, 0, 0, 0};
+    PvPlan plan = (L > 0) ? pv_plan(L, Hq, rg) : PvPlan{0, 0, 0, 0, 0, 0};
     float *partial = (float *)cache->workspace;
     float *zpart = partial + (int64_t)512 * Hq * 128;
     float *spartial = zpart + (int64_t)512 * Hq;
     float *lpart = spartial + (int64_t)512 * Hq * 128;
-    if (L > 0) {
+    PvBoth both;
+    const bool merged = L > 0 && pv_one_launch(cache, both);
+    // (the timing aid takes the launch that holds the dense kernel)
+    KvqProfile &prof = kvq_profile_state();
+    unsigned long long *span = nullptr;
+    hipEvent_t *pev = (L > 0 && prof.enabled && prof.use_events) ? prof.ev[1][prof.count[1] % KVQ_PROFILE_RING] : nullptr;
+    if (merged) {
+        plan.slabs = both.slabs;
+        plan.sslabs = both.n_sparse;
+        const unsigned grid = (unsigned)(both.n_sparse + both.slabs * (Hq / rg));
+        span = kvq_profile_span_slot(prof, 1, grid);
+        if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[0], s));
+        KVQ_HIP_CHECK(pv_with(cache->bits, rg, [&](auto b, auto g) {
+            constexpr int BITS = decltype(b)::value, RG = decltype(g)::value;
+            using Kernel = decltype(&kvq_pv_both<BITS, RG, false, false>);
+            static const Kernel kernels[2][2] = {{kvq_pv_both<BITS, RG, false, false>, kvq_pv_both<BITS, RG, false, true>},
+                                                 {kvq_pv_both<BITS, RG, true, false>, kvq_pv_both<BITS, RG, true, true>}};
+            // the dynamic-LDS limits are raised once (initialisation of a function-local static is thread-safe)
+            static const hipError_t lds_attr = [] {
+                for (auto &k : kernels)
+                    for (Kernel kern : k) {
+                        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, PV_BOTH_LDS);
+                        if (e != hipSuccess) return e;
+                    }
+                return hipSuccess;
+            }();
+            if (lds_attr != hipSuccess) return lds_attr;
+            kernels[stat_slots != nullptr][span != nullptr]<<<grid, (PvCfg<BITS, RG>::NT), both.lds, s>>>(
+                cache->params, D, cache->n_kv_heads, Hq, cache->cap_tokens, L, cache->v_codes, cache->v_sz, d_probs, ld_probs,
+                partial, zpart, plan.tiles, cache->n_sink, stat_slots, n_stat, lpart, both.n_sparse, both.slabs, cache->v_ptr,
+                kvq_flat_v(cache), (uint32_t)cache->cap_nnz_v, spartial, both.tokens_per_wave, span);
+            return hipSuccess;
+        }));
+    }
+    if (L > 0 && !merged) {
         const bool sink = cache->n_sink > 0;
         const int ri = (r == 1) ? 1 : (r == 2) ? 2 : (r == 4) ? 3 : (r == 8) ? 4 : 0;
         const bool fused = stat_slots != nullptr;
@@ -746,18 +910,16 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
         else if (rg == 2) LAUNCH_PV(B, 2);                                                                     \
         else LAUNCH_PV(B, 1);                                                                                  \
     } while (0)
-        KvqProfile &prof = kvq_profile_state();
-        unsigned long long *span = kvq_profile_span_slot(prof, 1, (int64_t)grid.x * grid.y);
-        hipEvent_t *pev = (prof.enabled && prof.use_events) ? prof.ev[1][prof.count[1] % KVQ_PROFILE_RING] : nullptr;
+        span = kvq_profile_span_slot(prof, 1, (int64_t)grid.x * grid.y);
         if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[0], s));
         if (cache->bits == 2) LAUNCH_PV_B(2);
         else if (cache->bits == 3) LAUNCH_PV_B(3);
         else LAUNCH_PV_B(4);
 #undef LAUNCH_PV_B
 #undef LAUNCH_PV
-        if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[1], s));
-        if (prof.enabled) ++prof.count[1];
     }
+    if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[1], s));
+    if (L > 0 && prof.enabled) ++prof.count[1];
     const int ns = (int)(cache->n_sink < L ? cache->n_sink : L);
     kvq_pv_reduce<<<4 * Hq, 1024, 0, s>>>(Hq, plan.slabs, plan.sslabs, partial, zpart, spartial, d_out, ns,
                                           cache->n_kv_heads, cache->sink_v, d_probs, ld_probs, stat_slots, n_stat, lpart);

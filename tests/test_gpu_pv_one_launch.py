@@ -1,0 +1,79 @@
+"""The sparse and dense Value kernels as one launch, at the edges of its rule and of its plan: against the oracle, and
+against the two launches (which blocked storage takes)."""
+import numpy as np
+import pytest
+
+import kvq_synth as S
+from kvq_testlib import Setup, fill_both, matvec_close
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bits,kv,hq,L,sink,p,full", [
+    (3, 1, 1, 2048, 0, 0.01, False),        # the shortest context that takes it
+    (2, 8, 8, 2049, 0, 0.01, False),        # a last tile and a last run with one token
+    (4, 2, 4, 4095, 3, 0.01, False),        # sink tokens, two heads per group at most
+    (3, 1, 8, 9001, 0, 0.01, False),        # eight heads on one
+    (4, 1, 6, 2500, 1, 0.01, False),        # a ratio that is not a power of two
+    (2, 8, 64, 2100, 0, 0.01, False),       # 64 query heads
+    (3, 5, 40, 2777, 0, 0.02, False),       # a head count that leaves compute units over
+    (4, 2, 2, 3000, 0, 0.0, False),         # no outliers
+    (3, 2, 4, 3000, 0, 0.02, True),         # outlier arrays that run full: tokens with fewer outliers, then none
+])
+def test_one_launch_against_oracle_and_two_launches(bits, kv, hq, L, sink, p, full):
+    import torch
+    import paper_2401_18079_amd as K
+    from oracle import kvq_oracle as O
+    wl = S.workload("c2", n_kv_heads=kv, n_q_heads=hq, bits=bits, outlier_fraction=p)
+    st = Setup(wl)
+    cap = (L + 1 + 127) // 128 * 128
+    k_side = st.k_side if p else 0
+    nnz = st.cap_nnz_k(cap)
+    nnz_v = max(1024, 2 * k_side * L)
+    if full:
+        nnz_v = nnz_v // 2 // 1024 * 1024                                # half the tokens, the last of them in part
+    oc = O.OracleCache(bits, kv, hq, cap, k_side, wl.rope_base, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi,
+                       cap_nnz_k=nnz, n_sink=sink)
+    gc, bc = (K.KvqCache(bits, kv, hq, cap, k_side, wl.rope_base, nnz, nnz_v, n_sink=sink, nnz_block_entries=be)
+              for be in (None, 1024))
+    for c in (gc, bc):
+        K.kvq_lut_load(c, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
+        fill_both(st, None if full or c is bc else oc, c, L, [1024])     # (the oracle has no full arrays)
+    assert (gc.status() != 0) == full and (bc.status() != 0) == full
+    w = np.random.default_rng(L + bits).random((hq, L)).astype(np.float32) / L
+    q = torch.from_numpy(S.gen_q(wl, 0, 0)).cuda()
+    got, fused, two, two_fused = (torch.full((hq, 128), 7.0, device="cuda") for _ in range(4))
+    scores = torch.zeros((hq, cap), device="cuda")
+
+    for c, plain, attended in ((gc, got, fused), (bc, two, two_fused)):
+        K.kvq_pv_matvec(c, torch.from_numpy(w).cuda(), plain)
+        if hq // kv in (1, 2, 4, 8):                                     # (the ratios that the Key half takes)
+            K.kvq_attention_decode(c, q, 1.0 / np.sqrt(128.0), scores, attended)
+    if not full:
+        ok, worst = matvec_close(got.cpu().numpy(), oc.pv(w), rel=1e-4)
+        assert ok, f"against the oracle: worst error / bound = {worst:.3f}"
+    for a, b in ((got, two), (fused, two_fused)):                        # the same terms summed in another order
+        ok, worst = matvec_close(a.cpu().numpy(), b.cpu().numpy(), rel=2e-5)
+        assert ok, f"against two launches: worst error / bound = {worst:.3f}"
+
+
+def test_contexts_outside_the_rule_keep_two_launches():
+    import paper_2401_18079_amd as K
+    cache = lambda kv, hq, cap, **kw: K.KvqCache(2, kv, hq, cap, 1, 10000.0, 4096, **kw)
+
+    def launches(c, n):
+        c.c.n_tokens_k = c.c.n_tokens_v = n
+        return K.kvq_decode_step_launches(c)
+
+    c = cache(1, 1, 600064)
+    K.kvq_lut_load(c, *[np.linspace(-1, 1, 4, dtype=np.float32)] * 2, *[np.full(128, v, np.float16) for v in (1, 0, -1, 1)])
+    assert [launches(c, n) for n in (0, 2046, 2047, 600000)] == [6, 6, 5, 5]
+    c = cache(32, 32, 1 << 16)               # more sparse work than the launch saves
+    K.kvq_lut_load(c, *[np.linspace(-1, 1, 4, dtype=np.float32)] * 2, *[np.full(4096, v, np.float16) for v in (1, 0, -1, 1)])
+    c.c.k_side_v = 20
+    assert [launches(c, n) for n in (2046, 2047, 60000)] == [6, 5, 5]
+    c.c.k_side_v = 2000
+    assert launches(c, 60000) == 6
+    c = cache(1, 1, 4096, nnz_block_entries=1024)
+    K.kvq_lut_load(c, *[np.linspace(-1, 1, 4, dtype=np.float32)] * 2, *[np.full(128, v, np.float16) for v in (1, 0, -1, 1)])
+    assert launches(c, 3000) == 6
