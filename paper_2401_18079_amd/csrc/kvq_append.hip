@@ -98,13 +98,10 @@ __device__ inline uint32_t block_rank(bool flag, uint32_t *wave_tot, uint32_t &t
 // Number of Key outliers of each new token (threshold test only).  One wavefront per token, eight
 // channels per lane and pass (16-byte loads of the fp16 vector, D is a multiple of 128): no barriers.
 constexpr int KVQ_COUNT_NT = 256;
-__global__ __launch_bounds__(KVQ_COUNT_NT) void kvq_k_count(const void *params, int D, int T, const uint16_t *k_new,
-                                                            uint32_t *cnt)
+__device__ __forceinline__ void k_count_token(const void *params, int D, const uint16_t *k_new, uint32_t *cnt, const int t)
 {
     KvqParamsView pv = kvq_params_view(params, D);
     const int lane = threadIdx.x & 63;
-    const int t = blockIdx.x * (KVQ_COUNT_NT / 64) + (threadIdx.x >> 6);
-    if (t >= T) return;
     const uint4 *row = (const uint4 *)(k_new + (int64_t)t * D);
     const float4 *lo4 = (const float4 *)pv.lo, *hi4 = (const float4 *)pv.hi;
     uint32_t mine = 0;
@@ -127,6 +124,12 @@ __global__ __launch_bounds__(KVQ_COUNT_NT) void kvq_k_count(const void *params, 
     }
     for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
     if (lane == 0) cnt[t] = mine;
+}
+__global__ __launch_bounds__(KVQ_COUNT_NT) void kvq_k_count(const void *params, int D, int T, const uint16_t *k_new,
+                                                            uint32_t *cnt)
+{
+    const int t = blockIdx.x * (KVQ_COUNT_NT / 64) + (threadIdx.x >> 6);
+    if (t < T) k_count_token(params, D, k_new, cnt, t);
 }
 
 // ptr[n0+1+t] = min(ptr[n0] + cnt[0] + ... + cnt[t], cap_nnz); one workgroup, T <= 4096.
@@ -1188,16 +1191,28 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
     if (overflow) atomicExch(d_status, (int32_t)KVQ_ERR_NNZ_OVERFLOW);
 }
 
+// In bulk a Value kernel's first `wgs` workgroups count the Key outliers of the same tokens (a wavefront per token):
+// reading the Keys and the thresholds, latency that the Values' arithmetic covers.  wgs = 0: Values only.
+struct KeyCount {
+    int wgs;
+    const uint16_t *k_new;
+    uint32_t *cnt;
+};
 template <int BITS, int JW, int W, int TOK, class SP>
 __global__ __launch_bounds__(64 * W * TOK) void kvq_v_quant4(const void *__restrict__ params, int D, int64_t cap,
                                                           int64_t n0, int T, int k_side,
                                                           const uint16_t *__restrict__ v_new,
                                                           uint8_t *__restrict__ v_codes, uint16_t *__restrict__ v_sz,
                                                           uint32_t *__restrict__ v_ptr, const SP vsp, int64_t cap_nnz,
-                                                          int32_t *d_status)
+                                                          int32_t *d_status, const KeyCount keys)
 {
+    if (TOK == 2 && (int)blockIdx.x < keys.wgs) {
+        const int t = (int)blockIdx.x * (W * TOK) + (int)(threadIdx.x >> 6);
+        if (t < T) k_count_token(params, D, keys.k_new, keys.cnt, t);
+        return;
+    }
     v_quant_token4<BITS, JW, W, TOK>(params, D, cap, n0, k_side, v_new, v_codes, v_sz, v_ptr, vsp, cap_nnz, d_status,
-                                     (int)blockIdx.x, T);
+                                     (int)blockIdx.x - (TOK == 2 ? keys.wgs : 0), T);
 }
 
 // HW = 0: the body for any number of heads.
@@ -1411,7 +1426,8 @@ static kvq_status append_checks(const kvq_cache *cache, const void *src, int32_t
     return KVQ_OK;
 }
 
-extern "C" kvq_status kvq_quantize_append_k(kvq_cache *cache, const uint16_t *d_k_new, int32_t T, void *stream)
+// counted: the tokens' outliers have been counted into the workspace on this stream already.
+static kvq_status append_k(kvq_cache *cache, const uint16_t *d_k_new, int32_t T, void *stream, bool counted)
 {
     kvq_status st = append_checks(cache, d_k_new, T, cache ? cache->n_tokens_k : 0);
     if (st != KVQ_OK) return st;
@@ -1421,7 +1437,8 @@ extern "C" kvq_status kvq_quantize_append_k(kvq_cache *cache, const uint16_t *d_
     if (!single) {
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
         uint32_t *cnt = (uint32_t *)cache->workspace;
-        kvq_k_count<<<(T + KVQ_COUNT_NT / 64 - 1) / (KVQ_COUNT_NT / 64), KVQ_COUNT_NT, 0, s>>>(cache->params, D, T, d_k_new, cnt);
+        if (!counted)
+            kvq_k_count<<<(T + KVQ_COUNT_NT / 64 - 1) / (KVQ_COUNT_NT / 64), KVQ_COUNT_NT, 0, s>>>(cache->params, D, T, d_k_new, cnt);
         kvq_ptr_scan<<<1, 1024, 0, s>>>(cache->k_ptr, cache->n_tokens_k, T, cnt, cache->cap_nnz_k, cache->d_status);
     }
 #define LAUNCH_KW(B, HW, W)                                                                                     \
@@ -1465,7 +1482,14 @@ extern "C" kvq_status kvq_quantize_append_k(kvq_cache *cache, const uint16_t *d_
     return KVQ_OK;
 }
 
-extern "C" kvq_status kvq_quantize_append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T, void *stream)
+extern "C" kvq_status kvq_quantize_append_k(kvq_cache *cache, const uint16_t *d_k_new, int32_t T, void *stream)
+{
+    return append_k(cache, d_k_new, T, stream, false);
+}
+
+// k_new: null, or the Keys of the same tokens, whose outliers are to be counted into the workspace by the same launch where
+// its kernel does that (*counted).
+static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T, void *stream, const uint16_t *k_new, bool *counted)
 {
     kvq_status st = append_checks(cache, d_v_new, T, cache ? cache->n_tokens_v : 0);
     if (st != KVQ_OK) return st;
@@ -1475,10 +1499,14 @@ extern "C" kvq_status kvq_quantize_append_v(kvq_cache *cache, const uint16_t *d_
     hipStream_t s = (hipStream_t)stream;
     const size_t dyn = 3 * (size_t)D;
 #define LAUNCH_V4W(B, J, WV, TOK, GRID)                                                                        \
-    kvq_v_quant4<B, J, WV, TOK><<<GRID, 64 * (WV) * (TOK), 0, s>>>(                                            \
+    kvq_v_quant4<B, J, WV, TOK><<<(GRID) + keys.wgs, 64 * (WV) * (TOK), 0, s>>>(                               \
         cache->params, D, cache->cap_tokens, cache->n_tokens_v, T, cache->k_side_v, d_v_new, cache->v_codes,   \
-        cache->v_sz, cache->v_ptr, vsp, cache->cap_nnz_v, cache->d_status)
+        cache->v_sz, cache->v_ptr, vsp, cache->cap_nnz_v, cache->d_status, keys)
     const int small = T < KVQ_VW_SMALL_TOKENS ? small_width(D) : 0;
+    const bool in_pairs = !small && (D == 4096 || D == 2048 || D == 1024 || (T >= KVQ_BULK_TOKENS && (D == 5120 || D == 6656 || D == 8192)));
+    KeyCount keys = {0, nullptr, nullptr};
+    if (counted) *counted = k_new != nullptr && in_pairs;
+    if (k_new && in_pairs) keys = {(T + 2 * KVQ_VW_WAVES - 1) / (2 * KVQ_VW_WAVES), k_new, (uint32_t *)cache->workspace};
     // a workgroup per pair of tokens (the two that share dwords), the first and the last perhaps with one token
     const unsigned pairs = (unsigned)(((cache->n_tokens_v + T - 1) >> 1) - (cache->n_tokens_v >> 1) + 1);
 #define LAUNCH_V4(B, J) LAUNCH_V4W(B, J, KVQ_VW_WAVES, 2, pairs)
@@ -1526,6 +1554,11 @@ extern "C" kvq_status kvq_quantize_append_v(kvq_cache *cache, const uint16_t *d_
     return KVQ_OK;
 }
 
+extern "C" kvq_status kvq_quantize_append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T, void *stream)
+{
+    return append_v(cache, d_v_new, T, stream, nullptr, nullptr);
+}
+
 extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d_k_new, const uint16_t *d_v_new,
                                              int32_t T, void *stream)
 {
@@ -1542,9 +1575,11 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
         // (From 129 tokens on, two workgroups of 1024 threads per token are more than the compute units hold at once.)
         // Every check of both calls has passed above.
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
-        st = kvq_quantize_append_k(cache, d_k_new, T, stream);
+        // Values first: their kernel counts the Keys' outliers on the way (see KeyCount).
+        bool counted = false;
+        st = append_v(cache, d_v_new, T, stream, d_k_new, &counted);
         if (st != KVQ_OK) return st;
-        return kvq_quantize_append_v(cache, d_v_new, T, stream);
+        return append_k(cache, d_k_new, T, stream, counted);
     }
     hipStream_t s = (hipStream_t)stream;
     const int single = (T == 1);
