@@ -136,8 +136,8 @@ __global__ __launch_bounds__(KVQ_COUNT_NT) void kvq_k_count(const void *params, 
 __global__ __launch_bounds__(1024) void kvq_ptr_scan(uint32_t *ptr, int64_t n0, int T, const uint32_t *cnt,
                                                      int64_t cap_nnz, int32_t *d_status)
 {
-    __shared__ uint32_t part[1024];
-    const int tid = threadIdx.x;
+    __shared__ uint32_t part[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t v[4], s = 0;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -145,15 +145,18 @@ __global__ __launch_bounds__(1024) void kvq_ptr_scan(uint32_t *ptr, int64_t n0, 
         v[j] = (t < T) ? cnt[t] : 0u;
         s += v[j];
     }
-    part[tid] = s;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        uint32_t add = (tid >= o) ? part[tid - o] : 0u;
-        __syncthreads();
-        part[tid] += add;
-        __syncthreads();
+    const uint64_t first = ptr[n0];
+    // sums over the wavefront's lanes up to this one, then over the wavefronts before: one barrier
+    uint32_t sum = s;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t add = __shfl_up(sum, o);
+        sum += lane >= o ? add : 0u;
     }
-    uint64_t run = (uint64_t)ptr[n0] + (part[tid] - s);
+    if (lane == 63) part[wave] = sum;
+    __syncthreads();
+    uint64_t run = first + (sum - s);
+#pragma unroll
+    for (int w = 0; w < 16; ++w) run += w < wave ? part[w] : 0u;
     bool over = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

@@ -7,7 +7,8 @@
 // gather of the fp16 pair (lut[a], lut[b]) from a layer-wide table gives two consecutive elements of a
 // matrix-core operand; the weights w = p*s, split in three fp16 parts, are the other operand (kvq_pv_dense).
 // The zero-point term sum_n p z_n is a per-head scalar.  Sparse outliers are handled by a balanced kernel
-// (lanes = outlier entries, fixed-point LDS accumulators); all partial results, and the fp16 rows of
+// (lanes = outlier entries, fixed-point LDS accumulators), in one launch with the dense one where neither fills the chip
+// (kvq_pv_both); all partial results, and the fp16 rows of
 // attention-sink tokens (paper Sec. 3.5) if any, are summed in a fixed order by a final small kernel.
 #include "kvq_common.hpp"
 #include <math.h>
@@ -115,7 +116,7 @@ inline bool pv_both(const kvq_cache *c, int rg, size_t dense_lds, PvBoth &p)
 {
     const int Hq = c->n_q_heads, r = Hq / c->n_kv_heads;
     const int64_t L = c->n_tokens_v;
-    if (c->nnz_block_shift || c->cap_nnz_v >= ((int64_t)1 << 31) || L < 2048) return false;
+    if (c->cap_nnz_v >= ((int64_t)1 << 31) || L < 2048) return false;
     const int waves = rg == 8 ? 8 : 16, cus = kvq_cu_count(), groups = Hq / rg;
     const size_t sparse_lds = (size_t)Hq * (1024 + 8) + (size_t)waves * pvs_wave_lds_floats(Hq) * 4;
     p.lds = sparse_lds > dense_lds ? sparse_lds : dense_lds;
@@ -648,10 +649,10 @@ void kvq_pv_sparse(int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__r
 
 // Short contexts: both as workgroups of one launch, the first n_sparse of them sparse (pv_both).  Neither kernel fills the
 // chip there, and each is mostly its launch and a chain of round trips.
-template <int BITS, int RG, bool FUSED, bool SPAN>
+template <int BITS, int RG, bool FUSED, bool SPAN, class SP>
 __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_both(KVQ_PV_DENSE_PARAMS, int n_sparse, int n_slabs,
                                                                     const uint32_t *__restrict__ v_ptr,
-                                                                    const KvqSparseFlat vsp, uint32_t nnz_cap,
+                                                                    const SP vsp, uint32_t nnz_cap,
                                                                     float *__restrict__ spartial, int64_t tokens_per_wave,
                                                                     unsigned long long *span)
 {
@@ -659,7 +660,7 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_both(KVQ_PV_DENS
     extern __shared__ __attribute__((aligned(16))) float dyn[];
     const int b = (int)blockIdx.x - n_sparse;
     if (b < 0)
-        pv_sparse_body<0, true, FUSED, KvqSparseFlat>(dyn, (int)blockIdx.x, n_kv_heads, n_q_heads, L, v_ptr, vsp, nnz_cap,
+        pv_sparse_body<0, true, FUSED, SP>(dyn, (int)blockIdx.x, n_kv_heads, n_q_heads, L, v_ptr, vsp, nnz_cap,
                                                       probs, ld, spartial, tokens_per_wave, n_sink, stat_slots, n_stat);
     else
         pv_dense_body<BITS, RG>((uint8_t *)dyn, b % n_slabs, n_slabs, b / n_slabs, KVQ_PV_DENSE_ARGS);
@@ -862,27 +863,31 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
         const unsigned grid = (unsigned)(both.n_sparse + both.slabs * (Hq / rg));
         span = kvq_profile_span_slot(prof, 1, grid);
         if (pev) KVQ_HIP_CHECK(hipEventRecord(pev[0], s));
-        KVQ_HIP_CHECK(pv_with(cache->bits, rg, [&](auto b, auto g) {
-            constexpr int BITS = decltype(b)::value, RG = decltype(g)::value;
-            using Kernel = decltype(&kvq_pv_both<BITS, RG, false, false>);
-            static const Kernel kernels[2][2] = {{kvq_pv_both<BITS, RG, false, false>, kvq_pv_both<BITS, RG, false, true>},
-                                                 {kvq_pv_both<BITS, RG, true, false>, kvq_pv_both<BITS, RG, true, true>}};
-            // the dynamic-LDS limits are raised once (initialisation of a function-local static is thread-safe)
-            static const hipError_t lds_attr = [] {
-                for (auto &k : kernels)
-                    for (Kernel kern : k) {
-                        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, PV_BOTH_LDS);
-                        if (e != hipSuccess) return e;
-                    }
+        const auto launch = [&](const auto vsp) {
+            using SP = std::remove_cv_t<decltype(vsp)>;
+            return pv_with(cache->bits, rg, [&](auto b, auto g) {
+                constexpr int BITS = decltype(b)::value, RG = decltype(g)::value;
+                using Kernel = decltype(&kvq_pv_both<BITS, RG, false, false, SP>);
+                static const Kernel kernels[2][2] = {{kvq_pv_both<BITS, RG, false, false, SP>, kvq_pv_both<BITS, RG, false, true, SP>},
+                                                     {kvq_pv_both<BITS, RG, true, false, SP>, kvq_pv_both<BITS, RG, true, true, SP>}};
+                // the dynamic-LDS limits are raised once (initialisation of a function-local static is thread-safe)
+                static const hipError_t lds_attr = [] {
+                    for (auto &k : kernels)
+                        for (Kernel kern : k) {
+                            const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, PV_BOTH_LDS);
+                            if (e != hipSuccess) return e;
+                        }
+                    return hipSuccess;
+                }();
+                if (lds_attr != hipSuccess) return lds_attr;
+                kernels[stat_slots != nullptr][span != nullptr]<<<grid, (PvCfg<BITS, RG>::NT), both.lds, s>>>(
+                    cache->params, D, cache->n_kv_heads, Hq, cache->cap_tokens, L, cache->v_codes, cache->v_sz, d_probs, ld_probs,
+                    partial, zpart, plan.tiles, cache->n_sink, stat_slots, n_stat, lpart, both.n_sparse, both.slabs, cache->v_ptr,
+                    vsp, (uint32_t)cache->cap_nnz_v, spartial, both.tokens_per_wave, span);
                 return hipSuccess;
-            }();
-            if (lds_attr != hipSuccess) return lds_attr;
-            kernels[stat_slots != nullptr][span != nullptr]<<<grid, (PvCfg<BITS, RG>::NT), both.lds, s>>>(
-                cache->params, D, cache->n_kv_heads, Hq, cache->cap_tokens, L, cache->v_codes, cache->v_sz, d_probs, ld_probs,
-                partial, zpart, plan.tiles, cache->n_sink, stat_slots, n_stat, lpart, both.n_sparse, both.slabs, cache->v_ptr,
-                kvq_flat_v(cache), (uint32_t)cache->cap_nnz_v, spartial, both.tokens_per_wave, span);
-            return hipSuccess;
-        }));
+            });
+        };
+        KVQ_HIP_CHECK(cache->nnz_block_shift ? launch(kvq_blocked_v(cache)) : launch(kvq_flat_v(cache)));
     }
     if (L > 0 && !merged) {
         const bool sink = cache->n_sink > 0;

@@ -1,5 +1,5 @@
-"""The sparse and dense Value kernels as one launch, at the edges of its rule and of its plan: against the oracle, and
-against the two launches (which blocked storage takes)."""
+"""The sparse and dense Value kernels as one launch, at the edges of its rule and of its plan, against the oracle and
+with either storage of the outliers."""
 import numpy as np
 import pytest
 
@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
     (4, 2, 2, 3000, 0, 0.0, False),         # no outliers
     (3, 2, 4, 3000, 0, 0.02, True),         # outlier arrays that run full: tokens with fewer outliers, then none
 ])
-def test_one_launch_against_oracle_and_two_launches(bits, kv, hq, L, sink, p, full):
+def test_one_launch_against_the_oracle(bits, kv, hq, L, sink, p, full):
     import torch
     import paper_2401_18079_amd as K
     from oracle import kvq_oracle as O
@@ -38,26 +38,30 @@ def test_one_launch_against_oracle_and_two_launches(bits, kv, hq, L, sink, p, fu
               for be in (None, 1024))
     for c in (gc, bc):
         K.kvq_lut_load(c, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
-        fill_both(st, None if full or c is bc else oc, c, L, [1024])     # (the oracle has no full arrays)
+        fill_both(st, oc if c is gc else None, c, L, [1024])
     assert (gc.status() != 0) == full and (bc.status() != 0) == full
+    if full:                                                             # (the oracle's have room for all: hand it these)
+        oc.v_ptr[:L + 1] = gc.v_ptr.cpu().numpy().view(np.uint32)[:L + 1]
     w = np.random.default_rng(L + bits).random((hq, L)).astype(np.float32) / L
     q = torch.from_numpy(S.gen_q(wl, 0, 0)).cuda()
-    got, fused, two, two_fused = (torch.full((hq, 128), 7.0, device="cuda") for _ in range(4))
+    scale = 1.0 / np.sqrt(128.0)
     scores = torch.zeros((hq, cap), device="cuda")
-
-    for c, plain, attended in ((gc, got, fused), (bc, two, two_fused)):
-        K.kvq_pv_matvec(c, torch.from_numpy(w).cuda(), plain)
+    outs = []
+    for c in (gc, bc):
+        out, attended = (torch.full((hq, 128), 7.0, device="cuda") for _ in range(2))
+        K.kvq_pv_matvec(c, torch.from_numpy(w).cuda(), out)
+        ok, worst = matvec_close(out.cpu().numpy(), oc.pv(w), rel=1e-4)
+        assert ok, f"worst error / bound = {worst:.3f}"
         if hq // kv in (1, 2, 4, 8):                                     # (the ratios that the Key half takes)
-            K.kvq_attention_decode(c, q, 1.0 / np.sqrt(128.0), scores, attended)
-    if not full:
-        ok, worst = matvec_close(got.cpu().numpy(), oc.pv(w), rel=1e-4)
-        assert ok, f"against the oracle: worst error / bound = {worst:.3f}"
-    for a, b in ((got, two), (fused, two_fused)):                        # the same terms summed in another order
-        ok, worst = matvec_close(a.cpu().numpy(), b.cpu().numpy(), rel=2e-5)
-        assert ok, f"against two launches: worst error / bound = {worst:.3f}"
+            K.kvq_attention_decode(c, q, scale, scores, attended)
+            # (twice the mat-vec tolerance: a score error delta multiplies a weight by e^delta)
+            ok, worst = matvec_close(attended.cpu().numpy(), oc.pv(O.softmax(scores[:, :L].cpu().numpy())), rel=2e-3)
+            assert ok, f"attention: worst error / bound = {worst:.3f}"
+        outs.append(out)
+    assert torch.equal(*outs)                                            # the same terms in the same order
 
 
-def test_contexts_outside_the_rule_keep_two_launches():
+def test_contexts_on_either_side_of_the_rule():
     import paper_2401_18079_amd as K
     cache = lambda kv, hq, cap, **kw: K.KvqCache(2, kv, hq, cap, 1, 10000.0, 4096, **kw)
 
@@ -76,4 +80,4 @@ def test_contexts_outside_the_rule_keep_two_launches():
     assert launches(c, 60000) == 6
     c = cache(1, 1, 4096, nnz_block_entries=1024)
     K.kvq_lut_load(c, *[np.linspace(-1, 1, 4, dtype=np.float32)] * 2, *[np.full(128, v, np.float16) for v in (1, 0, -1, 1)])
-    assert launches(c, 3000) == 6
+    assert launches(c, 3000) == 5
