@@ -81,7 +81,9 @@ __device__ __forceinline__ uint32_t field_shifted(const uint32_t (&Wg)[8], int i
 
 // 2- and 4-bit codes: nibble NIB of a dword, times 16, in one instruction that takes its byte out of the source as it
 // reads it (SDWA; a shift and a mask otherwise).  The tables of these widths therefore have entries 16 bytes apart,
-// with those of a neighbour in between: the two codes of a pair (4 bits) or two pairs (2 bits).
+// with those of a neighbour in between: the two codes of a pair (4 bits) or two pairs (2 bits).  us per launch before and
+// after: 4-bit codes, 32 heads, a million tokens 611 / 576 (two 8-byte gathers per pair and head bind it now), 2-bit codes, 32 heads
+// on 8, 524288 tokens 126 / 121.
 template <int NIB>
 __device__ __forceinline__ uint32_t nibble_x16(uint32_t w)
 {
@@ -483,9 +485,9 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
 // four heads, reloaded from LDS every 16 pairs.  One instruction then does what
 // four multiply-adds per element did, 2 RQ instructions and RQ gathers per pair.  Arithmetic, precision and
 // order of the sums over channels are those of an fp32 chain.
-// Lanes, tiles, piece streaming, grid and results as in kvq_qk_kernel.  Bound by VALU issue (7.5 instructions and
-// two matrix instructions per token, pair and KV head at four KV heads a workgroup; VALU busy 70 % of the
-// kernel, the matrix cores 26 %).  Times beside qk_grouped.
+// Lanes, tiles, piece streaming, grid and results as in kvq_qk_kernel.  Bound by VALU issue (7.5 instructions, 6.5
+// with 2-bit codes, and two matrix instructions per token, pair and KV head at four KV heads a workgroup; on 2-bit codes VALU
+// busy 65 % of the kernel, the matrix cores 26 %).  Times beside qk_grouped.
 typedef float float4_t __attribute__((ext_vector_type(4)));
 
 // 4-byte slot of entry f (16 of channel i, then 16 of channel i + 64) of table t = 64 * KV head + pair, 4-bit codes: entries
@@ -1134,7 +1136,7 @@ __global__ __launch_bounds__(64) void kvq_qk_sink(const void *__restrict__ param
 }
 
 // Which kernel takes `r` query heads per KV head: the grouped one from four heads on, and for two where the codes
-// have more than two bits.  Measured (us, (A,B) tables against grouped): 32 heads on 16, 100000 tokens: 2 bits 44
+// have more than two bits.  Measured (us, (A,B) tables against grouped, both before nibble_x16): 32 heads on 16, 100000 tokens: 2 bits 44
 // against 59, 3 bits 87 / 69, 4 bits 79 / 73; 32 on 8: 524288 tokens, 2 bits 168 / 137, 131072, 3 bits 88 / 47, 33001,
 // 4 bits 38 / 25, 4000, 4 bits 15.7 / 10.7; 32 on 4, 194971 tokens, 4 bits 121 / 54.  (Two heads use half the rows
 // of a matrix instruction, and 2-bit (A,B) tables of two heads are cheap to gather from.)
