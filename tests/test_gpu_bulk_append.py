@@ -132,3 +132,38 @@ def test_key_appends_above_64_heads(heads, T, bits):
     assert np.array_equal(oc.k_ptr[:T + 1], gc.k_ptr.cpu().numpy().view(np.uint32)[:T + 1])
     assert np.array_equal(oc.k_idx[:n], gc.k_idx.cpu().numpy().view(np.uint16)[:n])
     assert np.array_equal(oc.k_val[:n], gc.k_val.cpu().numpy().view(np.uint16)[:n])
+
+
+@pytest.mark.parametrize("heads,bits,lead,T,shift,blocked", [
+    (8, 3, 0, 256, 0, False),             # the smallest call that counts Key outliers in the Value kernel: whole workgroups
+    (8, 2, 1, 257, 1, False),             # one token in the last one, a lone Value token first, unaligned input
+    (16, 4, 3, 263, 0, True),             # one token short of whole, blocked storage
+    (40, 4, 2, 512, 0, False), (40, 4, 2, 511, 0, False),       # on either side of where this width does so
+    (24, 3, 0, 300, 0, False),            # a width that never does
+])
+def test_combined_bulk_append_counts_in_the_value_kernel(heads, bits, lead, T, shift, blocked):
+    import torch
+    import paper_2401_18079_amd as K
+    wl = S.workload("c2", n_kv_heads=heads, n_q_heads=heads, bits=bits)
+    st = Setup(wl)
+    cap = 640
+    oc = st.oracle_cache(cap)
+    gc = K.KvqCache(bits, heads, heads, cap, st.k_side, wl.rope_base, st.cap_nnz_k(cap),
+                    nnz_block_entries=1024 if blocked else None)
+    K.kvq_lut_load(gc, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
+
+    def dev(x):
+        buf = torch.zeros(x.size + shift, dtype=torch.float16, device="cuda")
+        view = buf[shift:].view(x.shape)
+        view.copy_(torch.from_numpy(x))
+        return view
+
+    for t0, n in ((0, lead), (lead, T)):
+        if n:
+            k, v = st.k(t0, n), st.v(t0, n)
+            oc.append_k(k); oc.append_v(v)
+            K.kvq_quantize_append_kv(gc, dev(k), dev(v))
+    torch.cuda.synchronize()
+    assert gc.status() == 0
+    bad = compare_caches(oc, gc)
+    assert not bad, bad
