@@ -219,6 +219,8 @@ kvq_status kvq_qk_matvec(const kvq_cache *cache, const float *d_q_rot, float sca
  * |sum over a workgroup's tokens of probs[q][n] * residual(n, c)| must stay below 2^23 for every
  * (q, c); with softmax weights (sum <= 1) and fp16 residuals (|r| <= 65504) it always does, with
  * arbitrary caller-made weights it is the caller's to ensure (no error is raised; the sum wraps).
+ * (Where the sparse and dense kernels share a launch the workgroups hold more tokens; their sums then
+ * have a fractional bit less and twice the range for every doubling.)
  */
 kvq_status kvq_pv_matvec(const kvq_cache *cache, const float *d_probs, int64_t ld_probs,
                          float *d_out, void *stream);
@@ -237,6 +239,8 @@ kvq_status kvq_pv_matvec(const kvq_cache *cache, const float *d_probs, int64_t l
  *   d_scores : DEVICE fp32 [n_q_heads][ld_scores] scratch, ld_scores >= n_tokens_k; on return it
  *              holds the raw scores (not the probabilities); entries n >= n_tokens_k untouched.
  *   d_out    : DEVICE fp32 [n_q_heads][128]; all zero when the cache is empty.
+ * Range: any finite fp16 residuals, in every token if need be (the weights here are 1 at most, and the
+ * point of the sparse sums is placed by the tokens that a workgroup sums).
  * Uses cache->workspace (kvq_workspace_bytes covers it).  Errors as for the two mat-vecs.
  */
 kvq_status kvq_attention_decode(const kvq_cache *cache, const float *d_q_rot, float scale,

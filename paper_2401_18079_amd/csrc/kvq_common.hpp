@@ -149,6 +149,18 @@ __device__ __forceinline__ float kvq_from_fixed_fast(unsigned long long v)
     const float hi = (float)(int)(uint32_t)(v >> 32), lo = (float)(uint32_t)v;
     return __builtin_fmaf(lo, 1.0f / 4294967296.0f, hi) * (1.0f / (float)(1 << SH));
 }
+// The same for sums whose fraction the caller chooses by a power of two in `y`: y * 2^32 as a whole part and a signed
+// fraction, rounded to the nearest for either sign, for |y| < 2^31.  One instruction more than kvq_to_fixed, which
+// rounds small negative values to 2^-24.  kvq_pv_matvec's sparse sums, relative error against 64 bits before and after:
+// 32 heads, 131072 tokens, normal residuals, softmax weights 3.4e-7 / 1.2e-7; 32 on 8, 262144 tokens 6.2e-7 / 1.3e-7;
+// the calls' times within 1 % (2-bit, 32 on 8, 524287 tokens 87 / 87 us; 3-bit, 64 on 32, 100000 tokens 59.5 / 59.8).
+__device__ __forceinline__ unsigned long long kvq_to_fixed_nearest(float y)
+{
+    const float whole = __builtin_rintf(y), frac = (y - whole) * 4294967296.0f;        // exact
+    int lo;
+    asm("v_cvt_rpi_i32_f32 %0, %1" : "=v"(lo) : "v"(frac));                           // floor(frac + 0.5); 2^31 saturates
+    return ((unsigned long long)(uint32_t)((int)whole + (lo >> 31)) << 32) | (uint32_t)lo;
+}
 template <int SH>
 __device__ __forceinline__ void kvq_lds_add_fixed(unsigned long long *cell, float x)
 {

@@ -96,6 +96,17 @@ inline PvPlan pv_plan(int64_t L, int n_q_heads, int rg)
     return p;
 }
 
+// Bits before the point (without the sign) of the sparse sums of a workgroup of `tokens` tokens, 64-bit words.  The fused
+// call's weights are 1 at most: enough for the largest fp16 residual (65504, and a margin for weights whose exponent is
+// rounded) in every token.  A caller's own weights: 23 in a launch of its own, of `own` tokens a workgroup; as much per
+// token in a larger workgroup.
+inline int pv_whole_bits(int64_t tokens, int64_t own, bool fused)
+{
+    int bits = 23;
+    while ((fused ? tokens * 66000 >> bits : tokens > own << (bits - 23)) && bits < 62) ++bits;
+    return bits;
+}
+
 // Plan of the one launch for both kernels.  The compute units are dealt out so that either kind takes as long, and the
 // launch is taken where it is then estimated to end sooner than two.  Work in us per 131072 tokens on the whole chip:
 // sparse 2 (pointers), 0.12 per query head (scores staged) and 0.08 + 0.11 per query head of the KV head for an outlier;
@@ -492,12 +503,13 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(KVQ_PV_DEN
 template <int R, bool SINK, bool FUSED, class SP>
 __device__ __forceinline__ void pv_sparse_body(float *dyn, const int bx, int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__restrict__ v_ptr,
                    const SP vsp, uint32_t nnz_cap,
-                   const float *__restrict__ probs, int64_t ld, float *__restrict__ spartial, int64_t tokens_per_wave,
+                   const float *__restrict__ probs, int64_t ld, float *__restrict__ spartial, int64_t tokens_per_wave, int whole_bits,
                    int n_sink, const float *__restrict__ stat_slots, int n_stat)
 {
+    // whole_bits: 23 and as many more as the sums of a workgroup need (pv_whole_bits)
     // FUSED: `probs` holds raw scores x; the workgroup takes every head's maximum m over its n_stat
     // slots once and scores become weights exp(x - m) on their way into the wavefront's LDS slice
-    unsigned long long *sacc = (unsigned long long *)dyn;     // [n_q_heads][128] 2^40-scaled sums
+    unsigned long long *sacc = (unsigned long long *)dyn;     // [n_q_heads][128] sums with 63 - whole_bits fractional bits
     float *sst = (float *)(sacc + n_q_heads * 128);           // [n_q_heads] log2(e) * maximum score (2 floats per head reserved)
     const int tid = threadIdx.x, lane = tid & 63, n_waves = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);           // scalar: loop bounds below are uniform
@@ -577,7 +589,7 @@ __device__ __forceinline__ void pv_sparse_body(float *dyn, const int bx, int n_k
                     const float e = kvq_stat_weight(w, sst[qh]);
                     w = (t < tc && (!SINK || t >= t_sink)) ? e : 0.f;
                 }
-                ps[qh * PVS_ROW + t] = w;
+                ps[qh * PVS_ROW + t] = __builtin_ldexpf(w, 31 - whole_bits);
             }
         }
         for (int j0 = 64 * 8; j0 < n_cells; j0 += 64) {      // models with more than 32 query heads
@@ -586,7 +598,7 @@ __device__ __forceinline__ void pv_sparse_body(float *dyn, const int bx, int n_k
                 const bool ok = t < tc && (!SINK || t >= t_sink);
                 float w = ok ? probs[(int64_t)qh * ld + nc + t] : 0.f;
                 if (FUSED && ok) w = kvq_stat_weight(w, sst[qh]);
-                ps[qh * PVS_ROW + t] = w;
+                ps[qh * PVS_ROW + t] = __builtin_ldexpf(w, 31 - whole_bits);
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -618,7 +630,7 @@ __device__ __forceinline__ void pv_sparse_body(float *dyn, const int bx, int n_k
                     const uint32_t kvh = ch >> 7, c = ch & 127u;
                     for (int j = 0; j < r; ++j) {
                         const uint32_t qh = kvh * r + j;
-                        kvq_lds_add_fixed<8>(&sacc[(R == 1) ? ch : qh * 128u + c], ps[qh * PVS_ROW + t] * v);
+                        atomicAdd(&sacc[(R == 1) ? ch : qh * 128u + c], kvq_to_fixed_nearest(ps[qh * PVS_ROW + t] * v));
                     }
                 }
             }
@@ -633,18 +645,18 @@ __device__ __forceinline__ void pv_sparse_body(float *dyn, const int bx, int n_k
     if (!cleared) __syncthreads();       // a wavefront without tokens still meets the workgroup's barrier
     __syncthreads();
     for (int j = tid; j < n_q_heads * 128; j += blockDim.x)
-        spartial[(int64_t)bx * n_q_heads * 128 + j] = kvq_from_fixed<8>(sacc[j]);
+        spartial[(int64_t)bx * n_q_heads * 128 + j] = __builtin_ldexpf(kvq_from_fixed<0>(sacc[j]), whole_bits - 31);
 }
 
 template <int R, bool SINK, bool FUSED, class SP>
 __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(6, 6)))
 void kvq_pv_sparse(int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__restrict__ v_ptr, const SP vsp,
                    uint32_t nnz_cap, const float *__restrict__ probs, int64_t ld, float *__restrict__ spartial,
-                   int64_t tokens_per_wave, int n_sink, const float *__restrict__ stat_slots, int n_stat)
+                   int64_t tokens_per_wave, int whole_bits, int n_sink, const float *__restrict__ stat_slots, int n_stat)
 {
     extern __shared__ __attribute__((aligned(16))) float dyn[];
     pv_sparse_body<R, SINK, FUSED, SP>(dyn, (int)blockIdx.x, n_kv_heads, n_q_heads, L, v_ptr, vsp, nnz_cap, probs, ld,
-                                       spartial, tokens_per_wave, n_sink, stat_slots, n_stat);
+                                       spartial, tokens_per_wave, whole_bits, n_sink, stat_slots, n_stat);
 }
 
 // Short contexts: both as workgroups of one launch, the first n_sparse of them sparse (pv_both).  Neither kernel fills the
@@ -653,7 +665,7 @@ template <int BITS, int RG, bool FUSED, bool SPAN, class SP>
 __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_both(KVQ_PV_DENSE_PARAMS, int n_sparse, int n_slabs,
                                                                     const uint32_t *__restrict__ v_ptr,
                                                                     const SP vsp, uint32_t nnz_cap,
-                                                                    float *__restrict__ spartial, int64_t tokens_per_wave,
+                                                                    float *__restrict__ spartial, int64_t tokens_per_wave, int whole_bits,
                                                                     unsigned long long *span)
 {
     const unsigned long long span_start = SPAN ? kvq_wall_clock() : 0;      // timing-aid instantiation (kvq_profile_*)
@@ -661,7 +673,7 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_both(KVQ_PV_DENS
     const int b = (int)blockIdx.x - n_sparse;
     if (b < 0)
         pv_sparse_body<0, true, FUSED, SP>(dyn, (int)blockIdx.x, n_kv_heads, n_q_heads, L, v_ptr, vsp, nnz_cap,
-                                                      probs, ld, spartial, tokens_per_wave, n_sink, stat_slots, n_stat);
+                                                      probs, ld, spartial, tokens_per_wave, whole_bits, n_sink, stat_slots, n_stat);
     else
         pv_dense_body<BITS, RG>((uint8_t *)dyn, b % n_slabs, n_slabs, b / n_slabs, KVQ_PV_DENSE_ARGS);
     if (SPAN) kvq_span_end(span, span_start);
@@ -798,10 +810,11 @@ static kvq_status pv_launch_sparse(const kvq_cache *cache, const SP vsp, int ri,
     // (Running this kernel on a second stream beside the dense one was tried: its LDS footprint
     // evicts dense workgroups from the CUs and the pair gets slower.)
     if (cache->cap_nnz_v >= ((int64_t)1 << 31)) return KVQ_ERR_UNSUPPORTED;      // byte offsets are 32-bit
+    const int64_t tokens = plan.tokens_per_swave * plan.swaves;
     sparse<<<plan.sslabs, 64 * plan.swaves, plan.slds, s>>>(cache->n_kv_heads, cache->n_q_heads, cache->n_tokens_v,
                                                             cache->v_ptr, vsp, (uint32_t)cache->cap_nnz_v, d_probs,
                                                             ld_probs, spartial, plan.tokens_per_swave,
-                                                            cache->n_sink, stat_slots, n_stat);
+                                                            pv_whole_bits(tokens, tokens, fused), cache->n_sink, stat_slots, n_stat);
     return KVQ_OK;
 }
 
@@ -858,6 +871,8 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
     unsigned long long *span = nullptr;
     hipEvent_t *pev = (L > 0 && prof.enabled && prof.use_events) ? prof.ev[1][prof.count[1] % KVQ_PROFILE_RING] : nullptr;
     if (merged) {
+        const int whole_bits = pv_whole_bits(both.tokens_per_wave * (rg == 8 ? 8 : 16), plan.tokens_per_swave * plan.swaves,
+                                             stat_slots != nullptr);
         plan.slabs = both.slabs;
         plan.sslabs = both.n_sparse;
         const unsigned grid = (unsigned)(both.n_sparse + both.slabs * (Hq / rg));
@@ -883,7 +898,7 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
                 kernels[stat_slots != nullptr][span != nullptr]<<<grid, (PvCfg<BITS, RG>::NT), both.lds, s>>>(
                     cache->params, D, cache->n_kv_heads, Hq, cache->cap_tokens, L, cache->v_codes, cache->v_sz, d_probs, ld_probs,
                     partial, zpart, plan.tiles, cache->n_sink, stat_slots, n_stat, lpart, both.n_sparse, both.slabs, cache->v_ptr,
-                    vsp, (uint32_t)cache->cap_nnz_v, spartial, both.tokens_per_wave, span);
+                    vsp, (uint32_t)cache->cap_nnz_v, spartial, both.tokens_per_wave, whole_bits, span);
                 return hipSuccess;
             });
         };
