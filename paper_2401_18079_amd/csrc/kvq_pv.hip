@@ -21,12 +21,18 @@ constexpr int PV_CHAIN = 16;               // tiles whose products one accumulat
 constexpr size_t PV_BOTH_LDS = 160 * 1024; // most LDS of a workgroup
 constexpr int PV_MIN_TILES = 8;            // tiles a workgroup should at least have: half of its wavefronts busy
 
+// The sparse kernel's wavefronts take consecutive runs of `units` times `unit` tokens (8 or 16), the first `longer` of them
+// one unit more.
+struct PvsRuns {
+    int unit, units, longer;
+};
+
 struct PvPlan {
     int slabs;              // workgroups per head group of the dense kernel (tiles are split evenly among them)
     int tiles;              // tiles of PV_TILE tokens
     int sslabs;             // workgroups of the sparse kernel
     int swaves;             // its wavefronts per workgroup
-    int64_t tokens_per_swave;
+    int64_t tokens_per_swave;   // a multiple of 8
     size_t slds;            // its dynamic LDS bytes
 };
 
@@ -107,20 +113,30 @@ inline int pv_whole_bits(int64_t tokens, int64_t own, bool fused)
     return bits;
 }
 
-// Plan of the one launch for both kernels.  The compute units are dealt out so that either kind takes as long, and the
-// launch is taken where it is then estimated to end sooner than two.  Work in us per 131072 tokens on the whole chip:
-// sparse 2 (pointers), 0.12 per query head (scores staged) and 0.08 + 0.11 per query head of the KV head for an outlier;
-// dense, per head group, 1.0, 1.4 or 1.6 (2, 3, 4 bits) and 0.2 more for every head of a group beyond the first, of which
-// 4-bit codes need 1.5 of the compute units (the rest is HBM).  Sparse wavefronts have 16 (eight-head groups: 8) beside them on a compute
-// unit here and up to 24 in their own kernel: 1.22 (2.0) times the work.  Two launches cost 8 us more: one launch and the
-// first and last round trips of a kernel.  From 2048 tokens on (shorter contexts keep the launches that
-// kvq_decode_step_launches has always stated for them).  kvq_attention_decode, us, two launches / one: 3-bit, 32 heads,
-// 2048 tokens 30.1 / 25.5, 16383 42.8 / 40.0, 65536 84.9 / 78.8, 115000 123 / 127, 131071 130 / 127, 150000 151 / 155; 4-bit 32767
-// 71.3 / 61.2; 32 on 8, 2-bit 131000 93 / 87, 262144 138 / 133, 4-bit 33001 62.3 / 52; 64 on 8, 3-bit, 100000 164 / 131; 32 on 4,
-// 4-bit, 60000 67.9 / 59.3, 131000 96.5 / 100.3; 40 heads, 3-bit, 90000 120 / 125; one head, 4095 24.8 / 20.4, 100000 31.9 / 26.7.
+// Plan of the one launch for both kernels.  The compute units are dealt out so that either kind takes as long, by its work in
+// us per 131072 tokens on the whole chip: sparse 2 (pointers), 0.12 per query head (scores staged) and 0.08 + 0.11 per query
+// head of the KV head for an outlier, times 1.22 (eight-head groups: 2) because its wavefronts have 16 (8) beside them on a
+// compute unit here and up to 24 in their own kernel; dense, per head group, 1.0, 1.4 or 1.5 (2, 3, 4 bits) and 0.2 more for
+// every head of a group beyond the first.  Sparse runs differ by one unit at most, so that the time has no steps along L:
+// with every run rounded up to the longest, 131073 tokens of 32 heads took 6 % more sparse time than 131072.
+//
+// One launch is taken where it is estimated to end sooner than two, by work of the same form with the constants that separate
+// some 3500 measured shapes best (1 to 40 KV heads, 1 to 8 query heads each, 2 to 4 bits, 0.1 and 1 % outliers, 2048 to 524288 tokens:
+// kvq_pv_matvec and kvq_attention_decode with either form forced); a second launch and the first and last round trips of a
+// kernel cost 8.82 us.  40 of the shapes are more than 2 % slower in the form taken (8.5 % at most, mostly 16 KV heads with 0.1 %
+// outliers), where runs rounded up and constants from sixty shapes left 101 (15 %).  Both sides grow with L in proportion, so a shape
+// has one context from which on there are two launches.
+// kvq_attention_decode, us, two launches / one: 3-bit, 32 heads, 2048 tokens 28.3 / 24.2, 16383 43.2 / 37.3, 65536 86.1 / 82.1, 82500 102.1 /
+// 103.1, 110000 127.0 / 125.6, 131072 137.3 / 135.7 (in a step 132.8 / 129.0), 150000 (the last) 159.6 / 162.8; 4-bit 32768 70.3 / 61.0; 32 on 8, 2-bit
+// 131100 102.3 / 96.3, 262144 136.8 / 135.4, 524288 (two) 241.9 / 246.1; 64 on 8, 3-bit, 98500 163 / 133, 524288 529 / 475; 32 on 4, 4-bit, 57000 66.4 / 58.4,
+// 262144 (two) 136 / 149; 40 heads, 3-bit, 90000 (two) 126.5 / 131.5; one head, 4096 26.3 / 18.7, 524288 55.7 / 50.2.
+//
+// Below 2048 tokens two launches would be the slower ones too (32 heads, 300 tokens 26.2 / 23.3, 1600 27.0 / 24.0; one head 21.6 / 18.2, 22.3 /
+// 18.8): they stay because kvq_decode_step_launches states five or six launches there, and its results are part of the interface.
 struct PvBoth {
     int n_sparse, slabs;               // sparse workgroups (of the dense one's width), dense ones per head group
-    int64_t tokens_per_wave;           // of the sparse ones
+    PvsRuns runs;                      // of the sparse ones
+    int64_t most_tokens;               // of one of these workgroups
     size_t lds;
 };
 inline bool pv_both(const kvq_cache *c, int rg, size_t dense_lds, PvBoth &p)
@@ -132,34 +148,40 @@ inline bool pv_both(const kvq_cache *c, int rg, size_t dense_lds, PvBoth &p)
     const size_t sparse_lds = (size_t)Hq * (1024 + 8) + (size_t)waves * pvs_wave_lds_floats(Hq) * 4;
     p.lds = sparse_lds > dense_lds ? sparse_lds : dense_lds;
     if (p.lds > PV_BOTH_LDS) return false;
-    const double sparse = 2.0 + 0.12 * Hq + 2.0 * c->k_side_v * (0.08 + 0.11 * r), sparse_here = sparse * (rg == 8 ? 2.0 : 1.22);
-    const double more = 0.2 * (rg - 1), dense = groups * ((c->bits == 2 ? 1.0 : c->bits == 3 ? 1.4 : 1.6) + more);
-    const double dense_here = groups * ((c->bits == 2 ? 1.0 : c->bits == 3 ? 1.4 : 1.5) + more);
+    const double sparse = (2.0 + 0.12 * Hq + 2.0 * c->k_side_v * (0.08 + 0.11 * r)) * (rg == 8 ? 2.0 : 1.22);
+    const double dense = groups * ((c->bits == 2 ? 1.0 : c->bits == 3 ? 1.4 : 1.5) + 0.2 * (rg - 1));
     auto slowest = [&](int slabs) {                        // of the two kinds
         const int left = cus - slabs * groups;
-        const double d = dense_here * cus / (slabs * groups), s = left < 1 ? 1e30 : sparse_here * cus / left;
+        const double d = dense * cus / (slabs * groups), s = left < 1 ? 1e30 : sparse * cus / left;
         return s > d ? s : d;
     };
-    int slabs = (int)(cus * dense_here / ((dense_here + sparse_here) * groups));
+    int slabs = (int)(cus * dense / ((dense + sparse) * groups));
     slabs = slabs < 1 ? 1 : slabs;
     if (slowest(slabs + 1) < slowest(slabs)) ++slabs;
     const int left = cus - slabs * groups;
     if (left < 1) return false;
     const int64_t wavefronts = (int64_t)left * waves;
-    p.tokens_per_wave = ((L + wavefronts - 1) / wavefronts + 7) & ~(int64_t)7;
-    p.n_sparse = (int)((L + p.tokens_per_wave * waves - 1) / (p.tokens_per_wave * waves));
+    // (whole sub-ranges, so that the scores of one start on 64 bytes; half ones where that leaves wavefronts without)
+    const int unit = L > 64 * wavefronts ? PVS_TW : PVS_TW / 2;
+    const int64_t units = (L + unit - 1) / unit;
+    p.n_sparse = (int)(units < wavefronts ? (units + waves - 1) / waves : left);
+    const int64_t runs = (int64_t)p.n_sparse * waves;
+    p.runs = {unit, (int)(units / runs), (int)(units % runs)};
+    p.most_tokens = (int64_t)unit * waves * (p.runs.units + (p.runs.longer > 0));
     const int64_t few = ((L + PV_TILE - 1) / PV_TILE + PV_MIN_TILES - 1) / PV_MIN_TILES;
     p.slabs = slabs > few ? (int)few : slabs;
     if (p.n_sparse > PVS_MAX_SLABS || p.slabs > 512) return false;
     const PvPlan two = pv_plan(L, Hq, rg);
     const int own = two.swaves * (int)(PV_BOTH_LDS / two.slds);         // sparse wavefronts on a compute unit in their own kernel
-    const double x = (double)L / 131072.0, fill = (double)p.tokens_per_wave * (double)wavefronts / (double)L;
-    const double s_one = sparse_here * cus / left * fill, d_one = dense_here * cus / (slabs * groups);
-    const double s_two = own < 24 ? sparse * sqrt(24.0 / own) : sparse;
+    const double x = (double)L / 131072.0;
+    const double sw = 1.76 + 0.0642 * Hq + 2.0 * c->k_side_v * (0.0307 + 0.167 * r);
+    const double dw = groups * ((c->bits == 2 ? 1.17 : c->bits == 3 ? 1.79 : 1.21) + 0.186 * (rg - 1));
+    const double s_one = sw * (rg == 8 ? 1.32 : 1.19) * cus / left, d_one = dw * cus / (slabs * groups);
+    const double s_two = own < 24 ? sw * sqrt(24.0 / own) : sw;
     const int64_t per_group = cus / groups;
-    const double d_two = per_group > 0 ? dense * cus / (double)(per_group * groups) : dense;
+    const double d_two = per_group > 0 ? dw * cus / (double)(per_group * groups) : dw;
     // (eight tokens per wavefront at least: short contexts leave compute units over, and the estimate is beside the point)
-    return p.tokens_per_wave == 8 || (s_one > d_one ? s_one : d_one) * x <= (s_two + d_two) * x + 8.0;
+    return units <= wavefronts || (s_one > d_one ? s_one : d_one) * x <= (s_two + d_two) * x + 8.82;
 }
 
 template <int FBITS>
@@ -503,7 +525,7 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_dense(KVQ_PV_DEN
 template <int R, bool SINK, bool FUSED, class SP>
 __device__ __forceinline__ void pv_sparse_body(float *dyn, const int bx, int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__restrict__ v_ptr,
                    const SP vsp, uint32_t nnz_cap,
-                   const float *__restrict__ probs, int64_t ld, float *__restrict__ spartial, int64_t tokens_per_wave, int whole_bits,
+                   const float *__restrict__ probs, int64_t ld, float *__restrict__ spartial, PvsRuns runs, int whole_bits,
                    int n_sink, const float *__restrict__ stat_slots, int n_stat)
 {
     // whole_bits: 23 and as many more as the sums of a workgroup need (pv_whole_bits)
@@ -517,8 +539,9 @@ __device__ __forceinline__ void pv_sparse_body(float *dyn, const int bx, int n_k
     const int r = R ? R : n_q_heads / n_kv_heads;
     for (int j = tid; j < n_q_heads * 128; j += blockDim.x) sacc[j] = 0ull;
     bool cleared = false;      // the barrier after the clearing comes once the first loads are requested
-    const int64_t nb = ((int64_t)bx * n_waves + wave) * tokens_per_wave;
-    int64_t ne = nb + tokens_per_wave;
+    const int run_no = bx * n_waves + wave;
+    const int64_t nb = runs.unit * ((int64_t)run_no * runs.units + (run_no < runs.longer ? run_no : runs.longer));
+    int64_t ne = nb + runs.unit * (runs.units + (run_no < runs.longer ? 1 : 0));
     if (ne > L) ne = L;
     const int n_cells = n_q_heads * PVS_TW;
     // the run is cut into equal sub-ranges of at most PVS_TW tokens; the pointers of the next one are
@@ -652,11 +675,11 @@ template <int R, bool SINK, bool FUSED, class SP>
 __global__ __launch_bounds__(768) __attribute__((amdgpu_waves_per_eu(6, 6)))
 void kvq_pv_sparse(int n_kv_heads, int n_q_heads, int64_t L, const uint32_t *__restrict__ v_ptr, const SP vsp,
                    uint32_t nnz_cap, const float *__restrict__ probs, int64_t ld, float *__restrict__ spartial,
-                   int64_t tokens_per_wave, int whole_bits, int n_sink, const float *__restrict__ stat_slots, int n_stat)
+                   PvsRuns runs, int whole_bits, int n_sink, const float *__restrict__ stat_slots, int n_stat)
 {
     extern __shared__ __attribute__((aligned(16))) float dyn[];
     pv_sparse_body<R, SINK, FUSED, SP>(dyn, (int)blockIdx.x, n_kv_heads, n_q_heads, L, v_ptr, vsp, nnz_cap, probs, ld,
-                                       spartial, tokens_per_wave, whole_bits, n_sink, stat_slots, n_stat);
+                                       spartial, runs, whole_bits, n_sink, stat_slots, n_stat);
 }
 
 // Short contexts: both as workgroups of one launch, the first n_sparse of them sparse (pv_both).  Neither kernel fills the
@@ -665,7 +688,7 @@ template <int BITS, int RG, bool FUSED, bool SPAN, class SP>
 __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_both(KVQ_PV_DENSE_PARAMS, int n_sparse, int n_slabs,
                                                                     const uint32_t *__restrict__ v_ptr,
                                                                     const SP vsp, uint32_t nnz_cap,
-                                                                    float *__restrict__ spartial, int64_t tokens_per_wave, int whole_bits,
+                                                                    float *__restrict__ spartial, PvsRuns runs, int whole_bits,
                                                                     unsigned long long *span)
 {
     const unsigned long long span_start = SPAN ? kvq_wall_clock() : 0;      // timing-aid instantiation (kvq_profile_*)
@@ -673,7 +696,7 @@ __global__ __launch_bounds__((PvCfg<BITS, RG>::NT)) void kvq_pv_both(KVQ_PV_DENS
     const int b = (int)blockIdx.x - n_sparse;
     if (b < 0)
         pv_sparse_body<0, true, FUSED, SP>(dyn, (int)blockIdx.x, n_kv_heads, n_q_heads, L, v_ptr, vsp, nnz_cap,
-                                                      probs, ld, spartial, tokens_per_wave, whole_bits, n_sink, stat_slots, n_stat);
+                                                      probs, ld, spartial, runs, whole_bits, n_sink, stat_slots, n_stat);
     else
         pv_dense_body<BITS, RG>((uint8_t *)dyn, b % n_slabs, n_slabs, b / n_slabs, KVQ_PV_DENSE_ARGS);
     if (SPAN) kvq_span_end(span, span_start);
@@ -813,7 +836,7 @@ static kvq_status pv_launch_sparse(const kvq_cache *cache, const SP vsp, int ri,
     const int64_t tokens = plan.tokens_per_swave * plan.swaves;
     sparse<<<plan.sslabs, 64 * plan.swaves, plan.slds, s>>>(cache->n_kv_heads, cache->n_q_heads, cache->n_tokens_v,
                                                             cache->v_ptr, vsp, (uint32_t)cache->cap_nnz_v, d_probs,
-                                                            ld_probs, spartial, plan.tokens_per_swave,
+                                                            ld_probs, spartial, PvsRuns{8, (int)(plan.tokens_per_swave / 8), 0},
                                                             pv_whole_bits(tokens, tokens, fused), cache->n_sink, stat_slots, n_stat);
     return KVQ_OK;
 }
@@ -871,7 +894,7 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
     unsigned long long *span = nullptr;
     hipEvent_t *pev = (L > 0 && prof.enabled && prof.use_events) ? prof.ev[1][prof.count[1] % KVQ_PROFILE_RING] : nullptr;
     if (merged) {
-        const int whole_bits = pv_whole_bits(both.tokens_per_wave * (rg == 8 ? 8 : 16), plan.tokens_per_swave * plan.swaves,
+        const int whole_bits = pv_whole_bits(both.most_tokens, plan.tokens_per_swave * plan.swaves,
                                              stat_slots != nullptr);
         plan.slabs = both.slabs;
         plan.sslabs = both.n_sparse;
@@ -898,7 +921,7 @@ kvq_status kvq_pv_run(const kvq_cache *cache, const float *d_probs, int64_t ld_p
                 kernels[stat_slots != nullptr][span != nullptr]<<<grid, (PvCfg<BITS, RG>::NT), both.lds, s>>>(
                     cache->params, D, cache->n_kv_heads, Hq, cache->cap_tokens, L, cache->v_codes, cache->v_sz, d_probs, ld_probs,
                     partial, zpart, plan.tiles, cache->n_sink, stat_slots, n_stat, lpart, both.n_sparse, both.slabs, cache->v_ptr,
-                    vsp, (uint32_t)cache->cap_nnz_v, spartial, both.tokens_per_wave, whole_bits, span);
+                    vsp, (uint32_t)cache->cap_nnz_v, spartial, both.runs, whole_bits, span);
                 return hipSuccess;
             });
         };

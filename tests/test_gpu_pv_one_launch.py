@@ -61,6 +61,41 @@ def test_one_launch_against_the_oracle(bits, kv, hq, L, sink, p, full):
     assert torch.equal(*outs)                                            # the same terms in the same order
 
 
+@pytest.mark.parametrize("bits,kv,hq,L,sink,p", [
+    (2, 1, 2, 55001, 0, 0.02),          # several sub-ranges a wavefront, in units of eight tokens
+    (4, 8, 64, 4401, 2, 0.01),          # two heads per group
+    (3, 8, 32, 26003, 0, 0.01),         # likewise, units of eight
+    (3, 8, 64, 12345, 1, 0.01),         # four heads per group
+    (2, 4, 32, 99003, 0, 0.01),         # eight: workgroups of eight wavefronts, units of sixteen
+    (4, 8, 64, 50007, 0, 0.005),
+])
+def test_longer_runs_and_groups_of_heads(bits, kv, hq, L, sink, p):
+    """Plans in which a wavefront walks through several sub-ranges, and those of every head group."""
+    test_one_launch_against_the_oracle(bits, kv, hq, L, sink, p, False)
+
+
+@pytest.mark.parametrize("bits,kv,hq,k_side,longest", [
+    (3, 32, 32, 20, 160000), (4, 40, 40, 26, 120000), (2, 16, 32, 10, 400000), (3, 8, 64, 5, 300000), (2, 4, 32, 3, 400000),
+    (4, 1, 8, 1, 600000),
+])
+def test_one_context_ends_the_one_launch(bits, kv, hq, k_side, longest):
+    """A decoder does not fall back and forth between the two forms as its context grows."""
+    import paper_2401_18079_amd as K
+    c = K.KvqCache(bits, kv, hq, 256, k_side, 10000.0, 1024, 1024)
+    D, lut = kv * 128, np.linspace(-1, 1, 1 << bits, dtype=np.float32)
+    K.kvq_lut_load(c, lut, lut, *[np.full(D, v, np.float16) for v in (1, 0, -1, 1)])
+    c.c.cap_tokens = (longest // 128 + 2) * 128        # (host arithmetic only: the arrays are not touched)
+    at = sorted({n for m in np.geomspace(2047, longest, 300).astype(int) for n in (m - m % 8 - 1, m - m % 8, m)
+                 if 2047 <= n <= longest} | {131071, 131072} & set(range(longest)))
+    seen = []
+    for n in at:
+        c.c.n_tokens_k = c.c.n_tokens_v = int(n)
+        seen.append(K.kvq_decode_step_launches(c))
+    c.c.n_tokens_k = c.c.n_tokens_v = 2000
+    assert seen[0] == K.kvq_decode_step_launches(c) - 1
+    assert sum(a != b for a, b in zip(seen, seen[1:])) <= 1, [n for n, a, b in zip(at[1:], seen, seen[1:]) if a != b]
+
+
 def test_contexts_on_either_side_of_the_rule():
     import paper_2401_18079_amd as K
     cache = lambda kv, hq, cap, **kw: K.KvqCache(2, kv, hq, cap, 1, 10000.0, 4096, **kw)
