@@ -46,16 +46,24 @@
 
 namespace {
 
-template <int BITS>
+// KVH KV heads per workgroup, RQ query heads per KV head.
+template <int BITS, int KVH, int RQ>
 struct QkCfg {
     static constexpr bool JOINT = BITS <= 3;
     static constexpr int NE = 1 << BITS;
     static constexpr int ENTRIES = JOINT ? (1 << (2 * BITS)) : 2 * NE;   // (A,B) entries per (head, pair)
     static constexpr int CW = 4 * BITS;                                  // dwords per chunk
-    // 8-byte slot of entry f of table t = 64 * head + pair (nibble_x16: 2- and 4-bit entries lie 16 bytes apart)
+    // Entries 16 bytes apart, those of a neighbour in between (nibble_x16).  2-bit tables where it is the faster form: with
+    // two query heads one address serves both heads' tables in one gather of two entries, which 16-byte
+    // strides make conflict (4 x 2: 18.8 M of 44.8 M LDS cycles, none of 26.0 M with 8); with one KV head per workgroup the instructions it saves are not what the wavefront waits for, and a
+    // wait state comes with each.  kvq_qk_matvec, us, 8 / 16 bytes apart (KV heads x query heads each): 4 x 2, 16 heads over
+    // 200000 tokens 99.1 / 137.2; 2 x 2, 8 over 131072 35.1 / 44.0; 1 x 2 1.5 % less with 16; 1 x 1, one head over 65536 8.9 / 9.6; 4 x 1, 16 over 32768
+    // 17.0 / 16.7; 8 x 1, 32 over 131072 63.9 / 63.2.
+    static constexpr bool SPREAD = BITS == 4 || (BITS == 2 && (RQ == 1 ? KVH >= 4 : RQ == 2 ? KVH == 1 : true));
+    // 8-byte slot of entry f of table t = 64 * head + pair
     static constexpr __host__ __device__ int slot(int t, int f)
     {
-        return BITS == 2 ? (t >> 1) * 32 + 2 * f + (t & 1) : BITS == 4 ? t * 32 + 2 * (f & (NE - 1)) + f / NE : t * ENTRIES + f;
+        return !SPREAD ? t * ENTRIES + f : BITS == 2 ? (t >> 1) * 32 + 2 * f + (t & 1) : t * 32 + 2 * (f & (NE - 1)) + f / NE;
     }
 };
 
@@ -80,8 +88,8 @@ __device__ __forceinline__ uint32_t field_shifted(const uint32_t (&Wg)[8], int i
 }
 
 // 2- and 4-bit codes: nibble NIB of a dword, times 16, in one instruction that takes its byte out of the source as it
-// reads it (SDWA; a shift and a mask otherwise).  The tables of these widths therefore have entries 16 bytes apart,
-// with those of a neighbour in between: the two codes of a pair (4 bits) or two pairs (2 bits).  us per launch before and
+// reads it (SDWA; a shift and a mask otherwise).  The tables of these widths therefore have entries 16 bytes apart (where
+// that pays: QkCfg), with those of a neighbour in between: the two codes of a pair (4 bits) or two pairs (2 bits).  us per launch before and
 // after: 4-bit codes, 32 heads, a million tokens 611 / 576 (two 8-byte gathers per pair and head bind it now), 2-bit codes, 32 heads
 // on 8, 524288 tokens 126 / 121.
 template <int NIB>
@@ -170,13 +178,13 @@ __device__ __forceinline__ void qk_group(uint32_t (&W)[KVH][8], float (&acc)[KVH
 {
     // nf: this lane's index inside its wavefront (as float); wave_base: lane i holds the reduced angle
     // (in revolutions) of channel pair i at the wavefront's first token
-    using C = QkCfg<BITS>;
+    using C = QkCfg<BITS, KVH, RQ>;
     constexpr int QH = KVH * RQ, R = RQ;
     constexpr int NE = C::NE;
     constexpr int ENT = C::ENTRIES;
     constexpr int NG = C::JOINT ? 1 : 2;          // gathers per (pair, query head)
     float2_t t[PAIR_GROUP][QH][NG];
-    if constexpr (BITS == 3) {
+    if constexpr (!C::SPREAD) {
 #pragma unroll
         for (int p = 0; p < PAIR_GROUP; ++p) {
             const int I = G0 * PAIR_GROUP + p;
@@ -225,7 +233,7 @@ __device__ __forceinline__ void qk_group(uint32_t (&W)[KVH][8], float (&acc)[KVH
         };
         gather(std::integral_constant<int, 0>{});
         if constexpr (PAIR_GROUP == 2) gather(std::integral_constant<int, 1>{});
-        static_assert(BITS == 3 || PAIR_GROUP <= 2, "two pairs a group at most");
+        static_assert(PAIR_GROUP <= 2, "two pairs a group at most");
     }
     float cs[PAIR_GROUP], sn[PAIR_GROUP];
 #pragma unroll
@@ -273,7 +281,7 @@ template <int BITS, int KVH, int RQ, int NT>
 __device__ __forceinline__ void qk_build_tables(float2_t *tab, float *qs, float2_t *szs, const KvqParamsView &pv,
                                                 const float *__restrict__ q_rot, float scale, int q0, int kv0)
 {
-    using C = QkCfg<BITS>;
+    using C = QkCfg<BITS, KVH, RQ>;
     constexpr int QH = KVH * RQ, R = RQ;
     constexpr int NE = C::NE;
     constexpr int ENT = C::ENTRIES;
@@ -331,7 +339,7 @@ __global__ __launch_bounds__(NT) void kvq_qk_kernel(const void *__restrict__ par
     // STATS: the workgroup also leaves the maximum of the scores it wrote (tokens below n_sink
     // excepted: the attention-sink kernel replaces their scores) in slot blockIdx.x of each of its
     // query heads.  A separate instantiation: the running maxima cost a register per head.
-    using C = QkCfg<BITS>;
+    using C = QkCfg<BITS, KVH, RQ>;
     constexpr int QH = KVH * RQ, R = RQ;
     constexpr int NE = C::NE;
     constexpr int ENT = C::ENTRIES;
@@ -508,7 +516,7 @@ __device__ __forceinline__ void qkg_group(std::integer_sequence<int, P...>, uint
                                           const uint8_t *cur_chunk, const uint8_t *next_chunk, int64_t plane, bool valid,
                                           bool next_valid)
 {
-    using C = QkCfg<BITS>;
+    using C = QkCfg<BITS, KVH, RQ>;
     constexpr int SETS = (RQ + 3) / 4, NE = C::NE;
     static_assert(16 % PG == 0, "a group's channels share the query registers");
     if (G0 * PG % 16 == 0) {                       // the queries of the next 16 channels and of those 64 further up
@@ -599,7 +607,7 @@ __global__ __launch_bounds__(NT) void kvq_qkg_kernel(const void *__restrict__ pa
                                                      unsigned long long *span)
 {
     const unsigned long long span_start = SPAN ? kvq_wall_clock() : 0;
-    using C = QkCfg<BITS>;
+    using C = QkCfg<BITS, KVH, RQ>;
     constexpr int QH = KVH * RQ, SETS = (RQ + 3) / 4, NE = C::NE;
     // Key elements of a (KV head, pair): joint entries (k_i, k_{i+64}) of 8 bytes, or NE + NE of 4 bytes
     constexpr int TAB = KVH * 64 * C::ENTRIES * (C::JOINT ? 8 : 4);
