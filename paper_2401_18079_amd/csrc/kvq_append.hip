@@ -1508,8 +1508,14 @@ static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T,
     const int small = T < KVQ_VW_SMALL_TOKENS ? small_width(D) : 0;
     const bool in_pairs = !small && (D == 4096 || D == 2048 || D == 1024 || (T >= KVQ_BULK_TOKENS && (D == 5120 || D == 6656 || D == 8192)));
     KeyCount keys = {0, nullptr, nullptr};
-    if (counted) *counted = k_new != nullptr && in_pairs;
-    if (k_new && in_pairs) keys = {(T + 2 * KVQ_VW_WAVES - 1) / (2 * KVQ_VW_WAVES), k_new, (uint32_t *)cache->workspace};
+    // Counting on the way saves a launch and its latency (time on the way over that with a launch of its own: 32 heads, 3 bits, 256 tokens 0.86 of
+    // the time, 1024 0.88, 2047 0.93, 4096 0.99-1.00; 40 heads, 2048 0.97), but not from 2048 tokens of 2048 or 4096 channels on with
+    // blocked outlier storage, whose Value kernel has no vector time to spare: 32 heads, 2 bits, 2048 tokens 1.06, 2600 1.03, 4096 1.00;
+    // 3 bits 1.05, 1.00, 1.00; 16 heads, 2 bits, 2300 1.01, 3000 1.06, 4096 1.03 (40 heads 1.02, 0.98, 0.98; flat storage 1.00, 0.98, 1.00).
+    const bool busy = cache->nnz_block_shift && T >= 2048 && (D == 2048 || D == 4096);
+    const bool count = k_new != nullptr && in_pairs && !busy;
+    if (counted) *counted = count;
+    if (count) keys = {(T + 2 * KVQ_VW_WAVES - 1) / (2 * KVQ_VW_WAVES), k_new, (uint32_t *)cache->workspace};
     // a workgroup per pair of tokens (the two that share dwords), the first and the last perhaps with one token
     const unsigned pairs = (unsigned)(((cache->n_tokens_v + T - 1) >> 1) - (cache->n_tokens_v >> 1) + 1);
 #define LAUNCH_V4(B, J) LAUNCH_V4W(B, J, KVQ_VW_WAVES, 2, pairs)

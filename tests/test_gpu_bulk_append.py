@@ -167,3 +167,26 @@ def test_combined_bulk_append_counts_in_the_value_kernel(heads, bits, lead, T, s
     assert gc.status() == 0
     bad = compare_caches(oc, gc)
     assert not bad, bad
+
+
+@pytest.mark.parametrize("heads,bits,lead,T", [
+    (16, 2, 1, 2047), (16, 3, 0, 2048), (32, 4, 1, 2049),      # on either side of where blocked storage counts by itself
+    (8, 2, 3, 2048),                                           # a width that counts on the way at any length
+])
+def test_combined_bulk_append_into_blocked_storage(heads, bits, lead, T):
+    import torch
+    import paper_2401_18079_amd as K
+    wl = S.workload("c2", n_kv_heads=heads, n_q_heads=heads, bits=bits)
+    st = Setup(wl)
+    cap = 2176
+    oc = st.oracle_cache(cap)
+    gc = K.KvqCache(bits, heads, heads, cap, st.k_side, wl.rope_base, st.cap_nnz_k(cap), nnz_block_entries=1 << 14)
+    K.kvq_lut_load(gc, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
+    for t0, n in ((0, lead), (lead, T)):
+        if n:
+            k, v = st.k(t0, n), st.v(t0, n)
+            oc.append_k(k); oc.append_v(v)
+            K.kvq_quantize_append_kv(gc, torch.from_numpy(k).cuda(), torch.from_numpy(v).cuda())
+    assert gc.status() == 0
+    bad = compare_caches(oc, gc)
+    assert not bad, bad
