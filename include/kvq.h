@@ -325,7 +325,9 @@ kvq_status kvq_softmax_f32(const float *d_x, int64_t ld_x, float *d_probs, int64
  * strictly inside, each rounded to fp16: the four arrays kvq_lut_load takes.  fraction = 0: thresholds
  * -65504 / +65504 and the full range.
  *   d_k_cal : DEVICE fp16 [T][D], pre-RoPE.  1 <= T <= 32768, 2k < T.
- *   d_s, d_z, d_lo, d_hi : DEVICE fp16 bit patterns [D] (copy them to the host for kvq_lut_load).
+ *   d_s, d_z, d_lo, d_hi : fp16 bit patterns [D] each, in any memory that the GPU can write: DEVICE, or
+ *       page-locked HOST memory.  Every element is stored once and none is read, so that host arrays
+ *       hold the results for kvq_lut_load as soon as the stream has been waited for.
  * Asynchronous on `stream`.  Errors: INVALID_ARG, UNSUPPORTED (T), HIP.
  */
 kvq_status kvq_calibrate_key_channels(const uint16_t *d_k_cal, int32_t T, int32_t D, float outlier_fraction,
