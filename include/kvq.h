@@ -377,7 +377,8 @@ kvq_status kvq_event_destroy(void *event);
 
 /*
  * Per-kernel timing aid for benchmarks, for the dense kernel of kvq_qk_matvec / kvq_pv_matvec /
- * kvq_attention_decode (`which`: 0 = QK dense kernel, 1 = PV dense kernel).  Two measurements, each
+ * kvq_attention_decode (`which`: 0 = QK dense kernel, 1 = PV dense kernel, or the launch that holds it
+ * and the sparse one where they share one).  Two measurements, each
  * kept per call in a ring of 256, so that many calls can be timed back to back without waiting for
  * the GPU in between:
  *   events : a pair of HIP events recorded on the launch stream around the launch.  The interval runs

@@ -1356,7 +1356,7 @@ __device__ __forceinline__ void qk_sparse_new_token(const StepFrontArgs &a)
 }
 
 // ROOMY: sixteen wavefronts per compute unit instead of 32, for contexts that do not fill more (the append roles are then
-// the launch's length: 16 us with their registers spilled at 2048 tokens of 4096 channels, 10.4 us without).
+// the launch's length: 16 us with their registers spilled at 2048 tokens of 4096 channels with 4-bit codes, 10.4 us without).
 // W: wavefronts on the Value token (D = 256 W channels: 16 or 4).  One instantiation per width: the
 // Value routine's static LDS arrays of several widths would add up and cost the sparse role a workgroup
 // per compute unit.
@@ -1683,9 +1683,12 @@ template <int BITS, int R>
 static kvq_status step_front_launch_br(kvq_cache *cache, StepFrontArgs &a, hipStream_t s, bool *done, bool dry)
 {
     // 4096 channels: up to twelve tokens per wavefront of one workgroup per compute unit, the launch with the registers
-    // that the append roles want.  us per step with it / with two workgroups per unit, whose append roles spill: 32
-    // heads, 4 bits, 1000 tokens 34.8 / 40.0, 8000 42.9 / 48.9, 16383 50.1 / 56.0, 32767 73.8 / 79.0; 3 bits, 50000 tokens
-    // 79.3 / 79.5, 131071 149 / 144.  (1024 channels spill nothing: 8 heads, 4 bits, 16000 tokens 32.6 / 30.7.)
+    // that the append roles of 4-bit codes want: with two workgroups per unit they spill 44.  us per step with one / two, 32 heads,
+    // 4 bits: 300 tokens 33.6 / 37.8, 8192 36.8 / 41.2, 16384 43.0 / 47.9, 32768 63.9 / 67.0, 48000 89.8 / 91.2, 52000 94.6 / 97.2, 65536 109.4 /
+    // 105.3.  2- and 3-bit codes spill nothing in either; one workgroup per unit then has half as many runs to start and end, which
+    // gains 1 to 3 % up to 24000 tokens and 1 % or less either way from there: 2 bits, 8192 tokens 31.8 / 32.4, 24000 43.5 / 44.8, 32768 49.6 /
+    // 49.2, 48000 64.1 / 63.7, 65536 78.4 / 73.5; 3 bits, 8192 31.7 / 32.4, 24000 48.1 / 49.5, 32768 54.5 / 54.1, 48000 71.6 / 71.8, 65536 87.4 / 81.9.
+    // (1024 channels spill nothing: 8 heads, 4 bits, 16000 tokens 32.6 / 30.7.)
     if (a.D == 4096)
         return a.n <= 12 * 16 * (int64_t)kvq_cu_count() ? step_front_launch_brw<BITS, R, 16, true>(cache, a, s, done, dry)
                                                         : step_front_launch_brw<BITS, R, 16, false>(cache, a, s, done, dry);

@@ -138,3 +138,39 @@ def test_step_with_full_outlier_arrays_reports_overflow_like_the_two_calls():
     assert a.status() == 4 and b.status() == 4
     assert torch.equal(a.k_ptr, b.k_ptr) and int(a.k_ptr[L0 + 3].item()) == 16 * cap
     assert torch.equal(a.k_idx, b.k_idx) and torch.equal(a.k_val, b.k_val) and torch.equal(a.k_codes, b.k_codes)
+
+
+@pytest.mark.parametrize("bits,hq", [(2, 32), (3, 32), (4, 32)])
+def test_first_launch_on_either_side_of_its_two_forms(bits, hq):
+    """4096 channels: up to twelve tokens per wavefront of one workgroup per compute unit the first launch has registers
+    for its append roles, beyond it two workgroups per compute unit.  A step in the last context of one form and in the
+    first of the other leaves what the append of the same token leaves, and scores and outputs of the two calls."""
+    import torch
+    import paper_2401_18079_amd as K
+    wl = S.workload("c2", n_kv_heads=32, n_q_heads=hq, bits=bits)
+    st = Setup(wl)
+    edge = 12 * 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    cap = (edge + 2 + 127) // 128 * 128
+    a, b = (K.KvqCache(bits, 32, hq, cap, st.k_side, wl.rope_base, st.cap_nnz_k(cap)) for _ in range(2))
+    k, v = torch.from_numpy(st.k(0, 4096)).cuda(), torch.from_numpy(st.v(0, 4096)).cuda()
+    for c in (a, b):
+        K.kvq_lut_load(c, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
+        for t in range(0, edge, 4096):
+            T = min(4096, edge - t)
+            K.kvq_quantize_append_kv(c, k[-T:], v[:T])
+    sa, sb = (torch.zeros((hq, cap), device="cuda") for _ in range(2))
+    oa, ob = (torch.zeros((hq, 128), device="cuda") for _ in range(2))
+    names = ("k_codes", "v_codes", "v_sz", "k_ptr", "v_ptr", "k_idx", "k_val", "v_idx", "v_val")
+    for i, n in enumerate((edge, edge + 1)):
+        assert a.n_tokens_k == n and K.kvq_decode_step_launches(a) == 4       # append and sparse Key kernel in one, Value kernels in one
+        kd, vd = torch.from_numpy(st.k(5000 + i, 1)).cuda(), torch.from_numpy(st.v(5000 + i, 1)).cuda()
+        q = torch.from_numpy(S.gen_q(wl, 0, 0, step=i)).cuda()
+        K.kvq_decode_step(a, kd, vd, q, SCALE, sa, oa)
+        K.kvq_quantize_append_kv(b, kd, vd)
+        K.kvq_attention_decode(b, q, SCALE, sb, ob)
+        ok, worst = matvec_close(sa.cpu().numpy()[:, :n + 1], sb.cpu().numpy()[:, :n + 1], rel=2e-5)
+        assert ok, f"{n} tokens: scores worst error / bound = {worst:.3f}"
+        ok, worst = matvec_close(oa.cpu().numpy(), ob.cpu().numpy(), rel=2e-5)
+        assert ok, f"{n} tokens: outputs worst error / bound = {worst:.3f}"
+        bad = [x for x in names if not torch.equal(getattr(a, x), getattr(b, x))]
+        assert not bad and a.status() == 0, bad

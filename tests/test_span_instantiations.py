@@ -62,3 +62,20 @@ def test_timed_kernels_are_the_plain_ones():
         assert timed[".vgpr_spill_count"] <= plain[".vgpr_spill_count"] + 2, timed[".name"]
         assert timed[".private_segment_fixed_size"] <= plain[".private_segment_fixed_size"] + 8, timed[".name"]
         assert timed[".vgpr_count"] <= plain[".vgpr_count"] + 4, timed[".name"]
+
+
+def test_timed_shared_launches_are_the_plain_ones():
+    """Likewise the launch that holds the sparse and dense Value kernels (its span flag is not the last argument)."""
+    if not os.path.exists(LIB):
+        pytest.skip("library not built")
+    kernels = _kernels()
+    pairs = []
+    for name, k in kernels.items():
+        m = re.match(r"(.*kvq_pv_bothILi\dELi\dELb[01]E)Lb1E(.*)$", name)
+        if m:
+            pairs.append((k, kernels[m.group(1) + "Lb0E" + m.group(2)]))
+    assert len(pairs) == 48
+    for timed, plain in pairs:
+        assert timed[".vgpr_spill_count"] <= plain[".vgpr_spill_count"] + 2, timed[".name"]
+        assert timed[".private_segment_fixed_size"] <= plain[".private_segment_fixed_size"] + 8, timed[".name"]
+        assert timed[".vgpr_count"] <= plain[".vgpr_count"] + 4, timed[".name"]
