@@ -273,7 +273,7 @@ kvq_status kvq_decode_step(kvq_cache *cache, const uint16_t *d_k_new, const uint
  * the step is the two calls (5 if the thresholds admit no Key outlier: no sparse Key kernel), one more
  * with attention-sink tokens (their score kernel), one less from 2048 tokens up to the context from which
  * on the sparse and dense Value kernels are faster in launches of their own (by heads, code width and
- * outliers: 157000 tokens of 32 heads with 3-bit codes and 1 % outliers, over 500000 of two heads);
+ * outliers: 189000 tokens of 32 heads with 3-bit codes and 1 % outliers, over 500000 of two heads);
  * copies of sink rows not counted.  -1: the descriptor is not usable for a step (the step call says why). */
 int32_t kvq_decode_step_launches(const kvq_cache *cache);
 

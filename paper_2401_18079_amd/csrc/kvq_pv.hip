@@ -123,13 +123,13 @@ inline int pv_whole_bits(int64_t tokens, int64_t own, bool fused)
 // One launch is taken where it is estimated to end sooner than two, by work of the same form with the constants that separate
 // some 3500 measured shapes best (1 to 40 KV heads, 1 to 8 query heads each, 2 to 4 bits, 0.1 and 1 % outliers, 2048 to 524288 tokens:
 // kvq_pv_matvec and kvq_attention_decode with either form forced); a second launch and the first and last round trips of a
-// kernel cost 8.82 us.  40 of the shapes are more than 2 % slower in the form taken (8.5 % at most, mostly 16 KV heads with 0.1 %
+// kernel cost 9.26 us.  36 of the shapes are more than 2 % slower in the form taken (8.5 % at most, mostly 16 KV heads with 0.1 %
 // outliers), where runs rounded up and constants from sixty shapes left 101 (15 %).  Both sides grow with L in proportion, so a shape
 // has one context from which on there are two launches.
 // kvq_attention_decode, us, two launches / one: 3-bit, 32 heads, 2048 tokens 28.3 / 24.2, 16383 43.2 / 37.3, 65536 86.1 / 82.1, 82500 102.1 /
-// 103.1, 110000 127.0 / 125.6, 131072 137.3 / 135.7 (in a step 132.8 / 129.0), 150000 (the last) 159.6 / 162.8; 4-bit 32768 70.3 / 61.0; 32 on 8, 2-bit
+// 103.1, 110000 127.0 / 125.6, 131072 137.3 / 135.7 (in a step 132.8 / 129.0), 150000 (two from 189000 on) 159.6 / 162.8; 4-bit 32768 70.3 / 61.0; 32 on 8, 2-bit
 // 131100 102.3 / 96.3, 262144 136.8 / 135.4, 524288 (two) 241.9 / 246.1; 64 on 8, 3-bit, 98500 163 / 133, 524288 529 / 475; 32 on 4, 4-bit, 57000 66.4 / 58.4,
-// 262144 (two) 136 / 149; 40 heads, 3-bit, 90000 (two) 126.5 / 131.5; one head, 4096 26.3 / 18.7, 524288 55.7 / 50.2.
+// 262144 (two) 136 / 149; 40 heads, 3-bit, 50000 112.0 / 108.7 (five calls), 90000 (two) 126.5 / 131.5; one head, 4096 26.3 / 18.7, 524288 55.7 / 50.2.
 //
 // Below 2048 tokens two launches would be the slower ones too (32 heads, 300 tokens 26.2 / 23.3, 1600 27.0 / 24.0; one head 21.6 / 18.2, 22.3 /
 // 18.8): they stay because kvq_decode_step_launches states five or six launches there, and its results are part of the interface.
@@ -174,14 +174,14 @@ inline bool pv_both(const kvq_cache *c, int rg, size_t dense_lds, PvBoth &p)
     const PvPlan two = pv_plan(L, Hq, rg);
     const int own = two.swaves * (int)(PV_BOTH_LDS / two.slds);         // sparse wavefronts on a compute unit in their own kernel
     const double x = (double)L / 131072.0;
-    const double sw = 1.76 + 0.0642 * Hq + 2.0 * c->k_side_v * (0.0307 + 0.167 * r);
-    const double dw = groups * ((c->bits == 2 ? 1.17 : c->bits == 3 ? 1.79 : 1.21) + 0.186 * (rg - 1));
-    const double s_one = sw * (rg == 8 ? 1.32 : 1.19) * cus / left, d_one = dw * cus / (slabs * groups);
+    const double sw = 1.45 + 0.0627 * Hq + 2.0 * c->k_side_v * (0.0713 + 0.151 * r);
+    const double dw = groups * ((c->bits == 2 ? 1.18 : c->bits == 3 ? 1.76 : 1.34) + 0.182 * (rg - 1));
+    const double s_one = sw * (rg == 8 ? 1.35 : 1.23) * cus / left, d_one = dw * cus / (slabs * groups);
     const double s_two = own < 24 ? sw * sqrt(24.0 / own) : sw;
     const int64_t per_group = cus / groups;
     const double d_two = per_group > 0 ? dw * cus / (double)(per_group * groups) : dw;
     // (eight tokens per wavefront at least: short contexts leave compute units over, and the estimate is beside the point)
-    return units <= wavefronts || (s_one > d_one ? s_one : d_one) * x <= (s_two + d_two) * x + 8.82;
+    return units <= wavefronts || (s_one > d_one ? s_one : d_one) * x <= (s_two + d_two) * x + 9.26;
 }
 
 template <int FBITS>
