@@ -334,6 +334,16 @@ kvq_status kvq_calibrate_key_channels(const uint16_t *d_k_cal, int32_t T, int32_
                                       uint16_t *d_s, uint16_t *d_z, uint16_t *d_lo, uint16_t *d_hi,
                                       void *stream);
 
+/*
+ * The same with scratch memory, which large calls need for a single pass over the Keys (without it they are read
+ * twice): DEVICE, 16-byte aligned, at least kvq_calibrate_key_channels_workspace_bytes() bytes (0: the call has no
+ * use for any).  d_workspace may be null; the results are the same.
+ */
+int64_t kvq_calibrate_key_channels_workspace_bytes(int32_t T, int32_t D, float outlier_fraction);
+kvq_status kvq_calibrate_key_channels_ws(const uint16_t *d_k_cal, int32_t T, int32_t D, float outlier_fraction,
+                                         uint16_t *d_s, uint16_t *d_z, uint16_t *d_lo, uint16_t *d_hi,
+                                         void *d_workspace, int64_t workspace_bytes, void *stream);
+
 int64_t kvq_calibrate_workspace_bytes(void);
 kvq_status kvq_calibrate_nuq(const float *d_x_norm, const float *d_w, int64_t n, int32_t bits,
                              int32_t iters, float *h_signposts, void *d_workspace,

@@ -70,6 +70,8 @@ def load_library():
         "kvq_softmax_workspace_bytes": (I64, [I32, I64]),
         "kvq_softmax_f32": (C.c_int, [V, I64, V, I64, I32, I64, V, I64, V]),
         "kvq_calibrate_key_channels": (C.c_int, [V, I32, I32, F, V, V, V, V, V]),
+        "kvq_calibrate_key_channels_workspace_bytes": (I64, [I32, I32, F]),
+        "kvq_calibrate_key_channels_ws": (C.c_int, [V, I32, I32, F, V, V, V, V, V, I64, V]),
         "kvq_calibrate_workspace_bytes": (I64, []),
         "kvq_calibrate_nuq": (C.c_int, [V, V, I64, I32, I32, V, V, I64, V]),
         "kvq_fp16_qk_matvec": (C.c_int, [V, I64, I32, I32, V, F, V, I64, V]),
@@ -104,7 +106,8 @@ EXPORTED_SYMBOLS = [
     "kvq_fp16_pv_matvec", "kvq_event_create", "kvq_event_record", "kvq_event_elapsed_ms", "kvq_event_destroy",
     "kvq_profile_enable", "kvq_profile_last_ms", "kvq_profile_count", "kvq_profile_read_ms",
     "kvq_profile_span_buffer_bytes", "kvq_profile_set_span_buffer", "kvq_profile_span_us", "kvq_calibrate_workspace_bytes", "kvq_calibrate_nuq",
-    "kvq_calibrate_key_channels", "kvq_stream_read_workspace_bytes", "kvq_stream_read",
+    "kvq_calibrate_key_channels", "kvq_calibrate_key_channels_workspace_bytes", "kvq_calibrate_key_channels_ws",
+    "kvq_stream_read_workspace_bytes", "kvq_stream_read",
 ]
 
 
@@ -441,8 +444,14 @@ def kvq_calibrate_key_channels(k_cal: torch.Tensor, outlier_fraction: float, str
     # without).
     outs = torch.empty(4 * D, dtype=torch.int16, pin_memory=True)
     p = outs.data_ptr()
-    _check(load_library().kvq_calibrate_key_channels(k_cal.data_ptr(), T, D, float(outlier_fraction),
-                                                     p, p + 2 * D, p + 4 * D, p + 6 * D, _stream_ptr(stream)),
+    lib = load_library()
+    ws_bytes = int(lib.kvq_calibrate_key_channels_workspace_bytes(T, D, float(outlier_fraction)))
+    try:
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device=k_cal.device) if ws_bytes else None
+    except torch.cuda.OutOfMemoryError:      # the call does without
+        ws, ws_bytes = None, 0
+    _check(lib.kvq_calibrate_key_channels_ws(k_cal.data_ptr(), T, D, float(outlier_fraction), p, p + 2 * D, p + 4 * D,
+                                             p + 6 * D, ws.data_ptr() if ws_bytes else None, ws_bytes, _stream_ptr(stream)),
            "kvq_calibrate_key_channels")
     (torch.cuda.current_stream() if stream is None else stream).synchronize()
     return tuple(outs.numpy().view(np.float16).reshape(4, D).copy())

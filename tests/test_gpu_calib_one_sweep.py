@@ -1,0 +1,72 @@
+"""Per-channel Key calibration in one sweep (long calls with scratch memory): shapes at either side of the rule that takes it,
+whole and ragged parts, outlier counts from none to the most its lists hold, and channels whose sample misleads it
+(constant, a handful of values, a far tail in rows that the sample cannot tell).  Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import kvq_calib_oracle as C
+
+pytestmark = pytest.mark.gpu
+
+
+def _keys(T, D, kind):
+    rng = np.random.default_rng(T + D)
+    x = rng.standard_normal((T, D)) * np.exp(rng.standard_normal(D)) + rng.standard_normal(D)
+    if kind == "drift":
+        x = x * (1.0 + np.arange(T)[:, None] / T)
+    elif kind == "coarse":
+        x = np.round(x) * 0.5
+    elif kind == "mixed":
+        x[:, 3] = 0.0                                     # a channel that never speaks
+        x[:, 4] = -1.5
+        x[:, 10] = np.where(np.arange(T) % 16 < 8, x[:, 10], 0.0)
+        x[T // 2:T // 2 + 700, 20] = 300.0 + np.arange(700) / 4       # a burst in some parts only
+        x[::2, 40] = -2.0                                 # half of a channel equal
+        x[:, 63] = np.arange(T) % 7 - 3
+    elif kind == "burst":
+        x[T - 2000:] *= 50.0                              # one part holds every outlier
+    return x.astype(np.float16)
+
+
+@pytest.mark.parametrize("T,D,p,kind", [
+    (24576, 64, 0.01, "plain"), (24575, 64, 0.01, "plain"),           # the smallest by rows, and one row fewer
+    (32768, 128, 0.01, "mixed"), (32768, 64, 0.0, "drift"), (32767, 64, 0.001, "coarse"), (32768, 192, 0.01, "burst"),
+    (24577, 192, 0.0, "mixed"), (30001, 128, 0.015, "plain"),
+    (32768, 64, 0.013, "plain"), (32768, 64, 0.03, "plain"),          # near and past the most outliers that the lists hold
+    (16384, 256, 0.01, "drift"), (16384, 192, 0.01, "plain"),
+    (8193, 2048, 0.01, "mixed"), (8192, 2112, 0.001, "plain"), (8191, 2112, 0.001, "plain"),
+    (4096, 5120, 0.01, "plain"), (4097, 5120, 0.0, "plain"), (16390, 8192, 0.01, "drift"),
+])
+def test_one_sweep_matches_the_oracle(T, D, p, kind):
+    import torch
+    import paper_2401_18079_amd as K
+    x = _keys(T, D, kind)
+    got = K.kvq_calibrate_key_channels(torch.from_numpy(x).cuda(), p)
+    for name, a, b in zip(("s", "z", "lo", "hi"), got, C.key_channel_constants(x, p)):
+        assert np.array_equal(a, b), (name, np.nonzero(a != b)[0][:5])
+
+
+def test_scratch_memory_is_optional_and_checked():
+    import ctypes
+    import torch
+    import paper_2401_18079_amd as K
+    T, D, p = 24576, 128, 0.01
+    x = torch.from_numpy(_keys(T, D, "mixed")).cuda()
+    lib = K.load_library()
+    need = lib.kvq_calibrate_key_channels_workspace_bytes(T, D, p)
+    assert need > 0 and lib.kvq_calibrate_key_channels_workspace_bytes(300, 4096, p) == 0
+    assert lib.kvq_calibrate_key_channels_workspace_bytes(32769, 4096, p) == 0
+    ref = K.kvq_calibrate_key_channels(x, p)
+    sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    for size, shift in ((need, 0), (need - 1, 0), (need + 16, 8), (0, 0)):       # whole, short, misaligned, none
+        ws = torch.full((need + 32,), 0x5A, dtype=torch.uint8, device="cuda")
+        out = torch.zeros(4 * D, dtype=torch.int16, device="cuda")
+        o = out.data_ptr()
+        st = lib.kvq_calibrate_key_channels_ws(x.data_ptr(), T, D, p, o, o + 2 * D, o + 4 * D, o + 6 * D,
+                                               ws.data_ptr() + shift if size else None, size, sp)
+        assert st == 0
+        torch.cuda.synchronize()
+        assert bool((ws[need + shift:] == 0x5A).all())
+        got = out.cpu().numpy().view(np.float16).reshape(4, D)
+        for a, b in zip(got, ref):
+            assert np.array_equal(a, b)
