@@ -5,7 +5,7 @@
 // and fp16 residuals are reproducible bit for bit.
 #include "kvq_common.hpp"
 #include "kvq_qk_sparse.hpp"
-#include "kvq_select.hpp"
+#include "kvq_append_common.hpp"
 #include <type_traits>
 
 namespace {
@@ -17,10 +17,10 @@ namespace {
 // In calls of fewer than KVQ_VW_SMALL_TOKENS tokens it takes every multiple of 1024 channels up to 8192 (small_width;
 // both appends of one token, 4 bits, us with the routine for any width and with it: 24 heads 12.2 / 8.8, 48 heads
 // 27.6 / 12.4, 64 heads 33.2 / 13.2; 63 tokens of 64 heads 43.7 / 25.8), one token per workgroup (two would lengthen the
-// one chain that counts).  In longer calls a workgroup takes the two tokens that share dwords, four wavefronts each:
-// 1024, 2048 and 4096 channels, and 5120, 6656 and 8192 from KVQ_BULK_TOKENS tokens on (4096 tokens of 4096: 74 us with a
-// token's bits merged into memory by two atomics per dword, 51 us with whole dwords stored; 777 tokens of 5120
-// channels: 37.6 -> 22.7 us).  All others take the routine for any width.
+// one chain that counts).  In longer calls a workgroup takes the two tokens that share dwords: kvq_v_pair.hip (see append_v), or, where
+// that does not apply, four wavefronts each: 1024, 2048 and 4096 channels, and 5120, 6656 and 8192 from KVQ_BULK_TOKENS
+// tokens on (4096 tokens of 4096: 74 us with a token's bits merged into memory by two atomics per dword, 51 us with whole
+// dwords stored).  All others take the routine for any width.
 constexpr int KVQ_BULK_TOKENS = 512;      // calls with at least this many tokens count as bulk appends
 constexpr int KVQ_KV_SPLIT_TOKENS = 256;  // from here on the combined call runs the Key and Value kernels in turn
 constexpr int KVQ_WAVE_TOKENS = 1024;     // Key appends of at least this many tokens: one wavefront per token
@@ -28,43 +28,6 @@ constexpr int KVQ_WAVE_TOKENS = 1024;     // Key appends of at least this many t
 // Workgroups have NT threads: 256 for narrow models, 1024 once a token vector has >= 2048 channels
 // (fewer passes over the vector, hence fewer barriers, for the single-token decode append).
 
-// Code of a normalised value: the number of thresholds it has reached (a compare and an add with carry each),
-// or, beyond the range in which that is the nearest signpost, the exhaustive search (KVQ_CODE_RANGE).  The
-// search costs four instructions per signpost; a token's channels are within the range all but always.
-template <int NE>
-struct KvqCoder {
-    float thr[NE - 1], range;
-    const float *lut;
-    __device__ __forceinline__ KvqCoder(const float *thresholds, const float *signposts) : lut(signposts)
-    {
-#pragma unroll
-        for (int j = 0; j < NE - 1; ++j) thr[j] = thresholds[j];
-        range = (thr[0] == thr[0]) ? KVQ_CODE_RANGE : -1.0f;
-    }
-    __device__ __forceinline__ bool far(float xn) const { return !(__builtin_fabsf(xn) <= range); }
-    __device__ __forceinline__ int count(float xn) const            // not far(xn) only
-    {
-        int code = 0;
-#pragma unroll
-        for (int j = 0; j < NE - 1; ++j) code += (xn >= thr[j]) ? 1 : 0;
-        return code;
-    }
-    __device__ __forceinline__ int search(float xn) const
-    {
-        float sp;
-        return kvq_nearest<NE>(lut, xn, sp);
-    }
-    __device__ __forceinline__ int operator()(float xn) const
-    {
-        if (NE == 4) return search(xn);       // (as short; with the branch below 5 % slower in the routines for any width)
-        int code = count(xn);
-        const bool f = far(xn);
-        if (__ballot(f) != 0ull) {
-            if (f) code = search(xn);
-        }
-        return code;
-    }
-};
 // The signposts in LDS, for the residuals of outliers (a dynamic index).  The caller's next barrier makes them visible.
 template <int NE>
 __device__ __forceinline__ void stage_lut(float *lut_s, const float *lut)
@@ -95,36 +58,6 @@ __device__ inline uint32_t block_rank(bool flag, uint32_t *wave_tot, uint32_t &t
     return before + prefix;
 }
 
-// Number of Key outliers of each new token (threshold test only).  One wavefront per token, eight
-// channels per lane and pass (16-byte loads of the fp16 vector, D is a multiple of 128): no barriers.
-constexpr int KVQ_COUNT_NT = 256;
-__device__ __forceinline__ void k_count_token(const void *params, int D, const uint16_t *k_new, uint32_t *cnt, const int t)
-{
-    KvqParamsView pv = kvq_params_view(params, D);
-    const int lane = threadIdx.x & 63;
-    const uint4 *row = (const uint4 *)(k_new + (int64_t)t * D);
-    const float4 *lo4 = (const float4 *)pv.lo, *hi4 = (const float4 *)pv.hi;
-    uint32_t mine = 0;
-    if ((uintptr_t)k_new & 15) {          // input not 16-byte aligned: one channel per lane and pass
-        for (int c = lane; c < D; c += 64) {
-            const float x = kvq_h2f(k_new[(int64_t)t * D + c]);
-            mine += ((x < pv.lo[c]) | (x > pv.hi[c])) ? 1u : 0u;
-        }
-    } else for (int v = lane; v < D / 8; v += 64) {
-        const uint4 h = row[v];
-        const float4 la = lo4[2 * v], lb = lo4[2 * v + 1], ha = hi4[2 * v], hb = hi4[2 * v + 1];
-        const uint32_t w[4] = {h.x, h.y, h.z, h.w};
-        const float lo[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
-        const float hi[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float x = kvq_h2f((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
-            mine += ((x < lo[e]) | (x > hi[e])) ? 1u : 0u;
-        }
-    }
-    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
-    if (lane == 0) cnt[t] = mine;
-}
 __global__ __launch_bounds__(KVQ_COUNT_NT) void kvq_k_count(const void *params, int D, int T, const uint16_t *k_new,
                                                             uint32_t *cnt)
 {
@@ -847,8 +780,6 @@ __device__ __forceinline__ void hist_count(uint32_t *hist, bool in, uint32_t bin
 // Calls of a few tokens take more wavefronts and one token per workgroup: fewer elements per lane, where the time of a token is the length of a lane's instruction stream
 // (a 4096-channel token: 16 elements per lane on four wavefronts, 4 on sixteen).
 constexpr int KVQ_VW_WAVES = 4;
-constexpr int KVQ_V_CAND = 128;              // candidates per side that a wavefront looks through (two per lane)
-constexpr uint32_t KVQ_V_BOUNDED = 52;       // outliers per side up to which the thresholds are bounded first
 constexpr int KVQ_VW_SMALL_TOKENS = 64;      // calls below this many tokens use one lane per four elements
 template <int BITS, int JW, int W, int TOK, class SP>
 __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, int D, int64_t cap, int64_t n0,
@@ -1194,13 +1125,6 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
     if (overflow) atomicExch(d_status, (int32_t)KVQ_ERR_NNZ_OVERFLOW);
 }
 
-// In bulk a Value kernel's first `wgs` workgroups count the Key outliers of the same tokens (a wavefront per token):
-// reading the Keys and the thresholds, latency that the Values' arithmetic covers.  wgs = 0: Values only.
-struct KeyCount {
-    int wgs;
-    const uint16_t *k_new;
-    uint32_t *cnt;
-};
 template <int BITS, int JW, int W, int TOK, class SP>
 __global__ __launch_bounds__(64 * W * TOK) void kvq_v_quant4(const void *__restrict__ params, int D, int64_t cap,
                                                           int64_t n0, int T, int k_side,
@@ -1507,15 +1431,23 @@ static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T,
         cache->v_sz, cache->v_ptr, vsp, cache->cap_nnz_v, cache->d_status, keys)
     const int small = T < KVQ_VW_SMALL_TOKENS ? small_width(D) : 0;
     const bool in_pairs = !small && (D == 4096 || D == 2048 || D == 1024 || (T >= KVQ_BULK_TOKENS && (D == 5120 || D == 6656 || D == 8192)));
+    // The pair kernel, one wavefront per 1024 channels and pair, takes calls of 64 tokens and more, but of one or two wavefronts a pair only
+    // longer ones: below, a token of 1024 or 2048 channels is sooner done by four wavefronts (us, four / one or two wavefronts: 1024 channels,
+    // 2 bits, 777 tokens 9.1 / 11.3, 1200 11.5 / 11.8, 2048 16.1 / 11.9, 4 bits, 1200 12.3 / 13.4, 2048 17.3 / 14.3; 2048 channels, 777 tokens 11.3 / 11.9
+    // and 13.1 / 14.7, 1200 14.5 / 11.4 and 16.7 / 14.3).  More than KVQ_V_BOUNDED outliers a side, other widths and unaligned input keep the
+    // other kernels.
+    const bool pair = !small && D % 1024 == 0 && D <= 1024 * KVQ_V_PAIR_MAX_WAVES && cache->k_side_v <= (int)KVQ_V_BOUNDED &&
+                      ((uintptr_t)d_v_new & 15) == 0 && T >= (D == 1024 ? 1500 : D == 2048 ? 1000 : KVQ_VW_SMALL_TOKENS);
     KeyCount keys = {0, nullptr, nullptr};
     // Counting on the way saves a launch and its latency (time on the way over that with a launch of its own: 32 heads, 3 bits, 256 tokens 0.86 of
     // the time, 1024 0.88, 2047 0.93, 4096 0.99-1.00; 40 heads, 2048 0.97), but not from 2048 tokens of 2048 or 4096 channels on with
     // blocked outlier storage, whose Value kernel has no vector time to spare: 32 heads, 2 bits, 2048 tokens 1.06, 2600 1.03, 4096 1.00;
     // 3 bits 1.05, 1.00, 1.00; 16 heads, 2 bits, 2300 1.01, 3000 1.06, 4096 1.03 (40 heads 1.02, 0.98, 0.98; flat storage 1.00, 0.98, 1.00).
     const bool busy = cache->nnz_block_shift && T >= 2048 && (D == 2048 || D == 4096);
-    const bool count = k_new != nullptr && in_pairs && !busy;
+    const bool count = k_new != nullptr && (in_pairs || pair) && !busy;
     if (counted) *counted = count;
-    if (count) keys = {(T + 2 * KVQ_VW_WAVES - 1) / (2 * KVQ_VW_WAVES), k_new, (uint32_t *)cache->workspace};
+    const int wg_waves = pair ? D / 1024 : 2 * KVQ_VW_WAVES;
+    if (count) keys = {(T + wg_waves - 1) / wg_waves, k_new, (uint32_t *)cache->workspace};
     // a workgroup per pair of tokens (the two that share dwords), the first and the last perhaps with one token
     const unsigned pairs = (unsigned)(((cache->n_tokens_v + T - 1) >> 1) - (cache->n_tokens_v >> 1) + 1);
 #define LAUNCH_V4(B, J) LAUNCH_V4W(B, J, KVQ_VW_WAVES, 2, pairs)
@@ -1547,7 +1479,8 @@ static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T,
                                                     cache->d_status);                                            \
     } while (0)
     const auto launch = [&](const auto vsp) {
-        if (cache->bits == 2) LAUNCH_V(2);
+        if (pair) kvq_v_pair_launch(cache, d_v_new, T, pairs, keys.wgs, keys.k_new, keys.cnt, s);
+        else if (cache->bits == 2) LAUNCH_V(2);
         else if (cache->bits == 3) LAUNCH_V(3);
         else LAUNCH_V(4);
     };

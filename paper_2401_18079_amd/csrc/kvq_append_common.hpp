@@ -1,0 +1,92 @@
+// What the append kernels share.
+#pragma once
+#include "kvq_select.hpp"
+
+namespace {
+
+// Code of a normalised value: the number of thresholds it has reached (a compare and an add with carry each),
+// or, beyond the range in which that is the nearest signpost, the exhaustive search (KVQ_CODE_RANGE).  The
+// search costs four instructions per signpost; a token's channels are within the range all but always.
+template <int NE>
+struct KvqCoder {
+    float thr[NE - 1], range;
+    const float *lut;
+    __device__ __forceinline__ KvqCoder(const float *thresholds, const float *signposts) : lut(signposts)
+    {
+#pragma unroll
+        for (int j = 0; j < NE - 1; ++j) thr[j] = thresholds[j];
+        range = (thr[0] == thr[0]) ? KVQ_CODE_RANGE : -1.0f;
+    }
+    __device__ __forceinline__ bool far(float xn) const { return !(__builtin_fabsf(xn) <= range); }
+    __device__ __forceinline__ int count(float xn) const            // not far(xn) only
+    {
+        int code = 0;
+#pragma unroll
+        for (int j = 0; j < NE - 1; ++j) code += (xn >= thr[j]) ? 1 : 0;
+        return code;
+    }
+    __device__ __forceinline__ int search(float xn) const
+    {
+        float sp;
+        return kvq_nearest<NE>(lut, xn, sp);
+    }
+    __device__ __forceinline__ int operator()(float xn) const
+    {
+        if (NE == 4) return search(xn);       // (as short; with the branch below 5 % slower in the routines for any width)
+        int code = count(xn);
+        const bool f = far(xn);
+        if (__ballot(f) != 0ull) {
+            if (f) code = search(xn);
+        }
+        return code;
+    }
+};
+// Number of Key outliers of each new token (threshold test only).  One wavefront per token, eight
+// channels per lane and pass (16-byte loads of the fp16 vector, D is a multiple of 128): no barriers.
+constexpr int KVQ_COUNT_NT = 256;
+__device__ __forceinline__ void k_count_token(const void *params, int D, const uint16_t *k_new, uint32_t *cnt, const int t)
+{
+    KvqParamsView pv = kvq_params_view(params, D);
+    const int lane = threadIdx.x & 63;
+    const uint4 *row = (const uint4 *)(k_new + (int64_t)t * D);
+    const float4 *lo4 = (const float4 *)pv.lo, *hi4 = (const float4 *)pv.hi;
+    uint32_t mine = 0;
+    if ((uintptr_t)k_new & 15) {          // input not 16-byte aligned: one channel per lane and pass
+        for (int c = lane; c < D; c += 64) {
+            const float x = kvq_h2f(k_new[(int64_t)t * D + c]);
+            mine += ((x < pv.lo[c]) | (x > pv.hi[c])) ? 1u : 0u;
+        }
+    } else for (int v = lane; v < D / 8; v += 64) {
+        const uint4 h = row[v];
+        const float4 la = lo4[2 * v], lb = lo4[2 * v + 1], ha = hi4[2 * v], hb = hi4[2 * v + 1];
+        const uint32_t w[4] = {h.x, h.y, h.z, h.w};
+        const float lo[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
+        const float hi[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float x = kvq_h2f((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
+            mine += ((x < lo[e]) | (x > hi[e])) ? 1u : 0u;
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+    if (lane == 0) cnt[t] = mine;
+}
+// In bulk a Value kernel's first `wgs` workgroups count the Key outliers of the same tokens (a wavefront per token):
+// reading the Keys and the thresholds, latency that the Values' arithmetic covers.  wgs = 0: Values only.
+struct KeyCount {
+    int wgs;
+    const uint16_t *k_new;
+    uint32_t *cnt;
+};
+
+constexpr int KVQ_V_CAND = 128;              // candidates per side that a wavefront looks through (two per lane)
+constexpr uint32_t KVQ_V_BOUNDED = 52;       // outliers per side up to which the thresholds are bounded first
+
+}  // namespace
+
+// Widest Value appends of kvq_v_pair.hip: one wavefront per 1024 channels.
+constexpr int KVQ_V_PAIR_MAX_WAVES = 8;
+// Launches the pair kernel over `pairs` pairs of tokens (and the counting workgroups).  D a multiple of 1024, up to 1024 KVQ_V_PAIR_MAX_WAVES;
+// k_side_v at most KVQ_V_BOUNDED; d_v_new 16-byte aligned.
+__attribute__((visibility("hidden"))) void kvq_v_pair_launch(const kvq_cache *cache, const uint16_t *d_v_new, int T, unsigned pairs,
+                                                             int count_wgs, const uint16_t *k_new, uint32_t *k_count, hipStream_t s);

@@ -1,0 +1,98 @@
+"""The bulk Value append with a workgroup per pair of tokens: whole and half pairs at either end, every width of its rule and
+the call lengths at either side of it, and tokens on which one of its short cuts does not hold: crowds of equal keys, thresholds
+at zero and between zeros of both signs, thresholds that coincide or that only some of their equals pass, scales of a few bits,
+outliers far beyond the code range.  Bit-exact against the oracle; infinities and NaN against one-token calls, which other
+kernels take."""
+import numpy as np
+import pytest
+
+import kvq_synth as S
+from oracle import kvq_oracle as O
+from kvq_testlib import Setup, compare_caches
+
+pytestmark = pytest.mark.gpu
+
+
+def _tokens(T, D, k, seed):
+    rng = np.random.default_rng(seed)
+    v = (rng.standard_normal((T, D)) * np.exp(0.5 * rng.standard_normal((T, 1)))).astype(np.float16)
+    for t in range(T):
+        kind, r = t % 13, rng.permutation(D)
+        if kind == 1:                                    # only some of a threshold's equals are outliers
+            v[t, r[:max(k, 1) + 3]] = v[t].max() * 2
+            v[t, r[200:200 + max(k, 1) + 1]] = v[t].min() * 2
+        elif kind == 2:
+            v[t] = np.float16(0.75)                      # thresholds coincide
+        elif kind == 3:
+            v[t] = rng.choice(np.float16([-1, 0, 0, 0, 1]), D)
+        elif kind == 4:                                  # fewer positive values than outliers a side: a threshold at zero
+            v[t] = -np.abs(v[t])
+            v[t, r[:k // 2]] = np.float16(2.0)
+            v[t, r[k // 2:2 * k + 40]] = rng.choice(np.float16([0.0, -0.0]), 2 * k + 40 - k // 2)
+        elif kind == 5:                                  # scale of a few bits
+            v[t] = (rng.integers(-3, 4, D) * 2.0 ** -24).astype(np.float16)
+        elif kind == 6:                                  # far outliers beside a small scale
+            v[t] = (rng.standard_normal(D) * 1e-3).astype(np.float16)
+            v[t, r[:max(1, k // 2)]] = np.float16(60000.0)
+            v[t, r[500:500 + k // 3]] = np.float16(-31.0)
+        elif kind == 7:                                  # large values: thresholds past the largest number
+            v[t] = (rng.uniform(-1, 1, D) * 65000).astype(np.float16)
+        elif kind == 8:                                  # one more value than outliers
+            v[t] = np.float16(3.0)
+            v[t, r[:k]] = np.float16(5.0)
+            v[t, r[k:2 * k]] = np.float16(-5.0)
+    return v
+
+
+@pytest.mark.parametrize("heads,bits,T,n0,k,blocked", [
+    (24, 2, 64, 0, 20, False), (24, 3, 65, 0, 15, True), (24, 4, 66, 1, 52, False), (24, 4, 64, 3, 1, False), (24, 3, 70, 2, 0, True),
+    (32, 2, 79, 1, 20, True), (32, 3, 78, 0, 20, False), (32, 4, 65, 1, 53, False), (40, 4, 64, 1, 25, False), (48, 3, 64, 1, 30, False),
+    (56, 2, 65, 0, 30, False), (64, 4, 66, 0, 41, False), (64, 3, 63, 0, 41, False),
+    (8, 3, 1500, 1, 5, False), (8, 4, 1499, 0, 5, False), (16, 2, 1000, 1, 10, False), (16, 3, 999, 0, 10, False), (8, 2, 1501, 0, 52, False),
+])
+def test_pairs_match_the_oracle(heads, bits, T, n0, k, blocked):
+    import torch
+    import paper_2401_18079_amd as K
+    wl = S.workload("c2", n_kv_heads=heads, n_q_heads=heads, bits=bits)
+    st = Setup(wl)
+    D, cap = wl.D, (n0 + T + 127) // 128 * 128
+    v = _tokens(n0 + T, D, k, heads * 1000 + T + k)
+    oc = O.OracleCache(bits, heads, heads, cap, k, wl.rope_base, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi, cap_nnz_k=1024)
+    gc = K.KvqCache(bits, heads, heads, cap, k, wl.rope_base, 1024, nnz_block_entries=1024 if blocked else None)
+    K.kvq_lut_load(gc, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
+    if n0:
+        oc.append_v(v[:n0]); K.kvq_quantize_append_v(gc, torch.from_numpy(v[:n0]).cuda())
+    oc.append_v(v[n0:]); K.kvq_quantize_append_v(gc, torch.from_numpy(v[n0:]).cuda())
+    bad = compare_caches(oc, gc)
+    assert not bad, bad
+
+
+def _values_of(gc):
+    return {n: getattr(gc, n).cpu().numpy().copy() for n in ("v_codes", "v_sz", "v_ptr", "v_idx", "v_val")}
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+def test_infinities_and_nan_as_in_one_token_calls(shift):
+    import torch
+    import paper_2401_18079_amd as K
+    heads, bits, T, k = 32, 3, 64, 20
+    wl = S.workload("c2", n_kv_heads=heads, n_q_heads=heads, bits=bits)
+    st = Setup(wl)
+    v = _tokens(T, wl.D, k, 5)
+    rng = np.random.default_rng(6)
+    for t in range(0, T, 3):
+        r, n = rng.permutation(wl.D), (3, 19, 20, 21, 60)[t % 5]
+        v[t, r[:n]] = (np.float16(np.inf), np.float16(-np.inf), np.float16(np.nan))[t % 3 if t % 2 else (t // 6) % 3]
+    buf = torch.zeros(T * wl.D + 8, dtype=torch.float16, device="cuda")
+    dev = buf[shift:shift + T * wl.D].view(T, wl.D)      # (shift 1: unaligned input, which the other kernels take)
+    dev.copy_(torch.from_numpy(v))
+    got = []
+    for whole in (True, False):
+        gc = K.KvqCache(bits, heads, heads, 128, k, wl.rope_base, 1024)
+        K.kvq_lut_load(gc, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
+        for t in range(1 if whole else T):
+            K.kvq_quantize_append_v(gc, dev if whole else dev[t:t + 1])
+        torch.cuda.synchronize()
+        got.append(_values_of(gc))
+    for n in got[0]:
+        assert np.array_equal(got[0][n].view(np.uint8), got[1][n].view(np.uint8)), n
