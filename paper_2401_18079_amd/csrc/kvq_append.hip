@@ -1361,12 +1361,16 @@ static kvq_status append_k(kvq_cache *cache, const uint16_t *d_k_new, int32_t T,
     const int D = cache->n_kv_heads * KVQ_HEAD_DIM;
     hipStream_t s = (hipStream_t)stream;
     const int single = (T == 1);
+    // us, kvq_k_bulk / the kernels below with kvq_ptr_scan before them: 64 tokens of 4096 channels, 3 bits 10.0 / 12.4; 777 12.6 / 17.2; 4096 27.0 / 40.5;
+    // of 1024 channels, 4096 13.9 / 16.2; of 5120, 4 bits 47.0 / 56.2; of 8192 56.1 / 85.8
+    const bool bulk = T >= KVQ_VW_SMALL_TOKENS && D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES && ((uintptr_t)d_k_new & 15) == 0 &&
+                      cache->workspace_bytes >= ((int64_t)T + 3) / 4 * 16;
     if (!single) {
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
         uint32_t *cnt = (uint32_t *)cache->workspace;
         if (!counted)
             kvq_k_count<<<(T + KVQ_COUNT_NT / 64 - 1) / (KVQ_COUNT_NT / 64), KVQ_COUNT_NT, 0, s>>>(cache->params, D, T, d_k_new, cnt);
-        kvq_ptr_scan<<<1, 1024, 0, s>>>(cache->k_ptr, cache->n_tokens_k, T, cnt, cache->cap_nnz_k, cache->d_status);
+        if (!bulk) kvq_ptr_scan<<<1, 1024, 0, s>>>(cache->k_ptr, cache->n_tokens_k, T, cnt, cache->cap_nnz_k, cache->d_status);
     }
 #define LAUNCH_KW(B, HW, W)                                                                                     \
     kvq_k_quant<B, HW, W><<<T, 64 * (W), 0, s>>>(cache->params, D, cache->cap_tokens, cache->n_tokens_k, d_k_new, \
@@ -1394,7 +1398,8 @@ static kvq_status append_k(kvq_cache *cache, const uint16_t *d_k_new, int32_t T,
     } while (0)
     // one set of kernels per layout of the outlier entries (flat arrays or a list of blocks)
     const auto launch = [&](const auto ksp) {
-        if (cache->bits == 2) LAUNCH_K(2);
+        if (bulk) kvq_k_bulk_launch(cache, d_k_new, T, (const uint32_t *)cache->workspace, s);
+        else if (cache->bits == 2) LAUNCH_K(2);
         else if (cache->bits == 3) LAUNCH_K(3);
         else LAUNCH_K(4);
     };
@@ -1436,14 +1441,13 @@ static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T,
     // 2 bits, 777 tokens 9.1 / 11.3, 1200 11.5 / 11.8, 2048 16.1 / 11.9, 4 bits, 1200 12.3 / 13.4, 2048 17.3 / 14.3; 2048 channels, 777 tokens 11.3 / 11.9
     // and 13.1 / 14.7, 1200 14.5 / 11.4 and 16.7 / 14.3).  More than KVQ_V_BOUNDED outliers a side, other widths and unaligned input keep the
     // other kernels.
-    const bool pair = !small && D % 1024 == 0 && D <= 1024 * KVQ_V_PAIR_MAX_WAVES && cache->k_side_v <= (int)KVQ_V_BOUNDED &&
+    const bool pair = !small && D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES && cache->k_side_v <= (int)KVQ_V_BOUNDED &&
                       ((uintptr_t)d_v_new & 15) == 0 && T >= (D == 1024 ? 1500 : D == 2048 ? 1000 : KVQ_VW_SMALL_TOKENS);
     KeyCount keys = {0, nullptr, nullptr};
-    // Counting on the way saves a launch and its latency (time on the way over that with a launch of its own: 32 heads, 3 bits, 256 tokens 0.86 of
-    // the time, 1024 0.88, 2047 0.93, 4096 0.99-1.00; 40 heads, 2048 0.97), but not from 2048 tokens of 2048 or 4096 channels on with
-    // blocked outlier storage, whose Value kernel has no vector time to spare: 32 heads, 2 bits, 2048 tokens 1.06, 2600 1.03, 4096 1.00;
-    // 3 bits 1.05, 1.00, 1.00; 16 heads, 2 bits, 2300 1.01, 3000 1.06, 4096 1.03 (40 heads 1.02, 0.98, 0.98; flat storage 1.00, 0.98, 1.00).
-    const bool busy = cache->nnz_block_shift && T >= 2048 && (D == 2048 || D == 4096);
+    // Counting on the way saves a launch and its latency (32 heads, blocked storage, 2048 tokens, us with a launch of its own / on the way: 2 bits 34.1 /
+    // 31.1, 4 bits 42.6 / 39.4; 4096 tokens 49.3 / 46.7, 65.0 / 62.4; 16 heads 33.7 / 33.5, 42.2 / 43.2), except in the kernel of four wavefronts a token from
+    // 2048 tokens of 2048 or 4096 channels on with blocked outlier storage, which has no vector time to spare.
+    const bool busy = !pair && cache->nnz_block_shift && T >= 2048 && (D == 2048 || D == 4096);
     const bool count = k_new != nullptr && (in_pairs || pair) && !busy;
     if (counted) *counted = count;
     const int wg_waves = pair ? D / 1024 : 2 * KVQ_VW_WAVES;
@@ -1511,10 +1515,11 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
     const int D = cache->n_kv_heads * KVQ_HEAD_DIM;
     if (cache->k_side_v < 0 || 2 * (int64_t)cache->k_side_v >= D) return KVQ_ERR_INVALID_ARG;
     if (D > 16384) return KVQ_ERR_UNSUPPORTED;       // the per-token Value selection keeps the vector in LDS
-    if (T >= KVQ_KV_SPLIT_TOKENS) {
-        // Such an append fills the GPU with either kernel alone.  Just below (255 tokens, 4 bits, us in one launch / in
-        // turn): 8 heads 15 / 20, 16 heads 20 / 20, 32 heads 36 / 26, 40 heads 35 / 40, 52 heads 68 / 48, 64 heads 46 / 52.
-        // (From 129 tokens on, two workgroups of 1024 threads per token are more than the compute units hold at once.)
+    if (T >= KVQ_KV_SPLIT_TOKENS || (T > 128 && D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES)) {
+        // Such an append fills the GPU with either kernel alone.  From 129 tokens on, two workgroups of 1024 threads per token are more than the
+        // compute units hold at once, and the bulk kernels are the faster ones (180 tokens, us in one launch / in turn: 24 heads 23.0 / 14.9,
+        // 32 heads 24.8 / 14.8, 64 heads 33.3 / 18.2; 8 heads, 4 bits, 13.2 / 12.3; 100 tokens, 32 heads 16.9 / 14.8, 40 heads 18.0 / 19.1, 16 heads, 4 bits,
+        // 13.3 / 15.1).  Other widths, 255 tokens, 4 bits: 52 heads 68 / 48.
         // Every check of both calls has passed above.
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
         // Values first: their kernel counts the Keys' outliers on the way (see KeyCount).

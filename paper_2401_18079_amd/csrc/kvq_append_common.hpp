@@ -84,9 +84,26 @@ constexpr uint32_t KVQ_V_BOUNDED = 52;       // outliers per side up to which th
 
 }  // namespace
 
-// Widest Value appends of kvq_v_pair.hip: one wavefront per 1024 channels.
-constexpr int KVQ_V_PAIR_MAX_WAVES = 8;
-// Launches the pair kernel over `pairs` pairs of tokens (and the counting workgroups).  D a multiple of 1024, up to 1024 KVQ_V_PAIR_MAX_WAVES;
+// Workgroup b of a launch runs on XCD b mod 8.  The codes of 64 consecutive tokens (or pairs) share lines, 16 bytes each: a launch of
+// kvq_xcd_grid(n) workgroups takes its n pieces of work in this order, so that an XCD has neighbours and its L2 puts their bytes together.
+// (The last ones may have none: place >= n.)
+__host__ __device__ inline unsigned kvq_xcd_grid(unsigned n) { return (n + 7) & ~7u; }
+__device__ __forceinline__ unsigned kvq_xcd_place(unsigned b, unsigned grid) { return (b & 7) * (grid >> 3) + (b >> 3); }
+
+// Widest bulk appends of kvq_v_pair.hip and kvq_k_bulk.hip: one wavefront per 1024 channels.
+constexpr int KVQ_BULK_MAX_WAVES = 8;
+// Launches the pair kernel over `pairs` pairs of tokens (and the counting workgroups).  D a multiple of 1024, up to 1024 KVQ_BULK_MAX_WAVES;
 // k_side_v at most KVQ_V_BOUNDED; d_v_new 16-byte aligned.
 __attribute__((visibility("hidden"))) void kvq_v_pair_launch(const kvq_cache *cache, const uint16_t *d_v_new, int T, unsigned pairs,
                                                              int count_wgs, const uint16_t *k_new, uint32_t *k_count, hipStream_t s);
+// Launches kvq_k_bulk; `counts`: the tokens' outlier counts, in a workspace with room for a multiple of four.  D a multiple of 1024 up to
+// 1024 KVQ_BULK_MAX_WAVES; d_k_new 16-byte aligned.
+__attribute__((visibility("hidden"))) void kvq_k_bulk_launch(const kvq_cache *cache, const uint16_t *d_k_new, int T, const uint32_t *counts,
+                                                             hipStream_t s);
+// Tokens of a workgroup's run.
+inline int kvq_k_bulk_run(int bits, int D, int T)
+{
+    // workgroups that the compute units hold at once (188 registers with 4 bits, 128 or fewer with 2 and 3)
+    const int waves = D / 1024, per_cu = (bits == 4 ? 8 : 16) / waves, most = kvq_cu_count() * (per_cu > 0 ? per_cu : 1);
+    return (T + most - 1) / most;
+}

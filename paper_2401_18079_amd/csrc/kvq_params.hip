@@ -1,7 +1,7 @@
 // Host-side helpers of the C ABI and kvq_lut_load (stages one layer's quantization constants).
 #include <math.h>
 #include <string.h>
-#include "kvq_common.hpp"
+#include "kvq_append_keys.hpp"
 
 extern "C" {
 
@@ -12,7 +12,7 @@ int64_t kvq_codes_bytes(int32_t bits, int32_t n_kv_heads, int64_t cap_tokens)
 
 int64_t kvq_params_bytes(int32_t n_kv_heads)
 {
-    int64_t b = kvq_params_bytes_D(n_kv_heads * KVQ_HEAD_DIM);
+    int64_t b = kvq_params_bytes_D(n_kv_heads * KVQ_HEAD_DIM) + kvq_key_params_bytes(n_kv_heads * KVQ_HEAD_DIM);
     return (b + 255) & ~(int64_t)255;
 }
 
@@ -228,6 +228,34 @@ __global__ void kvq_params_expand(void *block, int D)
     ((float *)v.hi)[c] = kvq_h2f(v.hi16[c]);
 }
 
+// What the bulk Key append compares keys with (KvqKeyParams); a workgroup of 64 channels.
+__global__ __launch_bounds__(64) void kvq_params_keys(void *block, int D, int n_thr)
+{
+    const KvqParamsView v = kvq_params_view(block, D);
+    const KvqKeyParams k = kvq_key_params(block, D);
+    const int c = blockIdx.x * 64 + threadIdx.x;         // (D is a multiple of 128)
+    const float s = kvq_h2f(v.s16[c]), z = kvq_h2f(v.z16[c]), rinv = __fdiv_rn(1.0f, s), lo = kvq_h2f(v.lo16[c]), hi = kvq_h2f(v.hi16[c]);
+    const bool normal = s > 0.0f && s < INFINITY && __builtin_fabsf(z) < INFINITY;
+    for (int j = 0; j < n_thr; ++j)                      // (thresholds that are not to be counted on: never read)
+        ((int16_t *)k.thr)[(int64_t)j * D + c] = (int16_t)(normal ? vp_first_key(v.hdr->thr_k[j], s, z, rinv) : 0);
+    // no outlier: not (x < lo or x > hi), where zeros are equal and a NaN bounds nothing
+    auto key = [](float x) { return x == 0.0f ? 0 : vp_key(x); };
+    const int from = lo == lo ? key(lo) - (lo == 0.0f ? 1 : 0) : -31745, to = hi == hi ? key(hi) : 31744;
+    // within the range of the code thresholds: from the first key that reaches -KVQ_CODE_RANGE to the last that does not pass KVQ_CODE_RANGE
+    int first = 32767, last = -32768;
+    if (normal) {
+        first = vp_first_key(-KVQ_CODE_RANGE, s, z, rinv);
+        last = vp_first_key(__builtin_bit_cast(float, __builtin_bit_cast(int, KVQ_CODE_RANGE) + 1), s, z, rinv) - 1;
+    }
+    const bool narrow = first > from || last < to;
+    first = first > from ? first : from;
+    last = last < to ? last : to;
+    ((int16_t *)k.first)[c] = (int16_t)first;
+    ((int16_t *)k.last)[c] = (int16_t)last;
+    const unsigned long long b = __ballot(narrow);
+    if (threadIdx.x < 8) ((uint8_t *)k.narrow)[blockIdx.x * 8 + threadIdx.x] = (uint8_t)(b >> (8 * threadIdx.x));
+}
+
 extern "C" kvq_status kvq_lut_load(kvq_cache *cache, const float *h_lut_k, const float *h_lut_v,
                                    const uint16_t *h_s_k, const uint16_t *h_z_k,
                                    const uint16_t *h_lo_k, const uint16_t *h_hi_k, void *stream)
@@ -270,6 +298,7 @@ extern "C" kvq_status kvq_lut_load(kvq_cache *cache, const float *h_lut_k, const
     KVQ_HIP_CHECK(hipMemcpy(blk + KVQ_PARAMS_HEADER_BYTES + 4 * (size_t)D, h_lo_k, 2 * (size_t)D, hipMemcpyHostToDevice));
     KVQ_HIP_CHECK(hipMemcpy(blk + KVQ_PARAMS_HEADER_BYTES + 6 * (size_t)D, h_hi_k, 2 * (size_t)D, hipMemcpyHostToDevice));
     kvq_params_expand<<<(D + 255) / 256, 256, 0, s>>>(cache->params, D);
+    kvq_params_keys<<<D / 64, 64, 0, s>>>(cache->params, D, ne - 1);
     KVQ_HIP_CHECK(hipGetLastError());
     // bit 0: loaded; bit 1: the thresholds admit no Key outlier at all (every finite fp16 passes), so
     // the score kernel can skip the sparse part

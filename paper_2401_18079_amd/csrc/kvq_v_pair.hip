@@ -1,6 +1,7 @@
 // Bulk Value append, a workgroup per pair of tokens (the two that share the dwords of their codes).
 #include <type_traits>
 #include "kvq_append_common.hpp"
+#include "kvq_append_keys.hpp"
 
 namespace {
 
@@ -20,50 +21,10 @@ namespace {
 // has two keys, take general_selection; far outliers are encoded one by one.  Same arithmetic, same
 // results, as v_quant_token.
 // us per Value append, the kernel with a token on four wavefronts and a lane per element (v_quant_token4) / this one, 1 % outliers:
-// 4096 tokens of 4096 channels, 2 bits 46.8 / 24.8, 3 bits 51.5 / 29.2, 4 bits 56.5 / 36.6; of 5120, 4 bits 77.1 / 54.4; of 8192 116 / 67; 777 of
-// 5120 22.5 / 18.4; 64 of 4096 13.8 / 11.3; 4096 of 3072 (the routine for any width before) 82.4 / 32.5.  Bound by vector issue still, with six wavefronts
-// a SIMD (five: 5120 channels 44.9 / 41.8, 3 bits; eight, which spill: 40.9, but 4096 channels 30.3).
+// 4096 tokens of 4096 channels, 2 bits 46.8 / 23.9, 3 bits 51.5 / 26.5, 4 bits 56.5 / 29.6; of 5120, 4 bits 77.1 / 44.2; of 8192 116 / 55; 777 of
+// 5120 22.5 / 15.0; 64 of 4096 13.8 / 11.3; 4096 of 3072 (the routine for any width before) 82.4 / 25.8.  Bound by vector issue, with six wavefronts
+// a SIMD (five: 5120 channels 44.9 / 41.8 at first, 3 bits; eight, which spill: 40.9, but 4096 channels 30.3 against 29.2).
 
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned short u16x2v __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ s16x2 vp_keys(uint32_t two)                     // and back again
-{
-    const s16x2 x = __builtin_bit_cast(s16x2, two);
-    const uint32_t sign = __builtin_bit_cast(uint32_t, x >> (short)15);
-    return __builtin_bit_cast(s16x2, two ^ (sign & 0x7FFF7FFFu));
-}
-__device__ __forceinline__ float vp_value(int key)
-{
-    return kvq_h2f((uint16_t)(key ^ ((key >> 15) & 0x7FFF)));
-}
-__device__ __forceinline__ int vp_key(float x)                              // of x rounded to fp16
-{
-    const int b = (int16_t)kvq_f2h_rn(x);
-    return b ^ ((b >> 15) & 0x7FFF);
-}
-__device__ __forceinline__ uint32_t vp_word(s16x2 v) { return __builtin_bit_cast(uint32_t, v); }
-__device__ __forceinline__ s16x2 vp_both(int k) { return s16x2{(short)k, (short)k}; }
-__device__ __forceinline__ s16x2 vp_pair(uint32_t w) { return __builtin_bit_cast(s16x2, w); }
-// all ones where a < b
-__device__ __forceinline__ uint32_t vp_less(s16x2 a, s16x2 b) { return vp_word(__builtin_elementwise_sub_sat(a, b) >> (short)15); }
-__device__ __forceinline__ uint32_t vp_select(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
-
-template <int CTRL, int ROWS = 0xf>
-__device__ __forceinline__ uint32_t vp_dpp(uint32_t old, uint32_t v)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xf, false);
-}
-// Sums over the lanes up to and including this one.
-__device__ __forceinline__ uint32_t vp_scan(uint32_t v)
-{
-    v += vp_dpp<0x111>(0u, v);
-    v += vp_dpp<0x112>(0u, v);
-    v += vp_dpp<0x114>(0u, v);
-    v += vp_dpp<0x118>(0u, v);
-    v += vp_dpp<0x142, 0xa>(0u, v);            // lane 15 of rows 0 and 2 into rows 1 and 3
-    v += vp_dpp<0x143, 0xc>(0u, v);            // lane 31 into rows 2 and 3
-    return v;
-}
 // Packed maxima over the wavefront (two numbers at once), in every lane.
 __device__ __forceinline__ s16x2 vp_wave_max(s16x2 v)
 {
@@ -84,9 +45,9 @@ struct VpLds {
     uint16_t cand[4][KVQ_V_CAND];              // candidates, + 32768
     int bound[4];
     struct { int tau; uint32_t need, n_eq; } found[4];     // threshold; how many of its equals are taken, how many there are
-    uint4 wave_red[KVQ_V_PAIR_MAX_WAVES];              // of a wavefront's inliers (tokens packed): largest, complement of smallest; outliers
+    __attribute__((aligned(16))) uint32_t wave_red[3][KVQ_BULK_MAX_WAVES];       // of a wavefront's inliers (tokens packed): largest, complement of smallest; outliers
     uint32_t counts[17][2];                    // general_selection's rounds
-    uint32_t eq[KVQ_V_PAIR_MAX_WAVES][2];
+    uint32_t eq[KVQ_BULK_MAX_WAVES][2];
     float lut[16];
 };
 
@@ -216,7 +177,7 @@ __device__ __forceinline__ uint32_t drop_equals(VpLds &lds, const s16x2 (&s)[2][
 }
 
 template <int BITS, class SP>
-__global__ __launch_bounds__(64 * KVQ_V_PAIR_MAX_WAVES) __attribute__((amdgpu_waves_per_eu(6))) void kvq_v_pair(const void *__restrict__ params, int D, int64_t cap, int64_t n0,
+__global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) __attribute__((amdgpu_waves_per_eu(6))) void kvq_v_pair(const void *__restrict__ params, int D, int64_t cap, int64_t n0,
                                                                 int T, int k_side, const uint16_t *__restrict__ v_new,
                                                                 uint8_t *__restrict__ v_codes, uint16_t *__restrict__ v_sz,
                                                                 uint32_t *__restrict__ v_ptr, const SP vsp, int64_t cap_nnz,
@@ -232,7 +193,9 @@ __global__ __launch_bounds__(64 * KVQ_V_PAIR_MAX_WAVES) __attribute__((amdgpu_wa
         if (t < T) k_count_token(params, D, count.k_new, count.cnt, t);
         return;
     }
-    const int64_t m = (n0 >> 1) + ((int)blockIdx.x - count.wgs);           // the pair
+    const unsigned place = kvq_xcd_place(blockIdx.x - count.wgs, gridDim.x - count.wgs);
+    const int64_t m = (n0 >> 1) + place;                                   // the pair
+    if (2 * m >= n0 + T) return;
     const int t0 = (int)(2 * m - n0);                                      // the first one's place in the call; -1: not of this call
     const uint32_t own = (t0 >= 0 ? 1u : 0u) | (t0 + 1 < T ? 2u : 0u);     // tokens of the call (a missing one repeats the other)
     const uint32_t K = (uint32_t)k_side;
@@ -255,6 +218,7 @@ __global__ __launch_bounds__(64 * KVQ_V_PAIR_MAX_WAVES) __attribute__((amdgpu_wa
     if (tid < 16) lds.lut[tid] = pv.hdr->lut_v[tid & (NE - 1)];
     for (int i = tid; i < 4 * 64; i += NT) (&lds.col_max[0][0])[i] = -32768;
     if (tid < 4) lds.n_cand[tid] = 0;
+    if (tid < 3 * KVQ_BULK_MAX_WAVES) (&lds.wave_red[0][0])[tid] = tid < 2 * KVQ_BULK_MAX_WAVES ? 0x80008000u : 0u;
     __syncthreads();
     s16x2 hi[2], lo[2];
 #pragma unroll
@@ -419,15 +383,22 @@ __global__ __launch_bounds__(64 * KVQ_V_PAIR_MAX_WAVES) __attribute__((amdgpu_wa
         auto smaller = [](s16x2 v) { return v.x < v.y ? v.x : v.y; };
         const s16x2 a = vp_wave_max(s16x2{larger(mx[0]), larger(mx[1])});
         const s16x2 b = vp_wave_max(s16x2{(short)~smaller(mn[0]), (short)~smaller(mn[1])});
-        if (lane == 63) lds.wave_red[wave] = uint4{vp_word(a), vp_word(b), upto, 0u};
+        if (lane == 63) { lds.wave_red[0][wave] = vp_word(a); lds.wave_red[1][wave] = vp_word(b); lds.wave_red[2][wave] = upto; }
         __syncthreads();
+        uint32_t r[3][8];                                // (wavefronts that there are not: no keys, no outliers)
+        static_assert(KVQ_BULK_MAX_WAVES == 8, "two loads");
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const uint4 x = *(const uint4 *)&lds.wave_red[i][0], y = *(const uint4 *)&lds.wave_red[i][4];
+            r[i][0] = x.x; r[i][1] = x.y; r[i][2] = x.z; r[i][3] = x.w; r[i][4] = y.x; r[i][5] = y.y; r[i][6] = y.z; r[i][7] = y.w;
+        }
         top = bot = vp_both(-32768);
         before = upto - n_out;
-        for (int w = 0; w < nw; ++w) {
-            const uint4 r = lds.wave_red[w];
-            top = __builtin_elementwise_max(top, vp_pair(r.x));
-            bot = __builtin_elementwise_max(bot, vp_pair(r.y));
-            before += w < wave ? r.z : 0u;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            top = __builtin_elementwise_max(top, vp_pair(r[0][w]));
+            bot = __builtin_elementwise_max(bot, vp_pair(r[1][w]));
+            before += w < wave ? r[2][w] : 0u;
         }
     };
     reduce();
@@ -484,27 +455,7 @@ __global__ __launch_bounds__(64 * KVQ_V_PAIR_MAX_WAVES) __attribute__((amdgpu_wa
     const bool plain = !nan && coder.range > 0.0f && s2[0] < INFINITY && s2[1] < INFINITY && __builtin_fabsf(z2[0]) < INFINITY &&
                        __builtin_fabsf(z2[1]) < INFINITY;
     if (plain) {
-        auto reaches = [&](int key) { return (vp_value(key) - zf) * rinv >= thr; };
-        const int guess = vp_key(__builtin_fmaf(thr, sf, zf));
-        int below = 0;
-        bool first = false, last = false;
-#pragma unroll
-        for (int i = -2; i <= 2; ++i) {
-            const bool r = reaches(guess + i);
-            below += r ? 0 : 1;
-            if (i == -2) first = r;
-            if (i == 2) last = r;
-        }
-        int kj = guess - 2 + below;
-        if (first || !last) {                            // (thresholds past the largest number, scales of few bits)
-            int a = -31744, b = 31744;                   // keys of finite numbers, and none
-            while (a < b) {
-                const int mid = (a + b) >> 1;
-                if (reaches(mid)) b = mid;
-                else a = mid + 1;
-            }
-            kj = a;
-        }
+        const int kj = vp_first_key(thr, sf, zf, rinv);
         const uint32_t twice = ((uint32_t)kj & 0xFFFFu) * 0x10001u;
 #pragma unroll
         for (int tok = 0; tok < 2; ++tok) {
@@ -622,9 +573,10 @@ void kvq_v_pair_launch(const kvq_cache *c, const uint16_t *d_v_new, int T, unsig
                        uint32_t *k_count, hipStream_t s)
 {
     const int D = c->n_kv_heads * KVQ_HEAD_DIM;
+    count_wgs = (int)kvq_xcd_grid(count_wgs);            // (the pairs' places count from a multiple of eight)
     const KeyCount count = {count_wgs, k_new, k_count};
     const auto launch = [&](auto bits, const auto vsp) {
-        kvq_v_pair<decltype(bits)::value><<<pairs + count_wgs, D / 16, 4 * D, s>>>(
+        kvq_v_pair<decltype(bits)::value><<<kvq_xcd_grid(pairs) + count_wgs, D / 16, 4 * D, s>>>(
             c->params, D, c->cap_tokens, c->n_tokens_v, T, c->k_side_v, d_v_new, c->v_codes, c->v_sz, c->v_ptr, vsp, c->cap_nnz_v,
             c->d_status, count);
     };

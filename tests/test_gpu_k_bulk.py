@@ -1,0 +1,107 @@
+"""The bulk Key append with packed keys: every width of its rule and the call lengths at either side of it, runs that end short,
+constants at which a short cut does not hold (open thresholds with elements beyond the code range, thresholds at zero of either
+sign, scales of a few bits, zero or huge, signposts whose codes cannot be counted), full outlier arrays, infinities and NaN.
+Bit-exact against the oracle, or, where constants or elements are outside its contract, against one-token calls, which another
+kernel takes."""
+import numpy as np
+import pytest
+
+import kvq_synth as S
+from oracle import kvq_oracle as O
+from kvq_testlib import Setup, compare_caches
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("heads,bits,T,n0,blocked", [
+    (8, 2, 64, 0, False), (8, 3, 65, 1, True), (8, 4, 63, 0, False), (16, 3, 129, 3, False), (24, 4, 131, 0, True), (32, 2, 255, 1, False),
+    (32, 3, 1027, 0, False), (32, 4, 700, 5, True), (40, 3, 64, 1, False), (40, 4, 771, 0, False), (48, 2, 130, 0, False), (56, 4, 129, 1, False),
+    (64, 3, 515, 0, False), (64, 4, 128, 0, True), (36, 3, 130, 0, False),
+])
+def test_keys_match_the_oracle(heads, bits, T, n0, blocked):
+    import torch
+    import paper_2401_18079_amd as K
+    wl = S.workload("c2", n_kv_heads=heads, n_q_heads=heads, bits=bits)
+    st = Setup(wl)
+    cap = (n0 + T + 127) // 128 * 128
+    k, v = st.k(0, n0 + T), st.v(0, n0 + T)
+    oc = O.OracleCache(bits, heads, heads, cap, st.k_side, wl.rope_base, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi,
+                       cap_nnz_k=max(1024, st.cap_nnz_k(cap)))
+    nnz = max(1024, st.cap_nnz_k(cap))
+    gc = K.KvqCache(bits, heads, heads, cap, st.k_side, wl.rope_base, nnz, nnz_block_entries=1024 if blocked else None)
+    K.kvq_lut_load(gc, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
+    for a, b in ((0, n0), (n0, n0 + T)):
+        if a < b:
+            oc.append_k(k[a:b]); oc.append_v(v[a:b])
+            K.kvq_quantize_append_kv(gc, torch.from_numpy(k[a:b]).cuda(), torch.from_numpy(v[a:b]).cuda())
+    bad = compare_caches(oc, gc)
+    assert not bad, bad
+
+
+def _constants(D, rng, kind):
+    s = np.exp(rng.standard_normal(D)).astype(np.float16)
+    z = rng.standard_normal(D).astype(np.float16)
+    lo, hi = (z - s).astype(np.float16), (z + s).astype(np.float16)
+    if kind == "open":
+        lo[:], hi[:] = np.float16(-65504), np.float16(65504)
+        s[::3] = np.float16(1e-3)                        # elements far beyond the code range that are no outliers
+    elif kind == "odd":
+        e = np.arange(D) % 16
+        lo[e == 0], hi[e == 1] = np.float16(0.0), np.float16(0.0)
+        lo[e == 2], hi[e == 3] = np.float16(-0.0), np.float16(-0.0)
+        s[e == 4] = np.float16(2.0 ** -24)
+        s[e == 5] = np.float16(0.0)
+        s[e == 6], z[e == 6] = np.float16(60000), np.float16(-60000)
+        lo[e == 7], hi[e == 7] = np.float16(2.0), np.float16(-2.0)               # everything is an outlier
+        lo[e == 8], hi[e == 8] = np.float16(np.nan), np.float16(np.nan)          # nothing is
+        lo[e == 9], hi[e == 10] = np.float16(-np.inf), np.float16(np.inf)
+        s[e == 11] = np.float16(-1.0)
+        z[e == 12] = np.float16(np.inf)
+    return s, z, lo, hi
+
+
+@pytest.mark.parametrize("heads,bits,kind,posts,nnz", [
+    (8, 2, "open", "plain", 1 << 16), (8, 3, "open", "plain", 1 << 16), (16, 4, "open", "plain", 1 << 17),
+    (8, 3, "odd", "plain", 1 << 17), (16, 4, "odd", "plain", 1 << 18), (24, 2, "odd", "plain", 1 << 18),
+    (8, 3, "plain", "wide", 1 << 17), (8, 4, "odd", "close", 1 << 17),           # codes that thresholds do not give
+    (8, 3, "plain", "plain", 3000), (8, 4, "odd", "plain", 20001),               # full arrays
+])
+def test_constants_at_the_edges_as_in_one_token_calls(heads, bits, kind, posts, nnz):
+    import torch
+    import paper_2401_18079_amd as K
+    rng = np.random.default_rng(heads + bits + nnz)
+    D, T, n0 = heads * 128, 67, 1
+    s, z, lo, hi = _constants(D, rng, kind)
+    lut = np.linspace(-1, 1, 1 << bits).astype(np.float32)
+    if posts == "wide":
+        lut = lut * 3
+    elif posts == "close":
+        lut[2] = lut[1] + np.float32(2.0 ** -10) / 64
+    x = (rng.standard_normal((n0 + T, D)) * 2 * np.exp(0.5 * rng.standard_normal(D))).astype(np.float16)
+    x[5, :200] = np.float16(0.0); x[5, 200:400] = np.float16(-0.0)
+    x[9, rng.permutation(D)[:60]] = np.float16(6e4)
+    x[20, rng.permutation(D)[:9]] = np.float16(np.nan)
+    x[33, rng.permutation(D)[:9]] = np.float16(np.inf)
+    x[34, rng.permutation(D)[:3]] = np.float16(-np.inf)
+    dev = torch.from_numpy(x).cuda()
+    got = []
+    for whole in (True, False):
+        gc = K.KvqCache(bits, heads, heads, 128, 1, 10000.0, nnz)
+        K.kvq_lut_load(gc, lut, lut, s, z, lo, hi)
+        K.kvq_quantize_append_k(gc, dev[:n0])
+        if whole:
+            K.kvq_quantize_append_k(gc, dev[n0:])
+        else:
+            for t in range(n0, n0 + T):
+                K.kvq_quantize_append_k(gc, dev[t:t + 1])
+        torch.cuda.synchronize()
+        n = int(gc.k_ptr.cpu().numpy().view(np.uint32)[n0 + T])
+        got.append((gc.status(), n, {f: getattr(gc, f).cpu().numpy().copy() for f in ("k_codes", "k_ptr")},
+                    gc.k_idx.cpu().numpy()[:n].copy(), gc.k_val.cpu().numpy()[:n].copy()))
+    a, b = got
+    assert a[0] == b[0] and (a[0] != 0) == (a[1] == nnz) and a[1] == b[1], (a[:2], b[:2])
+    for f in a[2]:
+        assert np.array_equal(a[2][f].view(np.uint8), b[2][f].view(np.uint8)), f
+    assert np.array_equal(a[3].view(np.uint16), b[3].view(np.uint16))
+    va, vb = a[4].view(np.float16), b[4].view(np.float16)
+    assert np.array_equal(va.view(np.uint16)[~np.isnan(va)], vb.view(np.uint16)[~np.isnan(vb)]) and np.array_equal(np.isnan(va), np.isnan(vb))
