@@ -764,6 +764,27 @@ __device__ __forceinline__ void hist_count(uint32_t *hist, bool in, uint32_t bin
     else if (in && bin != bin0) atomicAdd(&hist[bin], 1u);
 }
 
+// The largest x below 2^(2 STEPS) that at least `rank` of the wavefront's numbers reach (N a lane), two bits at a time: the three
+// questions of a step do not wait for one another.  For one wavefront alone: the steps are a chain of a ballot, a count and a choice,
+// and sixteen wavefronts that all went through it took four times as long.
+template <int N, int STEPS>
+__device__ __forceinline__ uint32_t wave_rank(const uint32_t (&v)[N], uint32_t rank, int steps = STEPS)
+{
+    auto reached = [&](uint32_t x) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i) c += (uint32_t)__popcll(__ballot(v[i] >= x));
+        return c >= rank;
+    };
+    uint32_t x = 0;
+    for (int s = steps - 1; s >= 0; --s) {
+        const uint32_t d = 1u << (2 * s);
+        const bool a = reached(x + d), b = reached(x + 2 * d), c = reached(x + 3 * d);
+        x += c ? 3 * d : b ? 2 * d : a ? d : 0u;
+    }
+    return x;
+}
+
 // ---- bulk Value append -----------------------------------------------------------------------
 // Value append: W wavefronts per token, D = 64 W JW channels; in bulk four (JW = 4, 8, 16, 20, 26 or 32), with two
 // tokens (TOK), the pair that shares dwords, in a workgroup.  Wavefront w of a token takes the channel groups j = w JW .. (w + 1) JW - 1, lane l of it the channels
@@ -799,6 +820,8 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
     __shared__ uint32_t col_max_s[TOK][2][64], n_cand_s[TOK][2];
     __shared__ uint16_t cand_s[TOK][2][KVQ_V_CAND];
     __shared__ float red_mx_s[TOK][W], red_mn_s[TOK][W];
+    // by side: the bound, as searched for; the threshold, likewise, how many candidates lie beyond it and how many equal it
+    __shared__ uint32_t bound_s[TOK][2], found_s[TOK][2][3];
     // wavefronts 0 .. W-1 take the pair's first token, the next W its second; `wave`: within the token
     const int lane = threadIdx.x & 63;
     const int tok = TOK == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x / NTW));
@@ -858,7 +881,7 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
     if (K > 0) {
         // Bounds of the thresholds.  The K-th largest of the 64 columns' largest keys is a lower bound of the
         // token's K-th largest key, since that many elements are at least as large; likewise for the smallest.
-        // Every wavefront finds both by bisection over the 16 key bits, with ballots.  With more outliers per side
+        // One wavefront finds each, two key bits at a time, with ballots.  With more outliers per side
         // than KVQ_V_BOUNDED the bounds let more keys pass than a list holds (64 columns: 64 ln(64 / (64 - K)) are
         // expected, 107 for K = 52): none are taken, every key goes to the histograms.
         atomicMax(&col_max[0][lane], kmax);
@@ -866,14 +889,13 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
         __syncthreads();
         uint32_t m_top = 0, m_bot = 0xffffu;
         if (K <= KVQ_V_BOUNDED) {
-            const uint32_t ct = col_max[0][lane], cb = col_max[1][lane];
-            uint32_t inv_bot = 0;
-            for (int bit = 15; bit >= 0; --bit) {
-                const uint32_t mt = m_top | (1u << bit), mb = inv_bot | (1u << bit);
-                if ((uint32_t)__popcll(__ballot(ct >= mt)) >= K) m_top = mt;
-                if ((uint32_t)__popcll(__ballot(cb >= mb)) >= K) inv_bot = mb;
+            if (wave < 2) {                      // a wavefront a side
+                const uint32_t c[1] = {col_max[wave][lane]}, x = wave_rank<1, 8>(c, K);
+                if (lane == 0) bound_s[tok][wave] = x;
             }
-            m_bot = 0xffffu - inv_bot;
+            __syncthreads();
+            m_top = bound_s[tok][0];
+            m_bot = 0xffffu - bound_s[tok][1];
         }
         // The few keys on and beyond the bounds (24 a side are expected of 4096 for K = 20) are collected,
         // in any order, and the thresholds are found among them.
@@ -918,33 +940,46 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
             few = few && other[0] <= KVQ_V_CAND && other[1] <= KVQ_V_CAND;
         }
         if (few) {
-            // K-th largest candidate of either list, bit by bit (a list has at least K entries)
-            uint32_t vt[KVQ_V_CAND / 64], vb[KVQ_V_CAND / 64];
-            constexpr int R = KVQ_V_CAND / 64;
+            // K-th largest candidate of either list, which has at least K entries; its keys lie between the bound and the largest, + 1
+            // from the bound, so that an absent entry is below all
+            if (wave < 2) {
+                const uint32_t n = wave ? nb : nt, from = bound_s[tok][wave];
+                constexpr int R = KVQ_V_CAND / 64;
+                uint32_t v[R], most = 0;
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const uint32_t e = (uint32_t)lane + 64u * r;
-                vt[r] = e < nt ? cand[0][e] + 1u : 0u;       // + 1: an absent entry is below every key
-                vb[r] = e < nb ? cand[1][e] + 1u : 0u;
-            }
-            auto at_least = [&](const uint32_t (&v)[R], uint32_t x) {
-                uint32_t c = 0;
+                for (int r = 0; r < R; ++r) {
+                    const uint32_t e = (uint32_t)lane + 64u * r;
+                    v[r] = e < n ? cand[wave][e] - from + 1u : 0u;
+                    most = v[r] > most ? v[r] : most;
+                }
+                most = kvq_dpp_max_u32(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0x128, 0xf, 0xf, false));
+                most = kvq_dpp_max_u32(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0x124, 0xf, 0xf, false));
+                most = kvq_dpp_max_u32(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0x122, 0xf, 0xf, false));
+                most = kvq_dpp_max_u32(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0x121, 0xf, 0xf, false));
+                most = (uint32_t)(__builtin_amdgcn_readlane((int)most, 0) | __builtin_amdgcn_readlane((int)most, 16) |
+                                  __builtin_amdgcn_readlane((int)most, 32) | __builtin_amdgcn_readlane((int)most, 48));   // (its highest bit)
+                const int steps = (33 - __builtin_clz(most)) / 2;
+                const uint32_t x = wave_rank<R, 9>(v, K, steps);
+                auto at_least = [&](uint32_t y) {
+                    uint32_t c = 0;
 #pragma unroll
-                for (int r = 0; r < R; ++r) c += (uint32_t)__popcll(__ballot(v[r] >= x));
-                return c;
-            };
-            uint32_t tt = 0, tb = 0;
-            for (int bit = 16; bit >= 0; --bit) {
-                if (at_least(vt, tt | (1u << bit)) >= K) tt |= 1u << bit;
-                if (at_least(vb, tb | (1u << bit)) >= K) tb |= 1u << bit;
+                    for (int r = 0; r < R; ++r) c += (uint32_t)__popcll(__ballot(v[r] >= y));
+                    return c;
+                };
+                const uint32_t beyond = at_least(x + 1u), reached = at_least(x);
+                if (lane == 0) {
+                    found_s[tok][wave][0] = x - 1u + from;
+                    found_s[tok][wave][1] = beyond;
+                    found_s[tok][wave][2] = reached - beyond;
+                }
             }
-            const uint32_t beyond_t = at_least(vt, tt + 1u), beyond_b = at_least(vb, tb + 1u);
-            n_eq_top = at_least(vt, tt) - beyond_t;
-            n_eq_bot = at_least(vb, tb) - beyond_b;
-            tau_top = tt - 1u;
-            tau_bot = 0xffffu - (tb - 1u);
-            need_top = K - beyond_t;
-            need_bot = K - beyond_b;
+            __syncthreads();
+            tau_top = found_s[tok][0][0];
+            tau_bot = 0xffffu - found_s[tok][1][0];
+            need_top = K - found_s[tok][0][1];
+            need_bot = K - found_s[tok][1][1];
+            n_eq_top = found_s[tok][0][2];
+            n_eq_bot = found_s[tok][1][2];
         } else {
             // Many equal keys, or more outliers per side than the bounds serve: radix selection on histograms,
             // of the keys that passed.  Counts are exact from the bounds outwards, which is all the searches read.
