@@ -785,6 +785,41 @@ __device__ __forceinline__ uint32_t wave_rank(const uint32_t (&v)[N], uint32_t r
     return x;
 }
 
+// A number whose highest bit is that of the largest of the wavefront's.
+__device__ __forceinline__ uint32_t wave_magnitude(uint32_t v)
+{
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xf, 0xf, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xf, 0xf, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xf, 0xf, false);
+    return (uint32_t)(__builtin_amdgcn_readlane((int)v, 0) | __builtin_amdgcn_readlane((int)v, 16) |
+                      __builtin_amdgcn_readlane((int)v, 32) | __builtin_amdgcn_readlane((int)v, 48));
+}
+// Among the wavefront's keys (N a lane; `extreme`: this lane's largest), the rank-th largest, how many of the keys equal to it are among the `rank`
+// largest, and how many there are.  The rank-th largest of the lanes' extremes bounds it from below.
+template <int N>
+__device__ __forceinline__ void wave_threshold(const uint32_t (&key)[N], uint32_t extreme, uint32_t rank, uint32_t &tau, uint32_t &need, uint32_t &n_eq)
+{
+    uint32_t from = 0;
+    if (N > 2 && rank <= 64u) {
+        const uint32_t c[1] = {extreme};
+        from = wave_rank<1, 8>(c, rank);
+    }
+    uint32_t v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = key[i] >= from ? key[i] - from + 1u : 0u;
+    const uint32_t x = wave_rank<N, 9>(v, rank, (33 - __builtin_clz(wave_magnitude(extreme >= from ? extreme - from + 1u : 0u))) / 2);
+    uint32_t beyond = 0, reached = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        beyond += (uint32_t)__popcll(__ballot(v[i] > x));
+        reached += (uint32_t)__popcll(__ballot(v[i] >= x));
+    }
+    tau = x - 1u + from;
+    need = rank - beyond;
+    n_eq = reached - beyond;
+}
+
 // ---- bulk Value append -----------------------------------------------------------------------
 // Value append: W wavefronts per token, D = 64 W JW channels; in bulk four (JW = 4, 8, 16, 20, 26 or 32), with two
 // tokens (TOK), the pair that shares dwords, in a workgroup.  Wavefront w of a token takes the channel groups j = w JW .. (w + 1) JW - 1, lane l of it the channels
@@ -884,6 +919,15 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
         // One wavefront finds each, two key bits at a time, with ballots.  With more outliers per side
         // than KVQ_V_BOUNDED the bounds let more keys pass than a list holds (64 columns: 64 ln(64 / (64 - K)) are
         // expected, 107 for K = 52): none are taken, every key goes to the histograms.
+        uint32_t tau_top, tau_bot, need_top, need_bot, n_eq_top, n_eq_bot;
+        if constexpr (W == 1) {                  // one wavefront has them all
+            uint32_t inv[JW];
+#pragma unroll
+            for (int i = 0; i < JW; ++i) inv[i] = 0xffffu - kc[i];
+            wave_threshold<JW>(kc, kmax, K, tau_top, need_top, n_eq_top);
+            wave_threshold<JW>(inv, 0xffffu - kmin, K, tau_bot, need_bot, n_eq_bot);
+            tau_bot = 0xffffu - tau_bot;
+        } else {
         atomicMax(&col_max[0][lane], kmax);
         atomicMax(&col_max[1][lane], 0xffffu - kmin);
         __syncthreads();
@@ -932,7 +976,6 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
             }
         }
         __syncthreads();
-        uint32_t tau_top, tau_bot, need_top, need_bot, n_eq_top, n_eq_bot;
         const uint32_t nt = n_cand[0], nb = n_cand[1];
         bool few = K <= KVQ_V_BOUNDED && nt <= KVQ_V_CAND && nb <= KVQ_V_CAND;
         if (TOK == 2) {                          // (barriers below: both tokens take the same way)
@@ -952,13 +995,7 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
                     v[r] = e < n ? cand[wave][e] - from + 1u : 0u;
                     most = v[r] > most ? v[r] : most;
                 }
-                most = kvq_dpp_max_u32(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0x128, 0xf, 0xf, false));
-                most = kvq_dpp_max_u32(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0x124, 0xf, 0xf, false));
-                most = kvq_dpp_max_u32(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0x122, 0xf, 0xf, false));
-                most = kvq_dpp_max_u32(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0x121, 0xf, 0xf, false));
-                most = (uint32_t)(__builtin_amdgcn_readlane((int)most, 0) | __builtin_amdgcn_readlane((int)most, 16) |
-                                  __builtin_amdgcn_readlane((int)most, 32) | __builtin_amdgcn_readlane((int)most, 48));   // (its highest bit)
-                const int steps = (33 - __builtin_clz(most)) / 2;
+                const int steps = (33 - __builtin_clz(wave_magnitude(most))) / 2;
                 const uint32_t x = wave_rank<R, 9>(v, K, steps);
                 auto at_least = [&](uint32_t y) {
                     uint32_t c = 0;
@@ -1020,6 +1057,7 @@ __device__ __forceinline__ void v_quant_token4(const void *__restrict__ params, 
             tau_bot = (bin_bot << 8) | lo_bot;
             need_top = K - (above_top + above_in);
             need_bot = K - (below_bot + below_in);
+        }
         }
         const bool same = tau_top == tau_bot;
         // ranks of equal keys are only needed when some but not all of them are taken (the same in all of a
@@ -1377,6 +1415,10 @@ static bool wide_wg(int D, int T) { return D >= 2048 && T < KVQ_BULK_TOKENS; }
 // 8192, spread over four (1024), eight (2048) or sixteen wavefronts with D / 1024 elements per lane; 0 for the others,
 // whose tokens v_quant_token selects from in LDS.
 static int small_width(int D) { return D % 1024 == 0 && D <= 8192 ? D / 1024 : 0; }
+// One to three heads, in bulk four: a wavefront per Value token, D / 64 elements per lane (0: wider).  us per Value append, 256 threads a token with
+// the selection in LDS / a wavefront: 4096 tokens of 128 channels, 2 bits 17.2 / 8.0, of 256 18.0 / 8.3, of 384 20.4 / 12.6, of 512 21.5 / 15.3; but 1000
+// tokens of 512, 4 bits, 11.4 / 10.7, 100 8.0 / 8.9; the append kernel of a step of one head 6.2 / 4.5.
+static int narrow_width(int D, int T) { return D <= (T >= 2048 ? 512 : 384) ? D / 128 : 0; }
 
 static kvq_status append_checks(const kvq_cache *cache, const void *src, int32_t T, int64_t n_now)
 {
@@ -1469,7 +1511,7 @@ static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T,
     kvq_v_quant4<B, J, WV, TOK><<<(GRID) + keys.wgs, 64 * (WV) * (TOK), 0, s>>>(                               \
         cache->params, D, cache->cap_tokens, cache->n_tokens_v, T, cache->k_side_v, d_v_new, cache->v_codes,   \
         cache->v_sz, cache->v_ptr, vsp, cache->cap_nnz_v, cache->d_status, keys)
-    const int small = T < KVQ_VW_SMALL_TOKENS ? small_width(D) : 0;
+    const int small = T < KVQ_VW_SMALL_TOKENS ? small_width(D) : 0, narrow = narrow_width(D, T);
     const bool in_pairs = !small && (D == 4096 || D == 2048 || D == 1024 || (T >= KVQ_BULK_TOKENS && (D == 5120 || D == 6656 || D == 8192)));
     // The pair kernel, one wavefront per 1024 channels and pair, takes calls of 64 tokens and more, but of one or two wavefronts a pair only
     // longer ones: below, a token of 1024 or 2048 channels is sooner done by four wavefronts (us, four / one or two wavefronts: 1024 channels,
@@ -1492,7 +1534,11 @@ static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T,
 #define LAUNCH_V4(B, J) LAUNCH_V4W(B, J, KVQ_VW_WAVES, 2, pairs)
 #define LAUNCH_V(B)                                                                                             \
     do {                                                                                                        \
-        if (small == 1) LAUNCH_V4W(B, 4, 4, 1, T);                                                              \
+        if (narrow == 1) LAUNCH_V4W(B, 2, 1, 1, T);                                                             \
+        else if (narrow == 2) LAUNCH_V4W(B, 4, 1, 1, T);                                                        \
+        else if (narrow == 3) LAUNCH_V4W(B, 6, 1, 1, T);                                                        \
+        else if (narrow == 4) LAUNCH_V4W(B, 8, 1, 1, T);                                                        \
+        else if (small == 1) LAUNCH_V4W(B, 4, 4, 1, T);                                                              \
         else if (small == 2) LAUNCH_V4W(B, 4, 8, 1, T);                                                         \
         else if (small == 3) LAUNCH_V4W(B, 3, 16, 1, T);                                                        \
         else if (small == 4) LAUNCH_V4W(B, 4, 16, 1, T);                                                        \
@@ -1576,7 +1622,10 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
 #define LAUNCH_KVW(B, NT, VJ, VW) kvq_kv_quant<B, NT, VJ, VW><<<2 * T, NT, (VJ) > 0 ? 0 : dyn, s>>>(a)
 #define LAUNCH_KV(B)                                                                     \
     do {                                                                                 \
-        switch (small_width(D)) {                                                        \
+        switch (narrow_width(D, T) ? -narrow_width(D, T) : small_width(D)) {             \
+        case -1: LAUNCH_KVW(B, 256, 2, 1); break;                                        \
+        case -2: LAUNCH_KVW(B, 256, 4, 1); break;                                        \
+        case -3: LAUNCH_KVW(B, 256, 6, 1); break;                                        \
         case 1: LAUNCH_KVW(B, 256, 4, 4); break;                                         \
         case 2: LAUNCH_KVW(B, 1024, 4, 8); break;                                        \
         case 3: LAUNCH_KVW(B, 1024, 3, 16); break;                                       \
