@@ -1,6 +1,7 @@
 // What the append kernels share.
 #pragma once
 #include "kvq_select.hpp"
+#include "kvq_append_keys.hpp"
 
 namespace {
 
@@ -41,31 +42,47 @@ struct KvqCoder {
         return code;
     }
 };
+
 // Number of Key outliers of each new token (threshold test only).  One wavefront per token, eight
-// channels per lane and pass (16-byte loads of the fp16 vector, D is a multiple of 128): no barriers.
+// channels per lane and pass (16-byte loads of the fp16 vector, D is a multiple of 128): no barriers.  Bound by its loads' latency in small calls
+// (64 tokens of 4096 channels, Keys and Values 16.8 us with fp32 thresholds, 64 bytes of them per 16 of Keys / 15.4), by vector issue beside the Value
+// kernel in large ones (4096 tokens 49.4 / 48.5).
 constexpr int KVQ_COUNT_NT = 256;
 __device__ __forceinline__ void k_count_token(const void *params, int D, const uint16_t *k_new, uint32_t *cnt, const int t)
 {
     KvqParamsView pv = kvq_params_view(params, D);
     const int lane = threadIdx.x & 63;
-    const uint4 *row = (const uint4 *)(k_new + (int64_t)t * D);
-    const float4 *lo4 = (const float4 *)pv.lo, *hi4 = (const float4 *)pv.hi;
     uint32_t mine = 0;
+    auto one = [&](int c) {
+        const float x = kvq_h2f(k_new[(int64_t)t * D + c]);
+        return ((x < pv.lo[c]) | (x > pv.hi[c])) ? 1u : 0u;
+    };
     if ((uintptr_t)k_new & 15) {          // input not 16-byte aligned: one channel per lane and pass
-        for (int c = lane; c < D; c += 64) {
-            const float x = kvq_h2f(k_new[(int64_t)t * D + c]);
-            mine += ((x < pv.lo[c]) | (x > pv.hi[c])) ? 1u : 0u;
-        }
-    } else for (int v = lane; v < D / 8; v += 64) {
-        const uint4 h = row[v];
-        const float4 la = lo4[2 * v], lb = lo4[2 * v + 1], ha = hi4[2 * v], hb = hi4[2 * v + 1];
-        const uint32_t w[4] = {h.x, h.y, h.z, h.w};
-        const float lo[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
-        const float hi[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
+        for (int c = lane; c < D; c += 64) mine += one(c);
+    } else {
+        // packed keys against the channels' first and last that are no outlier (KvqKeyParams); one by one where the range ends at the code range
+        // and something lies beyond, or an infinity or a NaN is among the elements
+        const KvqKeyParams kp = kvq_key_params(params, D);
+        const uint4 *row = (const uint4 *)(k_new + (int64_t)t * D), *first = (const uint4 *)kp.first, *last = (const uint4 *)kp.last;
+        for (int v = lane; v < D / 8; v += 64) {
+            const uint4 h = row[v], f = first[v], l = last[v];
+            uint32_t narrow = kp.narrow[v];
+            asm("" : "+v"(narrow));      // (requested with the others, not where it is needed)
+            const uint32_t w[4] = {h.x, h.y, h.z, h.w}, fw[4] = {f.x, f.y, f.z, f.w}, lw[4] = {l.x, l.y, l.z, l.w};
+            s16x2 out = {0, 0};           // less the outliers among the even and the odd channels
+            half2_t odd = {(half_t)0, (half_t)0};
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float x = kvq_h2f((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
-            mine += ((x < lo[e]) | (x > hi[e])) ? 1u : 0u;
+            for (int i = 0; i < 4; ++i) {
+                const s16x2 s = vp_keys(w[i]);
+                out += vp_pair(vp_less(s, vp_pair(fw[i])) | vp_less(vp_pair(lw[i]), s));
+                odd = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, w[i]), half2_t{(half_t)0, (half_t)0}, odd);
+            }
+            int n = -(out.x + out.y);
+            if (!(odd.x == (half_t)0) || !(odd.y == (half_t)0) || (n != 0 && narrow != 0)) {
+                n = 0;
+                for (int e = 0; e < 8; ++e) n += one(8 * v + e);
+            }
+            mine += (uint32_t)n;
         }
     }
     for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
