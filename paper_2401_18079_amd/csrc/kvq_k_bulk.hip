@@ -193,7 +193,20 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) void kvq_k_bulk(const void
             const int f = 2 * (w & 3) + half, c = c0 + 64 * up + f;
             const float x = vp_value(key_at(w, half));
             const uint16_t sb = ((const uint16_t *)&bulk_s[(2 + up) * NT + tid])[f], zb = ((const uint16_t *)&bulk_s[(4 + up) * NT + tid])[f];
-            const int code = (int)(uint32_t)(out >> (2 * BITS * f + BITS * up)) & (NE - 1);
+            int code = (int)(uint32_t)(out >> (2 * BITS * f + BITS * up)) & (NE - 1);
+            // Beyond KVQ_CODE_RANGE the thresholds do not give the code, and the outlier thresholds usually lie within it.  (First a test that
+            // needs no reciprocal: fp32 steps shift it by less than one in 2^21, so 126 scales are surely within 127.)
+            const float diff = x - kvq_h2f(zb);
+            if (!(__builtin_fabsf(diff) <= 126.0f * kvq_h2f(sb))) {
+                static_assert(KVQ_CODE_RANGE == 127.0f, "see above");
+                const float xn = diff * pv.rinv[c];
+                if (!(__builtin_fabsf(xn) <= KVQ_CODE_RANGE)) {
+                    float unused;
+                    code = kvq_nearest<NE>(pv.hdr->lut_k, xn, unused);
+                    const int at = 2 * BITS * f + BITS * up;
+                    out = (out & ~((uint64_t)(NE - 1) << at)) | (uint64_t)(uint32_t)code << at;
+                }
+            }
             const uint32_t lower = (((1u << w) - 1u) & (up ? 0xF0u : 0x0Fu)) * 0x00010001u | (half ? 1u << w : 0u);
             const uint64_t pos = base + (up ? rank_up : rank_low) + (uint32_t)__popc(outl & lower);
             if (pos < (uint64_t)cap_nnz)

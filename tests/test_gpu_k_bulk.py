@@ -105,3 +105,35 @@ def test_constants_at_the_edges_as_in_one_token_calls(heads, bits, kind, posts, 
     assert np.array_equal(a[3].view(np.uint16), b[3].view(np.uint16))
     va, vb = a[4].view(np.float16), b[4].view(np.float16)
     assert np.array_equal(va.view(np.uint16)[~np.isnan(va)], vb.view(np.uint16)[~np.isnan(vb)]) and np.array_equal(np.isnan(va), np.isnan(vb))
+
+
+@pytest.mark.parametrize("heads,bits,posts", [(8, 2, "plain"), (16, 3, "plain"), (8, 4, "plain"), (40, 4, "plain"), (8, 2, "near"), (8, 3, "near"),
+                                              (32, 4, "near")])
+def test_codes_of_outliers_beyond_the_code_range(heads, bits, posts):
+    """Channels whose outlier thresholds lie well within the code range, as calibrated ones do, and elements far beyond both: there fp32
+    distances to different signposts round to the same number, and the smaller index wins."""
+    import torch
+    import paper_2401_18079_amd as K
+    rng = np.random.default_rng(heads * 8 + bits)
+    D, T, n0 = heads * 128, 131, 1
+    s, z = np.full(D, 0.01, np.float16), np.zeros(D, np.float16)
+    s[D // 2:], z[D // 2:] = np.float16(0.25), np.float16(-0.5)
+    lo, hi = (z - s).astype(np.float16), (z + s).astype(np.float16)
+    lut = np.linspace(-1, 1, 1 << bits).astype(np.float32)
+    if posts == "near":                                  # two signposts 2^-10 apart at either end: codes can still be counted
+        lut[1], lut[-2] = lut[0] + np.float32(2.0 ** -10), lut[-1] - np.float32(2.0 ** -10)
+    x = (z + s * rng.standard_normal((n0 + T, D)) * 0.3).astype(np.float16)
+    for t in range(n0 + T):
+        at = rng.permutation(D)[:64]
+        far = np.concatenate([[6e4, -6e4, 1200, -1200, 120, -120], rng.uniform(1.2, 1.35, 10), rng.uniform(30, 33, 10), rng.uniform(-2000, 2000, 38)])
+        x[t, at] = far.astype(np.float16)
+    v = rng.standard_normal((n0 + T, D)).astype(np.float16)
+    nnz = 1 << 16
+    oc = O.OracleCache(bits, heads, heads, 256, 4, 10000.0, lut, lut, s, z, lo, hi, cap_nnz_k=nnz)
+    gc = K.KvqCache(bits, heads, heads, 256, 4, 10000.0, nnz)
+    K.kvq_lut_load(gc, lut, lut, s, z, lo, hi)
+    for a, b in ((0, n0), (n0, n0 + T)):
+        oc.append_k(x[a:b]); oc.append_v(v[a:b])
+        K.kvq_quantize_append_kv(gc, torch.from_numpy(x[a:b]).cuda(), torch.from_numpy(v[a:b]).cuda())
+    bad = compare_caches(oc, gc)
+    assert not bad, bad
