@@ -447,7 +447,9 @@ def kvq_calibrate_key_channels(k_cal: torch.Tensor, outlier_fraction: float, str
     lib = load_library()
     ws_bytes = int(lib.kvq_calibrate_key_channels_workspace_bytes(T, D, float(outlier_fraction)))
     try:
-        ws = torch.empty(ws_bytes, dtype=torch.uint8, device=k_cal.device) if ws_bytes else None
+        # (the stream that uses it owns it: one that another stream has freed may still be in that stream's use)
+        with torch.cuda.stream(stream):
+            ws = torch.empty(ws_bytes, dtype=torch.uint8, device=k_cal.device) if ws_bytes else None
     except torch.cuda.OutOfMemoryError:      # the call does without
         ws, ws_bytes = None, 0
     _check(lib.kvq_calibrate_key_channels_ws(k_cal.data_ptr(), T, D, float(outlier_fraction), p, p + 2 * D, p + 4 * D,

@@ -70,3 +70,16 @@ def test_scratch_memory_is_optional_and_checked():
         got = out.cpu().numpy().view(np.float16).reshape(4, D)
         for a, b in zip(got, ref):
             assert np.array_equal(a, b)
+
+
+def test_on_a_stream_of_the_caller():
+    import torch
+    import paper_2401_18079_amd as K
+    T, D, p = 24576, 128, 0.01
+    x = _keys(T, D, "mixed")
+    side = torch.cuda.Stream()
+    dev = torch.from_numpy(x).cuda()
+    side.wait_stream(torch.cuda.current_stream())
+    got = K.kvq_calibrate_key_channels(dev, p, stream=side)
+    for name, a, b in zip(("s", "z", "lo", "hi"), got, C.key_channel_constants(x, p)):
+        assert np.array_equal(a, b), name
