@@ -466,7 +466,8 @@ def kvq_calibrate_nuq(x_norm: torch.Tensor, w: torch.Tensor, bits: int, iters: i
     lib = load_library()
     c = np.ascontiguousarray(np.asarray(init, dtype=np.float32).copy())
     assert c.shape == (1 << bits,)
-    ws = torch.empty(int(lib.kvq_calibrate_workspace_bytes()), dtype=torch.uint8, device=x_norm.device)
+    with torch.cuda.stream(stream):          # (as in kvq_calibrate_key_channels)
+        ws = torch.empty(int(lib.kvq_calibrate_workspace_bytes()), dtype=torch.uint8, device=x_norm.device)
     _check(lib.kvq_calibrate_nuq(x_norm.data_ptr(), w.data_ptr(), x_norm.numel(), int(bits), int(iters),
                                  c.ctypes.data_as(C.c_void_p), ws.data_ptr(), ws.numel(), _stream_ptr(stream)),
            "kvq_calibrate_nuq")

@@ -71,3 +71,11 @@ def test_key_channel_calibration(allocations):
     B.kvq_calibrate_key_channels(_Tensor((32768, 128), torch.float16), 0.01, stream=side)
     B.kvq_calibrate_key_channels(_Tensor((32768, 128), torch.float16), 0.01)
     assert allocations == [(side, 4096), (None, 4096)]
+
+
+def test_signpost_calibration(allocations):
+    side = _side_stream()
+    x = _Tensor((1000,), torch.float32)
+    B.kvq_calibrate_nuq(x, x, 2, 1, [-1, -0.3, 0.3, 1], stream=side)
+    B.kvq_calibrate_nuq(x, x, 2, 1, [-1, -0.3, 0.3, 1])
+    assert allocations == [(side, 8192), (None, 8192)]

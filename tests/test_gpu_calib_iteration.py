@@ -38,3 +38,15 @@ def test_iterations_match_oracle(bits, n, kind):
     got = K.kvq_calibrate_nuq(torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), bits, 2, c0)
     ref = C.nuq_signposts(x, w, c0, 2)
     assert np.allclose(got, ref, rtol=0, atol=ATOL), (got, ref)
+
+
+def test_on_a_stream_of_the_caller():
+    import torch
+    import paper_2401_18079_amd as K
+    x, w = S.gen_calibration(4712, 70001)
+    c0 = _start("even", 4)
+    dx, dw = torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    got = K.kvq_calibrate_nuq(dx, dw, 4, 2, c0, stream=side)
+    assert np.allclose(got, C.nuq_signposts(x, w, c0, 2), rtol=0, atol=ATOL)
