@@ -58,11 +58,12 @@ __device__ inline uint32_t block_rank(bool flag, uint32_t *wave_tot, uint32_t &t
     return before + prefix;
 }
 
+template <bool PACKED>
 __global__ __launch_bounds__(KVQ_COUNT_NT) void kvq_k_count(const void *params, int D, int T, const uint16_t *k_new,
                                                             uint32_t *cnt)
 {
     const int t = blockIdx.x * (KVQ_COUNT_NT / 64) + (threadIdx.x >> 6);
-    if (t < T) k_count_token(params, D, k_new, cnt, t);
+    if (t < T) k_count_token<PACKED>(params, D, k_new, cnt, t);
 }
 
 // ptr[n0+1+t] = min(ptr[n0] + cnt[0] + ... + cnt[t], cap_nnz); one workgroup, T <= 4096.
@@ -1208,7 +1209,7 @@ __global__ __launch_bounds__(64 * W * TOK) void kvq_v_quant4(const void *__restr
 {
     if (TOK == 2 && (int)blockIdx.x < keys.wgs) {
         const int t = (int)blockIdx.x * (W * TOK) + (int)(threadIdx.x >> 6);
-        if (t < T) k_count_token(params, D, keys.k_new, keys.cnt, t);
+        if (t < T) k_count_token<true>(params, D, keys.k_new, keys.cnt, t);
         return;
     }
     v_quant_token4<BITS, JW, W, TOK>(params, D, cap, n0, k_side, v_new, v_codes, v_sz, v_ptr, vsp, cap_nnz, d_status,
@@ -1445,8 +1446,11 @@ static kvq_status append_k(kvq_cache *cache, const uint16_t *d_k_new, int32_t T,
     if (!single) {
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
         uint32_t *cnt = (uint32_t *)cache->workspace;
-        if (!counted)
-            kvq_k_count<<<(T + KVQ_COUNT_NT / 64 - 1) / (KVQ_COUNT_NT / 64), KVQ_COUNT_NT, 0, s>>>(cache->params, D, T, d_k_new, cnt);
+        if (!counted) {
+            const int grid = (T + KVQ_COUNT_NT / 64 - 1) / (KVQ_COUNT_NT / 64);
+            if (bulk) kvq_k_count<true><<<grid, KVQ_COUNT_NT, 0, s>>>(cache->params, D, T, d_k_new, cnt);
+            else kvq_k_count<false><<<grid, KVQ_COUNT_NT, 0, s>>>(cache->params, D, T, d_k_new, cnt);
+        }
         if (!bulk) kvq_ptr_scan<<<1, 1024, 0, s>>>(cache->k_ptr, cache->n_tokens_k, T, cnt, cache->cap_nnz_k, cache->d_status);
     }
 #define LAUNCH_KW(B, HW, W)                                                                                     \
@@ -1614,7 +1618,7 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
     if (!single) {
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
         uint32_t *cnt = (uint32_t *)cache->workspace;
-        kvq_k_count<<<(T + KVQ_COUNT_NT / 64 - 1) / (KVQ_COUNT_NT / 64), KVQ_COUNT_NT, 0, s>>>(cache->params, D, T, d_k_new, cnt);
+        kvq_k_count<false><<<(T + KVQ_COUNT_NT / 64 - 1) / (KVQ_COUNT_NT / 64), KVQ_COUNT_NT, 0, s>>>(cache->params, D, T, d_k_new, cnt);
         kvq_ptr_scan<<<1, 1024, 0, s>>>(cache->k_ptr, cache->n_tokens_k, T, cnt, cache->cap_nnz_k, cache->d_status);
     }
     const size_t dyn = 3 * (size_t)D;

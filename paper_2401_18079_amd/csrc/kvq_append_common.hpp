@@ -47,7 +47,10 @@ struct KvqCoder {
 // channels per lane and pass (16-byte loads of the fp16 vector, D is a multiple of 128): no barriers.  Bound by its loads' latency in small calls
 // (64 tokens of 4096 channels, Keys and Values 16.8 us with fp32 thresholds, 64 bytes of them per 16 of Keys / 15.4), by vector issue beside the Value
 // kernel in large ones (4096 tokens 49.4 / 48.5).
+// PACKED: for kvq_k_bulk, which reads the channels' first and last keys too.  The other Key kernels read the fp32 thresholds, which this one then
+// finds for them: two tokens, 4 bits, us per Key append, packed / fp32 thresholds: 16 heads 8.2 / 8.0, 32 heads 10.2 / 9.9, 64 heads 14.6 / 13.9.
 constexpr int KVQ_COUNT_NT = 256;
+template <bool PACKED>
 __device__ __forceinline__ void k_count_token(const void *params, int D, const uint16_t *k_new, uint32_t *cnt, const int t)
 {
     KvqParamsView pv = kvq_params_view(params, D);
@@ -57,13 +60,28 @@ __device__ __forceinline__ void k_count_token(const void *params, int D, const u
         const float x = kvq_h2f(k_new[(int64_t)t * D + c]);
         return ((x < pv.lo[c]) | (x > pv.hi[c])) ? 1u : 0u;
     };
+    const uint4 *row = (const uint4 *)(k_new + (int64_t)t * D);
     if ((uintptr_t)k_new & 15) {          // input not 16-byte aligned: one channel per lane and pass
         for (int c = lane; c < D; c += 64) mine += one(c);
+    } else if constexpr (!PACKED) {
+        const float4 *lo4 = (const float4 *)pv.lo, *hi4 = (const float4 *)pv.hi;
+        for (int v = lane; v < D / 8; v += 64) {
+            const uint4 h = row[v];
+            const float4 la = lo4[2 * v], lb = lo4[2 * v + 1], ha = hi4[2 * v], hb = hi4[2 * v + 1];
+            const uint32_t w[4] = {h.x, h.y, h.z, h.w};
+            const float lo[8] = {la.x, la.y, la.z, la.w, lb.x, lb.y, lb.z, lb.w};
+            const float hi[8] = {ha.x, ha.y, ha.z, ha.w, hb.x, hb.y, hb.z, hb.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float x = kvq_h2f((uint16_t)(w[e >> 1] >> (16 * (e & 1))));
+                mine += ((x < lo[e]) | (x > hi[e])) ? 1u : 0u;
+            }
+        }
     } else {
         // packed keys against the channels' first and last that are no outlier (KvqKeyParams); one by one where the range ends at the code range
         // and something lies beyond, or an infinity or a NaN is among the elements
         const KvqKeyParams kp = kvq_key_params(params, D);
-        const uint4 *row = (const uint4 *)(k_new + (int64_t)t * D), *first = (const uint4 *)kp.first, *last = (const uint4 *)kp.last;
+        const uint4 *first = (const uint4 *)kp.first, *last = (const uint4 *)kp.last;
         for (int v = lane; v < D / 8; v += 64) {
             const uint4 h = row[v], f = first[v], l = last[v];
             uint32_t narrow = kp.narrow[v];

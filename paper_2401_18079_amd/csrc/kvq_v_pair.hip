@@ -190,7 +190,7 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) __attribute__((amdgpu_wave
     const int NT = blockDim.x, nw = NT >> 6;
     if ((int)blockIdx.x < count.wgs) {
         const int t = (int)blockIdx.x * nw + wave;
-        if (t < T) k_count_token(params, D, count.k_new, count.cnt, t);
+        if (t < T) k_count_token<true>(params, D, count.k_new, count.cnt, t);
         return;
     }
     const unsigned place = kvq_xcd_place(blockIdx.x - count.wgs, gridDim.x - count.wgs);
