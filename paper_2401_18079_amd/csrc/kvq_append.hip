@@ -1418,8 +1418,14 @@ static bool wide_wg(int D, int T) { return D >= 2048 && T < KVQ_BULK_TOKENS; }
 static int small_width(int D) { return D % 1024 == 0 && D <= 8192 ? D / 1024 : 0; }
 // One to three heads, in bulk four: a wavefront per Value token, D / 64 elements per lane (0: wider).  us per Value append, 256 threads a token with
 // the selection in LDS / a wavefront: 4096 tokens of 128 channels, 2 bits 17.2 / 8.0, of 256 18.0 / 8.3, of 384 20.4 / 12.6, of 512 21.5 / 15.3; but 1000
-// tokens of 512, 4 bits, 11.4 / 10.7, 100 8.0 / 8.9; the append kernel of a step of one head 6.2 / 4.5.
-static int narrow_width(int D, int T) { return D <= (T >= 2048 ? 512 : 384) ? D / 128 : 0; }
+// tokens of 512, 4 bits, 11.4 / 10.7, 100 8.0 / 8.9; the append kernel of a step of one head 6.2 / 4.5.  Three heads in short calls, where the six
+// elements a lane make the searches longer than the 256 threads' radix selection (Keys and Values, blocked outlier storage, us): one token, 2 bits
+// 6.1 / 6.4, 3 bits 6.6 / 6.8, 4 bits 7.1 / 7.2; 200 tokens 11.2 / 11.6, 11.8 / 12.0, 12.2 / 12.0; 300 tokens 14.2 / 14.0; no outliers, one token 4.1 / 3.0.
+static int narrow_width(int bits, int D, int T, int k_side)
+{
+    if (D == 384 && k_side > 0 && bits < 4 && T < KVQ_KV_SPLIT_TOKENS) return 0;
+    return D <= (T >= 2048 ? 512 : 384) ? D / 128 : 0;
+}
 
 static kvq_status append_checks(const kvq_cache *cache, const void *src, int32_t T, int64_t n_now)
 {
@@ -1515,7 +1521,7 @@ static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T,
     kvq_v_quant4<B, J, WV, TOK><<<(GRID) + keys.wgs, 64 * (WV) * (TOK), 0, s>>>(                               \
         cache->params, D, cache->cap_tokens, cache->n_tokens_v, T, cache->k_side_v, d_v_new, cache->v_codes,   \
         cache->v_sz, cache->v_ptr, vsp, cache->cap_nnz_v, cache->d_status, keys)
-    const int small = T < KVQ_VW_SMALL_TOKENS ? small_width(D) : 0, narrow = narrow_width(D, T);
+    const int small = T < KVQ_VW_SMALL_TOKENS ? small_width(D) : 0, narrow = narrow_width(cache->bits, D, T, cache->k_side_v);
     const bool in_pairs = !small && (D == 4096 || D == 2048 || D == 1024 || (T >= KVQ_BULK_TOKENS && (D == 5120 || D == 6656 || D == 8192)));
     // The pair kernel, one wavefront per 1024 channels and pair, takes calls of 64 tokens and more, but of one or two wavefronts a pair only
     // longer ones: below, a token of 1024 or 2048 channels is sooner done by four wavefronts (us, four / one or two wavefronts: 1024 channels,
@@ -1622,11 +1628,12 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
         kvq_ptr_scan<<<1, 1024, 0, s>>>(cache->k_ptr, cache->n_tokens_k, T, cnt, cache->cap_nnz_k, cache->d_status);
     }
     const size_t dyn = 3 * (size_t)D;
+    const int narrow = narrow_width(cache->bits, D, T, cache->k_side_v);
     static_assert(KVQ_KV_SPLIT_TOKENS <= KVQ_BULK_TOKENS, "workgroups are wide for every D >= 2048 here");
 #define LAUNCH_KVW(B, NT, VJ, VW) kvq_kv_quant<B, NT, VJ, VW><<<2 * T, NT, (VJ) > 0 ? 0 : dyn, s>>>(a)
 #define LAUNCH_KV(B)                                                                     \
     do {                                                                                 \
-        switch (narrow_width(D, T) ? -narrow_width(D, T) : small_width(D)) {             \
+        switch (narrow ? -narrow : small_width(D)) {                                     \
         case -1: LAUNCH_KVW(B, 256, 2, 1); break;                                        \
         case -2: LAUNCH_KVW(B, 256, 4, 1); break;                                        \
         case -3: LAUNCH_KVW(B, 256, 6, 1); break;                                        \
