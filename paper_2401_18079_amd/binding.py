@@ -165,6 +165,14 @@ def _stream_ptr(stream=None):
     return C.c_void_p(s.cuda_stream)
 
 
+def _scratch(nbytes: int, device, stream) -> torch.Tensor:
+    """Scratch memory of the stream that uses it (memory that another stream has freed may still be in that stream's use)."""
+    if stream is None:                       # (the context alone takes 3 us)
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
 def _check(status: int, where: str):
     if status != 0:
         raise KvqError(status, where)
@@ -447,9 +455,7 @@ def kvq_calibrate_key_channels(k_cal: torch.Tensor, outlier_fraction: float, str
     lib = load_library()
     ws_bytes = int(lib.kvq_calibrate_key_channels_workspace_bytes(T, D, float(outlier_fraction)))
     try:
-        # (the stream that uses it owns it: one that another stream has freed may still be in that stream's use)
-        with torch.cuda.stream(stream):
-            ws = torch.empty(ws_bytes, dtype=torch.uint8, device=k_cal.device) if ws_bytes else None
+        ws = _scratch(ws_bytes, k_cal.device, stream) if ws_bytes else None
     except torch.cuda.OutOfMemoryError:      # the call does without
         ws, ws_bytes = None, 0
     _check(lib.kvq_calibrate_key_channels_ws(k_cal.data_ptr(), T, D, float(outlier_fraction), p, p + 2 * D, p + 4 * D,
@@ -466,8 +472,7 @@ def kvq_calibrate_nuq(x_norm: torch.Tensor, w: torch.Tensor, bits: int, iters: i
     lib = load_library()
     c = np.ascontiguousarray(np.asarray(init, dtype=np.float32).copy())
     assert c.shape == (1 << bits,)
-    with torch.cuda.stream(stream):          # (as in kvq_calibrate_key_channels)
-        ws = torch.empty(int(lib.kvq_calibrate_workspace_bytes()), dtype=torch.uint8, device=x_norm.device)
+    ws = _scratch(int(lib.kvq_calibrate_workspace_bytes()), x_norm.device, stream)
     _check(lib.kvq_calibrate_nuq(x_norm.data_ptr(), w.data_ptr(), x_norm.numel(), int(bits), int(iters),
                                  c.ctypes.data_as(C.c_void_p), ws.data_ptr(), ws.numel(), _stream_ptr(stream)),
            "kvq_calibrate_nuq")
