@@ -19,6 +19,7 @@
 // of 32-byte row pieces at 3.2 TB/s.  Neighbouring groups spread over the XCDs: 326 us.  Eight loads in
 // flight per thread instead of four, or the second sweep from the last row to the first: no change.
 #include <math.h>
+#include <type_traits>
 #include "kvq_select.hpp"
 
 namespace {
@@ -235,8 +236,10 @@ void kvq_calib_channels(const uint16_t *__restrict__ k_cal, int T, int D, int k,
 // ---- one sweep, with scratch memory -------------------------------------------------------------------------
 // Whole lines: a workgroup reads 64 channels (128 bytes) of a part of the rows.  A sample bounds the order statistics so
 // that one in thirty keys lies beyond the bounds; those are listed per channel and side in the scratch memory, and a second
-// launch finds the order statistics among them.  Channels whose sample misled (too few keys beyond the bounds, or
-// more than the lists hold: crowds of equal keys) take the two sweeps in that launch.
+// launch finds the order statistics among them.  Where many columns (below) meet at a bound, a crowd of equal keys, the keys strictly beyond
+// the bounds are listed and those on them counted.  Lists that were too short for a part of the rows (rows of larger keys, all in one part) are
+// made good by that launch from the part's rows.  Channels whose sample misled otherwise (too few keys beyond the bounds, or more than
+// CL_ALL) take the two sweeps there.
 // The bounds: every 16th row, a row of each sixteen picked by a hash, goes to one of 128 columns of threads, which keep
 // their largest and smallest key per channel; the r-th largest of the 128 column maxima is a lower bound of the sample's
 // r-th largest.  With r0 = (k + 1) / 16 of the order statistics' elements expected in the sample, r = r0 + 5 sqrt(r0) + 4 misses
@@ -245,7 +248,10 @@ void kvq_calib_channels(const uint16_t *__restrict__ k_cal, int T, int D, int k,
 // 16 channels a workgroup no faster than two); full columns go to the channels' lists.
 // Whole calls, us, two sweeps / one: 32768 x 4096 209 / 103 (of it 70 + 12 in the two launches; the sweep runs at 5.4 TB/s, what this
 // access pattern reaches alone), 32768 x 1024 111 / 61, 32768 x 5120 359 / 128.  A third of the first launch is the start, the sample
-// and the bounds.
+// and the bounds.  Keys that a sample describes less well, 32768 x 4096, two sweeps / one: multiples of 1/2 367 / 137, constant channels 700 / 112, half of
+// the keys zero 291 / 145, the last sixteenth of the rows fifty times as large 186 / 144, rows that grow sixfold 194 / 169, one channel of a layer whose
+// sampled rows alone stand out 210 / 184 (all its channels: 205 / 364, which is the worst).  Outliers past the lists, from 1.3 % at 32768 rows
+// on, take the two sweeps from the start (2 %: 224).
 constexpr int CL_C = 64;                 // channels of a workgroup
 constexpr int CL_LPR = 8;                // lanes of 8 channels to a row
 constexpr int CL_COLS = CK_NT / CL_LPR;
@@ -254,24 +260,30 @@ constexpr int CL_SLOTS = 12;             // keys that a lane holds
 constexpr int CL_ALL = 1536;             // keys of a channel's side in all parts that the second launch takes
 constexpr int CL_MAX_PARTS = 32;
 
+constexpr uint32_t CL_NONE = 0xFFFFu;    // instead of a list's length: the bounds are of no use
+
 struct CkPlan {
     int groups, parts, rows, rank;       // rows of a part; rank r of the bounds among the column maxima
 };
-struct CkLists {                         // of (64 channels, part): [2 c + side][CL_CAP] keys (side 1: the largest), counts
-    uint16_t *keys;
-    uint32_t *counts;
+// Of (64 channels, part), by [2 c + side]; on side 0 complements stand for the keys, so that either side is after the largest.
+struct CkLists {
+    uint16_t *keys;                      // [CL_CAP]
+    uint32_t *counts;                    // keys beyond the bound, which the list holds up to CL_CAP, and << 16 those on it (0: they are listed)
+    uint32_t *least;                     // the smallest key that is listed
 };
+constexpr int64_t CL_BYTES = CL_CAP * 2 + 2 * 4;
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u16x2 ck_two(uint32_t w) { return __builtin_bit_cast(u16x2, w); }
 __device__ __forceinline__ uint32_t ck_word(u16x2 v) { return __builtin_bit_cast(uint32_t, v); }
 
 // An x that at least `rank` of 128 keys reach, and hardly more than that where the keys allow it: built from the highest bit
-// down, until at most an eighth of `rank` are too many.  Eight neighbouring lanes hold the keys, two to a word.
-__device__ __forceinline__ uint32_t ck_bound(const u16x2 (&v)[8], uint32_t rank)
+// down, until at most an eighth of `rank` are too many (n: how many reach it).  Eight neighbouring lanes hold the keys, two to a word.
+__device__ __forceinline__ uint32_t ck_bound(const u16x2 (&v)[8], uint32_t rank, uint32_t &n)
 {
     const u16x2 one = ck_two(0x00010001u);
-    uint32_t x = 0, n = 2 * 64;
+    uint32_t x = 0;
+    n = 2 * 64;
 #pragma unroll 1
     for (int bit = 15; bit >= 0 && __ballot(n > rank + (rank >> 3)) != 0ull; --bit) {
         const uint32_t y = x | (1u << bit);
@@ -293,8 +305,9 @@ __global__ __launch_bounds__(CK_NT) void kvq_calib_list(const uint16_t *__restri
 {
     __shared__ __attribute__((aligned(16))) uint16_t chan[2 * CL_C][CL_CAP];     // the channels' lists; first the column extremes
     __shared__ uint32_t mine[CL_SLOTS][CK_NT];
-    __shared__ uint32_t n_listed[2 * CL_C];
+    __shared__ uint32_t n_listed[2 * CL_C], n_equal[2 * CL_C];
     __shared__ uint32_t top_s[CL_C], bot_s[CL_C];
+    __shared__ int crowd_s;
     static_assert(sizeof(chan) >= 2 * CL_C * CL_COLS * 2, "the column extremes fit");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int b = ck_spread((int)blockIdx.x, plan.groups * plan.parts), g = b / plan.parts, part = b % plan.parts;
@@ -343,7 +356,8 @@ __global__ __launch_bounds__(CK_NT) void kvq_calib_list(const uint16_t *__restri
                 e[CL_COLS] = mx[w][h];
             }
     }
-    if (tid < 2 * CL_C) n_listed[tid] = 0;
+    if (tid < 2 * CL_C) n_listed[tid] = n_equal[tid] = 0;
+    if (tid == 0) crowd_s = 0;
     load(t0 + col);
     __syncthreads();
     {
@@ -352,67 +366,103 @@ __global__ __launch_bounds__(CK_NT) void kvq_calib_list(const uint16_t *__restri
         const uint4 *from = (const uint4 *)(&chan[0][0] + i * CL_COLS) + 2 * (tid & 7);
         const uint4 p = from[0], q = from[1];
         const u16x2 ext[8] = {ck_two(p.x), ck_two(p.y), ck_two(p.z), ck_two(p.w), ck_two(q.x), ck_two(q.y), ck_two(q.z), ck_two(q.w)};
-        const uint32_t x = ck_bound(ext, (uint32_t)plan.rank);
+        uint32_t n;
+        const uint32_t x = ck_bound(ext, (uint32_t)plan.rank, n);
         if ((tid & 7) == 0) {
             if (i & 1) top_s[i >> 1] = x;
             else bot_s[i >> 1] = (~x) & 0xFFFFu;
+            if (n > (uint32_t)plan.rank + ((uint32_t)plan.rank >> 3) + 4u) crowd_s = 1;         // (a few more keys do no harm)
         }
     }
     __syncthreads();
-    // keys strictly between the bounds are passed over: key - first < span.  Bounds that meet: the channel's lists count as
-    // overfull.
-    u16x2 first[4], less[4];                                              // less: span - 1
-    if (tid < CL_C && top_s[tid] <= bot_s[tid] + 1u) n_listed[2 * tid] = n_listed[2 * tid + 1] = 0x40000000u;
+    if (tid < CL_C) {
+        if (top_s[tid] <= bot_s[tid] + 1u) crowd_s = 1;
+        if (top_s[tid] < bot_s[tid]) n_listed[2 * tid] = n_listed[2 * tid + 1] = CL_NONE;
+    }
+    __syncthreads();
+    // keys between the bounds, with a crowd also those on them, are passed over: key - first <= less (all, where the bounds are of no use)
+    const uint32_t crowd = (uint32_t)__builtin_amdgcn_readfirstlane(crowd_s);
+    u16x2 first[4], less[4];
 #pragma unroll
     for (int w = 0; w < 4; ++w)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const uint32_t c = lr * 8 + 2 * w + h, tb = top_s[c], bb = bot_s[c];
-            const bool met = tb <= bb + 1u;                               // (nothing is listed then)
-            first[w][h] = (unsigned short)(met ? 0u : bb + 1u);
-            less[w][h] = (unsigned short)(met ? 0xFFFFu : tb - bb - 2u);
+            first[w][h] = (unsigned short)(tb < bb ? 0u : bb + 1u - crowd);
+            less[w][h] = (unsigned short)(tb < bb ? 0xFFFFu : tb - bb - 2u + 2u * crowd);
         }
-    __syncthreads();
     uint32_t *slot = &mine[0][tid];
     auto flush = [&]() {
         const int n = (int)((slot - &mine[0][tid]) / CK_NT);
         for (int s = 0; __ballot(s < n) != 0ull; ++s) {
             if (s < n) {
                 const uint32_t e = mine[s][tid], key = e & 0xFFFFu, c = lr * 8 + (e >> 16);
-                const uint32_t l = 2 * c + (key >= top_s[c] ? 1u : 0u);
+                const uint32_t l = 2 * c + (key >= top_s[c] + crowd ? 1u : 0u);
                 const uint32_t at = atomicAdd(&n_listed[l], 1u);
                 if (at < CL_CAP) chan[l][at] = (uint16_t)key;
             }
         }
         slot = &mine[0][tid];
     };
-    for (int i0 = t0 + col; i0 - col < t1; i0 += U * CL_COLS) {            // (every lane of a wavefront makes as many rounds)
-        if (i0 - col > t0) load(i0);
+    u16x2 off[2][4];                       // by side: keys that are not on the bound
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (i0 + u * CL_COLS < t1) {
+    for (int w = 0; w < 4; ++w) off[0][w] = off[1][w] = ck_two(0u);
+    uint32_t rows = 0;                     // in both halves
+    auto sweep = [&](auto counted) {
+        for (int i0 = t0 + col; i0 - col < t1; i0 += U * CL_COLS) {        // (every lane of a wavefront makes as many rounds)
+            if (i0 - col > t0) load(i0);
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    const uint32_t key = ck_keys(v[u].w[w]);
-                    const uint32_t out = ck_word(__builtin_elementwise_sub_sat((u16x2)(ck_two(key) - first[w]), less[w]));
-                    if (out & 0xFFFFu) {
-                        *slot = (key & 0xFFFFu) | (uint32_t)(2 * w) << 16;
-                        slot += CK_NT;
-                    }
-                    if (out > 0xFFFFu) {
-                        *slot = __builtin_amdgcn_alignbit((uint32_t)(2 * w + 1), key, 16);
-                        slot += CK_NT;
+            for (int u = 0; u < U; ++u) {
+                if (i0 + u * CL_COLS < t1) {
+                    rows += 0x00010001u;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const uint32_t key = ck_keys(v[u].w[w]);
+                        const u16x2 at = (u16x2)(ck_two(key) - first[w]);
+                        const uint32_t out = ck_word(__builtin_elementwise_sub_sat(at, less[w]));
+                        if constexpr (decltype(counted)::value) {
+                            const u16x2 one = ck_two(0x00010001u);
+                            off[0][w] += __builtin_elementwise_min(at, one);
+                            off[1][w] += __builtin_elementwise_min((u16x2)(at ^ less[w]), one);
+                        }
+                        if (out & 0xFFFFu) {
+                            *slot = (key & 0xFFFFu) | (uint32_t)(2 * w) << 16;
+                            slot += CK_NT;
+                        }
+                        if (out > 0xFFFFu) {
+                            *slot = __builtin_amdgcn_alignbit((uint32_t)(2 * w + 1), key, 16);
+                            slot += CK_NT;
+                        }
                     }
                 }
+                if (__ballot(slot > &mine[CL_SLOTS - 8][tid]) != 0ull) flush();
             }
-            if (__ballot(slot > &mine[CL_SLOTS - 8][tid]) != 0ull) flush();
         }
+    };
+    if (crowd) {
+        sweep(std::true_type{});
+#pragma unroll
+        for (int side = 0; side < 2; ++side)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                uint32_t on = rows - ck_word(off[side][w]);                // (up to 256 in a lane)
+                for (int o = CL_LPR; o < 64; o <<= 1) on += __shfl_xor(on, o);
+                if (lane < CL_LPR) {
+                    atomicAdd(&n_equal[2 * (lr * 8 + 2 * w) + side], on & 0xFFFFu);
+                    atomicAdd(&n_equal[2 * (lr * 8 + 2 * w + 1) + side], on >> 16);
+                }
+            }
+    } else {
+        sweep(std::false_type{});
     }
     flush();
     __syncthreads();
-    uint32_t *counts = lists.counts + (int64_t)(g * plan.parts + part) * (2 * CL_C);
-    if (tid < 2 * CL_C) counts[tid] = n_listed[tid];
-    uint32_t *keys = (uint32_t *)(lists.keys + (int64_t)(g * plan.parts + part) * (2 * CL_C) * CL_CAP);
+    const int64_t l0 = (int64_t)(g * plan.parts + part) * (2 * CL_C);
+    if (tid < 2 * CL_C) {
+        lists.counts[l0 + tid] = n_listed[tid] | n_equal[tid] << 16;
+        lists.least[l0 + tid] = ((tid & 1) ? top_s[tid >> 1] : 0xFFFFu - bot_s[tid >> 1]) + crowd;
+    }
+    uint32_t *keys = (uint32_t *)(lists.keys + l0 * CL_CAP);
     for (int l = wave; l < 2 * CL_C; l += CK_NT / 64) {
         const int n = (int)(n_listed[l] < CL_CAP ? n_listed[l] : CL_CAP);
         for (int i = lane; 2 * i < n; i += 64) keys[l * (CL_CAP / 2) + i] = ((const uint32_t *)chan[l])[i];
@@ -471,71 +521,109 @@ void kvq_calib_pick(const uint16_t *__restrict__ k_cal, int T, int D, int k, con
     };
     __shared__ Lds lds;
     __shared__ uint32_t found[8][4];       // see ck_store
+    __shared__ uint32_t again_s;           // parts whose keys did not fit into a list of this workgroup's
+    __shared__ uint32_t least_s[CK_NT / 64], next_s[CK_NT / 64];
     __shared__ int failed;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g8 = (int)blockIdx.x, c = g8 * 8 + (wave >> 1), g = c / CL_C, cl = c % CL_C, side = wave & 1;
+    const int g8 = ck_spread((int)blockIdx.x, (int)gridDim.x), side = wave & 1, c = g8 * 8 + (wave >> 1);
     const uint32_t K1 = (uint32_t)k + 1u;
-    const int64_t l0 = (int64_t)g * plan.parts * (2 * CL_C) + 2 * cl + side;
-    const uint32_t n = lane < plan.parts ? lists.counts[l0 + (int64_t)lane * (2 * CL_C)] : 0u;
-    if (tid == 0) failed = 0;
+    // this wavefront's list, by part in the lanes: keys of the part, up to it, on the bound
+    const int64_t l0 = (int64_t)(c / CL_C) * plan.parts * (2 * CL_C) + 2 * (c % CL_C) + side;
+    const uint32_t count = lane < plan.parts ? lists.counts[l0 + (int64_t)lane * (2 * CL_C)] : 0u, n = count & 0xFFFFu;
+    const uint32_t least = lists.least[l0], over = (uint32_t)__ballot(n > CL_CAP);
+    if (tid == 0) { failed = 0; again_s = 0; }
     __syncthreads();
-    uint32_t sum = n;                      // up to this part
+    uint32_t sum = n, on = count >> 16;
     for (int o = 1; o < CL_MAX_PARTS; o <<= 1) {
         const uint32_t t = __shfl_up(sum, o);
         if (lane >= o) sum += t;
+        on += __shfl_xor(on, o);
     }
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)sum, plan.parts - 1);
-    if (__ballot(n > CL_CAP) != 0ull || total < K1 || total > CL_ALL) {
+    on = (uint32_t)__builtin_amdgcn_readfirstlane((int)on);
+    uint16_t *all = lds.pick.keys[wave];
+    if (__ballot(n == CL_NONE) != 0ull || total + on < K1 || total > CL_ALL) {
         if (lane == 0) failed = 1;
     } else {
-        uint16_t *all = lds.pick.keys[wave];
+        if (lane == 0 && over != 0u) atomicOr(&again_s, over);
         constexpr int W = (CL_CAP / 2 + 63) / 64;      // words a lane reads of a list
         for (int p0 = 0; p0 < plan.parts; p0 += 4) {
-            uint32_t e[4][W];
+            uint32_t e[4][W], n4[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int p = p0 + q < plan.parts ? p0 + q : p0;
                 const uint32_t np = p0 + q < plan.parts ? (uint32_t)__builtin_amdgcn_readlane((int)n, p) : 0u;
+                n4[q] = np <= CL_CAP ? np : 0u;
                 const uint32_t *from = (const uint32_t *)(lists.keys + (l0 + (int64_t)p * (2 * CL_C)) * CL_CAP);
 #pragma unroll
-                for (int u = 0; u < W; ++u) e[q][u] = 2 * (64 * u + lane) < (int)np ? from[64 * u + lane] : 0u;
+                for (int u = 0; u < W; ++u) e[q][u] = 2 * (64 * u + lane) < (int)n4[q] ? from[64 * u + lane] : 0u;
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int p = p0 + q < plan.parts ? p0 + q : p0;
-                const uint32_t np = p0 + q < plan.parts ? (uint32_t)__builtin_amdgcn_readlane((int)n, p) : 0u;
                 uint16_t *to = all + (uint32_t)__builtin_amdgcn_readlane((int)sum, p) - (uint32_t)__builtin_amdgcn_readlane((int)n, p);
 #pragma unroll
                 for (int u = 0; u < W; ++u) {
                     const uint32_t i = 2 * (64 * u + lane), v = side ? e[q][u] : ~e[q][u];
-                    if (i < np) to[i] = (uint16_t)v;
-                    if (i + 1 < np) to[i + 1] = (uint16_t)(v >> 16);
+                    if (i < n4[q]) to[i] = (uint16_t)v;
+                    if (i + 1 < n4[q]) to[i + 1] = (uint16_t)(v >> 16);
                 }
             }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        uint32_t larger, x = ck_pick(all, total, K1, lds.pick.hist[wave], lane, larger), xk = x;
-        if (larger == (uint32_t)k) {       // the k-th is the next key up; otherwise there are enough of x to make it the same
-            xk = 0xFFFFu;
-            for (uint32_t i = lane; i < total; i += 64) {
-                const uint32_t v = all[i];
-                xk = v > x && v < xk ? v : xk;
-            }
-            for (int o = 32; o > 0; o >>= 1) {
-                const uint32_t a = __shfl_xor(xk, o);
-                xk = a < xk ? a : xk;
-            }
-        }
-        if (lane == 0) {
-            found[wave >> 1][side ? 1 : 3] = side ? x : (~x & 0xFFFFu);
-            found[wave >> 1][side ? 0 : 2] = side ? xk : (~xk & 0xFFFFu);
         }
     }
     __syncthreads();
     if (failed) {
         ck_two_sweeps<8, 1>(k_cal, T, D, k, g8, lds.two, out);       // all eight channels
-    } else if (lane == 0 && side == 0) {
+        return;
+    }
+    for (uint32_t left = again_s; left != 0u; left &= left - 1u) {
+        const int p = __ffs((int)left) - 1, r1 = (p + 1) * plan.rows < T ? (p + 1) * plan.rows : T;
+        const uint32_t at0 = (uint32_t)__builtin_amdgcn_readlane((int)sum, p) - (uint32_t)__builtin_amdgcn_readlane((int)n, p);
+        if (lane == 0) {
+            least_s[wave] = (over >> p) & 1u ? least : 0x20000u;       // (no key is that large)
+            next_s[wave] = at0;
+        }
+        __syncthreads();
+        for (int i = p * plan.rows + tid; i < r1; i += CK_NT) {
+            const CkVec<8> v = ck_load<8>(k_cal + (int64_t)i * D + g8 * 8);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t key = (ck_keys(v.w[e >> 1]) >> (16 * (e & 1))) & 0xFFFFu;
+#pragma unroll
+                for (int sd = 0; sd < 2; ++sd) {
+                    const uint32_t x = sd ? key : 0xFFFFu - key;
+                    if (x >= least_s[2 * e + sd]) {
+                        const uint32_t at = atomicAdd(&next_s[2 * e + sd], 1u);
+                        if (at < CL_ALL) lds.pick.keys[2 * e + sd][at] = (uint16_t)x;
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // x: the (k+1)-th; xk: the k-th, the next key up where just k are larger, and otherwise the same
+    uint32_t larger = total, x = least - 1u;                   // (too few beyond the bound: the bound)
+    if (total >= K1) x = ck_pick(all, total, K1, lds.pick.hist[wave], lane, larger);
+    uint32_t xk = x;
+    if (larger == (uint32_t)k) {
+        xk = 0xFFFFu;
+        for (uint32_t i = lane; i < total; i += 64) {
+            const uint32_t v = all[i];
+            xk = v > x && v < xk ? v : xk;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const uint32_t a = __shfl_xor(xk, o);
+            xk = a < xk ? a : xk;
+        }
+    }
+    if (lane == 0) {
+        found[wave >> 1][side ? 1 : 3] = side ? x : (~x & 0xFFFFu);
+        found[wave >> 1][side ? 0 : 2] = side ? xk : (~xk & 0xFFFFu);
+    }
+    __syncthreads();
+    if (lane == 0 && side == 0) {
         const uint32_t key[4] = {found[wave >> 1][0], found[wave >> 1][1], found[wave >> 1][2], found[wave >> 1][3]};
         ck_store(out, c, k, key);
     }
@@ -590,7 +678,7 @@ extern "C" int64_t kvq_calibrate_key_channels_workspace_bytes(int32_t T, int32_t
     CkPlan plan;
     int k;
     if (T > 32768 || !ck_count(T, D, outlier_fraction, k) || !ck_plan(nullptr, T, D, k, plan)) return 0;
-    return (int64_t)plan.groups * plan.parts * (2 * CL_C) * (CL_CAP * 2 + 4);
+    return (int64_t)plan.groups * plan.parts * (2 * CL_C) * CL_BYTES;
 }
 
 extern "C" kvq_status kvq_calibrate_key_channels_ws(const uint16_t *d_k_cal, int32_t T, int32_t D, float outlier_fraction,
@@ -607,8 +695,10 @@ extern "C" kvq_status kvq_calibrate_key_channels_ws(const uint16_t *d_k_cal, int
     CkPlan plan;
     if (d_workspace && ((uintptr_t)d_workspace & 15) == 0 && ck_plan(d_k_cal, T, D, k, plan) &&
         workspace_bytes >= kvq_calibrate_key_channels_workspace_bytes(T, D, outlier_fraction)) {
-        const int64_t n = (int64_t)plan.groups * plan.parts;
-        const CkLists lists{(uint16_t *)d_workspace, (uint32_t *)((char *)d_workspace + n * (2 * CL_C) * CL_CAP * 2)};
+        const int64_t n = (int64_t)plan.groups * plan.parts, n_lists = n * (2 * CL_C);
+        uint16_t *keys = (uint16_t *)d_workspace;
+        uint32_t *counts = (uint32_t *)(keys + n_lists * CL_CAP);
+        const CkLists lists{keys, counts, counts + n_lists};
         kvq_calib_list<<<(unsigned)n, CK_NT, 0, s>>>(d_k_cal, T, D, plan, lists);
         kvq_calib_pick<<<(unsigned)(D / 8), CK_NT, 0, s>>>(d_k_cal, T, D, k, plan, lists, out);
         KVQ_HIP_CHECK(hipGetLastError());
