@@ -137,3 +137,74 @@ def test_codes_of_outliers_beyond_the_code_range(heads, bits, posts):
         K.kvq_quantize_append_kv(gc, torch.from_numpy(x[a:b]).cuda(), torch.from_numpy(v[a:b]).cuda())
     bad = compare_caches(oc, gc)
     assert not bad, bad
+
+
+# Thresholds by head, each on every fifth channel among ordinary ones: no channel's range ends at the code range, so that the packed keys alone decide.
+_EDGES = {
+    "none": lambda z, s: (z - s, z + s), "lo +0": lambda z, s: (0.0 * z, abs(z) + s), "lo -0": lambda z, s: (-0.0 * abs(z), abs(z) + s),
+    "hi +0": lambda z, s: (-abs(z) - s, 0.0 * abs(z)), "hi -0": lambda z, s: (-abs(z) - s, -0.0 * abs(z)),
+    "zeros": lambda z, s: (0.0 * abs(z), -0.0 * abs(z)), "crossed": lambda z, s: (z + s, z - s), "infinite": lambda z, s: (z + np.inf, z - np.inf),
+    "one value": lambda z, s: (z, z), "smallest": lambda z, s: (0 * z - 2.0 ** -24, 0 * z + 2.0 ** -24), "largest": lambda z, s: (0 * z - 65504.0, 0 * z + 65504.0),
+}
+
+
+@pytest.mark.parametrize("heads,bits,scales", [(16, 2, "normal"), (16, 3, "normal"), (24, 4, "normal"), (40, 3, "normal"), (24, 2, "mixed"), (16, 4, "mixed")])
+def test_thresholds_at_the_edges_among_ordinary_channels(heads, bits, scales):
+    """Against the oracle; with scales outside its contract on channels of their own heads ("mixed"), against one-token calls."""
+    import torch
+    import paper_2401_18079_amd as K
+    rng = np.random.default_rng(100 * heads + bits)
+    D, T, n0, nnz = heads * 128, 67, 1, heads * 128 * 68
+    c = np.arange(D)
+    s, z = np.exp(rng.standard_normal(D)).clip(0.1, 8).astype(np.float16), rng.standard_normal(D).astype(np.float16)
+    names, head, special = list(_EDGES), c // 128, (c % 5 == 3)
+    kind = np.where(special, head % len(names), 0)
+    s[kind == names.index("largest")] = np.float16(600)
+    z32, s32 = z.astype(np.float32), s.astype(np.float32)
+    lo, hi = np.empty(D, np.float16), np.empty(D, np.float16)
+    for i, name in enumerate(names):
+        a, b = _EDGES[name](z32, s32)
+        lo[kind == i], hi[kind == i] = a.astype(np.float16)[kind == i], b.astype(np.float16)[kind == i]
+    crossed = ~(lo <= hi)
+    assert np.all(crossed | ((lo >= z32 - 126 * s32) & (hi <= z32 + 126 * s32)))
+    if scales == "mixed":
+        odd = special & (head >= len(names))
+        s[odd & (c % 3 == 0)], s[odd & (c % 3 == 1)], s[odd & (c % 3 == 2)] = np.float16(0), np.float16(-1), np.float16(2.0 ** -24)
+    lut = np.linspace(-1, 1, 1 << bits).astype(np.float32)
+    x = (z32 + 0.6 * s32 * rng.standard_normal((n0 + T, D))).astype(np.float16)
+    at = rng.integers(0, 12, x.shape)                    # the thresholds themselves, their neighbours, zeros and the smallest numbers
+    finite = ~np.isinf(lo)
+    with np.errstate(over="ignore"):
+        beside = np.nextafter(lo, np.float16(-np.inf)), np.nextafter(hi, np.float16(np.inf))
+    for i, y in enumerate((lo, hi, *beside)):
+        x = np.where((at == i) & finite & np.isfinite(y), y, x)
+    for i, y in enumerate((0.0, -0.0, 2.0 ** -24, -2.0 ** -24)):
+        x = np.where(at == 4 + i, np.float16(y), x)
+    for t in range(0, n0 + T, 3):                        # tokens of which a few elements are out of the code range
+        x[t, rng.permutation(D)[:24]] = np.float16(6e4) * rng.choice([-1, 1], 24).astype(np.float16)
+    v = rng.standard_normal((n0 + T, D)).astype(np.float16)
+    dev, dev_v = torch.from_numpy(x).cuda(), torch.from_numpy(v).cuda()
+
+    def filled(step):
+        gc = K.KvqCache(bits, heads, heads, 128, 4, 10000.0, nnz)
+        K.kvq_lut_load(gc, lut, lut, s, z, lo, hi)
+        for t in [0] + list(range(n0, n0 + T, step)):
+            e = n0 if t < n0 else min(t + step, n0 + T)
+            K.kvq_quantize_append_k(gc, dev[t:e])
+            K.kvq_quantize_append_v(gc, dev_v[t:e])
+        torch.cuda.synchronize()
+        assert gc.status() == 0
+        return gc
+
+    gc = filled(T)
+    if scales == "normal":
+        oc = O.OracleCache(bits, heads, heads, 128, 4, 10000.0, lut, lut, s, z, lo, hi, cap_nnz_k=nnz)
+        oc.append_k(x); oc.append_v(v)
+        bad = compare_caches(oc, gc)
+        assert not bad, bad
+    else:
+        ref = filled(1)
+        for f in ("k_codes", "k_ptr", "k_idx"):
+            assert torch.equal(getattr(gc, f), getattr(ref, f)), f
+        a, b = (r.k_val.cpu().numpy().view(np.float16) for r in (gc, ref))
+        assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(a.view(np.uint16)[~np.isnan(a)], b.view(np.uint16)[~np.isnan(b)])
