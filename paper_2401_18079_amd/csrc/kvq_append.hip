@@ -1525,8 +1525,8 @@ static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T,
     const bool in_pairs = !small && (D == 4096 || D == 2048 || D == 1024 || (T >= KVQ_BULK_TOKENS && (D == 5120 || D == 6656 || D == 8192)));
     // The pair kernel, one wavefront per 1024 channels and pair, takes calls of 64 tokens and more, but of one or two wavefronts a pair only
     // longer ones: below, a token of 1024 or 2048 channels is sooner done by four wavefronts (us, four / one or two wavefronts: 1024 channels,
-    // 2 bits, 777 tokens 9.1 / 11.3, 1200 11.5 / 11.8, 2048 16.1 / 11.9, 4 bits, 1200 12.3 / 13.4, 2048 17.3 / 14.3; 2048 channels, 777 tokens 11.3 / 11.9
-    // and 13.1 / 14.7, 1200 14.5 / 11.4 and 16.7 / 14.3).  More than KVQ_V_BOUNDED outliers a side, other widths and unaligned input keep the
+    // 2 bits, 777 tokens 9.1 / 11.3, 1200 11.5 / 11.8, 2048 16.2 / 10.6, 4 bits, 1200 12.3 / 13.4, 2048 17.8 / 12.0; 2048 channels, 777 tokens 11.3 / 11.9
+    // and 13.1 / 14.7, 1200 14.5 / 9.9 and 17.3 / 11.5).  More than KVQ_V_BOUNDED outliers a side, other widths and unaligned input keep the
     // other kernels.
     const bool pair = !small && D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES && cache->k_side_v <= (int)KVQ_V_BOUNDED &&
                       ((uintptr_t)d_v_new & 15) == 0 && T >= (D == 1024 ? 1500 : D == 2048 ? 1000 : KVQ_VW_SMALL_TOKENS);

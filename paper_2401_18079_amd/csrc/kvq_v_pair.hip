@@ -11,19 +11,22 @@ namespace {
 // with packed 16-bit instructions:
 //  * keys: x as a signed number in the order of the values (-0 directly below 0);
 //  * the outlier thresholds as in v_quant_token4 - the k-th largest of 64 columns' maxima bounds the k-th largest key, the few
-//    keys beyond are collected and the thresholds found among them with ballots -, but each of the four searches (two
-//    tokens, two sides) by one wavefront for all;
+//    keys on and beyond the bounds are collected and the thresholds found among them with ballots -, but each of the four searches
+//    (two tokens, two sides) by one wavefront for all, and one list for both sides of a token;
 //  * codes: the normalised value grows with x, so that the code of x is the number of keys K_j <= x where K_j is the smallest
 //    fp16 number whose normalised value (the same fp32 steps) reaches the j-th threshold.  One lane per threshold and token
 //    finds its K_j, next to where the inverse of the normalisation points; an element's code is a binary search of
 //    log2 comparisons, each a saturating subtraction whose sign selects the next K_j.
-// Tokens with crowds of equal keys (more candidates than the lists hold, thresholds that coincide) and thresholds at zero, which
-// has two keys, take general_selection; far outliers are encoded one by one.  Same arithmetic, same
-// results, as v_quant_token.
+//  * outliers: their channels go to a list by rank, and a lane takes any of them, so that outliers crowded in few lanes' channels
+//    do not take longer; codes beyond the code range are put right by the lanes that hold them.
+// Where more keys than a list holds lie on and beyond the bounds, those beyond alone are listed (crowds of equal keys, zeros above all: with fewer than
+// k beyond, the bound is the threshold); then the same with other columns (the largest keys in few lanes), at last a bisection over all keys.
+// Where only some of a threshold's equals are outliers, they are ranked in channel order.  Same arithmetic, same results, as v_quant_token.
 // us per Value append, the kernel with a token on four wavefronts and a lane per element (v_quant_token4) / this one, 1 % outliers:
-// 4096 tokens of 4096 channels, 2 bits 46.8 / 23.9, 3 bits 51.5 / 26.5, 4 bits 56.5 / 29.6; of 5120, 4 bits 77.1 / 44.2; of 8192 116 / 55; 777 of
-// 5120 22.5 / 15.0; 64 of 4096 13.8 / 11.3; 4096 of 3072 (the routine for any width before) 82.4 / 25.8.  Bound by vector issue, with six wavefronts
-// a SIMD (five: 5120 channels 44.9 / 41.8 at first, 3 bits; eight, which spill: 40.9, but 4096 channels 30.3 against 29.2).
+// 4096 tokens of 4096 channels, 2 bits 46.5 / 22.5, 3 bits 50.9 / 25.1, 4 bits 56.5 / 27.9; of 5120, 4 bits 77.3 / 41.4; of 8192, 3 bits 107 / 47; 777 of
+// 5120, 4 bits, 22.9 / 14.2; 64 of 4096 14.3 / 9.0; 4096 of 3072 (the routine for any width before) 81.6 / 21.2.  4096 tokens of 4096 channels, 3 bits, that are
+// ordinary 50.9 / 25.1, zero 99 / 41, zero or positive 104 / 38, every third zero 78 / 37, with one head eight times as large 48 / 33, sixteen channels 50 / 35, but
+// sorted 46 / 62.  Bound by vector issue, with six wavefronts a SIMD, 80 registers and no spills (eight, which spilled: 4096 channels slower by 4 %).
 
 // Packed maxima over the wavefront (two numbers at once), in every lane.
 __device__ __forceinline__ s16x2 vp_wave_max(s16x2 v)
@@ -39,115 +42,138 @@ __device__ __forceinline__ s16x2 vp_wave_max(s16x2 v)
 }
 
 // Searches of a workgroup are numbered 2 token + side; side 1 works on complemented keys, so that either looks for the k-th largest.
+// Zeros of both signs are one key, 0, to them.
+constexpr int VP_CAND = 512;                     // candidates of a token that a list holds
 struct VpLds {
-    int col_max[4][64];                        // the largest keys of the 64 columns (lane l of every wavefront)
-    uint32_t n_cand[4];
-    uint16_t cand[4][KVQ_V_CAND];              // candidates, + 32768
-    int bound[4];
-    struct { int tau; uint32_t need, n_eq; } found[4];     // threshold; how many of its equals are taken, how many there are
+    union {
+        int col_max[4][64];                    // the largest keys of the 64 columns (lane l of every wavefront)
+        uint16_t cand[2][VP_CAND];             // candidates of either side, + 32768
+    };
+    uint32_t n_cand[2], n_side[2];             // tokens packed: candidates on and beyond the bounds, beyond them; by side, those beyond
+    int bound[4];                              // keys
+    struct { int tau; uint32_t need, n_eq; } found[4];     // threshold, a key; how many of its equals are taken, how many there are (~0: not known)
     __attribute__((aligned(16))) uint32_t wave_red[3][KVQ_BULK_MAX_WAVES];       // of a wavefront's inliers (tokens packed): largest, complement of smallest; outliers
     uint32_t counts[17][2];                    // general_selection's rounds
     uint32_t eq[KVQ_BULK_MAX_WAVES][2];
+    uint16_t ids[2][2 * KVQ_V_BOUNDED];        // channels of the outliers
     float lut[16];
 };
+// The smallest key that equals a threshold.
+__device__ __forceinline__ int vp_least_equal(int tau) { return tau == 0 ? -1 : tau; }
 
-// The outliers of both tokens where the lists do not serve: thresholds by bisection over all keys (-0 as 0), a barrier a bit; of a
-// threshold's equals the first in channel order.  Returns the outliers: bit w + 8 token + 16 half is half `half` of this lane's
-// word w.
-__device__ __forceinline__ uint32_t general_selection(VpLds &lds, const s16x2 (&s)[2][8], uint32_t K)
+// Of search i: the k-th largest among its token's n candidates, K <= n <= 64 R, bit by bit.  (Those of the other side change nothing.)
+template <int R>
+__device__ __forceinline__ void pick(VpLds &lds, int i, uint32_t n, uint32_t K)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NT = blockDim.x;
-    const u16x2v one = {1, 1};
-    u16x2v key[2][8];
+    const int lane = threadIdx.x & 63;
+    const uint16_t *list = lds.cand[i >> 1];
+    uint32_t v[R];
 #pragma unroll
-    for (int tok = 0; tok < 2; ++tok)
+    for (int r = 0; r < R; ++r) {
+        const uint32_t u = list[lane + 64 * r];
+        v[r] = (uint32_t)lane + 64u * r < n ? ((i & 1) ? 65536u - u : u + 1u) : 0u;        // (above an absent one)
+    }
+    auto at_least = [&](uint32_t x) {
+        uint32_t c = 0;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            const u16x2v not_neg_zero = __builtin_elementwise_min(__builtin_bit_cast(u16x2v, ~vp_word(s[tok][w])), one);
-            const uint32_t canonical = vp_word(s[tok][w] + (short)1 - __builtin_bit_cast(s16x2, not_neg_zero));
-            key[tok][w] = __builtin_bit_cast(u16x2v, canonical ^ 0x80008000u);
-        }
-    for (int i = tid; i < 17 * 2; i += NT) (&lds.counts[0][0])[i] = 0;
+        for (int r = 0; r < R; ++r) c += (uint32_t)__popcll(__ballot(v[r] >= x));
+        return c;
+    };
+    uint32_t x = 0;
+    for (int bit = 16; bit >= 0; --bit)
+        if (at_least(x | (1u << bit)) >= K) x |= 1u << bit;
+    const uint32_t beyond = at_least(x + 1u), reached = at_least(x);
+    if (lane == 0) {
+        lds.found[i].tau = ((i & 1) ? (int)(65536u - x) : (int)x - 1) - 32768;
+        lds.found[i].need = K - beyond;
+        lds.found[i].n_eq = reached - beyond;
+    }
+}
+
+// This lane's column where lanes do not serve: groups of four channels that lie a multiple of 256 apart, of a wavefront's channels.  Half of a
+// wavefront's words are exchanged for the other half's, then a row's for its neighbour's: packed extremes of either fall on one lane.
+__device__ __forceinline__ void vp_column_of_fours(const s16x2 (&s)[8], s16x2 &most, s16x2 &least)
+{
+    s16x2 mx[4], mn[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const auto r = __builtin_amdgcn_permlane32_swap(vp_word(s[j]), vp_word(s[j + 4]), false, false);
+        mx[j] = __builtin_elementwise_max(vp_pair(r[0]), vp_pair(r[1]));
+        mn[j] = __builtin_elementwise_min(vp_pair(r[0]), vp_pair(r[1]));
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const auto a = __builtin_amdgcn_permlane16_swap(vp_word(mx[j]), vp_word(mx[j + 2]), false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap(vp_word(mn[j]), vp_word(mn[j + 2]), false, false);
+        mx[j] = __builtin_elementwise_max(vp_pair(a[0]), vp_pair(a[1]));
+        mn[j] = __builtin_elementwise_min(vp_pair(b[0]), vp_pair(b[1]));
+    }
+    most = __builtin_elementwise_max(mx[0], mx[1]);
+    least = __builtin_elementwise_min(mn[0], mn[1]);
+}
+
+// The thresholds of both tokens where the lists do not serve either: by bisection over all keys, a barrier a bit.
+__device__ __forceinline__ void general_selection(VpLds &lds, const s16x2 (&s)[2][8], uint32_t K)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid; i < 17 * 2; i += blockDim.x) (&lds.counts[0][0])[i] = 0;
     __syncthreads();
-    uint32_t x[4] = {0, 0, 0, 0}, gt[4] = {0, 0, 0, 0};
+    uint32_t x[4] = {0, 0, 0, 0};                        // (of larger keys, and on side 1 of smaller ones)
+#pragma unroll 1
     for (int bit = 15; bit >= -1; --bit) {               // (the last round: how many exceed the thresholds themselves)
 #pragma unroll
         for (int tok = 0; tok < 2; ++tok) {
-            const unsigned short yt = (unsigned short)(bit >= 0 ? (x[2 * tok] | (1u << bit)) - 1u : x[2 * tok]);
-            const unsigned short yb = (unsigned short)(bit >= 0 ? (x[2 * tok + 1] | (1u << bit)) - 1u : x[2 * tok + 1]);
-            const u16x2v xt = {yt, yt}, xb = {yb, yb};
-            u16x2v a = {0, 0}, b = {0, 0};
+            // keys above a and below b
+            int a, b;
+            if (bit >= 0) {
+                a = vp_least_equal((int)(x[2 * tok] | (1u << bit)) - 32768) - 1;
+                b = 32767 - (int)(x[2 * tok + 1] | (1u << bit));
+                b = b == -1 ? -1 : b + 1;
+            } else {
+                a = (int)x[2 * tok] - 32768;
+                b = vp_least_equal(32767 - (int)x[2 * tok + 1]);
+            }
+            const s16x2 va = vp_both(a), vb = vp_both(b);
+            s16x2 above = {0, 0}, below = {0, 0};        // less their numbers
 #pragma unroll
             for (int w = 0; w < 8; ++w) {
-                a += __builtin_elementwise_min(__builtin_elementwise_sub_sat(key[tok][w], xt), one);
-                b += __builtin_elementwise_min(__builtin_elementwise_sub_sat((u16x2v)(~key[tok][w]), xb), one);
+                above += vp_pair(vp_less(va, s[tok][w]));
+                below += vp_pair(vp_less(s[tok][w], vb));
             }
-            // keys above either threshold, the token's sides packed
-            const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)vp_scan((uint32_t)(a.x + a.y) | (uint32_t)(b.x + b.y) << 16), 63);
+            const uint32_t n = (uint32_t)-(above.x + above.y) | (uint32_t)-(below.x + below.y) << 16;
+            const uint32_t sum = (uint32_t)__builtin_amdgcn_readlane((int)vp_scan(n), 63);
             if (lane == 0) atomicAdd(&lds.counts[15 - bit][tok], sum);
         }
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const uint32_t n = (lds.counts[15 - bit][i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
-            if (bit < 0) gt[i] = n;
-            else if (n >= K) x[i] |= 1u << bit;
-        }
-    }
-    // equals before this lane's channels
-    uint32_t before[2];
-#pragma unroll
-    for (int tok = 0; tok < 2; ++tok) {
-        uint32_t mine = 0;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            const u16x2v k = key[tok][w];
-            mine += (k.x == x[2 * tok] ? 1u : 0u) + (k.y == x[2 * tok] ? 1u : 0u);
-            mine += ((0xFFFFu ^ k.x) == x[2 * tok + 1] ? 0x10000u : 0u) + ((0xFFFFu ^ k.y) == x[2 * tok + 1] ? 0x10000u : 0u);
-        }
-        const uint32_t upto = vp_scan(mine);
-        before[tok] = upto - mine;
-        if (lane == 63) lds.eq[wave][tok] = upto;
-    }
-    __syncthreads();
-    uint32_t out = 0;
-#pragma unroll
-    for (int tok = 0; tok < 2; ++tok) {
-        for (int w = 0; w < wave; ++w) before[tok] += lds.eq[w][tok];
-        const uint32_t tt = x[2 * tok], tb = x[2 * tok + 1], need_t = K - gt[2 * tok], need_b = K - gt[2 * tok + 1];
-        const bool same = tt == 0xFFFFu - tb;
-        uint32_t rt = before[tok] & 0xFFFFu, rb = before[tok] >> 16;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) {
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const uint32_t k = half ? key[tok][w].y : key[tok][w].x, inv = 0xFFFFu ^ k;
-                const bool eq_t = k == tt, eq_b = inv == tb;
-                const bool is_top = k > tt || (eq_t && rt < need_t);
-                // thresholds coincide: the lower outliers take the equal keys that follow the upper ones'
-                const bool is_bot = inv > tb || (eq_b && (same ? (rb >= need_t && rb < need_t + need_b) : rb < need_b));
-                rt += eq_t ? 1u : 0u;
-                rb += eq_b ? 1u : 0u;
-                out |= (is_top || is_bot) ? 1u << (w + 8 * tok + 16 * half) : 0u;
+            if (bit >= 0) {
+                if (n >= K) x[i] |= 1u << bit;
+            } else if (tid == 0) {
+                lds.found[i].tau = (i & 1) ? 32767 - (int)x[i] : (int)x[i] - 32768;
+                lds.found[i].need = K - n;
+                lds.found[i].n_eq = ~0u;
             }
         }
     }
-    return out;
 }
 
-// Of the keys that equal a threshold only the first need[i] in channel order are outliers: takes the others out of `outl`.
-__device__ __forceinline__ uint32_t drop_equals(VpLds &lds, const s16x2 (&s)[2][8], uint32_t outl)
+// The outliers where only some of a threshold's equals are: the keys beyond, and of the equals the first in channel order.
+__device__ __forceinline__ uint32_t with_equals(VpLds &lds, const s16x2 (&s)[2][8])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t eq[2] = {0, 0}, before[2];                  // by side; bits as in the result
+    uint32_t outl = 0, eq[2] = {0, 0}, before[2];        // by side
 #pragma unroll
     for (int tok = 0; tok < 2; ++tok) {
-        const s16x2 tt = vp_both(lds.found[2 * tok].tau), tb = vp_both(~lds.found[2 * tok + 1].tau);
+        const int top = lds.found[2 * tok].tau, bot = lds.found[2 * tok + 1].tau;
+        const s16x2 t = vp_both(top), t0 = vp_both(vp_least_equal(top)), b = vp_both(bot), b0 = vp_both(vp_least_equal(bot));
 #pragma unroll
         for (int w = 0; w < 8; ++w) {
-            // (outliers on or beyond a threshold: equal where not beyond)
-            eq[0] |= ~(vp_less(s[tok][w], tt) | vp_less(tt, s[tok][w])) & (0x00010001u << (w + 8 * tok));
-            eq[1] |= ~(vp_less(s[tok][w], tb) | vp_less(tb, s[tok][w])) & (0x00010001u << (w + 8 * tok));
+            const uint32_t bits = 0x00010001u << (w + 8 * tok), above = vp_less(t, s[tok][w]), below = vp_less(s[tok][w], b0);
+            outl |= (above | below) & bits;
+            eq[0] |= ~(above | vp_less(s[tok][w], t0)) & bits;
+            eq[1] |= ~(below | vp_less(b, s[tok][w])) & bits;
         }
     }
 #pragma unroll
@@ -163,13 +189,21 @@ __device__ __forceinline__ uint32_t drop_equals(VpLds &lds, const s16x2 (&s)[2][
         for (int w = 0; w < wave; ++w) before[side] += lds.eq[w][side];
 #pragma unroll
         for (int tok = 0; tok < 2; ++tok) {
-            const uint32_t need = lds.found[2 * tok + side].need;
+            // equals from rank `from` to `to`; thresholds coincide: the lower outliers take those that follow the upper ones'
+            const bool same = lds.found[2 * tok].tau == lds.found[2 * tok + 1].tau;
+            const uint32_t from = side && same ? lds.found[2 * tok].need : 0u, to = from + lds.found[2 * tok + side].need;
             uint32_t rank = (before[side] >> (16 * tok)) & 0xFFFFu, left = (eq[side] >> (8 * tok)) & 0x00FF00FFu;
-            while (left != 0u) {                         // in channel order: words, then halves
-                const int w = __ffs((int)((left | left >> 16) & 0xFFu)) - 1;
-                const uint32_t bit = 1u << w & left ? 1u << w : 0x10000u << w;
-                left &= ~bit;
-                if (rank++ >= need) outl &= ~(bit << (8 * tok));
+            const uint32_t end = rank + (uint32_t)__popc(left);
+            if (rank >= from && end <= to) {             // all of them, or none: nearly every lane
+                outl |= left << (8 * tok);
+            } else if (rank < to && end > from) {
+                while (left != 0u) {                     // in channel order: words, then halves
+                    const int w = __ffs((int)((left | left >> 16) & 0xFFu)) - 1;
+                    const uint32_t bit = 1u << w & left ? 1u << w : 0x10000u << w;
+                    left &= ~bit;
+                    if (rank >= from && rank < to) outl |= bit << (8 * tok);
+                    ++rank;
+                }
             }
         }
     }
@@ -217,20 +251,21 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) __attribute__((amdgpu_wave
     const uint32_t first_entry = v_ptr[n0];
     if (tid < 16) lds.lut[tid] = pv.hdr->lut_v[tid & (NE - 1)];
     for (int i = tid; i < 4 * 64; i += NT) (&lds.col_max[0][0])[i] = -32768;
-    if (tid < 4) lds.n_cand[tid] = 0;
+    if (tid < 2) lds.n_cand[tid] = lds.n_side[tid] = 0;
     if (tid < 3 * KVQ_BULK_MAX_WAVES) (&lds.wave_red[0][0])[tid] = tid < 2 * KVQ_BULK_MAX_WAVES ? 0x80008000u : 0u;
     __syncthreads();
-    s16x2 hi[2], lo[2];
+    auto extremes = [&](int tok, s16x2 &most, s16x2 &least) {              // of this lane
+        most = least = s[tok][0];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) {
+            most = __builtin_elementwise_max(most, s[tok][w]);
+            least = __builtin_elementwise_min(least, s[tok][w]);
+        }
+    };
 #pragma unroll
     for (int tok = 0; tok < 2; ++tok) {
 #pragma unroll
         for (int w = 0; w < 8; ++w) s[tok][w] = vp_keys(vp_word(s[tok][w]));
-        hi[tok] = lo[tok] = s[tok][0];
-#pragma unroll
-        for (int w = 1; w < 8; ++w) {
-            hi[tok] = __builtin_elementwise_max(hi[tok], s[tok][w]);
-            lo[tok] = __builtin_elementwise_min(lo[tok], s[tok][w]);
-        }
 #pragma unroll
         for (int q = 0; q < 2; ++q)
             keys_s[(2 * tok + q) * NT + tid] = uint4{vp_word(s[tok][4 * q]), vp_word(s[tok][4 * q + 1]), vp_word(s[tok][4 * q + 2]),
@@ -239,127 +274,138 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) __attribute__((amdgpu_wave
     auto key_at = [&](int w, int tok, int half) {        // of this lane
         return (int)((const int16_t *)&keys_s[(2 * tok + (w >> 2)) * NT + tid])[2 * (w & 3) + half];
     };
-    uint32_t outl = 0;                                   // outliers: see general_selection
-    bool general = false, ties = false;                  // (the same in all wavefronts)
+    uint32_t outl = 0;                                   // outliers: bit w + 8 token + 16 half is half `half` of this lane's word w
+    bool ties = false;                                   // (the same in all wavefronts)
     if (K > 0) {
-#pragma unroll
-        for (int tok = 0; tok < 2; ++tok) {
-            atomicMax(&lds.col_max[2 * tok][lane], (int)(hi[tok].x > hi[tok].y ? hi[tok].x : hi[tok].y));
-            atomicMax(&lds.col_max[2 * tok + 1][lane], ~(int)(lo[tok].x < lo[tok].y ? lo[tok].x : lo[tok].y));
-        }
-        __syncthreads();
-        for (int i = wave; i < 4; i += nw) {
-            const uint32_t c = (uint32_t)(lds.col_max[i][lane] + 32768);
-            uint32_t x = 0;
-            for (int bit = 15; bit >= 0; --bit)
-                if ((uint32_t)__popcll(__ballot(c >= (x | (1u << bit)))) >= K) x |= 1u << bit;
-            if (lane == 0) lds.bound[i] = (int)x - 32768;
-        }
-        __syncthreads();
-        int bound[4];
-        uint32_t which = 0;
-#pragma unroll
-        for (int tok = 0; tok < 2; ++tok) {
-            bound[2 * tok] = lds.bound[2 * tok];
-            bound[2 * tok + 1] = lds.bound[2 * tok + 1];
-            const s16x2 bt = vp_both(bound[2 * tok]), bb = vp_both(~bound[2 * tok + 1]);
-#pragma unroll
-            for (int w = 0; w < 8; ++w)
-                which |= (vp_less(s[tok][w], bt) & vp_less(bb, s[tok][w])) & (0x00010001u << (w + 8 * tok));
-        }
-        which = ~which;
-        int round = 0;
-        while (__ballot(which != 0u) != 0ull) {          // (three rounds or so)
-            // full lists are of no use: a wavefront stops adding to them (see v_quant_token4)
-            if (++round > 4) {
-                bool full = false;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    full = full || __hip_atomic_load(&lds.n_cand[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) > KVQ_V_CAND;
-                if (full) break;
-            }
-            if (which != 0u) {
+        // Keys go to the token's list, a run of places for each wavefront's; none, if there are more than it holds.
+        auto collect = [&](uint32_t which, uint32_t *count) {
+            const uint32_t mine = (uint32_t)__popc(which & 0x00FF00FFu) | (uint32_t)__popc(which & 0xFF00FF00u) << 16, upto = vp_scan(mine);
+            uint32_t at = 0;
+            if (lane == 63) at = atomicAdd(count, upto);
+            at = (uint32_t)__builtin_amdgcn_readlane((int)at, 63);
+            const uint32_t end = at + (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+            if ((end & 0xFFFFu) > (uint32_t)VP_CAND || end >> 16 > (uint32_t)VP_CAND) return;
+            at += upto - mine;
+            while (__ballot(which != 0u) != 0ull) {      // (two or three rounds)
+                if (which == 0u) continue;
                 const int b = __ffs((int)which) - 1, tok = (b >> 3) & 1;
                 which &= which - 1u;
                 const int key = key_at(b & 7, tok, b >> 4);
-                const int bt = tok ? bound[2] : bound[0], bb = tok ? bound[3] : bound[1];
-                if (key >= bt) {
-                    const uint32_t at = atomicAdd(&lds.n_cand[2 * tok], 1u);
-                    if (at < KVQ_V_CAND) lds.cand[2 * tok][at] = (uint16_t)(key + 32768);
+                lds.cand[tok][tok ? at >> 16 : at & 0xFFFFu] = (uint16_t)((key == -1 ? 0 : key) + 32768);
+                at += tok ? 0x10000u : 1u;
+            }
+        };
+        auto full = [](uint32_t n) { return (n & 0xFFFFu) > (uint32_t)VP_CAND || n >> 16 > (uint32_t)VP_CAND; };
+        uint32_t n_cand;
+        bool crowd, general;
+#pragma unroll 1
+        for (int attempt = 0;; ++attempt) {
+#pragma unroll
+            for (int tok = 0; tok < 2; ++tok) {
+                s16x2 hi, lo;
+                if (attempt == 0) extremes(tok, hi, lo);
+                else vp_column_of_fours(s[tok], hi, lo);
+                atomicMax(&lds.col_max[2 * tok][lane], (int)(hi.x > hi.y ? hi.x : hi.y));
+                atomicMax(&lds.col_max[2 * tok + 1][lane], ~(int)(lo.x < lo.y ? lo.x : lo.y));
+            }
+            __syncthreads();
+            for (int i = wave; i < 4; i += nw) {
+                const uint32_t c = (uint32_t)(lds.col_max[i][lane] + 32768);
+                uint32_t x = 0;
+                for (int bit = 15; bit >= 0; --bit)
+                    if ((uint32_t)__popcll(__ballot(c >= (x | (1u << bit)))) >= K) x |= 1u << bit;
+                const int b = (i & 1) ? ~((int)x - 32768) : (int)x - 32768;
+                if (lane == 0) lds.bound[i] = b == -1 ? 0 : b;
+            }
+            __syncthreads();
+            uint32_t which = 0;
+#pragma unroll
+            for (int tok = 0; tok < 2; ++tok) {
+                const s16x2 t0 = vp_both(vp_least_equal(lds.bound[2 * tok])), b = vp_both(lds.bound[2 * tok + 1]);
+#pragma unroll
+                for (int w = 0; w < 8; ++w) which |= (vp_less(s[tok][w], t0) & vp_less(b, s[tok][w])) & (0x00010001u << (w + 8 * tok));
+            }
+            collect(~which, &lds.n_cand[0]);
+            __syncthreads();
+            n_cand = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds.n_cand[0]);
+            crowd = full(n_cand);
+            general = false;
+            if (crowd) {
+                // Many keys on a bound: those beyond are listed.  Where they are fewer than K, the bound is the threshold.
+                uint32_t beyond[2] = {0, 0};
+#pragma unroll
+                for (int tok = 0; tok < 2; ++tok) {
+                    const s16x2 t = vp_both(lds.bound[2 * tok]), b0 = vp_both(vp_least_equal(lds.bound[2 * tok + 1]));
+#pragma unroll
+                    for (int w = 0; w < 8; ++w) {
+                        beyond[0] |= vp_less(t, s[tok][w]) & (0x00010001u << (w + 8 * tok));
+                        beyond[1] |= vp_less(s[tok][w], b0) & (0x00010001u << (w + 8 * tok));
+                    }
                 }
-                if (~key >= bb) {
-                    const uint32_t at = atomicAdd(&lds.n_cand[2 * tok + 1], 1u);
-                    if (at < KVQ_V_CAND) lds.cand[2 * tok + 1][at] = (uint16_t)(~key + 32768);
+#pragma unroll
+                for (int side = 0; side < 2; ++side) {
+                    const uint32_t upto = vp_scan((uint32_t)__popc(beyond[side] & 0x00FF00FFu) | (uint32_t)__popc(beyond[side] & 0xFF00FF00u) << 16);
+                    if (lane == 63) atomicAdd(&lds.n_side[side], upto);
+                }
+                collect(beyond[0] | beyond[1], &lds.n_cand[1]);
+                __syncthreads();
+                n_cand = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds.n_cand[1]);
+                general = full(n_cand);
+            }
+            if (!general || attempt == 1) break;
+            // the largest keys in few lanes: once more with other columns
+            for (int i = tid; i < 4 * 64; i += NT) (&lds.col_max[0][0])[i] = -32768;
+            __syncthreads();
+            if (tid < 2) lds.n_cand[tid] = lds.n_side[tid] = 0;
+        }
+        if (general) {
+            general_selection(lds, s, K);
+        } else {
+            for (int i = wave; i < 4; i += nw) {
+                const uint32_t n = (n_cand >> (16 * (i >> 1))) & 0xFFFFu;
+                const uint32_t beyond = crowd ? (lds.n_side[i & 1] >> (16 * (i >> 1))) & 0xFFFFu : K;
+                if (beyond < K) {
+                    if (lane == 0) { lds.found[i].tau = lds.bound[i]; lds.found[i].need = K - beyond; lds.found[i].n_eq = ~0u; }
+                } else if (n <= 64u) {
+                    pick<1>(lds, i, n, K);
+                } else if (n <= 128u) {
+                    pick<2>(lds, i, n, K);
+                } else if (n <= 192u) {
+                    pick<3>(lds, i, n, K);
+                } else {
+                    pick<VP_CAND / 64>(lds, i, n, K);
                 }
             }
         }
         __syncthreads();
-        for (int i = wave; i < 4; i += nw) {
-            // K-th largest candidate, bit by bit (a list has at least K entries)
-            const uint32_t n = lds.n_cand[i];
-            uint32_t v[KVQ_V_CAND / 64];
-            constexpr int R = KVQ_V_CAND / 64;
 #pragma unroll
-            for (int r = 0; r < R; ++r) v[r] = (uint32_t)lane + 64u * r < n ? lds.cand[i][lane + 64 * r] + 1u : 0u;     // + 1: above an absent one
-            auto at_least = [&](uint32_t x) {
-                uint32_t c = 0;
-#pragma unroll
-                for (int r = 0; r < R; ++r) c += (uint32_t)__popcll(__ballot(v[r] >= x));
-                return c;
-            };
-            uint32_t x = 0;
-            for (int bit = 16; bit >= 0; --bit)
-                if (at_least(x | (1u << bit)) >= K) x |= 1u << bit;
-            const uint32_t beyond = at_least(x + 1u), reached = at_least(x);
-            if (lane == 0) {
-                lds.found[i].tau = (int)x - 1 - 32768;
-                lds.found[i].need = K - beyond;
-                lds.found[i].n_eq = n <= KVQ_V_CAND ? reached - beyond : ~0u;
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int tau = lds.found[i].tau;
-            ties = ties || lds.found[i].need != lds.found[i].n_eq;
-            general = general || lds.found[i].n_eq == ~0u || tau == 0 || tau == -1;      // (~0 is -1)
-        }
-        general = general || lds.found[0].tau == ~lds.found[1].tau || lds.found[2].tau == ~lds.found[3].tau;
-        general = __builtin_amdgcn_readfirstlane((int)general) != 0;
-        ties = __builtin_amdgcn_readfirstlane((int)ties) != 0 && !general;
-        if (general) outl = general_selection(lds, s, K);
+        for (int i = 0; i < 4; ++i) ties = ties || lds.found[i].need != lds.found[i].n_eq;
+        ties = ties || lds.found[0].tau == lds.found[1].tau || lds.found[2].tau == lds.found[3].tau;
+        ties = __builtin_amdgcn_readfirstlane((int)ties) != 0;
+        if (ties) outl = with_equals(lds, s);
     }
     // range of the remaining elements and the number of outliers
     s16x2 mx[2], mn[2];
     if (K == 0) {
 #pragma unroll
-        for (int tok = 0; tok < 2; ++tok) { mx[tok] = hi[tok]; mn[tok] = lo[tok]; }
-    } else if (!general) {
+        for (int tok = 0; tok < 2; ++tok) extremes(tok, mx[tok], mn[tok]);
+    } else if (!ties) {
         uint32_t in = 0;
 #pragma unroll
         for (int tok = 0; tok < 2; ++tok) {
-            const s16x2 tt = vp_both(lds.found[2 * tok].tau), tb = vp_both(~lds.found[2 * tok + 1].tau);
+            const s16x2 tt = vp_both(vp_least_equal(lds.found[2 * tok].tau)), tb = vp_both(lds.found[2 * tok + 1].tau);
             mx[tok] = vp_both(-32768);
             mn[tok] = vp_both(32767);
 #pragma unroll
             for (int w = 0; w < 8; ++w) {
                 const uint32_t below = vp_less(s[tok][w], tt), above = vp_less(tb, s[tok][w]);
-                // (a lower outlier is no larger than any inlier, of which there is one at least, and the other way round)
+                // (a lower outlier is less than any inlier, of which there is one at least, and the other way round)
                 mx[tok] = __builtin_elementwise_max(mx[tok], vp_pair(vp_select(below, vp_word(s[tok][w]), 0x80008000u)));
                 mn[tok] = __builtin_elementwise_min(mn[tok], vp_pair(vp_select(above, vp_word(s[tok][w]), 0x7FFF7FFFu)));
                 in |= (below & above) & (0x00010001u << (w + 8 * tok));
             }
         }
         outl = ~in;
-        if (ties) {
-            outl = drop_equals(lds, s, outl);
-            // a threshold with equals left over is the extreme of the rest
-#pragma unroll
-            for (int tok = 0; tok < 2; ++tok) {
-                if (lds.found[2 * tok].need < lds.found[2 * tok].n_eq) mx[tok] = vp_both(lds.found[2 * tok].tau);
-                if (lds.found[2 * tok + 1].need < lds.found[2 * tok + 1].n_eq) mn[tok] = vp_both(~lds.found[2 * tok + 1].tau);
-            }
-        }
     } else {
 #pragma unroll
         for (int tok = 0; tok < 2; ++tok) {
@@ -502,20 +548,52 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) __attribute__((amdgpu_wave
             }
         }
     }
-    // ---- outliers: the entries, and the codes of those too far out for the thresholds
+    // ---- outliers: a wavefront's channels into a list by their places among the token's, then an entry to a lane, whichever lanes they
+    // came from
     bool overflow = false;
-    uint32_t left = outl & ((own & 1u ? 0x00FF00FFu : 0u) | (own & 2u ? 0xFF00FF00u : 0u));
-    while (__ballot(left != 0u) != 0ull) {
-        if (left == 0u) continue;
-        const int b = __ffs((int)left) - 1, w = b & 7, tok = (b >> 3) & 1, half = b >> 4;
-        left &= left - 1u;
-        const float x = vp_value(key_at(w, tok, half));
-        const float z = tok ? z2[1] : z2[0], sc = tok ? s2[1] : s2[0], ri = tok ? r2[1] : r2[0];
-        const float diff = x - z, xn = diff * ri;
-        int code = coder.count(xn);
-        if (plain && coder.far(xn)) {
-            code = coder.search(xn);
-            const int at = 2 * BITS * (2 * w + half) + BITS * tok;
+    {
+        uint32_t left = outl & ((own & 1u ? 0x00FF00FFu : 0u) | (own & 2u ? 0xFF00FF00u : 0u));
+        while (__ballot(left != 0u) != 0ull) {
+            if (left == 0u) continue;
+            const int b = __ffs((int)left) - 1, w = b & 7, tok = (b >> 3) & 1, half = b >> 4;
+            left &= left - 1u;
+            const uint32_t lower = ((1u << w) - 1u) * 0x00010001u | (half ? 1u << w : 0u);    // this lane's channels below
+            const uint32_t rank = ((before >> (16 * tok)) & 0xFFFFu) + (uint32_t)__popc(outl & (lower << (8 * tok)));
+            if (rank < 2u * KVQ_V_BOUNDED) lds.ids[tok][rank] = (uint16_t)(16 * tid + 2 * w + half);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    const uint32_t first_rank = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
+    const uint32_t here = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    const int here0 = own & 1u ? (int)(here & 0xFFFFu) : 0, here1 = own & 2u ? (int)(here >> 16) : 0;
+    bool any_far = false;
+    for (int e = lane; __ballot(e < here0 + here1) != 0ull; e += 64) {
+        bool far = false;
+        if (e < here0 + here1) {
+            const int tok = e >= here0 ? 1 : 0;
+            const uint32_t rank = ((first_rank >> (16 * tok)) & 0xFFFFu) + (uint32_t)(tok ? e - here0 : e);
+            const uint32_t c = lds.ids[tok][rank];
+            const float x = vp_value((int)((const int16_t *)&keys_s[(2 * tok + ((c >> 3) & 1)) * NT + (c >> 4)])[c & 7]);
+            const float z = tok ? z2[1] : z2[0], sc = tok ? s2[1] : s2[0], ri = tok ? r2[1] : r2[0];
+            const float diff = x - z, xn = diff * ri;
+            far = coder.far(xn);
+            const int code = far ? coder.search(xn) : coder.count(xn);
+            const uint64_t pos = (uint64_t)first_entry + (uint32_t)(t0 + tok) * 2u * K + rank;
+            if (pos < (uint64_t)cap_nnz) vsp.put(pos, (uint16_t)c, kvq_f2h_rn(x - __builtin_fmaf(sc, lds.lut[code], z)));
+            else overflow = true;
+        }
+        any_far = any_far || __ballot(far) != 0ull;
+    }
+    if (plain && any_far) {                              // codes of those too far out for the thresholds
+        uint32_t left = outl;
+        while (__ballot(left != 0u) != 0ull) {
+            if (left == 0u) continue;
+            const int b = __ffs((int)left) - 1, w = b & 7, tok = (b >> 3) & 1, half = b >> 4;
+            left &= left - 1u;
+            const float xn = (vp_value(key_at(w, tok, half)) - (tok ? z2[1] : z2[0])) * (tok ? r2[1] : r2[0]);
+            if (!coder.far(xn)) continue;
+            const int code = coder.search(xn), at = 2 * BITS * (2 * w + half) + BITS * tok;
 #pragma unroll
             for (int d = 0; d < BITS; ++d) {
                 const int sh = at - 32 * d;
@@ -524,14 +602,7 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) __attribute__((amdgpu_wave
                     out[d] = (out[d] & ~mask) | (sh >= 0 ? (uint32_t)code << sh : (uint32_t)code >> -sh);
                 }
             }
-        } else if (!plain) {
-            code = coder(xn);
         }
-        const uint32_t lower = ((1u << w) - 1u) * 0x00010001u | (half ? 1u << w : 0u);        // this lane's channels below
-        const uint32_t rank = ((before >> (16 * tok)) & 0xFFFFu) + (uint32_t)__popc(outl & (lower << (8 * tok)));
-        const uint64_t pos = (uint64_t)first_entry + (uint32_t)(t0 + tok) * 2u * K + rank;
-        if (pos < (uint64_t)cap_nnz) vsp.put(pos, (uint16_t)(16 * tid + 2 * w + half), kvq_f2h_rn(x - __builtin_fmaf(sc, lds.lut[code], z)));
-        else overflow = true;
     }
     if (overflow) atomicExch(d_status, (int32_t)KVQ_ERR_NNZ_OVERFLOW);
     // ---- store: dwords (tid & 3) BITS .. + BITS - 1 of the chunk of 64 channels
