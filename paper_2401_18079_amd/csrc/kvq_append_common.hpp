@@ -79,7 +79,7 @@ __device__ __forceinline__ void k_count_token(const void *params, int D, const u
         }
     } else {
         // packed keys against the channels' first and last that are no outlier (KvqKeyParams); one by one where the range ends at the code range
-        // and something lies beyond, or an infinity or a NaN is among the elements
+        // and something lies beyond.  NaN lies beyond every range and is no outlier.
         const KvqKeyParams kp = kvq_key_params(params, D);
         const uint4 *first = (const uint4 *)kp.first, *last = (const uint4 *)kp.last;
         for (int v = lane; v < D / 8; v += 64) {
@@ -88,17 +88,25 @@ __device__ __forceinline__ void k_count_token(const void *params, int D, const u
             asm("" : "+v"(narrow));      // (requested with the others, not where it is needed)
             const uint32_t w[4] = {h.x, h.y, h.z, h.w}, fw[4] = {f.x, f.y, f.z, f.w}, lw[4] = {l.x, l.y, l.z, l.w};
             s16x2 out = {0, 0};           // less the outliers among the even and the odd channels
-            half2_t odd = {(half_t)0, (half_t)0};
+            half2_t odd = {(half_t)0, (half_t)0};                          // NaN: one of the elements is
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const s16x2 s = vp_keys(w[i]);
                 out += vp_pair(vp_less(s, vp_pair(fw[i])) | vp_less(vp_pair(lw[i]), s));
-                odd = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, w[i]), half2_t{(half_t)0, (half_t)0}, odd);
+                odd = __builtin_elementwise_maximum(odd, __builtin_bit_cast(half2_t, w[i]));
             }
             int n = -(out.x + out.y);
-            if (!(odd.x == (half_t)0) || !(odd.y == (half_t)0) || (n != 0 && narrow != 0)) {
+            if (n != 0 && narrow != 0) {
                 n = 0;
                 for (int e = 0; e < 8; ++e) n += one(8 * v + e);
+            } else if (!(odd.x == odd.x) || !(odd.y == odd.y)) {
+                s16x2 nan = {0, 0};       // less their number
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const s16x2 s = vp_keys(w[i]);
+                    nan += vp_pair(vp_less(vp_both(31744), s) | vp_less(s, vp_both(-31745)));
+                }
+                n += nan.x + nan.y;
             }
             mine += (uint32_t)n;
         }

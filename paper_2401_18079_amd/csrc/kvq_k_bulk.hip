@@ -93,10 +93,10 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) void kvq_k_bulk(const void
     bool overflow = false;
     for (int t = ta; t < tb; ++t) {
         s16x2 s[8];
-        half2_t odd = {(half_t)0, (half_t)0};                              // NaN: an infinity or a NaN among the elements
+        half2_t odd = {(half_t)0, (half_t)0};                              // NaN: one of the elements is
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            odd = __builtin_elementwise_fma(__builtin_bit_cast(half2_t, next[i]), half2_t{(half_t)0, (half_t)0}, odd);
+            odd = __builtin_elementwise_maximum(odd, __builtin_bit_cast(half2_t, next[i]));
             s[i] = vp_keys(next[i]);
         }
         if (t + 1 < tb) load(t + 1, next);
@@ -138,7 +138,8 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) void kvq_k_bulk(const void
             out |= (uint64_t)((fields & 0xFFFFu) | (fields >> 16)) << (4 * BITS * i);
         }
         out = ~out;
-        const bool check = !countable || !(odd.x == (half_t)0) || !(odd.y == (half_t)0) || (narrow && outl != 0u);
+        // (an infinity is an outlier like another: a channel whose threshold it does not pass has a range that ends before)
+        const bool check = !countable || !(odd.x == odd.x) || !(odd.y == odd.y) || (narrow && outl != 0u);
         if (__ballot(check) != 0ull) {
             if (check) {                                                   // one by one
                 const KvqCoder<NE> coder(pv.hdr->thr_k, pv.hdr->lut_k);
