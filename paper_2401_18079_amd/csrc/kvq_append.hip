@@ -1446,9 +1446,10 @@ static kvq_status append_k(kvq_cache *cache, const uint16_t *d_k_new, int32_t T,
     hipStream_t s = (hipStream_t)stream;
     const int single = (T == 1);
     // us, kvq_k_bulk / the kernels below with kvq_ptr_scan before them: 64 tokens of 4096 channels, 3 bits 10.0 / 12.4; 777 12.6 / 17.2; 4096 27.0 / 40.5;
-    // of 1024 channels, 4096 13.9 / 16.2; of 5120, 4 bits 47.0 / 56.2; of 8192 56.1 / 85.8
+    // of 1024 channels, 4096 13.9 / 16.2; of 5120, 4 bits 47.0 / 56.2; of 8192 56.1 / 85.8.  But where codes are searched for, not counted, which here
+    // a lane does one by one (signposts past 1): 4096 tokens of 4096 channels, 3 bits 129 / 49, 777 of 5120, 4 bits, 74 / 31, 64 of 4096 23 / 12.
     const bool bulk = T >= KVQ_VW_SMALL_TOKENS && D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES && ((uintptr_t)d_k_new & 15) == 0 &&
-                      cache->workspace_bytes >= ((int64_t)T + 3) / 4 * 16;
+                      cache->workspace_bytes >= ((int64_t)T + 3) / 4 * 16 && !(cache->loaded & KVQ_LOADED_SEARCH_K);
     if (!single) {
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
         uint32_t *cnt = (uint32_t *)cache->workspace;
@@ -1527,9 +1528,13 @@ static kvq_status append_v(kvq_cache *cache, const uint16_t *d_v_new, int32_t T,
     // longer ones: below, a token of 1024 or 2048 channels is sooner done by four wavefronts (us, four / one or two wavefronts: 1024 channels,
     // 2 bits, 777 tokens 9.1 / 11.3, 1200 11.5 / 11.8, 2048 16.2 / 10.6, 4 bits, 1200 12.3 / 13.4, 2048 17.8 / 12.0; 2048 channels, 777 tokens 11.3 / 11.9
     // and 13.1 / 14.7, 1200 14.5 / 9.9 and 17.3 / 11.5).  More than KVQ_V_BOUNDED outliers a side, other widths and unaligned input keep the
-    // other kernels.
+    // other kernels.  So do calls of up to 4 M elements whose codes are searched for, not counted, which here a lane does one by one (signposts past 1,
+    // us, four wavefronts a token / this one: 64 tokens of 4096 channels, 3 bits 16.0 / 19.2, 777 20.3 / 19.9, 4 bits 18.6 / 24.0, 25.1 / 26.4, 4096 75.6 /
+    // 71.1, 1000 of 2048 16.2 / 26.9, 4096 of 1024 31.2 / 34.0; but 2 bits, 64 of 4096 13.1 / 11.1; of 5120, 4 bits, 24.4 / 26.2, 1500 44.7 / 39.2).
+    const bool searched = (cache->loaded & KVQ_LOADED_SEARCH_V) && cache->bits > 2;
     const bool pair = !small && D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES && cache->k_side_v <= (int)KVQ_V_BOUNDED &&
-                      ((uintptr_t)d_v_new & 15) == 0 && T >= (D == 1024 ? 1500 : D == 2048 ? 1000 : KVQ_VW_SMALL_TOKENS);
+                      ((uintptr_t)d_v_new & 15) == 0 && T >= (D == 1024 ? 1500 : D == 2048 ? 1000 : KVQ_VW_SMALL_TOKENS) &&
+                      !(searched && in_pairs && D <= 4096 && (int64_t)T * D <= (4 << 20));
     KeyCount keys = {0, nullptr, nullptr};
     // Counting on the way saves a launch and its latency (32 heads, blocked storage, 2048 tokens, us with a launch of its own / on the way: 2 bits 34.1 /
     // 31.1, 4 bits 42.6 / 39.4; 4096 tokens 49.3 / 46.7, 65.0 / 62.4; 16 heads 33.7 / 33.5, 42.2 / 43.2), except in the kernel of four wavefronts a token from
@@ -1606,11 +1611,12 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
     const int D = cache->n_kv_heads * KVQ_HEAD_DIM;
     if (cache->k_side_v < 0 || 2 * (int64_t)cache->k_side_v >= D) return KVQ_ERR_INVALID_ARG;
     if (D > 16384) return KVQ_ERR_UNSUPPORTED;       // the per-token Value selection keeps the vector in LDS
-    if (T >= KVQ_KV_SPLIT_TOKENS || (T > 128 && D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES)) {
+    const bool searched = (cache->loaded & (KVQ_LOADED_SEARCH_K | KVQ_LOADED_SEARCH_V)) != 0;
+    if (T >= KVQ_KV_SPLIT_TOKENS || (T > 128 && D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES && !searched)) {
         // Such an append fills the GPU with either kernel alone.  From 129 tokens on, two workgroups of 1024 threads per token are more than the
         // compute units hold at once, and the bulk kernels are the faster ones (180 tokens, us in one launch / in turn: 24 heads 23.0 / 14.9,
         // 32 heads 24.8 / 14.8, 64 heads 33.3 / 18.2; 8 heads, 4 bits, 13.2 / 12.3; 100 tokens, 32 heads 16.9 / 14.8, 40 heads 18.0 / 19.1, 16 heads, 4 bits,
-        // 13.3 / 15.1).  Other widths, 255 tokens, 4 bits: 52 heads 68 / 48.
+        // 13.3 / 15.1).  Other widths, 255 tokens, 4 bits: 52 heads 68 / 48.  Codes that are searched for, 150 tokens, 4 bits: 40 heads 31.9 / 34.6.
         // Every check of both calls has passed above.
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
         // Values first: their kernel counts the Keys' outliers on the way (see KeyCount).

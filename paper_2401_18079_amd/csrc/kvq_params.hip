@@ -306,5 +306,7 @@ extern "C" kvq_status kvq_lut_load(kvq_cache *cache, const float *h_lut_k, const
     for (int c = 0; c < D && no_outliers; ++c)
         no_outliers = (h_lo_k[c] == 0xFBFFu) && (h_hi_k[c] == 0x7BFFu);   // -65504 / +65504
     cache->loaded = no_outliers ? 3 : 1;
+    if (!(hdr.thr_k[0] == hdr.thr_k[0])) cache->loaded |= KVQ_LOADED_SEARCH_K;
+    if (!(hdr.thr_v[0] == hdr.thr_v[0])) cache->loaded |= KVQ_LOADED_SEARCH_V;
     return KVQ_OK;
 }
