@@ -185,8 +185,9 @@ kvq_status kvq_quantize_append_v(kvq_cache *cache, const uint16_t *d_v_new, int3
  * Both appends of a decode step in one call and, for the quantization itself, one kernel launch:
  * exactly kvq_quantize_append_k(cache, d_k_new, T) followed by kvq_quantize_append_v(cache, d_v_new, T)
  * (paper Sec. 3.1-3.4, 3.6 as above), with the workgroups of the two running side by side: a
- * single-token append is latency-bound and the two do not depend on each other (from 256 tokens per
- * call on, where either kernel fills the GPU alone, the two run one after the other).  The checks of both
+ * single-token append is latency-bound and the two do not depend on each other (where either kernel
+ * fills the GPU alone, from 256 tokens per call on, or from 129 or 150 on for some layers of a multiple of
+ * 1024 channels, the two run one after the other).  The checks of both
  * calls are made before anything is launched; n_tokens_k and n_tokens_v both advance by T.
  */
 kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d_k_new, const uint16_t *d_v_new,

@@ -22,7 +22,9 @@ namespace {
 // tokens on (4096 tokens of 4096: 74 us with a token's bits merged into memory by two atomics per dword, 51 us with whole
 // dwords stored).  All others take the routine for any width.
 constexpr int KVQ_BULK_TOKENS = 512;      // calls with at least this many tokens count as bulk appends
-constexpr int KVQ_KV_SPLIT_TOKENS = 256;  // from here on the combined call runs the Key and Value kernels in turn
+constexpr int KVQ_KV_SPLIT_TOKENS = 256;  // from here on the combined call runs the Key and Value kernels in turn,
+constexpr int KVQ_KV_SPLIT_BULK = 129;    // from here on where they are those of multiples of 1024 channels, 3072 and more,
+constexpr int KVQ_KV_SPLIT_NARROW = 150;  // and from here on with 1024 or 2048 channels and 2 bits
 constexpr int KVQ_WAVE_TOKENS = 1024;     // Key appends of at least this many tokens: one wavefront per token
 
 // Workgroups have NT threads: 256 for narrow models, 1024 once a token vector has >= 2048 channels
@@ -1612,11 +1614,17 @@ extern "C" kvq_status kvq_quantize_append_kv(kvq_cache *cache, const uint16_t *d
     if (cache->k_side_v < 0 || 2 * (int64_t)cache->k_side_v >= D) return KVQ_ERR_INVALID_ARG;
     if (D > 16384) return KVQ_ERR_UNSUPPORTED;       // the per-token Value selection keeps the vector in LDS
     const bool searched = (cache->loaded & (KVQ_LOADED_SEARCH_K | KVQ_LOADED_SEARCH_V)) != 0;
-    if (T >= KVQ_KV_SPLIT_TOKENS || (T > 128 && D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES && !searched)) {
+    // (what the bulk kernels take; 4096 channels have a Value kernel for pairs of tokens besides)
+    const bool bulk = D % 1024 == 0 && D <= 1024 * KVQ_BULK_MAX_WAVES && !searched &&
+                      (D == 4096 || (cache->k_side_v <= (int)KVQ_V_BOUNDED && (((uintptr_t)d_k_new | (uintptr_t)d_v_new) & 15) == 0));
+    const int split = !bulk || (D <= 2048 && cache->bits > 2) ? KVQ_KV_SPLIT_TOKENS : D <= 2048 ? KVQ_KV_SPLIT_NARROW : KVQ_KV_SPLIT_BULK;
+    if (T >= split) {
         // Such an append fills the GPU with either kernel alone.  From 129 tokens on, two workgroups of 1024 threads per token are more than the
-        // compute units hold at once, and the bulk kernels are the faster ones (180 tokens, us in one launch / in turn: 24 heads 23.0 / 14.9,
-        // 32 heads 24.8 / 14.8, 64 heads 33.3 / 18.2; 8 heads, 4 bits, 13.2 / 12.3; 100 tokens, 32 heads 16.9 / 14.8, 40 heads 18.0 / 19.1, 16 heads, 4 bits,
-        // 13.3 / 15.1).  Other widths, 255 tokens, 4 bits: 52 heads 68 / 48.  Codes that are searched for, 150 tokens, 4 bits: 40 heads 31.9 / 34.6.
+        // compute units hold at once, and the bulk kernels are the faster ones, but hardly of one or two wavefronts a token (us in one launch / in turn: 129
+        // tokens, 4 bits, 24 heads 22.6 / 15.7, 40 heads 26.8 / 17.6, 16 heads 12.9 / 14.3, 8 heads 10.9 / 11.8; 165 tokens 13.6 / 14.5, 11.4 / 12.0, 255 14.6 /
+        // 14.7, 11.7 / 12.1; blocked storage, 200 tokens, 3 bits 13.8 / 14.5, 12.0 / 12.4, but 2 bits 13.5 / 13.1, 11.7 / 11.3; 64 heads 33 / 18; 100 tokens,
+        // 40 heads 18.0 / 19.1).  Other widths, 255 tokens, 4 bits: 52 heads 68 / 48.  What the bulk kernels do not take, 40 heads, 130
+        // tokens, 2 bits: 60 outliers a side 23.7 / 32.1, unaligned input 31.4 / 41.0, but 32 heads 21.7 / 18.5, 28.4 / 19.0; codes that are searched for, 150 tokens, 4 bits 31.9 / 34.6.
         // Every check of both calls has passed above.
         if (!cache->workspace || cache->workspace_bytes < (int64_t)T * 4) return KVQ_ERR_CAPACITY;
         // Values first: their kernel counts the Keys' outliers on the way (see KeyCount).

@@ -189,3 +189,33 @@ def test_append_kv_overflow_and_argument_errors():
     kp = g2.k_ptr.cpu().numpy().view(np.uint32)
     assert kp.max() <= 16 and np.all(np.diff(kp[:41].astype(np.int64)) >= 0)
     assert np.array_equal(g2.k_idx.cpu().numpy().view(np.uint16)[:16], oc.k_idx[:16])
+
+
+@pytest.mark.parametrize("heads,bits,T,side,shift", [
+    (8, 2, 149, 5, 0), (16, 2, 150, 10, 0), (16, 4, 129, 10, 0), (8, 3, 255, 5, 0), (24, 3, 128, 15, 0), (24, 3, 129, 15, 0), (64, 2, 129, 41, 0), (12, 3, 200, 8, 0),
+    (72, 2, 130, 46, 0), (40, 2, 130, 53, 0), (40, 4, 130, 26, 1), (32, 3, 130, 53, 0), (32, 3, 130, 20, 1),
+])
+def test_one_launch_and_two_at_either_side_of_the_rule(heads, bits, T, side, shift):
+    """Also more outliers a side than the bulk kernels take, and unaligned input."""
+    import torch
+    import paper_2401_18079_amd as K
+    wl = S.workload("c2", n_kv_heads=heads, n_q_heads=heads, bits=bits)
+    st = Setup(wl)
+    k, v = st.k(0, T + 1), st.v(0, T + 1)
+    nnz = st.cap_nnz_k(256)
+    oc = O.OracleCache(bits, heads, heads, 256, side, wl.rope_base, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi, cap_nnz_k=nnz)
+    gc = K.KvqCache(bits, heads, heads, 256, side, wl.rope_base, nnz)
+    K.kvq_lut_load(gc, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
+    oc.append_k(k); oc.append_v(v)
+
+    def dev(x):
+        x = torch.from_numpy(x).cuda()
+        buf = torch.zeros(x.numel() + 8, dtype=x.dtype, device="cuda")
+        y = buf[shift:shift + x.numel()].view(x.shape)
+        y.copy_(x)
+        return y
+
+    for a, b in ((0, 1), (1, T + 1)):
+        K.kvq_quantize_append_kv(gc, dev(k[a:b]), dev(v[a:b]))
+    bad = compare_caches(oc, gc)
+    assert not bad, bad
