@@ -644,10 +644,11 @@ bool ck_plan(const void *k_cal, int T, int D, int k, CkPlan &plan)
     // The sample, the bounds and the second launch cost 25 us, which short calls would not get back.  Whole calls, us, two sweeps / one,
     // without outliers and with 1 %: 24576 x 128 60.5 / 57.6, 62.1 / 59.3, 20000 x 128 53.4 / 57.2, 55.3 / 58.4; 16384 x 256 57.0 / 55.3,
     // 58.8 / 56.8; 16384 x 1024 59.1 / 51.9, 63.5 / 53.9; 12000 x 512 48.8 / 56.1, 50.6 / 56.8; 8192 x 2048 46.1 / 50.0, 52.2 / 51.3, 9000 x 2048
-    // 51.4 / 49.4, 54.5 / 50.9; 8192 x 4096 56.5 / 55.9, 67.5 / 58.6; 4096 x 5120 56.2 / 57.7, 70.8 / 60.3; 4096 x 4096 41.5 / 51.1, 48.5 / 52.9.
+    // 51.4 / 49.4, 54.5 / 50.9; 8192 x 4096 56.5 / 55.9, 67.5 / 58.6; 4096 x 5120 56.2 / 57.7, 70.8 / 60.3, 0.1 % 53.7 / 58.4, 0.5 % 58.0 / 59.0;
+    // 4096 x 4096 41.5 / 51.1, 48.5 / 52.9.
     const int64_t all_keys = (int64_t)T * D;
     if (!(T >= 24576 || (T >= 16384 && D >= 256) || (T >= 8192 && all_keys > (16 << 20)) ||
-          (k > 0 && T >= 4096 && all_keys >= (20 << 20))))
+          (k >= 16 && T >= 4096 && all_keys >= (20 << 20))))
         return false;
     const int n_sample = T / CK_STRIDE;
     const double r0 = (double)(k + 1) * n_sample / T, r = r0 + 5.0 * sqrt(r0) + 4.0;

@@ -147,3 +147,10 @@ def test_keys_that_suit_the_lists_ill_cost_little(kind):
     (a, ra), (b, rb) = ms(need), ms(0)
     assert np.array_equal(ra, rb)
     assert a < 1.25 * b, (a, b)
+
+
+def test_few_outliers_of_short_calls_take_the_two_sweeps():
+    """4096 rows: the lists pay from some sixteen outliers a side on."""
+    import paper_2401_18079_amd as K
+    need = K.load_library().kvq_calibrate_key_channels_workspace_bytes
+    assert need(4096, 5120, 0.001) == 0 and need(4096, 5120, 0.005) == 0 and need(4096, 5120, 0.01) > 0 and need(8192, 4096, 0.001) > 0
