@@ -15,8 +15,8 @@
 // launch.  fp32 distances with ties to the smaller index decide the assignment; sums are fp64 (w*x of two fp32 numbers is exact
 // in fp64).
 // 20 iterations, us, with a launch of one workgroup between two iterations that moved the signposts, and now: 16 signposts,
-// 33.6 M elements 1096 / 978, 8.4 M 521 / 407, 1 M 245 / 201, 100000 196 / 177; 4 signposts, 33.6 M 994 / 884, 1 M 224 / 189.
-// Bound: HBM (7 TB/s for what 33.6 M elements take longer than 16.8 M) behind 9 us per iteration of launch, sums, thresholds and
+// 33.6 M elements 1093 / 991, 4 M 379 / 292, 1 M 243 / 203, 100000 195 / 178; 4 signposts, 33.6 M 1018 / 887, 1 M 211 / 175.
+// Bound: HBM (an iteration over 33.6 M elements, 268 MB, takes 49 us, 5.5 TB/s) behind 9 us per iteration of launch, sums, thresholds and
 // cells.  Sweeps alternately from either end, for the last-level cache: no change; four groups ahead instead of two: 2 % slower.
 #include <algorithm>
 #include <type_traits>
