@@ -7,7 +7,7 @@
 // Pointers: a workgroup adds up the outlier counts of the tokens before its run (kvq_k_count) for itself, instead of a launch between.
 // Same arithmetic, same results, as k_quant_token.
 // us per Key append, a wavefront per token and a lane per element (kvq_k_quant_wave) / this one, the counts of 7 us included, 1 % outliers: 4096 tokens
-// of 4096 channels, 2 bits 37.7 / 24.0, 3 bits 40.5 / 27.0, 4 bits 47.5 / 32.1.  Of the 20 us of the 3-bit kernel nine are the bytes, the rest vector
+// of 4096 channels, 2 bits 36.6 / 24.4, 3 bits 39.7 / 27.3, 4 bits 46.3 / 32.9.  Of the 20 us of the 3-bit kernel nine are the bytes, the rest vector
 // issue and the latency of a token's chain (load, ranks over a barrier, outliers one by one) at four wavefronts a SIMD.  What it took: the channels'
 // constants loaded at once and not in a loop (-4 us); neighbouring runs on one XCD (-3 %).
 #include <type_traits>
