@@ -104,11 +104,20 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) void kvq_k_bulk(const void
         bulk_s[NT + tid] = uint4{vp_word(s[4]), vp_word(s[5]), vp_word(s[6]), vp_word(s[7])};
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");             // (read by this lane only)
         auto key_at = [&](int w, int half) { return (int)((const int16_t *)&bulk_s[(w >> 2) * NT + tid])[2 * (w & 3) + half]; };
+        uint32_t nan = 0;                                                  // no outliers, code 0: below every threshold from here on
+        if (__ballot(!(odd.x == odd.x) || !(odd.y == odd.y)) != 0ull) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t m = vp_less(vp_both(31744), s[i]) | vp_less(s[i], vp_both(-31745));
+                nan |= m & (0x00010001u << i);
+                s[i] = vp_pair(vp_select(m, 0x80008000u, vp_word(s[i])));
+            }
+        }
         // outliers: bit w + 16 half is half `half` of word w
         uint32_t in = 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) in |= ~(vp_less(s[i], vp_pair(first[i])) | vp_less(vp_pair(last[i]), s[i])) & (0x00010001u << i);
-        uint32_t outl = ~in & 0x00FF00FFu;
+        uint32_t outl = ~(in | nan) & 0x00FF00FFu;
         // fields: 16 BITS bits from the lowest on; a mask says that the key lies below a threshold, so the bits are inverted at first
         uint64_t out = 0;
 #pragma unroll
@@ -139,7 +148,7 @@ __global__ __launch_bounds__(64 * KVQ_BULK_MAX_WAVES) void kvq_k_bulk(const void
         }
         out = ~out;
         // (an infinity is an outlier like another: a channel whose threshold it does not pass has a range that ends before)
-        const bool check = !countable || !(odd.x == odd.x) || !(odd.y == odd.y) || (narrow && outl != 0u);
+        const bool check = !countable || (narrow && outl != 0u);
         if (__ballot(check) != 0ull) {
             if (check) {                                                   // one by one
                 const KvqCoder<NE> coder(pv.hdr->thr_k, pv.hdr->lut_k);

@@ -225,8 +225,9 @@ def _append_ms(gc, k, timer):
     return min(best)
 
 
-def test_infinities_cost_no_more_than_other_outliers():
-    """A channel of infinities is a channel of outliers.  A factor of 2.9 when every lane that met one coded its elements one by one."""
+@pytest.mark.parametrize("what", ["infinite", "NaN"])
+def test_infinities_and_nan_cost_no_more_than_other_elements(what):
+    """A factor of 2.9 when every lane that met one coded its elements one by one."""
     import torch
     import paper_2401_18079_amd as K
     heads, T = 32, 4096
@@ -234,7 +235,7 @@ def test_infinities_cost_no_more_than_other_outliers():
     st = Setup(wl)
     x = torch.from_numpy(np.asarray(st.k(0, 256)).view(np.float16)).cuda().repeat(T // 256, 1)
     y = x.clone()
-    y[:, 7] = float("inf")
+    y[:, 7] = float("inf") if what == "infinite" else float("nan")
     gc = K.KvqCache(4, heads, heads, T, 20, wl.rope_base, 1 << 20)
     K.kvq_lut_load(gc, st.lut_k, st.lut_v, st.s, st.z, st.lo, st.hi)
     timer = K.binding.HipEventTimer()
