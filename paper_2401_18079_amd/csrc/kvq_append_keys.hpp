@@ -2,6 +2,10 @@
 #pragma once
 #include "kvq_common.hpp"
 
+// Bits 3 and 4 of kvq_cache.loaded, set by kvq_lut_load too: the Keys' (the Values') codes cannot be counted with thresholds (KVQ_CODE_RANGE).
+#define KVQ_LOADED_SEARCH_K 8
+#define KVQ_LOADED_SEARCH_V 16
+
 namespace {
 
 typedef short s16x2 __attribute__((ext_vector_type(2)));

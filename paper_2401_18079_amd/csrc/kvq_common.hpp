@@ -375,9 +375,6 @@ __attribute__((visibility("hidden"))) kvq_status kvq_pv_run(const kvq_cache *cac
 // Bit 2 never appears in a caller's descriptor: kvq_decode_step sets it on its own copy when its first
 // launch has already written the sparse part of the scores.
 #define KVQ_LOADED_SPARSE_SCORES_DONE 4
-// Bits 3 and 4, set by kvq_lut_load: the Keys' (the Values') codes cannot be counted with thresholds (KVQ_CODE_RANGE).
-#define KVQ_LOADED_SEARCH_K 8
-#define KVQ_LOADED_SEARCH_V 16
 // First launch of kvq_decode_step: the append of one token's Key and Value and the sparse Key kernel over
 // the tokens before it, as workgroups of one kernel (kvq_append.hip).  *done = false, nothing launched,
 // nothing changed: the shape is not covered and the caller takes the two calls instead.
